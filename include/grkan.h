@@ -201,17 +201,26 @@ grkan_status_t grkan_bwd(const void *x, const void *dy, const float *A, const fl
  * workspace, results independent of the launch (fixed summation order per
  * output).  The first call of a kernel variant on a device raises that kernel's
  * dynamic-LDS limit (no allocation).
- * Sizing: a workgroup owns 112 rows x one channel block (768, 384 or 192
- * channels) and walks the whole of D_in by itself, so the kernel is at its best
- * from about as many such tiles as the chip has compute units (at 3072 -> 768:
- * from about 20,000 rows); far below that, grkan_fwd and a library product are
- * the faster route.
+ * Sizing: a workgroup owns a tile of rows x channels and walks the whole of
+ * D_in by itself.  Large inputs run in tiles of 112 rows x 768, 384 or 192
+ * channels, small ones in tiles of 16 x 64 up to 64 x 384 (whichever is
+ * estimated to be fastest for rows, D_in and D_out), so that the tiles fill the
+ * compute units.  The summation order of an output, and so its last bits,
+ * depends on the tile.
  */
 grkan_status_t grkan_linear_fwd(const void *x, const float *A, const float *B, const void *W,
                                 const float *bias, void *out,
                                 int64_t rows, int32_t D_in, int32_t D_out, int32_t G,
                                 int32_t m, int32_t n, grkan_dtype_t io, grkan_dtype_t out_dtype,
                                 void *hip_stream);
+
+/*
+ * Host-only: the estimated device time of grkan_linear_fwd in microseconds
+ * (rounds of workgroups times the measured time of a round of the tile that is
+ * used), for callers that choose between it and grkan_fwd plus a product of
+ * their own.  0 for sizes that are not positive.
+ */
+double grkan_linear_estimate_us(int64_t rows, int32_t D_in, int32_t D_out);
 
 /*
  * The same layer with the weights in a packed copy, for callers whose weights do

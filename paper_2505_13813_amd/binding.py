@@ -89,6 +89,8 @@ def load_library():
     lib.grkan_linear_fwd.restype = ctypes.c_int
     lib.grkan_linear_fwd_packed.argtypes = lib.grkan_linear_fwd.argtypes
     lib.grkan_linear_fwd_packed.restype = ctypes.c_int
+    lib.grkan_linear_estimate_us.argtypes = [i64, i32, i32]
+    lib.grkan_linear_estimate_us.restype = ctypes.c_double
     lib.grkan_linear_packed_w_bytes.argtypes = [i32, i32]
     lib.grkan_linear_packed_w_bytes.restype = ctypes.c_size_t
     lib.grkan_linear_pack_w.argtypes = [vp, vp, i32, i32, vp]
@@ -326,6 +328,11 @@ def grkan_linear_fwd(x, A, B, W, bias=None, out=None, out_dtype=None, stream=Non
     if st:
         raise GrkanError(st, "grkan_linear_fwd_packed" if packed else "grkan_linear_fwd")
     return out
+
+
+def grkan_linear_estimate_us(rows: int, D_in: int, D_out: int) -> float:
+    """Estimated device time of grkan_linear_fwd in microseconds (host only)."""
+    return float(load_library().grkan_linear_estimate_us(int(rows), int(D_in), int(D_out)))
 
 
 NOALLOC_SCRATCH_BYTES = 4 << 20

@@ -77,8 +77,19 @@ struct LinArgs {
     int32_t dgc;       // channels per coefficient group (a multiple of 32)
     int32_t mblocks;   // ceil(rows / BM)
     int32_t nblocks;   // ceil(Nout / BN)
-    int32_t wtiles;    // packed W only: 16-row tiles per stage, nblocks * BN / 16
+    int32_t wtiles;    // packed W only: 16-row tiles per stage
+    int32_t n_major;   // small kernel: tiles of one channel block share an XCD (else: of one token block)
 };
+
+// LDS of the small kernel: four x buffers of a 64-k block for each group of WN wavefronts, and a ring of
+// 2 KB weight slots per wavefront, as deep as 160 KB allow
+constexpr int small_x_bytes(int MT, int WN) { return (8 / WN) * 4 * MT * 2048; }
+constexpr int small_ring(int MT, int WN)
+{
+    const int fit = (160 * 1024 - small_x_bytes(MT, WN)) / (8 * 2048);
+    return fit > 8 ? 8 : fit;
+}
+constexpr size_t small_lds_bytes(int MT, int WN) { return (size_t)8 * small_ring(MT, WN) * 2048 + small_x_bytes(MT, WN); }
 
 __device__ __forceinline__ uint64_t uniform_u64(uint64_t v)
 {
@@ -646,6 +657,323 @@ __global__ __launch_bounds__(64 * NW, 1) void grkan_linear_fwd_kernel(const LinA
 }
 
 // --------------------------------------------------------------------------
+// the same layer for inputs of too few rows to fill the chip with 112-row tiles
+// --------------------------------------------------------------------------
+//
+// A workgroup of eight wavefronts, WK groups of WN: group kg takes the 64-k blocks kg, kg + WK, .. of
+// the contraction, wavefront wn of a group the 16 NT channels [16 NT wn, 16 NT (wn + 1)) of the tile, all
+// of them the tile's BM = 16 MT tokens; the WK partial tiles are added in group order at the end.
+//   * W: LDS-direct loads into a ring of kRing 2 KB slots per wavefront (16 rows x 64 k), private to it;
+//     the two 64-byte halves of the rows are fetched back to back, so that the second half of each
+//     cache line comes from the vector cache (measured from L2: 50 B per clock and CU, 26 when the
+//     halves are fetched apart).
+//   * x: LDS-direct loads too, three blocks ahead, in the layout of the weights; a wavefront replaces the
+//     units it has fetched by F of them in place, one block ahead of their use.  (With LDS-direct loads in
+//     flight the compiler can wait for a load into registers only by waiting for everything.)  With WN = 1
+//     a wavefront reads what it wrote itself and the loop has no barrier.
+template <int MT, int NT, int WN, typename OUT, bool PACKED, int M, int N>
+__global__ __launch_bounds__(512, 1) void grkan_linear_small_kernel(const LinArgs a)
+{
+    constexpr int WK = 8 / WN;
+    constexpr int BM = 16 * MT;
+    constexpr int BN = 16 * NT * WN;
+    constexpr int PU = 2 * MT / WN; // 16-row, 32-k units of x a wavefront turns into F per block
+    constexpr uint32_t kXB = 2u * MT * 1024u; // bytes of a block of x: unit q at 1024 q, half q / MT, rows 16 (q % MT) ..
+    constexpr int kRing = small_ring(MT, WN);
+    constexpr uint32_t kX0 = 8u * kRing * 2048u;
+    static_assert(WN * WK == 8 && PU >= 1 && PU * WN == 2 * MT, "eight wavefronts share the units of a block evenly");
+    static_assert(kRing <= 2 * NT + 2, "a weight tile waited for must be younger than the x needed with it");
+    extern __shared__ __align__(16) char smem[];
+    const lptr_t lds = (lptr_t)smem;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wn = wave % WN;
+    const int kg = wave / WN;
+
+    // Workgroup -> tile.  Workgroups go round-robin over the 8 XCDs; the tiles that share the larger of the
+    // two operands' slices run on one XCD, so that its L2 is the only one to fetch them.
+    const int xcd = (int)blockIdx.x & 7;
+    const int slot = (int)blockIdx.x >> 3;
+    int mb, nb;
+    if (a.n_major) {
+        mb = slot % a.mblocks;
+        nb = (slot / a.mblocks) * 8 + xcd;
+    } else {
+        nb = slot % a.nblocks;
+        mb = (slot / a.nblocks) * 8 + xcd;
+    }
+    if (mb >= a.mblocks || nb >= a.nblocks)
+        return;
+    const int64_t m0 = (int64_t)mb * BM;
+    const int32_t n0 = nb * BN;
+    const uint32_t K2 = (uint32_t)a.K * 2u;
+    const int32_t n_blocks = a.K >> 6;
+    const int32_t n_iter = (n_blocks + WK - 1) / WK;           // the same for every wavefront (barriers)
+    const int32_t mine = (n_blocks - kg + WK - 1) / WK;        // blocks of this group
+
+    // 16-byte pieces of a row are permuted as in the big kernel: slot = piece xor g(row)
+    const uint32_t w_g = (uint32_t)((lane >> 4) ^ (lane >> 3)) & 3u;
+
+    // ---- x: unit q = wn PU + u of a block is half q / MT of the 64 k, rows 16 (q % MT) + lane / 4
+    uint32_t x_lane[PU];
+#pragma unroll
+    for (int u = 0; u < PU; ++u) {
+        const int q = wn * PU + u;
+        int64_t xg = m0 + 16 * (q % MT) + (lane >> 2);
+        if (xg > a.rows - 1)
+            xg = a.rows - 1; // rows past the end read the last row (never stored)
+        x_lane[u] = (uint32_t)((xg - m0) * (int64_t)K2) + (uint32_t)(q / MT) * 64u + (((uint32_t)lane & 3u) ^ w_g) * 16u;
+    }
+    const uint64_t x_base = reinterpret_cast<uint64_t>(a.x) + (uint64_t)m0 * K2;
+    // byte offset inside a row of this group's block i (blocks past the end repeat the last one)
+    const int32_t last = mine > 0 ? mine - 1 : 0;
+    auto kbyte = [&](int32_t i) {
+        const int32_t b = kg + (i < last ? i : last) * WK;
+        return (uint32_t)(b < n_blocks ? b : n_blocks - 1) * 128u; // (a group without any block: never consumed)
+    };
+    const uint32_t x_group = kX0 + (uint32_t)kg * 4u * kXB;                          // this group's four buffers
+    const uint32_t x_own = x_group + (uint32_t)(wn * PU) * 1024u;                    // this wavefront's units
+
+    // ---- W ring
+    uint64_t w_base;
+    uint32_t w_lane[NT];
+    const uint64_t w_stage_bytes = (uint64_t)(uint32_t)a.wtiles * 1024u; // packed: bytes per 32 k
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+        if constexpr (PACKED) {
+            int t = (n0 >> 4) + NT * wn + i;
+            if (t > a.wtiles - 1)
+                t = a.wtiles - 1;
+            w_lane[i] = (uint32_t)t * 1024u + (uint32_t)lane * 16u;
+        } else {
+            int r = n0 + 16 * (NT * wn + i) + (lane >> 2);
+            if (r > a.Nout - 1)
+                r = a.Nout - 1;
+            w_lane[i] = (uint32_t)(r - n0) * K2 + (((uint32_t)lane & 3u) ^ w_g) * 16u;
+        }
+    }
+    w_base = reinterpret_cast<uint64_t>(a.W) + (PACKED ? 0 : (uint64_t)(uint32_t)n0 * K2);
+    const lptr_t ring = lds + (uint32_t)wave * (kRing * 2048u);
+    // operand read: row lane % 16 of a 1 KB unit, piece lane / 16
+    const uint32_t op_lane = (uint32_t)(lane & 15) * kWRow +
+                             ((((uint32_t)(lane >> 4)) ^ ((uint32_t)(((lane & 15) >> 2) ^ ((lane & 15) >> 1)) & 3u)) * 16u);
+    const uint32_t ring_read = lds0 + (uint32_t)wave * (kRing * 2048u) + op_lane;
+    // tile i (static) of the group's block `blk` into ring slot `slot_bytes`
+    auto w_fetch = [&](auto ic, int32_t blk, uint32_t slot_bytes) {
+        constexpr int i = decltype(ic)::value;
+        const uint32_t kb = kbyte(blk);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            gcptr_t src;
+            if constexpr (PACKED)
+                src = (gcptr_t)uniform_u64(w_base + (uint64_t)((kb >> 6) + h) * w_stage_bytes) + w_lane[i];
+            else
+                src = (gcptr_t)uniform_u64(w_base + kb + h * 64u) + w_lane[i];
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
+                                             (__attribute__((address_space(3))) void *)(ring + slot_bytes + h * 1024u), 16, 0, 0);
+        }
+    };
+
+    // ---- coefficients of the groups of the wave's units (one group per 32 k)
+    typedef const __attribute__((address_space(4))) float *cfloat_ptr;
+    constexpr int kHalves = PU > MT ? 2 : 1; // halves of the 64 k the wave's units lie in
+    Coef<M, N> c[kHalves];
+    int cur_g[kHalves];
+    auto coef_for = [&](int32_t i, bool first) {
+#pragma unroll
+        for (int h = 0; h < kHalves; ++h) {
+            const uint32_t k = kbyte(i) / 2u + (uint32_t)((wn * PU) / MT + h) * 32u;
+            const int g = __builtin_amdgcn_readfirstlane((int)(k / (uint32_t)a.dgc));
+            if (first || g != cur_g[h]) {
+                const cfloat_ptr pa = (cfloat_ptr)(uintptr_t)(a.A + (size_t)g * (M + 1));
+                const cfloat_ptr pb = (cfloat_ptr)(uintptr_t)(a.B + (size_t)g * N);
+#pragma unroll
+                for (int j = 0; j <= M; ++j)
+                    c[h].a[j] = pa[j];
+#pragma unroll
+                for (int j = 0; j < N; ++j)
+                    c[h].b[j] = pb[j];
+                cur_g[h] = g;
+            }
+            // In vector registers from here on: an instruction with a scalar operand issues at 0.6 of the rate
+            // (these tiles are bound by the F evaluations: 5 % of their time).
+#pragma unroll
+            for (int j = 0; j <= M; ++j)
+                asm volatile("" : "+v"(c[h].a[j]));
+#pragma unroll
+            for (int j = 0; j < N; ++j)
+                asm volatile("" : "+v"(c[h].b[j]));
+        }
+    };
+
+    auto x_fetch = [&](int32_t i) {
+        const uint64_t base = uniform_u64(x_base + kbyte(i));
+#pragma unroll
+        for (int u = 0; u < PU; ++u)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)((gcptr_t)base + x_lane[u]),
+                                             (__attribute__((address_space(3))) void *)(lds + x_own + ((uint32_t)i & 3u) * kXB + u * 1024u),
+                                             16, 0, 0);
+    };
+    // the wavefront's units of the group's block i
+    auto x_at = [&](int32_t i) { return lds0 + x_own + ((uint32_t)i & 3u) * kXB + (uint32_t)lane * 16u; };
+    auto x_raw = [&](u32x4 (&v)[PU], int32_t i) {
+#pragma unroll
+        for (int u = 0; u < PU; ++u)
+            v[u] = *(const __attribute__((address_space(3))) u32x4 *)(uintptr_t)(x_at(i) + u * 1024u);
+    };
+    auto f_write = [&](const u32x4 (&v)[PU], int32_t i) {
+#pragma unroll
+        for (int u = 0; u < PU; ++u)
+            lds_write16(x_at(i) + u * 1024u, v[u]);
+    };
+
+    auto block_barrier = [&]() {
+        // with one wavefront per group the F values it reads are its own (LDS accesses of a wavefront are in order)
+        if constexpr (WN > 1)
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        else
+            asm volatile("" ::: "memory");
+    };
+
+    f32x4 acc[NT][MT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+            acc[nt][mt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+    // ---- prologue: x of the first three blocks, the ring filled, F of the first block
+    x_fetch(0);
+    x_fetch(1);
+    x_fetch(2);
+    static_for<0, kRing - 1>([&](auto tc) {
+        constexpr int t = decltype(tc)::value;
+        w_fetch(std::integral_constant<int, t % NT>{}, t / NT, (uint32_t)t * 2048u);
+    });
+    coef_for(0, true);
+    wait_loads<2 * (kRing - 1) + 2 * PU>(); // x of block 0
+    {
+        u32x4 v[PU];
+        x_raw(v, 0);
+#pragma unroll
+        for (int u = 0; u < PU; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                v[u][j] = rational_pair<M, N>(v[u][j], c[kHalves == 2 ? u / MT : 0]);
+        f_write(v, 0);
+    }
+    coef_for(1, false);
+    block_barrier();
+
+    // Tile t of the walk (block t / NT of the group, 16-row tile t % NT) sits in ring slot t % kRing.  Step t
+    // first refills the slot of tile t - 1 (multiplied in the step before), then waits for tile t + 1 by
+    // load count (and so for the x of block b + 1, which is older) and reads its operands, then multiplies tile t.  The refills past the end of the walk fetch
+    // its last block again, so that the count stays the same to the end; they are never read.  (x loads
+    // issued in between only make the wait stricter than it has to be.)
+    uint32_t s_cur = 0;                          // slot of tile t, in bytes
+    auto next_slot = [&](uint32_t s) { return s + 2048u == kRing * 2048u ? 0u : s + 2048u; };
+    bf16x8 w0, w1;
+    wait_loads<2 * (kRing - 2)>();
+    w0 = lds_read16(ring_read);
+    w1 = lds_read16(ring_read + 1024u);
+
+    for (int32_t b = 0; b < mine; ++b) {
+        x_fetch(b + 3); // into the buffer of block b - 1
+        bf16x8 xf[2][MT];
+        const uint32_t fb = lds0 + x_group + ((uint32_t)b & 3u) * kXB + op_lane;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+                xf[h][mt] = lds_read16(fb + (uint32_t)(h * MT + mt) * 1024u);
+        constexpr int kWords = 4 * PU;                         // words of x (two elements) a lane turns into F
+        constexpr int kWordsPerStep = (kWords + NT - 1) / NT;
+        u32x4 xv[PU], y[PU];
+        static_for<0, NT>([&](auto ntc) {
+            constexpr int nt = decltype(ntc)::value;
+            // tile t - 1 + kRing = block b + (nt - 1 + kRing) / NT, into the slot before this one
+            // (the operands of tile t are in their registers here, so those of tile t - 1, read before them, are too)
+            constexpr int ahead = nt - 1 + kRing;
+            const uint32_t s_prev = s_cur == 0 ? (kRing - 1) * 2048u : s_cur - 2048u;
+            asm volatile("" ::"v"(w0), "v"(w1) : "memory");
+            w_fetch(std::integral_constant<int, ahead % NT>{}, b + ahead / NT, s_prev);
+            wait_loads<2 * (kRing - 2)>();
+            s_cur = next_slot(s_cur);
+            const bf16x8 n0v = lds_read16(ring_read + s_cur);
+            const bf16x8 n1v = lds_read16(ring_read + s_cur + 1024u);
+            if constexpr (nt == 0)
+                x_raw(xv, b + 1);
+            // F of the next block in pieces between the matrix instructions (see rational_piece)
+            PairState ps[kWordsPerStep];
+            uint32_t res[kWordsPerStep];
+            static_for<0, 2 * MT>([&](auto mc) {
+                constexpr int m = decltype(mc)::value;
+                constexpr int mt = m % MT;
+                acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(m < MT ? w0 : w1, xf[m / MT][mt], acc[nt][mt], 0, 0, 0);
+                static_for<0, 7>([&](auto sc) {
+                    constexpr int sp = decltype(sc)::value;
+                    if constexpr (sp * 2 * MT / 7 == m) {
+                        static_for<0, kWordsPerStep>([&](auto ic) {
+                            constexpr int j = nt * kWordsPerStep + decltype(ic)::value;
+                            if constexpr (j < kWords)
+                                rational_piece<sp>(ps[decltype(ic)::value], xv[j >> 2][j & 3],
+                                                   c[kHalves == 2 ? (j >> 2) / MT : 0], res[decltype(ic)::value]);
+                        });
+                    }
+                });
+            });
+            static_for<0, kWordsPerStep>([&](auto ic) {
+                constexpr int j = nt * kWordsPerStep + decltype(ic)::value;
+                if constexpr (j < kWords)
+                    y[j >> 2][j & 3] = res[decltype(ic)::value];
+            });
+            w0 = n0v;
+            w1 = n1v;
+        });
+        f_write(y, b + 1);
+        coef_for(b + 2, false);
+        block_barrier();
+    }
+    if (mine < n_iter) // a group with one block less than others: the same number of barriers for all
+        block_barrier();
+
+    // ---- epilogue: the partial tiles go to LDS as [WK][BM][BN + 4] float32 and leave as whole rows
+    constexpr int kPitchF = BN + 4;
+    static_assert((size_t)WK * BM * kPitchF * 4 <= small_lds_bytes(MT, WN), "partial tiles must fit the operand buffers");
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // every fetch into the ring has landed
+    __syncthreads();
+    {
+        const uint32_t dst = lds0 + ((uint32_t)kg * BM + (uint32_t)(lane & 15)) * (kPitchF * 4u) +
+                             (uint32_t)(wn * 16 * NT + (lane >> 4) * 4) * 4u;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+                *(__attribute__((address_space(3))) f32x4 *)(uintptr_t)(dst + (uint32_t)(mt * 16) * (kPitchF * 4u) + (uint32_t)nt * 64u) =
+                    acc[nt][mt];
+    }
+    __syncthreads();
+    constexpr int QPR = BN / 4; // four channels per lane
+    for (int i = tid; i < BM * QPR; i += 512) {
+        const int r = i / QPR;
+        const int o = n0 + (i - r * QPR) * 4;
+        if (m0 + r >= a.rows || o >= a.Nout)
+            continue;
+        const uint32_t src = lds0 + (uint32_t)r * (kPitchF * 4u) + (uint32_t)(o - n0) * 4u;
+        f32x4 v = *(const __attribute__((address_space(3))) f32x4 *)(uintptr_t)src;
+#pragma unroll
+        for (int g = 1; g < WK; ++g)
+            v += *(const __attribute__((address_space(3))) f32x4 *)(uintptr_t)(src + (uint32_t)g * (BM * kPitchF * 4u));
+        if (a.bias)
+            v += *(const f32x4 *)(a.bias + o);
+        OutPack<OUT>::store((gptr_t)(a.out + ((m0 + r) * a.Nout + o) * (int)sizeof(OUT)), v);
+    }
+}
+
+// --------------------------------------------------------------------------
 // host side
 // --------------------------------------------------------------------------
 using LinKernel = void (*)(const LinArgs);
@@ -669,6 +997,68 @@ static Variant pick_variant(int32_t D_out)
     return Variant{4, 3};
 }
 
+// Tile variants of the small kernel: (16-token sub-tiles, 16-channel sub-tiles per wave, waves side by side)
+struct SmallVariant {
+    int mt, nt, wn;
+    double fixed_us, us_per_1k; // time of one round of workgroups: fixed_us + us_per_1k D_in / 1024
+    int bm() const { return 16 * mt; }
+    int bn() const { return 16 * nt * wn; }
+};
+
+// One round of up to 256 workgroups (one per compute unit) takes a time that depends on the tile and D_in
+// only, and the time of a layer is that times the rounds, to within 15 % over 1 .. 12,608 rows of 3072 -> 768,
+// 1536 -> 384, 768 -> 192 and 768 -> 3072 (measured on MI355X, us per round at D_in = 768 / 1536 / 3072, the
+// chip filled):
+//   16 x 64: 6.6 / 7.8 / 11.7    32 x 128: 8.5 / 12.2 / 20.5    64 x 192: 13.2 / 21 / 36
+//   64 x 384: 17.5 / 28.5 / 51   112 x 768: 41 / - / 133   112 x 384: - / 43 / -   112 x 192: 24 / - / -
+static const SmallVariant kSmall[] = {
+    {1, 4, 1, 4.8, 2.3},
+    {2, 4, 2, 4.4, 5.3},
+    {4, 3, 4, 5.7, 10.1},
+    {4, 3, 8, 6.5, 14.7},
+};
+constexpr int kRound = 256;
+
+static double rounds_us(int64_t rows, int32_t D_in, int32_t D_out, int bm, int bn, double fixed_us, double us_per_1k)
+{
+    const int64_t wgs = ((rows + bm - 1) / bm) * (((int64_t)D_out + bn - 1) / bn);
+    return (double)((wgs + kRound - 1) / kRound) * (fixed_us + us_per_1k * D_in / 1024.0);
+}
+
+// The tile for a layer: the one with the least estimated time.  A layer of few rows takes many small tiles
+// (each evaluates F on its rows for its channels only, over all of the contraction), one that fills the chip
+// with 112-row tiles takes those (NULL).  The choice depends on the sizes alone, never on the packing.
+static const SmallVariant *pick_small(int64_t rows, int32_t D_in, int32_t D_out, double *estimate_us)
+{
+    const Variant v = pick_variant(D_out);
+    double best = v.nt == 6 ? rounds_us(rows, D_in, D_out, kBM, v.bn(), 10.5, 40.0)
+                            : rounds_us(rows, D_in, D_out, kBM, v.bn(), 5.0, 24.0);
+    const SmallVariant *pick = nullptr;
+    for (const SmallVariant &s : kSmall) {
+        const double t = rounds_us(rows, D_in, D_out, s.bm(), s.bn(), s.fixed_us, s.us_per_1k);
+        if (t < best) {
+            best = t;
+            pick = &s;
+        }
+    }
+    if (estimate_us)
+        *estimate_us = best;
+    return pick;
+}
+
+template <typename OUT, bool PACKED> static LinKernel select_small(SmallVariant v)
+{
+    if (v.mt == 1 && v.nt == 4 && v.wn == 1)
+        return grkan_linear_small_kernel<1, 4, 1, OUT, PACKED, 5, 4>;
+    if (v.mt == 2 && v.nt == 4 && v.wn == 2)
+        return grkan_linear_small_kernel<2, 4, 2, OUT, PACKED, 5, 4>;
+    if (v.mt == 4 && v.nt == 3 && v.wn == 4)
+        return grkan_linear_small_kernel<4, 3, 4, OUT, PACKED, 5, 4>;
+    if (v.mt == 4 && v.nt == 3 && v.wn == 8)
+        return grkan_linear_small_kernel<4, 3, 8, OUT, PACKED, 5, 4>;
+    return nullptr;
+}
+
 template <typename OUT, bool PACKED> static LinKernel select_kernel(Variant v, bool nedge)
 {
     if (v.nw == 8 && v.nt == 6)
@@ -688,12 +1078,12 @@ static size_t lds_bytes(Variant v) { return (size_t)2 * kXBuf + (size_t)2 * v.bn
 static bool allow_lds(const void *kernel, size_t bytes)
 {
     static std::mutex mu;
-    static const void *done[64][16];
+    static const void *done[64][32];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64)
         return false;
     std::lock_guard<std::mutex> lock(mu);
-    for (int i = 0; i < 16; ++i) {
+    for (int i = 0; i < 32; ++i) {
         if (done[dev][i] == kernel)
             return true;
         if (!done[dev][i]) {
@@ -775,16 +1165,21 @@ static grkan_status_t linear_fwd_impl(const void *x, const float *A, const float
         return GRKAN_OK;
 
     const Variant v = pick_variant(D_out);
-    const int bn = v.bn();
+    const SmallVariant *const small = pick_small(rows, D_in, D_out, nullptr);
+    const int bm = small ? small->bm() : kBM, bn = small ? small->bn() : v.bn();
     const bool nedge = D_out % bn != 0;
     LinKernel kernel;
-    if (packed)
+    if (small && packed)
+        kernel = out_dtype == GRKAN_BF16 ? select_small<bf16_out, true>(*small) : select_small<float, true>(*small);
+    else if (small)
+        kernel = out_dtype == GRKAN_BF16 ? select_small<bf16_out, false>(*small) : select_small<float, false>(*small);
+    else if (packed)
         kernel = out_dtype == GRKAN_BF16 ? select_kernel<bf16_out, true>(v, nedge) : select_kernel<float, true>(v, nedge);
     else
         kernel = out_dtype == GRKAN_BF16 ? select_kernel<bf16_out, false>(v, nedge) : select_kernel<float, false>(v, nedge);
     if (!kernel)
         return GRKAN_ERR_LAUNCH;
-    const size_t lds = lds_bytes(v);
+    const size_t lds = small ? small_lds_bytes(small->mt, small->wn) : lds_bytes(v);
     if (!allow_lds(reinterpret_cast<const void *>(kernel), lds))
         return GRKAN_ERR_LAUNCH;
 
@@ -799,17 +1194,19 @@ static grkan_status_t linear_fwd_impl(const void *x, const float *A, const float
     a.K = D_in;
     a.Nout = D_out;
     a.dgc = D_in / G;
-    const int64_t mblocks = (rows + kBM - 1) / kBM;
+    const int64_t mblocks = (rows + bm - 1) / bm;
     const int64_t nblocks = (D_out + bn - 1) / bn;
-    const int64_t grid = ((mblocks + 7) / 8) * 8 * nblocks;
+    // small kernel: the tiles that share the larger operand's slice on one XCD
+    a.n_major = small && rows < D_out;
+    const int64_t grid = a.n_major ? ((nblocks + 7) / 8) * 8 * mblocks : ((mblocks + 7) / 8) * 8 * nblocks;
     if (mblocks > INT32_MAX / 2 || grid > INT32_MAX)
         return GRKAN_ERR_UNSUPPORTED;
     a.mblocks = (int32_t)mblocks;
     a.nblocks = (int32_t)nblocks;
     a.wtiles = (int32_t)packed_tiles(D_out);
     void *args[] = {&a};
-    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3((unsigned)grid), dim3(64 * v.nw),
-                                         args, lds, static_cast<hipStream_t>(hip_stream));
+    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3((unsigned)grid),
+                                         dim3(small ? 512 : 64 * v.nw), args, lds, static_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? GRKAN_OK : GRKAN_ERR_LAUNCH;
 }
 
@@ -834,6 +1231,15 @@ extern "C" grkan_status_t grkan_linear_fwd_packed(const void *x, const float *A,
                                                   void *hip_stream)
 {
     return linear_fwd_impl(x, A, B, Wp, true, bias, out, rows, D_in, D_out, G, m, n, io, out_dtype, hip_stream);
+}
+
+extern "C" double grkan_linear_estimate_us(int64_t rows, int32_t D_in, int32_t D_out)
+{
+    if (rows <= 0 || D_in <= 0 || D_out <= 0)
+        return 0.0;
+    double us = 0.0;
+    pick_small(rows, D_in, D_out, &us);
+    return us;
 }
 
 extern "C" size_t grkan_linear_packed_w_bytes(int32_t D_in, int32_t D_out)

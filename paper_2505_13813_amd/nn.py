@@ -81,15 +81,22 @@ def fused_layer_supported(x, A, weight) -> bool:
 
 
 def fused_layer_pays(rows: int, D_in: int, D_out: int) -> bool:
-    """Whether the one-kernel layer is the faster route at this size (measured on MI355X, bfloat16).
-    A workgroup owns 112 tokens x one channel block (768, 384 or 192 channels) and walks the whole
-    contraction by itself, so the kernel needs about as many workgroups as the chip has compute units:
-    at D_in = 3072 -> 768 it takes 109 us for anything up to 6,000 tokens (the two kernels: 34 - 53 us)
-    and wins from about 20,000 tokens on (135 against 192 us at 25,216); with a short contraction
-    (D_in <= 768) a workgroup is quick and one launch instead of two wins at every size measured."""
+    """Whether the layer's 112-row tiles (of 768, 384 or 192 channels) fill the chip, or the contraction is so
+    short that a tile is quick: the sizes at which that tile alone is the faster route.  (The module decides
+    by one_kernel_is_faster, which knows the smaller tiles too.)"""
     bn = 768 if D_out % 768 == 0 else (384 if D_out % 384 == 0 else 192)
     workgroups = -(-int(rows) // 112) * -(-int(D_out) // bn)
     return workgroups >= 200 or D_in <= 768
+
+
+def one_kernel_is_faster(rows: int, D_in: int, D_out: int) -> bool:
+    """Whether the one-kernel layer is the faster route in inference (measured on MI355X, bfloat16, 50 - 25,216
+    rows of ten layer shapes).  The two kernels take about 11 us + the elementwise pass at 5.5 TB/s + the
+    library product at 950 TFLOP/s, and 50 us of host time, so that one launch of up to 25 us is faster
+    whatever the device times are (3072 -> 768: 197 rows 21.6 us against 54 us of wall time, 6,304 rows 56
+    against 59, 12,608 rows 107 against 96, 25,216 rows 133 against 197)."""
+    two_us = 11.0 + rows * D_in * 4 / 5.5e6 + 2.0 * rows * D_in * D_out / 0.95e9
+    return binding.grkan_linear_estimate_us(rows, D_in, D_out) <= max(25.0, two_us)
 
 
 class GRKANLayerFunction(torch.autograd.Function):
@@ -215,8 +222,8 @@ class GRKANLinear(nn.Module):
                  degrees: Tuple[int, int] = (M_DEGREE, N_DEGREE), fused: str = "inference"):
         """`fused`: when the one-kernel layer (F inside the matrix product) is used where it applies
         (bfloat16, see fused_layer_supported): "inference" = when no gradient is recorded (in training
-        its backward pass has to recompute F(x)) and the input is large enough for it to be the faster
-        route (fused_layer_pays); "always" = wherever it applies; "never"."""
+        its backward pass has to recompute F(x)) and it is the faster route at this size
+        (one_kernel_is_faster); "always" = wherever it applies; "never"."""
         super().__init__()
         if in_features % groups:
             raise ValueError("in_features must be a multiple of groups")
@@ -252,8 +259,8 @@ class GRKANLinear(nn.Module):
             A, B = self.rational.coefficient_rows()
             if fused_layer_supported(x, A, self.linear.weight):
                 rows = x.numel() // x.shape[-1]
-                pays = self.fused == "always" or fused_layer_pays(rows, x.shape[-1], self.linear.weight.shape[0])
-                if not torch.is_grad_enabled() and pays:
+                if not torch.is_grad_enabled() and (
+                        self.fused == "always" or one_kernel_is_faster(rows, x.shape[-1], self.linear.weight.shape[0])):
                     pw, b32, A32, B32 = self._inference_weights()
                     return binding.grkan_linear_fwd(x.contiguous(), A32, B32, pw, b32, out_dtype=x.dtype)
                 if self.fused == "always":
@@ -270,9 +277,9 @@ class KATMlp(nn.Module):
                  degrees: Tuple[int, int] = (M_DEGREE, N_DEGREE), fused: str = "inference"):
         super().__init__()
         hidden = 4 * dim if hidden is None else hidden
-        # the one-kernel layer pays for the wide input (fc2: long contraction, few outputs); for fc1
-        # the library product after the elementwise kernel is faster on this hardware
-        self.fc1 = GRKANLinear(dim, hidden, groups, init="identity", degrees=degrees, fused="never")
+        # in training the library product after the elementwise kernel is the faster route for fc1
+        self.fc1 = GRKANLinear(dim, hidden, groups, init="identity", degrees=degrees,
+                               fused="never" if fused == "never" else "inference")
         self.fc2 = GRKANLinear(hidden, dim, groups, init="swish", degrees=degrees, fused=fused)
 
     def forward(self, x):
