@@ -250,6 +250,25 @@ grkan_status_t grkan_linear_fwd_packed(const void *x, const float *A, const floa
                                        void *hip_stream);
 
 /*
+ * Gradients of the layer's product (training): with out = Y W^T + bias, Y = F(x) [rows, D_in],
+ *
+ *     dW[o, i] = sum_r dout[r, o] Y[r, i]        dbias[o] = sum_r dout[r, o]
+ *
+ * in bfloat16 with float32 sums; OVERWRITTEN, fixed summation order, no atomics.
+ *   dout DEVICE bfloat16 [rows, D_out], y DEVICE bfloat16 [rows, D_in], dW DEVICE bfloat16 [D_out, D_in]:
+ *        contiguous, 16-byte aligned; dbias DEVICE bfloat16 [D_out] or NULL
+ *   workspace DEVICE scratch of grkan_linear_wgrad_workspace_bytes() bytes (host-only query; 0 for sizes the
+ *        kernel does not cover), 16-byte aligned, untouched until the enqueued work has finished
+ * io must be GRKAN_BF16 (else GRKAN_ERR_DTYPE); D_in and D_out must be multiples of 8 (else
+ * GRKAN_ERR_UNSUPPORTED).  rows == 0 writes zeros.
+ */
+size_t grkan_linear_wgrad_workspace_bytes(int64_t rows, int32_t D_in, int32_t D_out);
+grkan_status_t grkan_linear_wgrad(const void *dout, const void *y, void *dW, void *dbias,
+                                  void *workspace, size_t workspace_bytes,
+                                  int64_t rows, int32_t D_in, int32_t D_out,
+                                  grkan_dtype_t io, void *hip_stream);
+
+/*
  * grkan_bwd for callers that cannot allocate device memory or pass a workspace:
  * code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Same arguments, results and kernels as grkan_bwd (bit-identical

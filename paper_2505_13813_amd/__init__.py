@@ -18,7 +18,9 @@ from .binding import (  # noqa: F401
     grkan_bwd_workspace_bytes,
     grkan_fwd,
     PackedWeight,
+    grkan_linear_estimate_us,
     grkan_linear_fwd,
+    grkan_linear_wgrad,
     grkan_linear_pack_w,
     grkan_fwd_raw,
     load_library,

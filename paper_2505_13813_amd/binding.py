@@ -89,6 +89,10 @@ def load_library():
     lib.grkan_linear_fwd.restype = ctypes.c_int
     lib.grkan_linear_fwd_packed.argtypes = lib.grkan_linear_fwd.argtypes
     lib.grkan_linear_fwd_packed.restype = ctypes.c_int
+    lib.grkan_linear_wgrad.argtypes = [vp, vp, vp, vp, vp, sz, i64, i32, i32, ctypes.c_int, vp]
+    lib.grkan_linear_wgrad.restype = ctypes.c_int
+    lib.grkan_linear_wgrad_workspace_bytes.argtypes = [i64, i32, i32]
+    lib.grkan_linear_wgrad_workspace_bytes.restype = sz
     lib.grkan_linear_estimate_us.argtypes = [i64, i32, i32]
     lib.grkan_linear_estimate_us.restype = ctypes.c_double
     lib.grkan_linear_packed_w_bytes.argtypes = [i32, i32]
@@ -333,6 +337,31 @@ def grkan_linear_fwd(x, A, B, W, bias=None, out=None, out_dtype=None, stream=Non
 def grkan_linear_estimate_us(rows: int, D_in: int, D_out: int) -> float:
     """Estimated device time of grkan_linear_fwd in microseconds (host only)."""
     return float(load_library().grkan_linear_estimate_us(int(rows), int(D_in), int(D_out)))
+
+
+def grkan_linear_wgrad(dout, y, bias: bool = True, stream=None):
+    """(dW, dbias or None) of out = y W^T + bias: dout [..., D_out] and y [..., D_in] contiguous bfloat16
+    of the same leading shape; dW [D_out, D_in] and dbias [D_out] bfloat16."""
+    import torch
+
+    if not dout.is_cuda or y.device != dout.device or dout.dtype != torch.bfloat16 or y.dtype != torch.bfloat16:
+        raise ValueError("dout and y must be bfloat16 tensors on one HIP device")
+    if not dout.is_contiguous() or not y.is_contiguous() or dout.dim() < 1 or dout.shape[:-1] != y.shape[:-1]:
+        raise ValueError("dout and y must be contiguous and agree in all but the last dimension")
+    D_out, D_in = int(dout.shape[-1]), int(y.shape[-1])
+    rows = int(dout.numel() // D_out) if D_out else 0
+    lib = load_library()
+    need = int(lib.grkan_linear_wgrad_workspace_bytes(rows, D_in, D_out))
+    if need == 0:
+        raise GrkanError(8, "grkan_linear_wgrad_workspace_bytes")
+    ws = torch.empty(need, dtype=torch.uint8, device=dout.device)
+    dW = torch.empty((D_out, D_in), dtype=torch.bfloat16, device=dout.device)
+    db = torch.empty(D_out, dtype=torch.bfloat16, device=dout.device) if bias else None
+    st = int(lib.grkan_linear_wgrad(dout.data_ptr(), y.data_ptr(), dW.data_ptr(), db.data_ptr() if bias else None,
+                                    ws.data_ptr(), need, rows, D_in, D_out, GRKAN_BF16, _stream_ptr(stream)))
+    if st:
+        raise GrkanError(st, "grkan_linear_wgrad")
+    return dW, db
 
 
 NOALLOC_SCRATCH_BYTES = 4 << 20

@@ -132,6 +132,69 @@ class GRKANLayerFunction(torch.autograd.Function):
         return dx, dA, dB, dW, dbias
 
 
+def wgrad_pays(rows: int, D_in: int, D_out: int) -> bool:
+    """Whether grkan_linear_wgrad is the faster route for the gradients of a bfloat16 product (measured on
+    MI355X against the library's product and column sum): it was at every size tried from 640 rows up
+    (25,216 rows: 384 x 1536 50 us against 184, 768 x 3072 143 against 308; 1,000 rows of 384 x 1536 20 against
+    23) as long as its 192 x 192 tiles fit the chip's 256 compute units once; but below about 1e10 multiply-adds
+    a training step is bound by the host, which torch's own linear keeps less busy than an autograd function."""
+    return (rows * D_in * D_out >= 10 ** 10 and D_in % 8 == 0 and D_out % 8 == 0
+            and -(-D_in // 192) * -(-D_out // 192) <= 256)
+
+
+class ProductFunction(torch.autograd.Function):
+    """out = y W^T + bias as torch's linear computes it (library product), with dW and dbias from
+    grkan_linear_wgrad.  Saves what torch's linear saves: y and W."""
+
+    @staticmethod
+    def forward(ctx, y, weight, bias):
+        ctx.save_for_backward(y, weight)
+        ctx.has_bias = bias is not None
+        return nn.functional.linear(y, weight, bias)
+
+    @staticmethod
+    def backward(ctx, dout):
+        y, weight = ctx.saved_tensors
+        want_y, want_w, want_b = ctx.needs_input_grad
+        want_b = want_b and ctx.has_bias
+        D_in, D_out = int(weight.shape[1]), int(weight.shape[0])
+        dout2, y2 = dout.reshape(-1, D_out), y.reshape(-1, D_in)
+        dy = dout2.mm(weight).view(y.shape) if want_y else None
+        dW = db = None
+        # with a graph of the backward pass wanted, operations that torch can differentiate
+        if want_w and not torch.is_grad_enabled() and dout2.dtype == torch.bfloat16:
+            dout2, y2 = dout2.contiguous(), y2.contiguous()
+            if dout2.data_ptr() % 16 == 0 and y2.data_ptr() % 16 == 0:
+                dW, db = binding.grkan_linear_wgrad(dout2, y2, want_b)
+        if want_w and dW is None:
+            dW = dout2.t().mm(y2)
+        if want_b and db is None:
+            db = dout2.sum(0)
+        return dy, dW, db
+
+
+def _takes_product_function(linear, y) -> bool:
+    """Plain bfloat16 training on the GPU, with nothing attached to the linear layer that its own call would
+    run or change (hooks, parametrisations, subclasses of tensors, autocast, tracing, function transforms)."""
+    w, b = linear.weight, linear.bias
+    return (type(linear) is nn.Linear and "forward" not in linear.__dict__ and torch.is_grad_enabled()
+            and type(w) is nn.Parameter and (b is None or type(b) is nn.Parameter)
+            and y.dtype == torch.bfloat16 and w.dtype == torch.bfloat16 and (b is None or b.dtype == torch.bfloat16)
+            and w.is_cuda and y.device == w.device and w.is_contiguous() and w.requires_grad
+            and not (linear._forward_hooks or linear._forward_pre_hooks or linear._backward_hooks
+                     or linear._backward_pre_hooks or _global_hooks())
+            and not torch.is_autocast_enabled() and not torch.compiler.is_compiling() and not torch.jit.is_tracing()
+            and type(y) is torch.Tensor and not torch._C._are_functorch_transforms_active()
+            and torch.autograd.forward_ad._current_level < 0
+            and wgrad_pays(y.numel() // y.shape[-1], w.shape[1], w.shape[0]))
+
+
+def _global_hooks() -> bool:
+    m = nn.modules.module
+    return bool(m._global_forward_hooks or m._global_forward_pre_hooks or m._global_backward_hooks
+                or m._global_backward_pre_hooks)
+
+
 def group_rational(x, A, B):
     """Functional form: x [..., D] float32 / bfloat16 / float16 on the GPU, A [G, m+1], B [G, n] float32."""
     return GroupRationalFunction.apply(x, A, B)
@@ -266,7 +329,10 @@ class GRKANLinear(nn.Module):
                 if self.fused == "always":
                     return GRKANLayerFunction.apply(x, A.to(torch.float32), B.to(torch.float32), self.linear.weight,
                                                     self.linear.bias)
-        return self.linear(self.rational(x))
+        y = self.rational(x)
+        if _takes_product_function(self.linear, y):
+            return ProductFunction.apply(y, self.linear.weight, self.linear.bias)
+        return self.linear(y)
 
 
 class KATMlp(nn.Module):
