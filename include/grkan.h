@@ -177,6 +177,28 @@ grkan_status_t grkan_bwd(const void *x, const void *dy, const float *A, const fl
                          grkan_dtype_t io, void *hip_stream);
 
 /*
+ * grkan_fwd / grkan_bwd on the parameters as a model keeps them, so that no small kernels run around every
+ * call to expand, convert or sum them:
+ *   coef_dtype        GRKAN_F32 or GRKAN_BF16: dtype of A, B, dA and dB (bfloat16 coefficients are widened
+ *                     exactly, their gradients rounded once to nearest even)
+ *   shared_numerator  0: A and dA are [G, m+1]; else they are [m+1], one row for all groups, and dA is the
+ *                     sum over the groups too (fixed order, in double)
+ * Everything else is as for grkan_fwd / grkan_bwd.  grkan_bwd_model asks `alloc(bytes, alloc_context)` once,
+ * during the call, for its workspace: device memory, 16-byte aligned, that stays untouched until the
+ * enqueued work has finished.  `alloc` must not throw; NULL from it gives GRKAN_ERR_WORKSPACE.
+ */
+typedef void *(*grkan_alloc_t)(size_t bytes, void *context);
+grkan_status_t grkan_fwd_model(const void *x, const void *A, const void *B, void *y,
+                               int64_t rows, int32_t D, int32_t G, int32_t m, int32_t n,
+                               grkan_dtype_t io, grkan_dtype_t coef_dtype, int32_t shared_numerator,
+                               void *hip_stream);
+grkan_status_t grkan_bwd_model(const void *x, const void *dy, const void *A, const void *B,
+                               void *dx, void *dA, void *dB, grkan_alloc_t alloc, void *alloc_context,
+                               int64_t rows, int32_t D, int32_t G, int32_t m, int32_t n,
+                               grkan_dtype_t io, grkan_dtype_t coef_dtype, int32_t shared_numerator,
+                               void *hip_stream);
+
+/*
  * The GR-KAN layer in one kernel (Sec. "Kolmogorov-Arnold Transformer", Eq. "GR_KAN" with F of Eq. "pade"):
  *
  *     out[r, o] = sum_c W[o, c] * F_{g(c)}(x[r, c])  (+ bias[o]),   g(c) = c div d_g, d_g = D_in / G

@@ -107,6 +107,24 @@ def load_library():
     return lib
 
 
+_native = None
+
+
+def load_native():
+    """The extension module with the C++ autograd route (built beside the library)."""
+    global _native
+    if _native is None:
+        load_library()
+        if not (_PKG / "_native.so").exists():
+            from . import build as _build
+
+            _build.build_native(force=True)
+        import importlib
+
+        _native = importlib.import_module(__package__ + "._native")
+    return _native
+
+
 def status_string(status: int) -> str:
     return load_library().grkan_status_string(int(status)).decode()
 

@@ -14,6 +14,11 @@ SOURCES = [CSRC / "grkan_kernels.hip", CSRC / "grkan_plan.cpp", CSRC / "grkan_al
 HEADERS = [CSRC / "grkan_walk.h", CSRC / "grkan_plan.h", CSRC / "grkan_elem.h", PKG.parent / "include" / "grkan.h",
            PKG.parent / "include" / "grkan_alg1.h"]
 
+# the C++ autograd route of the PyTorch front end: host code only, over the C ABI of the library above
+NATIVE = PKG / "_native.so"
+NATIVE_SOURCES = [CSRC / "grkan_torch.cpp"]
+NATIVE_HEADERS = [PKG.parent / "include" / "grkan.h"]
+
 # packed-fp32 code generation is switched off on purpose (hipcc flag, device side)
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -52,5 +57,34 @@ def build_library(force: bool = True, verbose: bool = False) -> Path:
     return LIB
 
 
+def build_native(force: bool = True, verbose: bool = False) -> Path:
+    """Compile the extension module (torch's headers, no device code).  libgrkan.so has to be there."""
+    if not force and NATIVE.exists() and all(p.stat().st_mtime <= NATIVE.stat().st_mtime
+                                             for p in NATIVE_SOURCES + NATIVE_HEADERS):
+        return NATIVE
+    import sysconfig
+
+    import torch
+
+    root = Path(torch.__file__).resolve().parent
+    rocm = Path(hipcc()).resolve().parent.parent
+    tmp = NATIVE.with_name("_native.so.tmp%d" % os.getpid())
+    cmd = [shutil.which("g++") or "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-I%s" % (root / "include"), "-I%s" % (root / "include" / "torch" / "csrc" / "api" / "include"),
+           "-I%s" % (rocm / "include"), "-I/opt/rocm/include", "-I%s" % sysconfig.get_paths()["include"],
+           *map(str, NATIVE_SOURCES), "-o", str(tmp), "-L%s" % (root / "lib"), "-lc10", "-ltorch_cpu", "-ltorch",
+           "-ltorch_python", "-lc10_hip", "-L%s" % PKG, "-l:libgrkan.so", "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd))
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        tmp.unlink(missing_ok=True)
+        raise RuntimeError("g++ failed:\n" + res.stdout + res.stderr)
+    os.replace(tmp, NATIVE)
+    return NATIVE
+
+
 if __name__ == "__main__":
     print(build_library(force=True, verbose=True))
+    print(build_native(force=True, verbose=True))

@@ -21,11 +21,44 @@ template <int M, int N> struct Coef {
     double bd[N];    // b_j in double, for the float32-I/O kernels (see aden_of)
 };
 
-template <int M, int N>
-__device__ __forceinline__ Coef<M, N> load_coef(const float *__restrict__ A, const float *__restrict__ B, int g)
+// Where the coefficient rows are.  A model that shares one numerator row between the groups has a_stride = 0;
+// a bfloat16 model's coefficients are read as they are (widened exactly), so that no conversion kernels run
+// in front of every call.
+struct CoefRows {
+    const void *A;    // row g at element g * a_stride
+    const void *B;    // row g at element g * n
+    int32_t a_stride; // m + 1, or 0: one numerator row for all groups
+    int32_t bf16;     // 1: bfloat16 rows, 0: float32
+};
+
+// UNIFORM: g is the same in all lanes, and the coefficients stay in scalar registers (there is no scalar load
+// of 16 bits; a value loaded by the lanes is moved back).
+template <int M, int N, bool UNIFORM> __device__ __forceinline__ Coef<M, N> load_coef(const CoefRows &rows, int g)
 {
-    const float *a = A + (size_t)g * (M + 1);
-    const float *b = B + (size_t)g * N;
+    auto widen = [](uint16_t v) {
+        const uint32_t w = (uint32_t)v << 16;
+        return __builtin_bit_cast(float, UNIFORM ? (uint32_t)__builtin_amdgcn_readfirstlane((int)w) : w);
+    };
+    float a[M + 1], b[N];
+    if (rows.bf16) {
+        const uint16_t *pa = static_cast<const uint16_t *>(rows.A) + (size_t)g * rows.a_stride;
+        const uint16_t *pb = static_cast<const uint16_t *>(rows.B) + (size_t)g * N;
+#pragma unroll
+        for (int i = 0; i <= M; ++i)
+            a[i] = widen(pa[i]);
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+            b[j] = widen(pb[j]);
+    } else {
+        const float *pa = static_cast<const float *>(rows.A) + (size_t)g * rows.a_stride;
+        const float *pb = static_cast<const float *>(rows.B) + (size_t)g * N;
+#pragma unroll
+        for (int i = 0; i <= M; ++i)
+            a[i] = pa[i];
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+            b[j] = pb[j];
+    }
     Coef<M, N> c;
 #pragma unroll
     for (int i = 0; i <= M; ++i) {

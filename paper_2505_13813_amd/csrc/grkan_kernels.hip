@@ -296,8 +296,7 @@ __device__ __forceinline__ float wave_sum(float v)
 struct FwdArgs {
     const char *x;
     char *y;
-    const float *A;
-    const float *B;
+    CoefRows coef;
     int32_t dgc; // channels per coefficient group (walk.dg is the walk's: a whole row in the flat walk)
     Walk walk;
 };
@@ -306,8 +305,7 @@ struct BwdArgs {
     const char *x;
     const char *dy;
     char *dx;
-    const float *A;
-    const float *B;
+    CoefRows coef;
     float *partial; // [G][workspace rows per group][m + 1 + n]
     int32_t dgc;    // channels per coefficient group (walk.dg is the walk's: a whole row in the flat walk,
                     // a column block of the group when the plan splits groups)
@@ -337,7 +335,7 @@ __global__ __launch_bounds__(kThreadsPerWg) void grkan_fwd_kernel(const FwdArgs 
                    (uint32_t)a.dgc);
     else
         cg = p.dg == a.dgc ? id.g : (int)((uint32_t)id.g * (uint32_t)p.dg / (uint32_t)a.dgc);
-    const Coef<M, N> c = load_coef<M, N>(a.A, a.B, cg);
+    const Coef<M, N> c = load_coef<M, N, !LANECOEF>(a.coef, cg);
     const int32_t n_it = full_visits(p, id.w);
     const bool tail = owns_tail(p, id.w) && lane < p.rem;
     constexpr int64_t ES = sizeof(IO);
@@ -427,7 +425,7 @@ __global__ __launch_bounds__(kThreadsPerWg) void grkan_bwd_stage1_kernel(const B
                    (uint32_t)a.dgc);
     else
         cg = p.dg == a.dgc ? id.g : (int)((uint32_t)id.g * (uint32_t)p.dg / (uint32_t)a.dgc);
-    const Coef<M, N> c = load_coef<M, N>(a.A, a.B, cg);
+    const Coef<M, N> c = load_coef<M, N, !LANECOEF>(a.coef, cg);
     const int32_t n_it = full_visits(p, id.w);
     const bool tail = owns_tail(p, id.w) && lane < p.rem;
     constexpr int64_t ES = sizeof(IO);
@@ -597,11 +595,23 @@ constexpr int kStage2MaxThreads = 4 * kWave;
 
 static int stage2_threads(int32_t rows_per_group) { return rows_per_group > kWave ? kStage2MaxThreads : kWave; }
 
+//
+// With one numerator row shared by the groups (G_shared > 0) the workgroups below G_shared write dB only, and
+// M + 1 more, of four wavefronts, add one numerator sum each over the rows of all groups the same way.
+__device__ __forceinline__ void store_coef_grad(void *p, int32_t i, double v, int32_t bf16)
+{
+    if (bf16)
+        static_cast<uint16_t *>(p)[i] = narrow_one<bf16_t>((float)v);
+    else
+        static_cast<float *>(p)[i] = (float)v;
+}
+
 template <int M, int N>
 __global__ __launch_bounds__(kStage2MaxThreads) void grkan_bwd_stage2_kernel(const float *__restrict__ partial,
                                                                              int32_t rows_per_group,
-                                                                             float *__restrict__ dA,
-                                                                             float *__restrict__ dB)
+                                                                             void *__restrict__ dA,
+                                                                             void *__restrict__ dB,
+                                                                             int32_t G_shared, int32_t bf16)
 {
     constexpr int kNumCoef = M + 1 + N;
     constexpr int kBlocks = kStage2MaxThreads / kWave;
@@ -610,6 +620,28 @@ __global__ __launch_bounds__(kStage2MaxThreads) void grkan_bwd_stage2_kernel(con
     const int g = blockIdx.x;
     const int tid = threadIdx.x;
     const int T = blockDim.x; // 64 or 256
+    if (G_shared > 0 && g >= G_shared) {
+        const int k = g - G_shared;
+        double s = 0.0;
+        for (int64_t r = tid; r < (int64_t)G_shared * rows_per_group; r += T)
+            s += (double)partial[r * kNumCoef + k];
+        thread_sum[0][tid] = s;
+        __syncthreads();
+        if (tid < T / kWave) {
+            double t = 0.0;
+            for (int l = 0; l < kWave; ++l)
+                t += thread_sum[0][tid * kWave + l];
+            block_sum[0][tid] = t;
+        }
+        __syncthreads();
+        if (tid == 0) {
+            double t = 0.0;
+            for (int b = 0; b < T / kWave; ++b)
+                t += block_sum[0][b];
+            store_coef_grad(dA, k, t, bf16);
+        }
+        return;
+    }
     const float *base = partial + (size_t)g * rows_per_group * kNumCoef;
 
     double s[kNumCoef];
@@ -638,10 +670,10 @@ __global__ __launch_bounds__(kStage2MaxThreads) void grkan_bwd_stage2_kernel(con
         double t = 0.0;
         for (int b = 0; b < nblocks; ++b)
             t += block_sum[tid][b];
-        if (tid <= M)
-            dA[g * (M + 1) + tid] = (float)t;
-        else
-            dB[g * N + (tid - (M + 1))] = (float)t;
+        if (tid > M)
+            store_coef_grad(dB, g * N + (tid - (M + 1)), t, bf16);
+        else if (G_shared == 0)
+            store_coef_grad(dA, g * (M + 1) + tid, t, bf16);
     }
 }
 
@@ -702,7 +734,7 @@ static int32_t common_alignment(std::initializer_list<const void *> ptrs)
 // occupancy and launch it.
 using FwdKernel = void (*)(const FwdArgs);
 using BwdKernel = void (*)(const BwdArgs);
-using Stage2Kernel = void (*)(const float *, int32_t, float *, float *);
+using Stage2Kernel = void (*)(const float *, int32_t, void *, void *, int32_t, int32_t);
 
 template <typename IO, int VEC, int M, int N> static FwdKernel fwd_variant(bool fixed, bool lane_coef)
 {
@@ -958,19 +990,26 @@ extern "C" grkan_status_t grkan_device_query(int32_t *out)
     return GRKAN_OK;
 }
 
-extern "C" grkan_status_t grkan_fwd(const void *x, const float *A, const float *B, void *y,
-                                    int64_t rows, int32_t D, int32_t G, int32_t m, int32_t n,
-                                    grkan_dtype_t io, void *hip_stream)
+namespace grkan {
+
+// The coefficient operands of a call: float32 or bfloat16, the numerator one row per group or one for all.
+static CoefRows coef_rows(const void *A, const void *B, int32_t m, bool shared, grkan_dtype_t dtype)
+{
+    return CoefRows{A, B, shared ? 0 : m + 1, dtype == GRKAN_BF16};
+}
+
+static grkan_status_t fwd_impl(const void *x, const CoefRows &coef, void *y, int64_t rows, int32_t D, int32_t G, int32_t m,
+                               int32_t n, grkan_dtype_t io, void *hip_stream)
 {
     const DegreeOps *ops = nullptr;
     grkan_status_t st = check_common(rows, D, G, m, n, io, &ops);
     if (st != GRKAN_OK)
         return st;
-    if (!A || !B || (rows > 0 && (!x || !y)))
+    if (!coef.A || !coef.B || (rows > 0 && (!x || !y)))
         return GRKAN_ERR_NULL;
     const int es = elem_size(io);
     if ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(y)) % es != 0 ||
-        (reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) % 4 != 0)
+        (reinterpret_cast<uintptr_t>(coef.A) | reinterpret_cast<uintptr_t>(coef.B)) % (coef.bf16 ? 2 : 4) != 0)
         return GRKAN_ERR_ALIGN;
     if (rows == 0)
         return GRKAN_OK;
@@ -988,13 +1027,31 @@ extern "C" grkan_status_t grkan_fwd(const void *x, const float *A, const float *
         return st;
     a.x = static_cast<const char *>(x);
     a.y = static_cast<char *>(y);
-    a.A = A;
-    a.B = B;
+    a.coef = coef;
     a.dgc = D / G;
     void *args[] = {&a};
     const hipError_t e = hipLaunchKernel(kernel, dim3(pl.grid), dim3(kThreadsPerWg), args, 0,
                                          static_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? GRKAN_OK : GRKAN_ERR_LAUNCH;
+}
+
+} // namespace grkan
+
+extern "C" grkan_status_t grkan_fwd(const void *x, const float *A, const float *B, void *y,
+                                    int64_t rows, int32_t D, int32_t G, int32_t m, int32_t n,
+                                    grkan_dtype_t io, void *hip_stream)
+{
+    return fwd_impl(x, coef_rows(A, B, m, false, GRKAN_F32), y, rows, D, G, m, n, io, hip_stream);
+}
+
+extern "C" grkan_status_t grkan_fwd_model(const void *x, const void *A, const void *B, void *y,
+                                          int64_t rows, int32_t D, int32_t G, int32_t m, int32_t n,
+                                          grkan_dtype_t io, grkan_dtype_t coef_dtype, int32_t shared_numerator,
+                                          void *hip_stream)
+{
+    if (coef_dtype != GRKAN_F32 && coef_dtype != GRKAN_BF16)
+        return GRKAN_ERR_DTYPE;
+    return fwd_impl(x, coef_rows(A, B, m, shared_numerator != 0, coef_dtype), y, rows, D, G, m, n, io, hip_stream);
 }
 
 namespace grkan {
@@ -1024,24 +1081,30 @@ static grkan_status_t scratch_of_device(int dev, void **out)
     return GRKAN_OK;
 }
 
-// Both backward entry points.  own_scratch: the workspace is the library's
-// fixed array (then `workspace` / `workspace_bytes` are ignored).
-static grkan_status_t bwd_impl(const void *x, const void *dy, const float *A, const float *B,
-                               void *dx, float *dA, float *dB,
-                               void *workspace, size_t workspace_bytes, bool own_scratch,
-                               int64_t rows, int32_t D, int32_t G, int32_t m, int32_t n,
+// The three backward entry points.  Where the workspace comes from: a buffer of the caller's, the library's
+// fixed array, or the caller's allocation function, asked once the launch is planned.
+struct Workspace {
+    void *ptr;
+    size_t bytes;
+    bool own_scratch;
+    grkan_alloc_t alloc;
+    void *alloc_context;
+};
+
+static grkan_status_t bwd_impl(const void *x, const void *dy, const CoefRows &coef, void *dx, void *dA, void *dB,
+                               const Workspace &ws, int64_t rows, int32_t D, int32_t G, int32_t m, int32_t n,
                                grkan_dtype_t io, void *hip_stream)
 {
     const DegreeOps *ops = nullptr;
     grkan_status_t st = check_common(rows, D, G, m, n, io, &ops);
     if (st != GRKAN_OK)
         return st;
-    if (!A || !B || !dA || !dB || (rows > 0 && (!x || !dy || !dx)))
+    if (!coef.A || !coef.B || !dA || !dB || (rows > 0 && (!x || !dy || !dx)))
         return GRKAN_ERR_NULL;
     const int es = elem_size(io);
     if ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(dy) | reinterpret_cast<uintptr_t>(dx)) % es != 0 ||
-        (reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B) | reinterpret_cast<uintptr_t>(dA) |
-         reinterpret_cast<uintptr_t>(dB)) % 4 != 0)
+        (reinterpret_cast<uintptr_t>(coef.A) | reinterpret_cast<uintptr_t>(coef.B) | reinterpret_cast<uintptr_t>(dA) |
+         reinterpret_cast<uintptr_t>(dB)) % (coef.bf16 ? 2 : 4) != 0)
         return GRKAN_ERR_ALIGN;
 
     int dev;
@@ -1056,14 +1119,19 @@ static grkan_status_t bwd_impl(const void *x, const void *dy, const float *A, co
     if (st != GRKAN_OK)
         return st;
     const size_t need = workspace_for(pl, G, m + 1 + n);
-    if (own_scratch) {
+    void *workspace = ws.ptr;
+    if (ws.own_scratch) {
         if (need > kScratchBytes)
             return GRKAN_ERR_SCRATCH_LIMIT;
         st = scratch_of_device(dev, &workspace);
         if (st != GRKAN_OK)
             return st;
+    } else if (ws.alloc) {
+        workspace = need > 0 ? ws.alloc(need, ws.alloc_context) : nullptr;
+        if (need > 0 && (!workspace || reinterpret_cast<uintptr_t>(workspace) % 16 != 0))
+            return GRKAN_ERR_WORKSPACE;
     } else if (need > 0 &&
-               (!workspace || workspace_bytes < need || reinterpret_cast<uintptr_t>(workspace) % 16 != 0)) {
+               (!workspace || ws.bytes < need || reinterpret_cast<uintptr_t>(workspace) % 16 != 0)) {
         return GRKAN_ERR_WORKSPACE;
     }
 
@@ -1071,8 +1139,7 @@ static grkan_status_t bwd_impl(const void *x, const void *dy, const float *A, co
     a.x = static_cast<const char *>(x);
     a.dy = static_cast<const char *>(dy);
     a.dx = static_cast<char *>(dx);
-    a.A = A;
-    a.B = B;
+    a.coef = coef;
     a.partial = static_cast<float *>(workspace);
     a.dgc = D / G;
     if (pl.grid > 0) {
@@ -1085,9 +1152,13 @@ static grkan_status_t bwd_impl(const void *x, const void *dy, const float *A, co
     // writes zeros.
     const float *partial = a.partial;
     int32_t rows_per_group = pl.partials_per_group;
-    void *args2[] = {&partial, &rows_per_group, &dA, &dB};
-    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(ops->stage2), dim3(G),
-                                         dim3(stage2_threads(rows_per_group)), args2, 0, stream);
+    int32_t G_shared = coef.a_stride == 0 ? G : 0;
+    int32_t bf16 = coef.bf16;
+    void *args2[] = {&partial, &rows_per_group, &dA, &dB, &G_shared, &bf16};
+    const int threads = G_shared > 0 ? kStage2MaxThreads : stage2_threads(rows_per_group);
+    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(ops->stage2),
+                                         dim3((unsigned)G + (G_shared > 0 ? (unsigned)(m + 1) : 0u)), dim3(threads), args2, 0,
+                                         stream);
     return e == hipSuccess ? GRKAN_OK : GRKAN_ERR_LAUNCH;
 }
 
@@ -1099,7 +1170,8 @@ extern "C" grkan_status_t grkan_bwd(const void *x, const void *dy, const float *
                                     int64_t rows, int32_t D, int32_t G, int32_t m, int32_t n,
                                     grkan_dtype_t io, void *hip_stream)
 {
-    return bwd_impl(x, dy, A, B, dx, dA, dB, workspace, workspace_bytes, false, rows, D, G, m, n, io, hip_stream);
+    return bwd_impl(x, dy, coef_rows(A, B, m, false, GRKAN_F32), dx, dA, dB,
+                    Workspace{workspace, workspace_bytes, false, nullptr, nullptr}, rows, D, G, m, n, io, hip_stream);
 }
 
 extern "C" grkan_status_t grkan_bwd_noalloc(const void *x, const void *dy, const float *A, const float *B,
@@ -1107,5 +1179,20 @@ extern "C" grkan_status_t grkan_bwd_noalloc(const void *x, const void *dy, const
                                             int64_t rows, int32_t D, int32_t G, int32_t m, int32_t n,
                                             grkan_dtype_t io, void *hip_stream)
 {
-    return bwd_impl(x, dy, A, B, dx, dA, dB, nullptr, 0, true, rows, D, G, m, n, io, hip_stream);
+    return bwd_impl(x, dy, coef_rows(A, B, m, false, GRKAN_F32), dx, dA, dB, Workspace{nullptr, 0, true, nullptr, nullptr},
+                    rows, D, G, m, n, io, hip_stream);
+}
+
+extern "C" grkan_status_t grkan_bwd_model(const void *x, const void *dy, const void *A, const void *B,
+                                          void *dx, void *dA, void *dB, grkan_alloc_t alloc, void *alloc_context,
+                                          int64_t rows, int32_t D, int32_t G, int32_t m, int32_t n,
+                                          grkan_dtype_t io, grkan_dtype_t coef_dtype, int32_t shared_numerator,
+                                          void *hip_stream)
+{
+    if (coef_dtype != GRKAN_F32 && coef_dtype != GRKAN_BF16)
+        return GRKAN_ERR_DTYPE;
+    if (!alloc)
+        return GRKAN_ERR_NULL;
+    return bwd_impl(x, dy, coef_rows(A, B, m, shared_numerator != 0, coef_dtype), dx, dA, dB,
+                    Workspace{nullptr, 0, false, alloc, alloc_context}, rows, D, G, m, n, io, hip_stream);
 }

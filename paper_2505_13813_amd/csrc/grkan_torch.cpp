@@ -1,0 +1,245 @@
+// Native autograd route of the PyTorch front end: the group-wise rational function and the layer's product
+// as C++ autograd functions over the C ABI (include/grkan.h).  What runs on the device is the same as through
+// the Python functions; what goes is the host time around it (argument marshalling, and small kernels that
+// expand, convert and sum the coefficients of a model).
+//
+// Every entry returns "not taken" (an empty optional) for anything but plain dense tensors on the current
+// GPU outside of tracing, function transforms, forward-mode differentiation and dispatch modes; the caller
+// then takes the Python route, which handles or refuses the call as it always did.
+#include <torch/csrc/autograd/custom_function.h>
+#include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/jit/frontend/tracer.h>
+#include <torch/csrc/utils/pybind.h>
+
+#include <ATen/ATen.h>
+#include <c10/core/impl/LocalDispatchKeySet.h>
+#include <c10/core/impl/TorchDispatchModeTLS.h>
+#include <c10/hip/HIPFunctions.h>
+#include <c10/hip/HIPStream.h>
+
+#include <exception>
+#include <optional>
+
+#include "../../include/grkan.h"
+
+namespace {
+
+using at::Tensor;
+using torch::autograd::AutogradContext;
+using torch::autograd::variable_list;
+
+constexpr c10::DispatchKeySet kNotPlain({
+    c10::DispatchKey::Python, c10::DispatchKey::PythonTLSSnapshot, c10::DispatchKey::FuncTorchBatched,
+    c10::DispatchKey::FuncTorchGradWrapper, c10::DispatchKey::FuncTorchVmapMode, c10::DispatchKey::Batched,
+    c10::DispatchKey::Functionalize, c10::DispatchKey::Negative, c10::DispatchKey::Conjugate,
+    c10::DispatchKey::ZeroTensor});
+
+bool plain(const Tensor &t, const c10::Device &dev)
+{
+    return t.defined() && t.device() == dev && t.layout() == at::kStrided && !t.key_set().has_any(kNotPlain) &&
+           !t._fw_grad(0).defined();
+}
+
+bool plain_context()
+{
+    return !torch::jit::tracer::isTracing() && !c10::impl::TorchDispatchModeTLS::any_modes_set() &&
+           !c10::impl::tls_is_dispatch_key_included(c10::DispatchKey::FuncTorchDynamicLayerFrontMode);
+}
+
+bool on_current_gpu(const Tensor &t) { return t.is_cuda() && t.get_device() == c10::hip::current_device(); }
+
+void *stream_of(const Tensor &t) { return c10::hip::getCurrentHIPStream(t.get_device()).stream(); }
+
+std::optional<grkan_dtype_t> io_of(const Tensor &t)
+{
+    switch (t.scalar_type()) {
+    case at::kFloat: return GRKAN_F32;
+    case at::kBFloat16: return GRKAN_BF16;
+    case at::kHalf: return GRKAN_F16;
+    default: return std::nullopt;
+    }
+}
+
+void check(grkan_status_t st, const char *where)
+{
+    TORCH_CHECK(st == GRKAN_OK, where, ": ", grkan_status_string(st), " (status ", (int)st, ")");
+}
+
+// A workspace from torch's allocator (its streams and lifetimes), handed out during one call of the C ABI.
+struct Scratch {
+    at::TensorOptions options;
+    Tensor memory;
+    std::exception_ptr error;
+
+    static void *alloc(size_t bytes, void *self) noexcept
+    {
+        auto *s = static_cast<Scratch *>(self);
+        try {
+            s->memory = at::empty({(int64_t)bytes}, s->options);
+            return s->memory.data_ptr();
+        } catch (...) {
+            s->error = std::current_exception();
+            return nullptr;
+        }
+    }
+    void rethrow() const
+    {
+        if (error)
+            std::rethrow_exception(error);
+    }
+};
+
+struct Sizes {
+    int64_t rows;
+    int32_t D, G, m, n;
+    bool shared;
+};
+
+Sizes sizes_of(const Tensor &x, const Tensor &A, const Tensor &B)
+{
+    const int64_t D = x.size(-1);
+    return Sizes{x.numel() / D, (int32_t)D, (int32_t)B.size(0), (int32_t)A.size(-1) - 1, (int32_t)B.size(1), A.dim() == 1};
+}
+
+// y = F(x); A [G, m+1] or, shared by the groups, [m+1].
+struct Rational : public torch::autograd::Function<Rational> {
+    static Tensor forward(AutogradContext *ctx, const Tensor &x_in, const Tensor &A_in, const Tensor &B_in)
+    {
+        const Tensor x = x_in.contiguous(), A = A_in.contiguous(), B = B_in.contiguous();
+        ctx->save_for_backward({x, A, B});
+        const Sizes s = sizes_of(x, A, B);
+        Tensor y = at::empty_like(x, at::MemoryFormat::Contiguous);
+        check(grkan_fwd_model(x.data_ptr(), A.data_ptr(), B.data_ptr(), y.data_ptr(), s.rows, s.D, s.G, s.m, s.n, *io_of(x),
+                              *io_of(A), s.shared, stream_of(x)),
+              "grkan_fwd");
+        return y;
+    }
+
+    static variable_list backward(AutogradContext *ctx, const variable_list &grads)
+    {
+        const auto saved = ctx->get_saved_variables();
+        const Tensor &x = saved[0], &A = saved[1], &B = saved[2];
+        if (!grads[0].defined())
+            return {Tensor(), Tensor(), Tensor()};
+        at::AutoGradMode no_grad(false);
+        const Tensor dy = grads[0].contiguous();
+        TORCH_CHECK_VALUE(dy.sizes() == x.sizes() && dy.scalar_type() == x.scalar_type() && dy.device() == x.device(),
+                          "dy must match x");
+        const Sizes s = sizes_of(x, A, B);
+        Tensor dx = at::empty_like(x), dA = at::empty_like(A), dB = at::empty_like(B);
+        Scratch scratch{x.options().dtype(at::kByte), Tensor(), nullptr};
+        const grkan_status_t st =
+            grkan_bwd_model(x.data_ptr(), dy.data_ptr(), A.data_ptr(), B.data_ptr(), dx.data_ptr(), dA.data_ptr(), dB.data_ptr(),
+                            &Scratch::alloc, &scratch, s.rows, s.D, s.G, s.m, s.n, *io_of(x), *io_of(A), s.shared, stream_of(x));
+        scratch.rethrow();
+        check(st, "grkan_bwd");
+        return {dx, dA, dB};
+    }
+};
+
+// out = y W^T + bias with dW and dbias from grkan_linear_wgrad; saves what torch's linear saves.
+struct Product : public torch::autograd::Function<Product> {
+    static Tensor forward(AutogradContext *ctx, const Tensor &y, const Tensor &W, const std::optional<Tensor> &bias)
+    {
+        ctx->save_for_backward({y, W});
+        ctx->saved_data["has_bias"] = bias.has_value();
+        return at::linear(y, W, bias);
+    }
+
+    static variable_list backward(AutogradContext *ctx, const variable_list &grads)
+    {
+        const auto saved = ctx->get_saved_variables();
+        const Tensor &y = saved[0], &W = saved[1];
+        const Tensor &dout = grads[0];
+        if (!dout.defined())
+            return {Tensor(), Tensor(), Tensor()};
+        const bool want_y = ctx->needs_input_grad(0), want_w = ctx->needs_input_grad(1);
+        const bool want_b = ctx->saved_data["has_bias"].toBool() && ctx->needs_input_grad(2);
+        const int64_t D_in = W.size(1), D_out = W.size(0);
+        Tensor dout2 = dout.reshape({-1, D_out}), y2 = y.reshape({-1, D_in});
+        Tensor dy, dW, db;
+        if (want_y)
+            dy = dout2.mm(W).view(y.sizes());
+        // with a graph of the backward pass wanted, operations that torch can differentiate
+        if (want_w && !at::GradMode::is_enabled() && plain(dout2, y.device()) && dout2.scalar_type() == at::kBFloat16) {
+            dout2 = dout2.contiguous();
+            y2 = y2.contiguous();
+            const size_t need = grkan_linear_wgrad_workspace_bytes(dout2.size(0), (int32_t)D_in, (int32_t)D_out);
+            if (need > 0 && reinterpret_cast<uintptr_t>(dout2.data_ptr()) % 16 == 0 &&
+                reinterpret_cast<uintptr_t>(y2.data_ptr()) % 16 == 0) {
+                const Tensor ws = at::empty({(int64_t)need}, y.options().dtype(at::kByte));
+                dW = at::empty({D_out, D_in}, W.options());
+                if (want_b)
+                    db = at::empty({D_out}, W.options());
+                check(grkan_linear_wgrad(dout2.data_ptr(), y2.data_ptr(), dW.data_ptr(), want_b ? db.data_ptr() : nullptr,
+                                         ws.data_ptr(), need, dout2.size(0), (int32_t)D_in, (int32_t)D_out, GRKAN_BF16,
+                                         stream_of(y)),
+                      "grkan_linear_wgrad");
+            }
+        }
+        if (want_w && !dW.defined())
+            dW = dout2.t().mm(y2);
+        if (want_b && !db.defined())
+            db = dout2.sum(0);
+        return {dy, dW, db};
+    }
+};
+
+// Shapes and types that grkan_fwd / grkan_bwd take; anything else is left to the Python route and its errors.
+std::optional<Tensor> rational(const Tensor &x, const Tensor &A, const Tensor &B)
+{
+    if (!plain_context() || !on_current_gpu(x) || !plain(x, x.device()) || !plain(A, x.device()) || !plain(B, x.device()))
+        return std::nullopt;
+    if (!io_of(x) || A.scalar_type() != B.scalar_type() ||
+        (A.scalar_type() != at::kFloat && A.scalar_type() != at::kBFloat16) || x.dim() < 1 || B.dim() != 2 || A.dim() < 1 ||
+        A.dim() > 2 || (A.dim() == 2 && A.size(0) != B.size(0)))
+        return std::nullopt;
+    const int64_t D = x.size(-1), G = B.size(0), m = A.size(-1) - 1, n = B.size(1);
+    const bool degrees = (m == 5 && n == 4) || (m == 3 && n == 2) || (m == 7 && n == 6);
+    if (!degrees || G <= 0 || D <= 0 || D > INT32_MAX || D % G != 0 || x.numel() == 0)
+        return std::nullopt;
+    return Rational::apply(x, A, B);
+}
+
+// The product of a bfloat16 layer in training.  (Hooks and the like on the linear module are the caller's to check.)
+std::optional<Tensor> product(const Tensor &y, const Tensor &W, const std::optional<Tensor> &bias)
+{
+    if (!plain_context() || !on_current_gpu(y) || !plain(y, y.device()) || !plain(W, y.device()) ||
+        (bias && !plain(*bias, y.device())))
+        return std::nullopt;
+    if (y.scalar_type() != at::kBFloat16 || W.scalar_type() != at::kBFloat16 || (bias && bias->scalar_type() != at::kBFloat16) ||
+        W.dim() != 2 || y.dim() < 1 || y.size(-1) != W.size(1) || !W.is_contiguous())
+        return std::nullopt;
+    return Product::apply(y, W, bias);
+}
+
+// The one-kernel layer on packed weights (inference): all operands as the module keeps them.
+std::optional<Tensor> layer_packed(const Tensor &x_in, const Tensor &A, const Tensor &B, const Tensor &Wp, int64_t D_out,
+                                   const std::optional<Tensor> &bias)
+{
+    if (!plain_context() || !on_current_gpu(x_in) || !plain(x_in, x_in.device()) || x_in.scalar_type() != at::kBFloat16 ||
+        x_in.numel() == 0 || !plain(A, x_in.device()) || !plain(B, x_in.device()) || !plain(Wp, x_in.device()) ||
+        (bias && !plain(*bias, x_in.device())))
+        return std::nullopt;
+    const Tensor x = x_in.contiguous();
+    if (reinterpret_cast<uintptr_t>(x.data_ptr()) % 16 != 0)
+        return std::nullopt;
+    const Sizes s = sizes_of(x, A, B);
+    auto shape = x.sizes().vec();
+    shape.back() = D_out;
+    Tensor out = at::empty(shape, x.options());
+    check(grkan_linear_fwd_packed(x.data_ptr(), A.data_ptr<float>(), B.data_ptr<float>(), Wp.data_ptr(),
+                                  bias ? bias->data_ptr<float>() : nullptr, out.data_ptr(), s.rows, s.D, (int32_t)D_out, s.G, s.m,
+                                  s.n, GRKAN_BF16, GRKAN_BF16, stream_of(x)),
+          "grkan_linear_fwd_packed");
+    return out;
+}
+
+} // namespace
+
+PYBIND11_MODULE(_native, mod)
+{
+    mod.def("rational", &rational, pybind11::call_guard<pybind11::gil_scoped_release>());
+    mod.def("product", &product, pybind11::call_guard<pybind11::gil_scoped_release>());
+    mod.def("layer_packed", &layer_packed, pybind11::call_guard<pybind11::gil_scoped_release>());
+}

@@ -89,6 +89,7 @@ def fused_layer_pays(rows: int, D_in: int, D_out: int) -> bool:
     return workgroups >= 200 or D_in <= 768
 
 
+@lru_cache(maxsize=1024)
 def one_kernel_is_faster(rows: int, D_in: int, D_out: int) -> bool:
     """Whether the one-kernel layer is the faster route in inference (measured on MI355X, bfloat16, 50 - 25,216
     rows of ten layer shapes).  The two kernels take about 11 us + the elementwise pass at 5.5 TB/s + the
@@ -136,57 +137,22 @@ def wgrad_pays(rows: int, D_in: int, D_out: int) -> bool:
     """Whether grkan_linear_wgrad is the faster route for the gradients of a bfloat16 product (measured on
     MI355X against the library's product and column sum): it was at every size tried from 640 rows up
     (25,216 rows: 384 x 1536 50 us against 184, 768 x 3072 143 against 308; 1,000 rows of 384 x 1536 20 against
-    23) as long as its 192 x 192 tiles fit the chip's 256 compute units once; but below about 1e10 multiply-adds
-    a training step is bound by the host, which torch's own linear keeps less busy than an autograd function."""
-    return (rows * D_in * D_out >= 10 ** 10 and D_in % 8 == 0 and D_out % 8 == 0
-            and -(-D_in // 192) * -(-D_out // 192) <= 256)
+    23) as long as its 192 x 192 tiles fit the chip's 256 compute units once."""
+    return rows >= 512 and D_in % 8 == 0 and D_out % 8 == 0 and -(-D_in // 192) * -(-D_out // 192) <= 256
 
 
-class ProductFunction(torch.autograd.Function):
-    """out = y W^T + bias as torch's linear computes it (library product), with dW and dbias from
-    grkan_linear_wgrad.  Saves what torch's linear saves: y and W."""
-
-    @staticmethod
-    def forward(ctx, y, weight, bias):
-        ctx.save_for_backward(y, weight)
-        ctx.has_bias = bias is not None
-        return nn.functional.linear(y, weight, bias)
-
-    @staticmethod
-    def backward(ctx, dout):
-        y, weight = ctx.saved_tensors
-        want_y, want_w, want_b = ctx.needs_input_grad
-        want_b = want_b and ctx.has_bias
-        D_in, D_out = int(weight.shape[1]), int(weight.shape[0])
-        dout2, y2 = dout.reshape(-1, D_out), y.reshape(-1, D_in)
-        dy = dout2.mm(weight).view(y.shape) if want_y else None
-        dW = db = None
-        # with a graph of the backward pass wanted, operations that torch can differentiate
-        if want_w and not torch.is_grad_enabled() and dout2.dtype == torch.bfloat16:
-            dout2, y2 = dout2.contiguous(), y2.contiguous()
-            if dout2.data_ptr() % 16 == 0 and y2.data_ptr() % 16 == 0:
-                dW, db = binding.grkan_linear_wgrad(dout2, y2, want_b)
-        if want_w and dW is None:
-            dW = dout2.t().mm(y2)
-        if want_b and db is None:
-            db = dout2.sum(0)
-        return dy, dW, db
-
-
-def _takes_product_function(linear, y) -> bool:
-    """Plain bfloat16 training on the GPU, with nothing attached to the linear layer that its own call would
-    run or change (hooks, parametrisations, subclasses of tensors, autocast, tracing, function transforms)."""
+def _native_product(linear, y):
+    """The linear layer on y with grkan_linear_wgrad in its backward pass, or None where that route is not
+    taken: plain bfloat16 training on the GPU, at sizes it pays for, with nothing attached to the linear layer
+    that its own call would run or change (hooks, parametrisations, autocast, tracing, tensor subclasses)."""
     w, b = linear.weight, linear.bias
-    return (type(linear) is nn.Linear and "forward" not in linear.__dict__ and torch.is_grad_enabled()
-            and type(w) is nn.Parameter and (b is None or type(b) is nn.Parameter)
-            and y.dtype == torch.bfloat16 and w.dtype == torch.bfloat16 and (b is None or b.dtype == torch.bfloat16)
-            and w.is_cuda and y.device == w.device and w.is_contiguous() and w.requires_grad
-            and not (linear._forward_hooks or linear._forward_pre_hooks or linear._backward_hooks
-                     or linear._backward_pre_hooks or _global_hooks())
-            and not torch.is_autocast_enabled() and not torch.compiler.is_compiling() and not torch.jit.is_tracing()
-            and type(y) is torch.Tensor and not torch._C._are_functorch_transforms_active()
-            and torch.autograd.forward_ad._current_level < 0
-            and wgrad_pays(y.numel() // y.shape[-1], w.shape[1], w.shape[0]))
+    if (type(linear) is not nn.Linear or y.dtype != torch.bfloat16 or not torch.is_grad_enabled() or not w.requires_grad
+            or type(w) is not nn.Parameter or (b is not None and type(b) is not nn.Parameter) or type(y) is not torch.Tensor
+            or "forward" in linear.__dict__ or linear._forward_hooks or linear._forward_pre_hooks or linear._backward_hooks
+            or linear._backward_pre_hooks or _global_hooks() or torch.is_autocast_enabled()
+            or torch.compiler.is_compiling() or not wgrad_pays(y.numel() // y.shape[-1], w.shape[1], w.shape[0])):
+        return None
+    return binding.load_native().product(y, w, b)
 
 
 def _global_hooks() -> bool:
@@ -197,6 +163,10 @@ def _global_hooks() -> bool:
 
 def group_rational(x, A, B):
     """Functional form: x [..., D] float32 / bfloat16 / float16 on the GPU, A [G, m+1], B [G, n] float32."""
+    if not torch.compiler.is_compiling() and A.dim() == 2 and A.dtype == torch.float32 and B.dtype == torch.float32:
+        y = binding.load_native().rational(x, A, B)
+        if y is not None:
+            return y
     return GroupRationalFunction.apply(x, A, B)
 
 
@@ -273,6 +243,11 @@ class GroupRational(nn.Module):
         return float(np.mean([second_moment(A[g], B[g]) for g in range(self.groups)]))
 
     def forward(self, x):
+        if not torch.compiler.is_compiling():
+            # the parameters as they are: one numerator row for all groups, float32 or bfloat16
+            y = binding.load_native().rational(x, self.numerator, self.denominator)
+            if y is not None:
+                return y
         A, B = self.coefficient_rows()
         return group_rational(x, A.to(torch.float32), B.to(torch.float32))
 
@@ -318,21 +293,24 @@ class GRKANLinear(nn.Module):
         return self._packed
 
     def forward(self, x):
-        if self.fused != "never":
+        if self.fused == "always" or (self.fused == "inference" and not torch.is_grad_enabled()):
             A, B = self.rational.coefficient_rows()
             if fused_layer_supported(x, A, self.linear.weight):
-                rows = x.numel() // x.shape[-1]
+                rows, D_in = x.numel() // x.shape[-1], x.shape[-1]
                 if not torch.is_grad_enabled() and (
-                        self.fused == "always" or one_kernel_is_faster(rows, x.shape[-1], self.linear.weight.shape[0])):
+                        self.fused == "always" or one_kernel_is_faster(rows, D_in, self.linear.weight.shape[0])):
                     pw, b32, A32, B32 = self._inference_weights()
+                    if D_in == pw.D_in and not torch.compiler.is_compiling():
+                        out = binding.load_native().layer_packed(x, A32, B32, pw.data, pw.D_out, b32)
+                        if out is not None:
+                            return out
                     return binding.grkan_linear_fwd(x.contiguous(), A32, B32, pw, b32, out_dtype=x.dtype)
                 if self.fused == "always":
                     return GRKANLayerFunction.apply(x, A.to(torch.float32), B.to(torch.float32), self.linear.weight,
                                                     self.linear.bias)
         y = self.rational(x)
-        if _takes_product_function(self.linear, y):
-            return ProductFunction.apply(y, self.linear.weight, self.linear.bias)
-        return self.linear(y)
+        out = _native_product(self.linear, y)
+        return self.linear(y) if out is None else out
 
 
 class KATMlp(nn.Module):

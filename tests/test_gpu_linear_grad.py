@@ -104,25 +104,25 @@ def test_weight_gradient_rejects_what_it_does_not_cover():
 
 
 def test_module_training_route_matches_torchs_linear():
-    """The layer's gradients through ProductFunction against the same layer through torch's own linear (one
+    """The layer's gradients through the native product against the same layer through torch's own linear (one
     rounding each); frozen parameters; a differentiable backward pass; hooks on the linear layer keep it called."""
     import torch
 
     from paper_2505_13813_amd import nn as gnn
 
     torch.manual_seed(4)
-    layer = gnn.GRKANLinear(1024, 1000, 2, init="swish").to("cuda:0").to(torch.bfloat16)
-    x = torch.randn(3, 3300, 1024, device="cuda:0").to(torch.bfloat16).requires_grad_()
-    dy = torch.randn(3, 3300, 1000, device="cuda:0").to(torch.bfloat16)
+    layer = gnn.GRKANLinear(192, 392, 2, init="swish").to("cuda:0").to(torch.bfloat16)
+    x = torch.randn(3, 200, 192, device="cuda:0").to(torch.bfloat16).requires_grad_()
+    dy = torch.randn(3, 200, 392, device="cuda:0").to(torch.bfloat16)
     params = [x] + list(layer.parameters())
     out = layer(x)
-    assert type(out.grad_fn).__name__ == "ProductFunctionBackward"
+    assert "Product" in out.grad_fn.name()
     got = torch.autograd.grad(out, params, dy)
 
     calls = []
     handle = layer.linear.register_forward_hook(lambda *a: calls.append(1))
     ref_out = layer(x)
-    assert calls and type(ref_out.grad_fn).__name__ != "ProductFunctionBackward"
+    assert calls and "Product" not in ref_out.grad_fn.name()
     ref = torch.autograd.grad(ref_out, params, dy)
     handle.remove()
     assert torch.equal(out, ref_out)
