@@ -29,7 +29,8 @@
  *   - D % G != 0 is GRKAN_ERR_SHAPE.  rows == 0 is valid.
  *   - Pointers must be aligned to the element size.  16-byte aligned tensors
  *     with d_g a multiple of 4 (float32) or 8 (16-bit formats) take the fast
- *     128-bit path; anything else silently takes a narrower-vector variant.
+ *     128-bit path; anything else silently takes a narrower-vector variant or
+ *     overlapping vectors (grkan_overlapped_cover_errors).
  */
 #ifndef GRKAN_H_
 #define GRKAN_H_
@@ -120,6 +121,17 @@ grkan_status_t grkan_plan(int64_t rows, int32_t D, int32_t G, grkan_dtype_t io,
  */
 int64_t grkan_plan_cover_errors(int64_t rows, int32_t D, int32_t G, grkan_dtype_t io,
                                 const grkan_plan_t *plan);
+
+/*
+ * Groups whose d_g is not a whole number of 16-byte vectors but holds one (d_g = 75, say) take a third walk when no output
+ * shares memory with an input: a flat walk of full 16-byte vectors, aligned to their elements only, of which
+ * the last of a group repeats elements of the one before (computed twice, counted once).  It is not described
+ * by grkan_plan; this host-only check walks it as the kernels do and returns the number of elements that are not
+ * stored, are outside their group or the array, or are not counted exactly once: 0 is right, -2 if the shape
+ * does not take that walk, -1 if it is too large to simulate.
+ */
+int64_t grkan_overlapped_cover_errors(int64_t rows, int32_t D, int32_t G, grkan_dtype_t io,
+                                      int32_t num_cu, int32_t wg_per_cu);
 
 /*
  * Bytes of device workspace grkan_bwd needs for this shape on the current

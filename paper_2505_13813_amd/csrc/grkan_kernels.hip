@@ -40,17 +40,19 @@ namespace grkan {
 // element's M + 1 + N terms to acc (acc[0..M] numerator, acc[M+1..M+N]
 // denominator, the latter with the opposite sign until negate_b_sums is
 // applied).  P/Q^2 is formed as (P r) r with r = 1/Q, so Q^2 is never computed.
-template <bool WIDE, int M, int N>
-__device__ __forceinline__ float bwd_elem(float x, float d, const Coef<M, N> &c, float (&acc)[M + 1 + N])
+// MASKED: `skip` keeps the element out of the sums (powers and weights become zeros, whatever x is).
+template <bool WIDE, int M, int N, bool MASKED = false>
+__device__ __forceinline__ float bwd_elem(float x, float d, const Coef<M, N> &c, float (&acc)[M + 1 + N], bool skip = false)
 {
     // x^k: squares for even k, one more factor x for odd k
     constexpr int K = M > N ? M : N;
+    const float xs = MASKED && skip ? 0.0f : x;
     float pw[K + 1];
     pw[0] = 1.0f;
-    pw[1] = x;
+    pw[1] = xs;
 #pragma unroll
     for (int k = 2; k <= K; ++k)
-        pw[k] = (k % 2 == 0) ? pw[k / 2] * pw[k / 2] : pw[k - 1] * x;
+        pw[k] = (k % 2 == 0) ? pw[k / 2] * pw[k / 2] : pw[k - 1] * xs;
 
     const float p = numerator_of(x, c);
 
@@ -70,19 +72,21 @@ __device__ __forceinline__ float bwd_elem(float x, float d, const Coef<M, N> &c,
     const float r = __builtin_amdgcn_rcpf(q);
 
     const float t = d * r; // dy / Q
-    acc[0] += t;
+    const float ts = MASKED && skip ? 0.0f : t;
+    acc[0] += ts;
 #pragma unroll
     for (int i = 1; i <= M; ++i)
-        acc[i] = fmaf(t, pw[i], acc[i]);
+        acc[i] = fmaf(ts, pw[i], acc[i]);
 
     // s / Q with s = sign(Aden), sign(0) = 0: r > 0, so the sign is copied onto it bitwise
     const float sr = aden != 0.0f ? __builtin_copysignf(r, aden) : 0.0f;
     // acc[M+1..] collect +dy s P x^j / Q^2; the minus sign of Eq. "grad_b" is
     // applied once per lane after the loop (negate_b_sums)
     const float wb = t * (p * sr); // (dy / Q) (P s / Q) = dy s P / Q^2
+    const float ws = MASKED && skip ? 0.0f : wb;
 #pragma unroll
     for (int j = 1; j <= N; ++j)
-        acc[M + j] = fmaf(wb, pw[j], acc[M + j]);
+        acc[M + j] = fmaf(ws, pw[j], acc[M + j]);
 
     // dx = dy (P'/Q - s Aden' P/Q^2) = (dy/Q) P' - (dy s P/Q^2) Aden'
     const float dx = fmaf(t, dp, -(wb * dh));
@@ -204,10 +208,17 @@ template <int BYTES> __device__ __forceinline__ uint32_t raw_word(const typename
 // converting at load time would make the wave wait for the data immediately.
 template <typename IO, int VEC> using RawT = typename RawOf<(int)sizeof(IO) * VEC>::type;
 
-template <typename IO, int VEC> __device__ __forceinline__ RawT<IO, VEC> load_raw(gcptr_t p)
+// LOOSE: the vector is aligned to its elements only (the overlapped walk; global memory instructions take
+// any byte address on this target).
+template <typename IO, int VEC, bool LOOSE = false> __device__ __forceinline__ RawT<IO, VEC> load_raw(gcptr_t p)
 {
     using Raw = RawT<IO, VEC>;
-    return __builtin_nontemporal_load((const __attribute__((address_space(1))) Raw *)p);
+    if constexpr (LOOSE) {
+        typedef Raw LooseRaw __attribute__((aligned(sizeof(IO))));
+        return *(const __attribute__((address_space(1))) LooseRaw *)p;
+    } else {
+        return __builtin_nontemporal_load((const __attribute__((address_space(1))) Raw *)p);
+    }
 }
 
 // Reads a loaded vector at this point (no instruction is emitted), so that the wait for its load is
@@ -235,12 +246,13 @@ template <typename IO, int VEC> __device__ __forceinline__ void unpack(const Raw
     }
 }
 
-template <typename IO, int VEC> __device__ __forceinline__ void load_vec(gcptr_t p, float (&out)[VEC])
+template <typename IO, int VEC, bool LOOSE = false> __device__ __forceinline__ void load_vec(gcptr_t p, float (&out)[VEC])
 {
-    unpack<IO, VEC>(load_raw<IO, VEC>(p), out);
+    unpack<IO, VEC>(load_raw<IO, VEC, LOOSE>(p), out);
 }
 
-template <typename IO, int VEC> __device__ __forceinline__ void store_vec(gptr_t p, const float (&in)[VEC])
+template <typename IO, int VEC, bool LOOSE = false>
+__device__ __forceinline__ void store_vec(gptr_t p, const float (&in)[VEC])
 {
     constexpr int BYTES = (int)sizeof(IO) * VEC;
     using Raw = typename RawOf<BYTES>::type;
@@ -265,7 +277,12 @@ template <typename IO, int VEC> __device__ __forceinline__ void store_vec(gptr_t
                 r[i] = w;
         }
     }
-    __builtin_nontemporal_store(r, (__attribute__((address_space(1))) Raw *)p);
+    if constexpr (LOOSE) {
+        typedef Raw LooseRaw __attribute__((aligned(sizeof(IO))));
+        *(__attribute__((address_space(1))) LooseRaw *)p = r;
+    } else {
+        __builtin_nontemporal_store(r, (__attribute__((address_space(1))) Raw *)p);
+    }
 }
 
 // --------------------------------------------------------------------------
@@ -318,10 +335,12 @@ struct BwdArgs {
 // so that the chip as a whole keeps about 4 MB of loads in flight (measured
 // optimum of this memory system for a streaming read/write mix; both deeper
 // per-wave prefetch and more resident waves were measured slower).
-template <typename IO, int VEC, bool FIXED, bool LANECOEF, int M, int N>
+// LOOSE: the overlapped walk (a flat walk whose vectors are aligned to their elements only).
+template <typename IO, int VEC, bool FIXED, bool LANECOEF, int M, int N, bool LOOSE = false>
 __global__ __launch_bounds__(kThreadsPerWg) void grkan_fwd_kernel(const FwdArgs a)
 {
     static_assert(FIXED || !LANECOEF, "per-lane coefficients need fixed columns");
+    static_assert(LANECOEF || !LOOSE, "the overlapped walk is a flat walk");
     const Walk &p = a.walk;
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -331,7 +350,7 @@ __global__ __launch_bounds__(kThreadsPerWg) void grkan_fwd_kernel(const FwdArgs 
     // fixed column inside the wave's block of whole groups (vector registers)
     int cg;
     if constexpr (LANECOEF)
-        cg = (int)(((uint32_t)id.g * (uint32_t)p.dg + fixed_lane_col(p, id.w, lane).ccol * (uint32_t)p.vec) /
+        cg = (int)(((uint32_t)id.g * (uint32_t)p.dg + fixed_col_elem(p, fixed_lane_col(p, id.w, lane).ccol)) /
                    (uint32_t)a.dgc);
     else
         cg = p.dg == a.dgc ? id.g : (int)((uint32_t)id.g * (uint32_t)p.dg / (uint32_t)a.dgc);
@@ -345,11 +364,11 @@ __global__ __launch_bounds__(kThreadsPerWg) void grkan_fwd_kernel(const FwdArgs 
 
     auto one = [&](uint64_t off) {
         float xv[VEC], yv[VEC];
-        load_vec<IO, VEC>((gcptr_t)(x0 + off), xv);
+        load_vec<IO, VEC, LOOSE>((gcptr_t)(x0 + off), xv);
 #pragma unroll
         for (int e = 0; e < VEC; ++e)
             yv[e] = fwd_elem<WIDE, M, N>(xv[e], c);
-        store_vec<IO, VEC>((gptr_t)(y0 + off), yv);
+        store_vec<IO, VEC, LOOSE>((gptr_t)(y0 + off), yv);
     };
 
     if constexpr (FIXED) {
@@ -367,29 +386,29 @@ __global__ __launch_bounds__(kThreadsPerWg) void grkan_fwd_kernel(const FwdArgs 
 #pragma unroll
             for (int e = 0; e < VEC; ++e)
                 yv[e] = fwd_elem<WIDE, M, N>(xs[e], c);
-            store_vec<IO, VEC>(yout(i), yv);
+            store_vec<IO, VEC, LOOSE>(yout(i), yv);
         };
         if (n_it > 0) {
             // Two register sets take turns, so nothing is copied from "next" to "current" and the loop
             // body has no conditional load.  Per half trip: issue the loads of the following chunk
             // (raw, untouched), work on the current one, then wait for those loads before issuing any
             // more - one chunk of loads in flight per wave, which is what the persistent grid is sized for.
-            RawT<IO, VEC> ra = load_raw<IO, VEC>(xin(0));
+            RawT<IO, VEC> ra = load_raw<IO, VEC, LOOSE>(xin(0));
             arrived<IO, VEC>(ra); // the loop is entered, like re-entered, with nothing to wait for
             int32_t it = 0;
             for (; it + 2 < n_it; it += 2) {
                 keep_in_loop(lo);
-                const RawT<IO, VEC> rb = load_raw<IO, VEC>(xin(it + 1));
+                const RawT<IO, VEC> rb = load_raw<IO, VEC, LOOSE>(xin(it + 1));
                 issue_before_what_follows();
                 work(ra, it);
                 arrived<IO, VEC>(rb);
-                ra = load_raw<IO, VEC>(xin(it + 2));
+                ra = load_raw<IO, VEC, LOOSE>(xin(it + 2));
                 issue_before_what_follows();
                 work(rb, it + 1);
                 arrived<IO, VEC>(ra);
             }
             if (it + 1 < n_it) {
-                const RawT<IO, VEC> rb = load_raw<IO, VEC>(xin(it + 1));
+                const RawT<IO, VEC> rb = load_raw<IO, VEC, LOOSE>(xin(it + 1));
                 issue_before_what_follows();
                 work(ra, it);
                 work(rb, it + 1);
@@ -411,17 +430,18 @@ __global__ __launch_bounds__(kThreadsPerWg) void grkan_fwd_kernel(const FwdArgs 
 }
 
 // Backward, stage 1 (see the file header).
-template <typename IO, int VEC, bool FIXED, bool LANECOEF, int M, int N>
+template <typename IO, int VEC, bool FIXED, bool LANECOEF, int M, int N, bool LOOSE = false>
 __global__ __launch_bounds__(kThreadsPerWg) void grkan_bwd_stage1_kernel(const BwdArgs a)
 {
     static_assert(FIXED || !LANECOEF, "per-lane coefficients need fixed columns");
+    static_assert(LANECOEF || !LOOSE, "the overlapped walk is a flat walk");
     const Walk &p = a.walk;
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const WaveId id = wave_id(p, (int32_t)blockIdx.x, wv);
     int cg;
     if constexpr (LANECOEF)
-        cg = (int)(((uint32_t)id.g * (uint32_t)p.dg + fixed_lane_col(p, id.w, lane).ccol * (uint32_t)p.vec) /
+        cg = (int)(((uint32_t)id.g * (uint32_t)p.dg + fixed_col_elem(p, fixed_lane_col(p, id.w, lane).ccol)) /
                    (uint32_t)a.dgc);
     else
         cg = p.dg == a.dgc ? id.g : (int)((uint32_t)id.g * (uint32_t)p.dg / (uint32_t)a.dgc);
@@ -433,6 +453,8 @@ __global__ __launch_bounds__(kThreadsPerWg) void grkan_bwd_stage1_kernel(const B
     const uint64_t x0 = reinterpret_cast<uint64_t>(a.x);
     const uint64_t dy0 = reinterpret_cast<uint64_t>(a.dy);
     const uint64_t dx0 = reinterpret_cast<uint64_t>(a.dx);
+    // elements at the front of this lane's vectors that another lane counts (overlapped walk)
+    const int skip = LOOSE ? (int)overlap_skip(p, fixed_lane_col(p, id.w, lane).ccol) : 0;
 
     constexpr int kNumCoef = M + 1 + N; // sums per group
     float acc[kNumCoef];
@@ -442,12 +464,12 @@ __global__ __launch_bounds__(kThreadsPerWg) void grkan_bwd_stage1_kernel(const B
 
     auto one = [&](uint64_t off) {
         float xv[VEC], dv[VEC], ov[VEC];
-        load_vec<IO, VEC>((gcptr_t)(x0 + off), xv);
-        load_vec<IO, VEC>((gcptr_t)(dy0 + off), dv);
+        load_vec<IO, VEC, LOOSE>((gcptr_t)(x0 + off), xv);
+        load_vec<IO, VEC, LOOSE>((gcptr_t)(dy0 + off), dv);
 #pragma unroll
         for (int e = 0; e < VEC; ++e)
-            ov[e] = bwd_elem<WIDE, M, N>(xv[e], dv[e], c, acc);
-        store_vec<IO, VEC>((gptr_t)(dx0 + off), ov);
+            ov[e] = bwd_elem<WIDE, M, N, LOOSE>(xv[e], dv[e], c, acc, e < skip);
+        store_vec<IO, VEC, LOOSE>((gptr_t)(dx0 + off), ov);
     };
 
     if constexpr (FIXED) {
@@ -466,37 +488,37 @@ __global__ __launch_bounds__(kThreadsPerWg) void grkan_bwd_stage1_kernel(const B
             unpack<IO, VEC>(rd, ds);
 #pragma unroll
             for (int e = 0; e < VEC; ++e)
-                ov[e] = bwd_elem<WIDE, M, N>(xs[e], ds[e], c, acc);
-            store_vec<IO, VEC>(dxout(i), ov);
+                ov[e] = bwd_elem<WIDE, M, N, LOOSE>(xs[e], ds[e], c, acc, e < skip);
+            store_vec<IO, VEC, LOOSE>(dxout(i), ov);
         };
         if (n_it > 0) {
             // Two register sets take turns, so nothing is copied from "next" to "current" and the loop
             // body has no conditional load.  Per half trip: issue the loads of the following chunk
             // (raw, untouched), work on the current one, then wait for those loads before issuing any
             // more - one chunk of loads in flight per wave, which is what the persistent grid is sized for.
-            RawT<IO, VEC> xa = load_raw<IO, VEC>(xin(0));
-            RawT<IO, VEC> da = load_raw<IO, VEC>(dyin(0));
+            RawT<IO, VEC> xa = load_raw<IO, VEC, LOOSE>(xin(0));
+            RawT<IO, VEC> da = load_raw<IO, VEC, LOOSE>(dyin(0));
             arrived<IO, VEC>(xa); // the loop is entered, like re-entered, with nothing to wait for
             arrived<IO, VEC>(da);
             int32_t it = 0;
             for (; it + 2 < n_it; it += 2) {
                 keep_in_loop(lo);
-                const RawT<IO, VEC> xb = load_raw<IO, VEC>(xin(it + 1));
-                const RawT<IO, VEC> db = load_raw<IO, VEC>(dyin(it + 1));
+                const RawT<IO, VEC> xb = load_raw<IO, VEC, LOOSE>(xin(it + 1));
+                const RawT<IO, VEC> db = load_raw<IO, VEC, LOOSE>(dyin(it + 1));
                 issue_before_what_follows();
                 work(xa, da, it);
                 arrived<IO, VEC>(xb);
                 arrived<IO, VEC>(db);
-                xa = load_raw<IO, VEC>(xin(it + 2));
-                da = load_raw<IO, VEC>(dyin(it + 2));
+                xa = load_raw<IO, VEC, LOOSE>(xin(it + 2));
+                da = load_raw<IO, VEC, LOOSE>(dyin(it + 2));
                 issue_before_what_follows();
                 work(xb, db, it + 1);
                 arrived<IO, VEC>(xa);
                 arrived<IO, VEC>(da);
             }
             if (it + 1 < n_it) {
-                const RawT<IO, VEC> xb = load_raw<IO, VEC>(xin(it + 1));
-                const RawT<IO, VEC> db = load_raw<IO, VEC>(dyin(it + 1));
+                const RawT<IO, VEC> xb = load_raw<IO, VEC, LOOSE>(xin(it + 1));
+                const RawT<IO, VEC> db = load_raw<IO, VEC, LOOSE>(dyin(it + 1));
                 issue_before_what_follows();
                 work(xa, da, it);
                 work(xb, db, it + 1);
@@ -555,7 +577,7 @@ __global__ __launch_bounds__(kThreadsPerWg) void grkan_bwd_stage1_kernel(const B
         for (int k = 0; k < kNumCoef; ++k)
             lane_part[k][tid] = acc[k];
         __syncthreads();
-        const uint32_t vt = (uint32_t)a.dgc / (uint32_t)p.vec; // lanes per run
+        const uint32_t vt = LOOSE ? (uint32_t)p.gvecs : (uint32_t)a.dgc / (uint32_t)p.vec; // lanes per run
         const uint32_t V = (uint32_t)p.v;                       // vectors per row of the walk's column block
         const uint32_t Gb = (uint32_t)p.dg / (uint32_t)a.dgc;   // coefficient groups per column block
         const uint32_t c0 = ((uint32_t)id.wg_index * kThreadsPerWg) % V; // column of lane 0
@@ -750,8 +772,12 @@ template <typename IO, int VEC, int M, int N> static BwdKernel bwd_variant(bool 
                  : grkan_bwd_stage1_kernel<IO, VEC, false, false, M, N>;
 }
 
-template <int M, int N> static FwdKernel select_fwd(grkan_dtype_t io, int vec, bool fixed, bool lane_coef)
+template <int M, int N> static FwdKernel select_fwd(grkan_dtype_t io, int vec, bool fixed, bool lane_coef, bool overlapped)
 {
+    if (overlapped) // full vectors only
+        return io == GRKAN_F32    ? grkan_fwd_kernel<float, 4, true, true, M, N, true>
+               : io == GRKAN_BF16 ? grkan_fwd_kernel<bf16_t, 8, true, true, M, N, true>
+                                  : grkan_fwd_kernel<f16_t, 8, true, true, M, N, true>;
     switch (io) {
     case GRKAN_F32:
         switch (vec) {
@@ -780,8 +806,12 @@ template <int M, int N> static FwdKernel select_fwd(grkan_dtype_t io, int vec, b
     return nullptr;
 }
 
-template <int M, int N> static BwdKernel select_bwd(grkan_dtype_t io, int vec, bool fixed, bool lane_coef)
+template <int M, int N> static BwdKernel select_bwd(grkan_dtype_t io, int vec, bool fixed, bool lane_coef, bool overlapped)
 {
+    if (overlapped)
+        return io == GRKAN_F32    ? grkan_bwd_stage1_kernel<float, 4, true, true, M, N, true>
+               : io == GRKAN_BF16 ? grkan_bwd_stage1_kernel<bf16_t, 8, true, true, M, N, true>
+                                  : grkan_bwd_stage1_kernel<f16_t, 8, true, true, M, N, true>;
     switch (io) {
     case GRKAN_F32:
         switch (vec) {
@@ -815,8 +845,8 @@ template <int M, int N> static BwdKernel select_bwd(grkan_dtype_t io, int vec, b
 // units of the same family.
 struct DegreeOps {
     int m, n;
-    FwdKernel (*fwd)(grkan_dtype_t, int, bool, bool);
-    BwdKernel (*bwd)(grkan_dtype_t, int, bool, bool);
+    FwdKernel (*fwd)(grkan_dtype_t, int, bool, bool, bool);
+    BwdKernel (*bwd)(grkan_dtype_t, int, bool, bool, bool);
     Stage2Kernel stage2;
 };
 
@@ -882,13 +912,22 @@ static Want bwd_want(grkan_dtype_t io)
 }
 
 // Plans the launch with the wanted workgroups per unit, then clamps to what
-// the selected kernel can keep resident and re-plans if needed.
+// the selected kernel can keep resident and re-plans if needed.  may_overlap: no output shares memory with an
+// input, so that an element may be computed by two lanes.
 template <typename Select>
 static grkan_status_t plan_resident(int64_t rows, int32_t D, int32_t G, grkan_dtype_t io, int32_t align,
                                     const DeviceInfo &info, int dev, Want want, bool forward, Select select,
-                                    grkan_plan_t *pl, Walk *walk, const void **kernel)
+                                    bool may_overlap, grkan_plan_t *pl, Walk *walk, const void **kernel)
 {
     int per_cu = want.group_walk;
+    if (may_overlap && make_overlapped(rows, D, G, io, info.num_cu, want.flat_walk, pl, walk)) {
+        *kernel = reinterpret_cast<const void *>(select(io, pl->vec, true, true, true));
+        const int fit = resident_wg_per_cu(*kernel, dev);
+        if (fit <= 0)
+            return GRKAN_ERR_LAUNCH;
+        if (fit >= want.flat_walk || make_overlapped(rows, D, G, io, info.num_cu, fit, pl, walk))
+            return GRKAN_OK;
+    }
     grkan_status_t st = make_plan(rows, D, G, io, align, info.num_cu, per_cu, forward, pl, walk);
     if (st != GRKAN_OK)
         return st;
@@ -905,7 +944,7 @@ static grkan_status_t plan_resident(int64_t rows, int32_t D, int32_t G, grkan_dt
                 return st;
         }
     }
-    *kernel = reinterpret_cast<const void *>(select(io, pl->vec, pl->fixed_col != 0, pl->lane_coef != 0));
+    *kernel = reinterpret_cast<const void *>(select(io, pl->vec, pl->fixed_col != 0, pl->lane_coef != 0, false));
     if (!*kernel)
         return GRKAN_ERR_LAUNCH;
     const int fit = resident_wg_per_cu(*kernel, dev);
@@ -916,7 +955,7 @@ static grkan_status_t plan_resident(int64_t rows, int32_t D, int32_t G, grkan_dt
         st = make_plan(rows, D, G, io, align, info.num_cu, fit, forward, pl, walk);
         if (st != GRKAN_OK)
             return st;
-        *kernel = reinterpret_cast<const void *>(select(io, pl->vec, pl->fixed_col != 0, pl->lane_coef != 0));
+        *kernel = reinterpret_cast<const void *>(select(io, pl->vec, pl->fixed_col != 0, pl->lane_coef != 0, false));
         if (!*kernel || (pl->lane_coef != was_flat && resident_wg_per_cu(*kernel, dev) <= 0))
             return GRKAN_ERR_LAUNCH;
     }
@@ -956,11 +995,13 @@ extern "C" size_t grkan_bwd_workspace_bytes(int64_t rows, int32_t D, int32_t G, 
         for (int align = elem_size(io); align <= 16; align *= 2) {
             grkan_plan_t pl;
             const void *kernel = nullptr;
-            if (plan_resident(rows, D, G, io, align, info, dev, bwd_want(io), false, ops.bwd, &pl, nullptr, &kernel) !=
-                GRKAN_OK)
-                return 0;
-            const size_t b = workspace_for(pl, G, ops.m + 1 + ops.n);
-            need = b > need ? b : need;
+            for (int overlap = 0; overlap < 2; ++overlap) {
+                if (plan_resident(rows, D, G, io, align, info, dev, bwd_want(io), false, ops.bwd, overlap != 0, &pl, nullptr,
+                                  &kernel) != GRKAN_OK)
+                    return 0;
+                const size_t b = workspace_for(pl, G, ops.m + 1 + ops.n);
+                need = b > need ? b : need;
+            }
         }
     }
     return need;
@@ -998,6 +1039,12 @@ static CoefRows coef_rows(const void *A, const void *B, int32_t m, bool shared, 
     return CoefRows{A, B, shared ? 0 : m + 1, dtype == GRKAN_BF16};
 }
 
+static bool disjoint(const void *p, const void *q, size_t bytes)
+{
+    const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
+    return a + bytes <= b || b + bytes <= a;
+}
+
 static grkan_status_t fwd_impl(const void *x, const CoefRows &coef, void *y, int64_t rows, int32_t D, int32_t G, int32_t m,
                                int32_t n, grkan_dtype_t io, void *hip_stream)
 {
@@ -1021,8 +1068,9 @@ static grkan_status_t fwd_impl(const void *x, const CoefRows &coef, void *y, int
     grkan_plan_t pl;
     FwdArgs a;
     const void *kernel = nullptr;
-    st = plan_resident(rows, D, G, io, common_alignment({x, y}), info, dev, fwd_want(io), true, ops->fwd, &pl,
-                       &a.walk, &kernel);
+    const size_t bytes = (size_t)rows * (size_t)D * (size_t)es;
+    st = plan_resident(rows, D, G, io, common_alignment({x, y}), info, dev, fwd_want(io), true, ops->fwd,
+                       disjoint(x, y, bytes), &pl, &a.walk, &kernel);
     if (st != GRKAN_OK)
         return st;
     a.x = static_cast<const char *>(x);
@@ -1114,11 +1162,22 @@ static grkan_status_t bwd_impl(const void *x, const void *dy, const CoefRows &co
     grkan_plan_t pl;
     BwdArgs a;
     const void *kernel = nullptr;
-    st = plan_resident(rows, D, G, io, common_alignment({x, dy, dx}), info, dev, bwd_want(io), false, ops->bwd, &pl,
-                       &a.walk, &kernel);
+    const size_t bytes = (size_t)rows * (size_t)D * (size_t)es;
+    bool may_overlap = disjoint(x, dx, bytes) && disjoint(dy, dx, bytes);
+    st = plan_resident(rows, D, G, io, common_alignment({x, dy, dx}), info, dev, bwd_want(io), false, ops->bwd, may_overlap,
+                       &pl, &a.walk, &kernel);
     if (st != GRKAN_OK)
         return st;
-    const size_t need = workspace_for(pl, G, m + 1 + n);
+    size_t need = workspace_for(pl, G, m + 1 + n);
+    // a workspace that is too small for the overlapped walk may do for the other
+    const size_t limit = ws.own_scratch ? kScratchBytes : ws.alloc ? SIZE_MAX : ws.bytes;
+    if (a.walk.gvecs > 0 && need > limit) {
+        st = plan_resident(rows, D, G, io, common_alignment({x, dy, dx}), info, dev, bwd_want(io), false, ops->bwd, false, &pl,
+                           &a.walk, &kernel);
+        if (st != GRKAN_OK)
+            return st;
+        need = workspace_for(pl, G, m + 1 + n);
+    }
     void *workspace = ws.ptr;
     if (ws.own_scratch) {
         if (need > kScratchBytes)

@@ -33,10 +33,10 @@ static int pick_vec(int32_t dg, int es, int32_t align_bytes)
 // Plan of the group walk over `Gw` groups of `dgw` channels with vectors of
 // `vec` elements (Gw = 1, dgw = D describes the flat walk over whole rows).
 static grkan_status_t plan_walk(int64_t rows, int32_t D, int32_t Gw, int32_t vec, int es, int32_t num_cu,
-                                int32_t wg_per_cu, grkan_plan_t *out)
+                                int32_t wg_per_cu, grkan_plan_t *out, int32_t vecs_per_row = 0)
 {
     const int32_t dg = D / Gw;
-    const int32_t v = dg / vec;
+    const int32_t v = vecs_per_row > 0 ? vecs_per_row : dg / vec; // (given: the overlapped walk)
     const int32_t nw = kWavesPerWg;
 
     // Adjacent groups share a workgroup when one group's row segment is not a
@@ -175,6 +175,49 @@ grkan_status_t make_plan(int64_t rows, int32_t D, int32_t G, grkan_dtype_t io, i
     return GRKAN_OK;
 }
 
+static grkan_status_t set_walk(int64_t rows, const grkan_plan_t &pl, Walk *walk);
+
+bool make_overlapped(int64_t rows, int32_t D, int32_t G, grkan_dtype_t io, int32_t num_cu, int32_t wg_per_cu,
+                     grkan_plan_t *out, Walk *walk)
+{
+    if (check_shape(rows, D, G, io) != GRKAN_OK || rows == 0 || num_cu <= 0 || wg_per_cu <= 0)
+        return false;
+    const int es = elem_size(io);
+    const int32_t dg = D / G, vec = 16 / es;
+    // Whenever no 16-byte vector divides d_g and a group holds one at all.  Measured against the vectors that do
+    // divide it, forward / backward in us: of 2 bytes (f16 [15677, 600], d_g = 75) 21.0 / 27.0 -> 8.0 / 21.5;
+    // of 4 (f32 [15677, 1000], d_g = 125) 38.4 / 59.2 -> 19.9 / 38; of 8 (f32 [15677, 1040], d_g = 130)
+    // 26.3 / 43.9 -> 21.2 / 38.1, (bf16 [15677, 800], d_g = 100) 11.5 / 24.8 -> 9.3 / 23.3.  The duplicated
+    // elements and the masks of the sums cost less than the narrow accesses at every d_g tried, down to 9 of 8.
+    int32_t divides = vec;
+    while (dg % divides != 0)
+        divides /= 2;
+    if (divides * es > 8 || dg < vec)
+        return false;
+    const int64_t gvecs = (dg + vec - 1) / vec;
+    if (gvecs * G > INT32_MAX / kWave)
+        return false;
+    grkan_plan_t pl;
+    if (plan_walk(rows, D, 1, vec, es, num_cu, wg_per_cu, &pl, (int32_t)(gvecs * G)) != GRKAN_OK || !pl.fixed_col ||
+        pl.groups_per_wg != 1)
+        return false;
+    pl.lane_coef = 1;
+    Walk w;
+    w.rows = rows;
+    w.D = D;
+    w.G = 1;
+    w.dg = D;
+    w.vec = vec;
+    w.gvecs = (int32_t)gvecs;
+    w.gdim = dg;
+    if (set_walk(rows, pl, &w) != GRKAN_OK)
+        return false;
+    *out = pl;
+    if (walk)
+        *walk = w;
+    return true;
+}
+
 grkan_status_t walk_from_plan(int64_t rows, int32_t D, int32_t G, grkan_dtype_t io,
                               const grkan_plan_t &pl, Walk *walk)
 {
@@ -198,10 +241,18 @@ grkan_status_t walk_from_plan(int64_t rows, int32_t D, int32_t G, grkan_dtype_t 
     walk->G = Gw;
     walk->dg = dg;
     walk->vec = pl.vec;
+    walk->gvecs = 0;
+    walk->gdim = 0;
+    return set_walk(rows, pl, walk);
+}
+
+// The part of a walk that follows from its D, G, dg, vec and the plan's geometry.
+static grkan_status_t set_walk(int64_t rows, const grkan_plan_t &pl, Walk *walk)
+{
     walk->v = pl.vecs_per_segment;
     walk->k = pl.groups_per_wg;
     walk->ns = pl.waves_per_group_in_wg;
-    walk->nb = Gw / pl.groups_per_wg;
+    walk->nb = walk->G / pl.groups_per_wg;
     walk->wg_per_bundle = pl.wg_per_bundle;
     const int64_t Wg = (int64_t)pl.wg_per_bundle * walk->ns;
     if (Wg >= ((int64_t)1 << 25))
@@ -309,6 +360,54 @@ extern "C" int64_t grkan_plan_cover_errors(int64_t rows, int32_t D, int32_t G, g
     if (plan->fixed_col && w.dr != 0)
         return 1;
     return grkan::cover_errors(w, plan->fixed_col != 0, grkan::elem_size(io));
+}
+
+extern "C" int64_t grkan_overlapped_cover_errors(int64_t rows, int32_t D, int32_t G, grkan_dtype_t io,
+                                                 int32_t num_cu, int32_t wg_per_cu)
+{
+    using namespace grkan;
+    grkan_plan_t pl;
+    Walk p;
+    if (!make_overlapped(rows, D, G, io, num_cu, wg_per_cu, &pl, &p))
+        return -2;
+    if (rows * (int64_t)D > ((int64_t)1 << 28))
+        return -1;
+    // every element is stored (by one or two lanes of its own group) and counted in exactly one sum
+    std::vector<uint8_t> stored((size_t)(rows * D), 0), summed((size_t)(rows * D), 0);
+    int64_t bad = p.dr != 0 ? 1 : 0;
+    const int es = elem_size(io);
+    auto visit = [&](int64_t off, uint32_t ccol) {
+        const uint32_t skip = overlap_skip(p, ccol);
+        const int64_t g = ccol / p.gvecs;
+        for (int32_t e = 0; e < p.vec; ++e) {
+            const int64_t at = off + e;
+            if (at < 0 || at >= rows * (int64_t)D || (at % D) / p.gdim != g) {
+                ++bad;
+                continue;
+            }
+            stored[(size_t)at] = 1;
+            if ((uint32_t)e >= skip && summed[(size_t)at]++)
+                ++bad;
+        }
+    };
+    for (int32_t b = 0; b < pl.grid; ++b)
+        for (int32_t wv = 0; wv < p.k * p.ns; ++wv) {
+            const WaveId id = wave_id(p, b, wv);
+            const int32_t n_it = full_visits(p, id.w);
+            for (int32_t lane = 0; lane < kWave; ++lane) {
+                const uint64_t lo = fixed_lane_offset(p, id.w, lane);
+                if ((lo * es) >> 32)
+                    ++bad;
+                const uint32_t ccol = fixed_lane_col(p, id.w, lane).ccol;
+                const int32_t visits = n_it + (owns_tail(p, id.w) && lane < p.rem ? 1 : 0);
+                for (int32_t it = 0; it < visits; ++it)
+                    visit(fixed_base0(p, id.g, id.w) + (int64_t)it * fixed_step(p) + (int64_t)lo, ccol);
+            }
+        }
+    for (size_t i = 0; i < stored.size(); ++i)
+        if (!stored[i] || summed[i] != 1)
+            ++bad;
+    return bad;
 }
 
 extern "C" const char *grkan_status_string(grkan_status_t s)

@@ -19,6 +19,11 @@
 // lane belongs to one coefficient group for the whole kernel and keeps that
 // group's coefficients in vector registers.  Likewise a walk group can be a
 // column block of one coefficient group (few, long groups are cut up).
+//
+// Overlapped walk: groups of d_g channels that are not whole vectors (d_g = 75, say) are cut into
+// ceil(d_g / vec) vectors of which the last starts at d_g - vec and so repeats elements of the one before.
+// It is a flat walk otherwise (fixed columns, coefficients per lane).  Repeated elements are computed and
+// stored twice with the same result and enter the sums once (overlap_skip).
 #ifndef GRKAN_WALK_H_
 #define GRKAN_WALK_H_
 
@@ -65,6 +70,8 @@ struct Walk {
     int32_t visits_base;   // n_full div Wg : full chunks every wave visits (< 2^31 - 1)
     int32_t visits_rem;    // n_full mod Wg : waves below this index visit one more
     int32_t rem;           // lanes in range in the last, partial chunk (0 = none)
+    int32_t gvecs;         // overlapped walk: vectors per coefficient group (0 in every other walk)
+    int32_t gdim;          // overlapped walk: channels per coefficient group
 };
 
 // Which group and which wave-of-the-group a wavefront is.
@@ -163,10 +170,29 @@ GRKAN_HD LaneCol fixed_lane_col(const Walk &p, int32_t w, int32_t lane)
     return lc;
 }
 
+// Element a lane's vector starts at, from the row's (or the column block's) start.
+GRKAN_HD uint32_t fixed_col_elem(const Walk &p, uint32_t ccol)
+{
+    if (p.gvecs == 0)
+        return ccol * (uint32_t)p.vec;
+    const uint32_t g = ccol / (uint32_t)p.gvecs, j = ccol - g * (uint32_t)p.gvecs;
+    const uint32_t at = j * (uint32_t)p.vec, most = (uint32_t)(p.gdim - p.vec);
+    return g * (uint32_t)p.gdim + (at < most ? at : most);
+}
+
+// Leading elements of the vector that the vector before it holds too (0 outside the overlapped walk).
+GRKAN_HD uint32_t overlap_skip(const Walk &p, uint32_t ccol)
+{
+    if (p.gvecs == 0)
+        return 0;
+    const uint32_t j = ccol % (uint32_t)p.gvecs;
+    return j + 1 == (uint32_t)p.gvecs ? (uint32_t)(p.gvecs * p.vec - p.gdim) : 0u;
+}
+
 GRKAN_HD uint32_t fixed_lane_offset(const Walk &p, int32_t w, int32_t lane)
 {
     const LaneCol lc = fixed_lane_col(p, w, lane);
-    return lc.rrow * (uint32_t)p.D + lc.ccol * (uint32_t)p.vec;
+    return lc.rrow * (uint32_t)p.D + fixed_col_elem(p, lc.ccol);
 }
 
 } // namespace grkan
