@@ -645,6 +645,7 @@ __global__ __launch_bounds__(kStage2MaxThreads) void grkan_bwd_stage2_kernel(con
     if (G_shared > 0 && g >= G_shared) {
         const int k = g - G_shared;
         double s = 0.0;
+#pragma unroll 8
         for (int64_t r = tid; r < (int64_t)G_shared * rows_per_group; r += T)
             s += (double)partial[r * kNumCoef + k];
         thread_sum[0][tid] = s;
@@ -670,6 +671,7 @@ __global__ __launch_bounds__(kStage2MaxThreads) void grkan_bwd_stage2_kernel(con
 #pragma unroll
     for (int k = 0; k < kNumCoef; ++k)
         s[k] = 0.0;
+#pragma unroll 4
     for (int r = tid; r < rows_per_group; r += T) {
 #pragma unroll
         for (int k = 0; k < kNumCoef; ++k)
