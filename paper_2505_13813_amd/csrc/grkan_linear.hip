@@ -81,15 +81,18 @@ struct LinArgs {
     int32_t n_major;   // small kernel: tiles of one channel block share an XCD (else: of one token block)
 };
 
-// LDS of the small kernel: four x buffers of a 64-k block for each group of WN wavefronts, and a ring of
-// 2 KB weight slots per wavefront, as deep as 160 KB allow
-constexpr int small_x_bytes(int MT, int WN) { return (8 / WN) * 4 * MT * 2048; }
-constexpr int small_ring(int MT, int WN)
+// LDS of the small kernel: four x buffers of a 64-k block for each group of WN of the NW wavefronts, and a
+// ring of 2 KB weight slots per wavefront, as deep as 160 KB allow
+constexpr int small_x_bytes(int NW, int MT, int WN) { return (NW / WN) * 4 * MT * 2048; }
+constexpr int small_ring(int NW, int MT, int WN)
 {
-    const int fit = (160 * 1024 - small_x_bytes(MT, WN)) / (8 * 2048);
+    const int fit = (160 * 1024 - small_x_bytes(NW, MT, WN)) / (NW * 2048);
     return fit > 8 ? 8 : fit;
 }
-constexpr size_t small_lds_bytes(int MT, int WN) { return (size_t)8 * small_ring(MT, WN) * 2048 + small_x_bytes(MT, WN); }
+constexpr size_t small_lds_bytes(int NW, int MT, int WN)
+{
+    return (size_t)NW * small_ring(NW, MT, WN) * 2048 + small_x_bytes(NW, MT, WN);
+}
 
 __device__ __forceinline__ uint64_t uniform_u64(uint64_t v)
 {
@@ -660,7 +663,7 @@ __global__ __launch_bounds__(64 * NW, 1) void grkan_linear_fwd_kernel(const LinA
 // the same layer for inputs of too few rows to fill the chip with 112-row tiles
 // --------------------------------------------------------------------------
 //
-// A workgroup of eight wavefronts, WK groups of WN: group kg takes the 64-k blocks kg, kg + WK, .. of
+// A workgroup of NW wavefronts, WK groups of WN: group kg takes the 64-k blocks kg, kg + WK, .. of
 // the contraction, wavefront wn of a group the 16 NT channels [16 NT wn, 16 NT (wn + 1)) of the tile, all
 // of them the tile's BM = 16 MT tokens; the WK partial tiles are added in group order at the end.
 //   * W: LDS-direct loads into a ring of kRing 2 KB slots per wavefront (16 rows x 64 k), private to it;
@@ -671,17 +674,17 @@ __global__ __launch_bounds__(64 * NW, 1) void grkan_linear_fwd_kernel(const LinA
 //     units it has fetched by F of them in place, one block ahead of their use.  (With LDS-direct loads in
 //     flight the compiler can wait for a load into registers only by waiting for everything.)  With WN = 1
 //     a wavefront reads what it wrote itself and the loop has no barrier.
-template <int MT, int NT, int WN, typename OUT, bool PACKED, int M, int N>
-__global__ __launch_bounds__(512, 1) void grkan_linear_small_kernel(const LinArgs a)
+template <int NW, int MT, int NT, int WN, typename OUT, bool PACKED, int M, int N>
+__global__ __launch_bounds__(64 * NW, 1) void grkan_linear_small_kernel(const LinArgs a)
 {
-    constexpr int WK = 8 / WN;
+    constexpr int WK = NW / WN;
     constexpr int BM = 16 * MT;
     constexpr int BN = 16 * NT * WN;
     constexpr int PU = 2 * MT / WN; // 16-row, 32-k units of x a wavefront turns into F per block
     constexpr uint32_t kXB = 2u * MT * 1024u; // bytes of a block of x: unit q at 1024 q, half q / MT, rows 16 (q % MT) ..
-    constexpr int kRing = small_ring(MT, WN);
-    constexpr uint32_t kX0 = 8u * kRing * 2048u;
-    static_assert(WN * WK == 8 && PU >= 1 && PU * WN == 2 * MT, "eight wavefronts share the units of a block evenly");
+    constexpr int kRing = small_ring(NW, MT, WN);
+    constexpr uint32_t kX0 = (uint32_t)NW * kRing * 2048u;
+    static_assert(WN * WK == NW && PU >= 1 && PU * WN == 2 * MT, "a group's wavefronts share the units of a block evenly");
     static_assert(kRing <= 2 * NT + 2, "a weight tile waited for must be younger than the x needed with it");
     extern __shared__ __align__(16) char smem[];
     const lptr_t lds = (lptr_t)smem;
@@ -941,23 +944,44 @@ __global__ __launch_bounds__(512, 1) void grkan_linear_small_kernel(const LinArg
         block_barrier();
 
     // ---- epilogue: the partial tiles go to LDS as [WK][BM][BN + 4] float32 and leave as whole rows
+    // (as many groups at a time as fit; the first ones add what the others left in their place)
     constexpr int kPitchF = BN + 4;
-    static_assert((size_t)WK * BM * kPitchF * 4 <= small_lds_bytes(MT, WN), "partial tiles must fit the operand buffers");
+    constexpr int kSlab = BM * kPitchF * 4;
+    constexpr int kSlabs = WK * kSlab <= (int)small_lds_bytes(NW, MT, WN) ? WK : WK / 2;
+    static_assert(kSlabs >= 1 && kSlabs * kSlab <= (int)small_lds_bytes(NW, MT, WN), "partial tiles must fit the operand buffers");
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // every fetch into the ring has landed
     __syncthreads();
-    {
-        const uint32_t dst = lds0 + ((uint32_t)kg * BM + (uint32_t)(lane & 15)) * (kPitchF * 4u) +
+    const uint32_t slab_at = lds0 + (uint32_t)(kg % kSlabs) * kSlab + (uint32_t)(lane & 15) * (kPitchF * 4u) +
                              (uint32_t)(wn * 16 * NT + (lane >> 4) * 4) * 4u;
+    auto slab = [&](int nt, int mt) {
+        return (__attribute__((address_space(3))) f32x4 *)(uintptr_t)(slab_at + (uint32_t)(mt * 16) * (kPitchF * 4u) + (uint32_t)nt * 64u);
+    };
+    if (kSlabs < WK) {
+        if (kg >= kSlabs) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    *slab(nt, mt) = acc[nt][mt];
+        }
+        __syncthreads();
+        if (kg < kSlabs) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    *slab(nt, mt) = acc[nt][mt] + *slab(nt, mt);
+        }
+    } else {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
-                *(__attribute__((address_space(3))) f32x4 *)(uintptr_t)(dst + (uint32_t)(mt * 16) * (kPitchF * 4u) + (uint32_t)nt * 64u) =
-                    acc[nt][mt];
+                *slab(nt, mt) = acc[nt][mt];
     }
     __syncthreads();
     constexpr int QPR = BN / 4; // four channels per lane
-    for (int i = tid; i < BM * QPR; i += 512) {
+    for (int i = tid; i < BM * QPR; i += 64 * NW) {
         const int r = i / QPR;
         const int o = n0 + (i - r * QPR) * 4;
         if (m0 + r >= a.rows || o >= a.Nout)
@@ -965,8 +989,8 @@ __global__ __launch_bounds__(512, 1) void grkan_linear_small_kernel(const LinArg
         const uint32_t src = lds0 + (uint32_t)r * (kPitchF * 4u) + (uint32_t)(o - n0) * 4u;
         f32x4 v = *(const __attribute__((address_space(3))) f32x4 *)(uintptr_t)src;
 #pragma unroll
-        for (int g = 1; g < WK; ++g)
-            v += *(const __attribute__((address_space(3))) f32x4 *)(uintptr_t)(src + (uint32_t)g * (BM * kPitchF * 4u));
+        for (int g = 1; g < kSlabs; ++g)
+            v += *(const __attribute__((address_space(3))) f32x4 *)(uintptr_t)(src + (uint32_t)g * kSlab);
         if (a.bias)
             v += *(const f32x4 *)(a.bias + o);
         OutPack<OUT>::store((gptr_t)(a.out + ((m0 + r) * a.Nout + o) * (int)sizeof(OUT)), v);
@@ -997,9 +1021,12 @@ static Variant pick_variant(int32_t D_out)
     return Variant{4, 3};
 }
 
-// Tile variants of the small kernel: (16-token sub-tiles, 16-channel sub-tiles per wave, waves side by side)
+// Tile variants of the small kernel: (waves, 16-token sub-tiles, 16-channel sub-tiles per wave, waves side by
+// side).  The widest tile has sixteen waves, four per SIMD, in two groups: with eight in one group the F
+// evaluations, the matrix instructions and the operand reads of a block all waited for each other at its
+// barrier (one round at D_in = 3072: 51 -> 45 us).  The others have no room in LDS for sixteen.
 struct SmallVariant {
-    int mt, nt, wn;
+    int nw, mt, nt, wn;
     double fixed_us, us_per_1k; // time of one round of workgroups: fixed_us + us_per_1k D_in / 1024
     int bm() const { return 16 * mt; }
     int bn() const { return 16 * nt * wn; }
@@ -1010,12 +1037,12 @@ struct SmallVariant {
 // 1536 -> 384, 768 -> 192 and 768 -> 3072 (measured on MI355X, us per round at D_in = 768 / 1536 / 3072, the
 // chip filled):
 //   16 x 64: 6.6 / 7.8 / 11.7    32 x 128: 8.5 / 12.2 / 20.5    64 x 192: 13.2 / 21 / 36
-//   64 x 384: 17.5 / 28.5 / 51   112 x 768: 41 / - / 133   112 x 384: - / 43 / -   112 x 192: 24 / - / -
+//   64 x 384: 15.8 / 24.5 / 45   112 x 768: 41 / - / 133   112 x 384: - / 43 / -   112 x 192: 24 / - / -
 static const SmallVariant kSmall[] = {
-    {1, 4, 1, 4.8, 2.3},
-    {2, 4, 2, 4.4, 5.3},
-    {4, 3, 4, 5.7, 10.1},
-    {4, 3, 8, 6.5, 14.7},
+    {8, 1, 4, 1, 4.8, 2.3},
+    {8, 2, 4, 2, 4.4, 5.3},
+    {8, 4, 3, 4, 5.7, 10.1},
+    {16, 4, 3, 8, 6.0, 12.7},
 };
 constexpr int kRound = 256;
 
@@ -1049,13 +1076,13 @@ static const SmallVariant *pick_small(int64_t rows, int32_t D_in, int32_t D_out,
 template <typename OUT, bool PACKED> static LinKernel select_small(SmallVariant v)
 {
     if (v.mt == 1 && v.nt == 4 && v.wn == 1)
-        return grkan_linear_small_kernel<1, 4, 1, OUT, PACKED, 5, 4>;
+        return grkan_linear_small_kernel<8, 1, 4, 1, OUT, PACKED, 5, 4>;
     if (v.mt == 2 && v.nt == 4 && v.wn == 2)
-        return grkan_linear_small_kernel<2, 4, 2, OUT, PACKED, 5, 4>;
+        return grkan_linear_small_kernel<8, 2, 4, 2, OUT, PACKED, 5, 4>;
     if (v.mt == 4 && v.nt == 3 && v.wn == 4)
-        return grkan_linear_small_kernel<4, 3, 4, OUT, PACKED, 5, 4>;
+        return grkan_linear_small_kernel<8, 4, 3, 4, OUT, PACKED, 5, 4>;
     if (v.mt == 4 && v.nt == 3 && v.wn == 8)
-        return grkan_linear_small_kernel<4, 3, 8, OUT, PACKED, 5, 4>;
+        return grkan_linear_small_kernel<16, 4, 3, 8, OUT, PACKED, 5, 4>;
     return nullptr;
 }
 
@@ -1179,7 +1206,7 @@ static grkan_status_t linear_fwd_impl(const void *x, const float *A, const float
         kernel = out_dtype == GRKAN_BF16 ? select_kernel<bf16_out, false>(v, nedge) : select_kernel<float, false>(v, nedge);
     if (!kernel)
         return GRKAN_ERR_LAUNCH;
-    const size_t lds = small ? small_lds_bytes(small->mt, small->wn) : lds_bytes(v);
+    const size_t lds = small ? small_lds_bytes(small->nw, small->mt, small->wn) : lds_bytes(v);
     if (!allow_lds(reinterpret_cast<const void *>(kernel), lds))
         return GRKAN_ERR_LAUNCH;
 
@@ -1206,7 +1233,7 @@ static grkan_status_t linear_fwd_impl(const void *x, const float *A, const float
     a.wtiles = (int32_t)packed_tiles(D_out);
     void *args[] = {&a};
     const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3((unsigned)grid),
-                                         dim3(small ? 512 : 64 * v.nw), args, lds, static_cast<hipStream_t>(hip_stream));
+                                         dim3(64 * (small ? small->nw : v.nw)), args, lds, static_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? GRKAN_OK : GRKAN_ERR_LAUNCH;
 }
 
