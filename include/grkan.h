@@ -123,15 +123,16 @@ int64_t grkan_plan_cover_errors(int64_t rows, int32_t D, int32_t G, grkan_dtype_
                                 const grkan_plan_t *plan);
 
 /*
- * Groups whose d_g is not a whole number of 16-byte vectors but holds one (d_g = 75, say) take a third walk when no output
- * shares memory with an input: a flat walk of full 16-byte vectors, aligned to their elements only, of which
- * the last of a group repeats elements of the one before (computed twice, counted once).  It is not described
- * by grkan_plan; this host-only check walks it as the kernels do and returns the number of elements that are not
- * stored, are outside their group or the array, or are not counted exactly once: 0 is right, -2 if the shape
+ * Groups whose d_g is not a whole number of 16-byte vectors but holds one (d_g = 75, say; in the backward pass
+ * not a whole number of 8-byte vectors either) take a third walk when no output shares memory with an input: a
+ * flat walk of full 16-byte vectors, aligned to their elements only, of which the last of a group repeats
+ * elements of the one before (computed twice, counted once).  It is not described by grkan_plan; this host-only
+ * check walks it as the kernels do and returns the number of elements that are not stored, are outside their
+ * group or the array, or are not counted exactly once: 0 is right, -2 if the shape
  * does not take that walk, -1 if it is too large to simulate.
  */
 int64_t grkan_overlapped_cover_errors(int64_t rows, int32_t D, int32_t G, grkan_dtype_t io,
-                                      int32_t num_cu, int32_t wg_per_cu);
+                                      int32_t num_cu, int32_t wg_per_cu, int32_t forward);
 
 /*
  * Bytes of device workspace grkan_bwd needs for this shape on the current

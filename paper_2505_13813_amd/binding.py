@@ -75,7 +75,7 @@ def load_library():
     lib.grkan_plan.restype = ctypes.c_int
     lib.grkan_plan_cover_errors.argtypes = [i64, i32, i32, ctypes.c_int, ctypes.POINTER(Plan)]
     lib.grkan_plan_cover_errors.restype = i64
-    lib.grkan_overlapped_cover_errors.argtypes = [i64, i32, i32, ctypes.c_int, i32, i32]
+    lib.grkan_overlapped_cover_errors.argtypes = [i64, i32, i32, ctypes.c_int, i32, i32, i32]
     lib.grkan_overlapped_cover_errors.restype = i64
     lib.grkan_device_query.argtypes = [ctypes.POINTER(ctypes.c_int32)]
     lib.grkan_device_query.restype = ctypes.c_int
@@ -147,9 +147,10 @@ def plan_cover_errors(rows: int, D: int, G: int, io: int, p: Plan) -> int:
     return int(load_library().grkan_plan_cover_errors(rows, D, G, io, ctypes.byref(p)))
 
 
-def overlapped_cover_errors(rows: int, D: int, G: int, io: int, num_cu: int = 256, wg_per_cu: int = 4) -> int:
+def overlapped_cover_errors(rows: int, D: int, G: int, io: int, num_cu: int = 256, wg_per_cu: int = 4,
+                            forward: bool = False) -> int:
     """Host-only check of the overlapped walk (see grkan.h); -2 if the shape does not take it."""
-    return int(load_library().grkan_overlapped_cover_errors(rows, D, G, io, num_cu, wg_per_cu))
+    return int(load_library().grkan_overlapped_cover_errors(rows, D, G, io, num_cu, wg_per_cu, 1 if forward else 0))
 
 
 # ---------------------------------------------------------------- raw pointer level

@@ -922,12 +922,12 @@ static grkan_status_t plan_resident(int64_t rows, int32_t D, int32_t G, grkan_dt
                                     bool may_overlap, grkan_plan_t *pl, Walk *walk, const void **kernel)
 {
     int per_cu = want.group_walk;
-    if (may_overlap && make_overlapped(rows, D, G, io, info.num_cu, want.flat_walk, pl, walk)) {
+    if (may_overlap && make_overlapped(rows, D, G, io, info.num_cu, want.flat_walk, forward, pl, walk)) {
         *kernel = reinterpret_cast<const void *>(select(io, pl->vec, true, true, true));
         const int fit = resident_wg_per_cu(*kernel, dev);
         if (fit <= 0)
             return GRKAN_ERR_LAUNCH;
-        if (fit >= want.flat_walk || make_overlapped(rows, D, G, io, info.num_cu, fit, pl, walk))
+        if (fit >= want.flat_walk || make_overlapped(rows, D, G, io, info.num_cu, fit, forward, pl, walk))
             return GRKAN_OK;
     }
     grkan_status_t st = make_plan(rows, D, G, io, align, info.num_cu, per_cu, forward, pl, walk);

@@ -178,21 +178,23 @@ grkan_status_t make_plan(int64_t rows, int32_t D, int32_t G, grkan_dtype_t io, i
 static grkan_status_t set_walk(int64_t rows, const grkan_plan_t &pl, Walk *walk);
 
 bool make_overlapped(int64_t rows, int32_t D, int32_t G, grkan_dtype_t io, int32_t num_cu, int32_t wg_per_cu,
-                     grkan_plan_t *out, Walk *walk)
+                     bool forward, grkan_plan_t *out, Walk *walk)
 {
     if (check_shape(rows, D, G, io) != GRKAN_OK || rows == 0 || num_cu <= 0 || wg_per_cu <= 0)
         return false;
     const int es = elem_size(io);
     const int32_t dg = D / G, vec = 16 / es;
-    // Whenever no 16-byte vector divides d_g and a group holds one at all.  Measured against the vectors that do
-    // divide it, forward / backward in us: of 2 bytes (f16 [15677, 600], d_g = 75) 21.0 / 27.0 -> 8.0 / 21.5;
-    // of 4 (f32 [15677, 1000], d_g = 125) 38.4 / 59.2 -> 19.9 / 38; of 8 (f32 [15677, 1040], d_g = 130)
-    // 26.3 / 43.9 -> 21.2 / 38.1, (bf16 [15677, 800], d_g = 100) 11.5 / 24.8 -> 9.3 / 23.3.  The duplicated
-    // elements and the masks of the sums cost less than the narrow accesses at every d_g tried, down to 9 of 8.
+    // When a group holds a 16-byte vector but is not a whole number of them: the forward pass always, the backward
+    // pass unless 8-byte vectors fit.  Measured against the vectors that divide d_g, forward / backward in us: of
+    // 2 bytes (f16 [15677, 600], d_g = 75) 21.0 / 27.0 -> 8.0 / 21.5; of 4 (f32 [15677, 1000], d_g = 125)
+    // 38.4 / 59.2 -> 19.9 / 38, ([50432, 3000], d_g = 375) 433 / 471 -> 253 / 364; of 8 (f32 [34620, 592],
+    // d_g = 74) 32.0 / 50.5 -> 25.9 / 53, ([100000, 400], d_g = 50) 59.2 / 90 -> 56 / 95, (bf16 [100000, 800],
+    // d_g = 100) 58.9 / 104 -> 56.6 / 110.  In the backward pass the masks of the sums and the column blocks it
+    // gives up weigh more than 8-byte accesses do.
     int32_t divides = vec;
     while (dg % divides != 0)
         divides /= 2;
-    if (divides * es > 8 || dg < vec)
+    if (divides * es > (forward ? 8 : 4) || dg < vec)
         return false;
     const int64_t gvecs = (dg + vec - 1) / vec;
     if (gvecs * G > INT32_MAX / kWave)
@@ -363,12 +365,12 @@ extern "C" int64_t grkan_plan_cover_errors(int64_t rows, int32_t D, int32_t G, g
 }
 
 extern "C" int64_t grkan_overlapped_cover_errors(int64_t rows, int32_t D, int32_t G, grkan_dtype_t io,
-                                                 int32_t num_cu, int32_t wg_per_cu)
+                                                 int32_t num_cu, int32_t wg_per_cu, int32_t forward)
 {
     using namespace grkan;
     grkan_plan_t pl;
     Walk p;
-    if (!make_overlapped(rows, D, G, io, num_cu, wg_per_cu, &pl, &p))
+    if (!make_overlapped(rows, D, G, io, num_cu, wg_per_cu, forward != 0, &pl, &p))
         return -2;
     if (rows * (int64_t)D > ((int64_t)1 << 28))
         return -1;

@@ -21,7 +21,7 @@ grkan_status_t make_plan(int64_t rows, int32_t D, int32_t G, grkan_dtype_t io, i
 // The overlapped walk (grkan_walk.h) for groups that are not whole vectors: true if the shape takes it, with
 // the plan and the walk.  It is an addition to make_plan, whose plans (and grkan_plan's) never overlap.
 bool make_overlapped(int64_t rows, int32_t D, int32_t G, grkan_dtype_t io, int32_t num_cu, int32_t wg_per_cu,
-                     grkan_plan_t *out, Walk *walk);
+                     bool forward, grkan_plan_t *out, Walk *walk);
 
 // Rebuilds the walk parameters from a public plan (validating it).
 grkan_status_t walk_from_plan(int64_t rows, int32_t D, int32_t G, grkan_dtype_t io,

@@ -10,7 +10,8 @@ from paper_2505_13813_amd import GRKAN_BF16, GRKAN_F16, GRKAN_F32
 
 def test_cover_of_random_shapes():
     """Every element stored by lanes of its own group, counted once, nothing outside: awkward group sizes, row
-    counts and device sizes; and the rule takes every d_g that holds a 16-byte vector and is not a whole number of them."""
+    counts and device sizes; and the rule takes every d_g that holds a 16-byte vector and is not a whole number of
+    them (backward: of 8-byte vectors)."""
     rng = random.Random(75)
     taken = 0
     for trial in range(400):
@@ -22,10 +23,11 @@ def test_cover_of_random_shapes():
         if rows * G * dg > 300_000:
             rows = max(1, 300_000 // (G * dg))
         cu, wg = rng.choice([(256, 3), (256, 8), (8, 1), (1, 1), (64, 7)])
-        errors = grkan.binding.overlapped_cover_errors(rows, G * dg, G, io, cu, wg)
+        forward = rng.random() < 0.5
+        errors = grkan.binding.overlapped_cover_errors(rows, G * dg, G, io, cu, wg, forward)
         vec = 16 // es
         divides = next(v for v in (vec, vec // 2, vec // 4, 1) if v and dg % v == 0)
-        if divides * es > 8 or dg < vec:
+        if divides * es > (8 if forward else 4) or dg < vec:
             assert errors == -2, (rows, G, dg, io)
         else:
             assert errors in (0, -2), (trial, rows, G, dg, io, cu, wg, errors)  # -2: columns cannot be fixed
