@@ -890,27 +890,38 @@ static int resident_wg_per_cu(const void *kernel, int dev)
 // With one chunk of loads in flight per wave (1 KB forward, 2 KB backward),
 // 4 and 2 workgroups per unit put about 4 MB of loads in flight on 256 units,
 // which is where the HBM-bound kernels were measured fastest (a backward pass
-// that sweeps whole rows as one stream - no column blocks - measured best at 3).  The bfloat16 backward pass moves half the
-// bytes for the same arithmetic and is bound by the vector ALU instead: it
-// takes every wave slot it can get (requests are clamped to the kernel's real
-// occupancy).  The overrides above apply to both walks.
+// that sweeps whole rows as one stream - no column blocks - measured best at 3).  The 16-bit backward pass moves
+// half the bytes for the same arithmetic: with degrees (3, 2) it is bound by HBM like the others and takes 2; with (5, 4)
+// and (7, 6) by the vector ALU, and takes every wave slot it can get (requests are clamped to the kernel's real
+// occupancy) - but in the flat walk, where each workgroup more is one more workspace row for each of its groups,
+// no more than leave every wave about four chunks.  Measured in us with 2 / 3 / 4 / as many as fit:
+//   bf16 (3,2) [25216, 3072] 78.6 / 81.8 / 84.0 / 85.6     bf16 (5,4) [25216, 3072] 96.7 / 93.6 / 94.5 / 93.3
+//   flat walk, bf16 (5,4): [25216, 192] 15.1 / 15.6 / 15.7 / 17.6   [25216, 384] 19.2 / 18.9 / 18.7 / 22.1
+//   [25216, 3072] in 64 groups - / - / 101 / 99
+// The overrides above apply to every walk.
 struct Want {
     int group_walk;
-    int flat_walk;
+    int flat_blocks; // flat walk over column blocks
+    int flat_rows;   // one sweep over whole rows
 };
 
 static Want fwd_want(grkan_dtype_t)
 {
     const int e = g_fwd_wg_per_cu.load(std::memory_order_relaxed);
-    return e ? Want{e, e} : Want{4, 4};
+    return e ? Want{e, e, e} : Want{4, 4, 4};
 }
 
-static Want bwd_want(grkan_dtype_t io)
+static Want bwd_want(grkan_dtype_t io, int m, int64_t rows, int32_t D, int num_cu)
 {
     const int e = g_bwd_wg_per_cu.load(std::memory_order_relaxed);
     if (e)
-        return Want{e, e};
-    return io == GRKAN_F32 ? Want{2, 3} : Want{8, 8}; // both 16-bit formats are ALU-bound
+        return Want{e, e, e};
+    if (io == GRKAN_F32 || m <= 3)
+        return Want{2, 2, 3};
+    const int64_t vectors = rows * (int64_t)D / (16 / elem_size(io));
+    const int64_t fit = vectors / kThreadsPerWg * 2 / (9 * (int64_t)num_cu); // 4.5 chunks for every wave
+    const int flat = fit < 3 ? 3 : fit > 8 ? 8 : (int)fit;
+    return Want{8, flat, flat};
 }
 
 // Plans the launch with the wanted workgroups per unit, then clamps to what
@@ -922,12 +933,12 @@ static grkan_status_t plan_resident(int64_t rows, int32_t D, int32_t G, grkan_dt
                                     bool may_overlap, grkan_plan_t *pl, Walk *walk, const void **kernel)
 {
     int per_cu = want.group_walk;
-    if (may_overlap && make_overlapped(rows, D, G, io, info.num_cu, want.flat_walk, forward, pl, walk)) {
+    if (may_overlap && make_overlapped(rows, D, G, io, info.num_cu, want.flat_rows, forward, pl, walk)) {
         *kernel = reinterpret_cast<const void *>(select(io, pl->vec, true, true, true));
         const int fit = resident_wg_per_cu(*kernel, dev);
         if (fit <= 0)
             return GRKAN_ERR_LAUNCH;
-        if (fit >= want.flat_walk || make_overlapped(rows, D, G, io, info.num_cu, fit, forward, pl, walk))
+        if (fit >= want.flat_rows || make_overlapped(rows, D, G, io, info.num_cu, fit, forward, pl, walk))
             return GRKAN_OK;
     }
     grkan_status_t st = make_plan(rows, D, G, io, align, info.num_cu, per_cu, forward, pl, walk);
@@ -936,11 +947,12 @@ static grkan_status_t plan_resident(int64_t rows, int32_t D, int32_t G, grkan_dt
     // one sweep over whole rows (flat walk without column blocks, or a single unsplit group) against
     // several interleaved column streams: the two were measured best at different grid sizes
     const bool rows_walk = (pl->lane_coef ? pl->column_split : G * pl->column_split) == 1;
-    if (rows_walk && want.flat_walk != per_cu) {
+    const int other = rows_walk ? want.flat_rows : pl->lane_coef ? want.flat_blocks : per_cu;
+    if (other != per_cu) {
         grkan_plan_t alt;
-        if (make_plan(rows, D, G, io, align, info.num_cu, want.flat_walk, forward, &alt, nullptr) == GRKAN_OK &&
+        if (make_plan(rows, D, G, io, align, info.num_cu, other, forward, &alt, nullptr) == GRKAN_OK &&
             alt.lane_coef == pl->lane_coef) {
-            per_cu = want.flat_walk;
+            per_cu = other;
             st = make_plan(rows, D, G, io, align, info.num_cu, per_cu, forward, pl, walk);
             if (st != GRKAN_OK)
                 return st;
@@ -994,11 +1006,12 @@ extern "C" size_t grkan_bwd_workspace_bytes(int64_t rows, int32_t D, int32_t G, 
     size_t need = 16; // never zero, so that callers can always allocate it
     // the query names no degrees: the bound covers every built (m, n), whose kernels differ in occupancy
     for (const DegreeOps &ops : kDegrees) {
+        const Want want = bwd_want(io, ops.m, rows, D, info.num_cu);
         for (int align = elem_size(io); align <= 16; align *= 2) {
             grkan_plan_t pl;
             const void *kernel = nullptr;
             for (int overlap = 0; overlap < 2; ++overlap) {
-                if (plan_resident(rows, D, G, io, align, info, dev, bwd_want(io), false, ops.bwd, overlap != 0, &pl, nullptr,
+                if (plan_resident(rows, D, G, io, align, info, dev, want, false, ops.bwd, overlap != 0, &pl, nullptr,
                                   &kernel) != GRKAN_OK)
                     return 0;
                 const size_t b = workspace_for(pl, G, ops.m + 1 + ops.n);
@@ -1166,7 +1179,8 @@ static grkan_status_t bwd_impl(const void *x, const void *dy, const CoefRows &co
     const void *kernel = nullptr;
     const size_t bytes = (size_t)rows * (size_t)D * (size_t)es;
     bool may_overlap = disjoint(x, dx, bytes) && disjoint(dy, dx, bytes);
-    st = plan_resident(rows, D, G, io, common_alignment({x, dy, dx}), info, dev, bwd_want(io), false, ops->bwd, may_overlap,
+    const Want want = bwd_want(io, m, rows, D, info.num_cu);
+    st = plan_resident(rows, D, G, io, common_alignment({x, dy, dx}), info, dev, want, false, ops->bwd, may_overlap,
                        &pl, &a.walk, &kernel);
     if (st != GRKAN_OK)
         return st;
@@ -1174,7 +1188,7 @@ static grkan_status_t bwd_impl(const void *x, const void *dy, const CoefRows &co
     // a workspace that is too small for the overlapped walk may do for the other
     const size_t limit = ws.own_scratch ? kScratchBytes : ws.alloc ? SIZE_MAX : ws.bytes;
     if (a.walk.gvecs > 0 && need > limit) {
-        st = plan_resident(rows, D, G, io, common_alignment({x, dy, dx}), info, dev, bwd_want(io), false, ops->bwd, false, &pl,
+        st = plan_resident(rows, D, G, io, common_alignment({x, dy, dx}), info, dev, want, false, ops->bwd, false, &pl,
                            &a.walk, &kernel);
         if (st != GRKAN_OK)
             return st;
