@@ -192,10 +192,11 @@ grkan_status_t grkan_bwd(const void *x, const void *dy, const float *A, const fl
 /*
  * grkan_fwd / grkan_bwd on the parameters as a model keeps them, so that no small kernels run around every
  * call to expand, convert or sum them:
- *   coef_dtype        GRKAN_F32 or GRKAN_BF16: dtype of A, B, dA and dB (bfloat16 coefficients are widened
- *                     exactly, their gradients rounded once to nearest even)
+ *   coef_dtype        GRKAN_F32, or with bfloat16 I/O GRKAN_BF16: dtype of A, B, dA and dB (bfloat16
+ *                     coefficients are widened exactly, their gradients rounded once to nearest even)
  *   shared_numerator  0: A and dA are [G, m+1]; else they are [m+1], one row for all groups, and dA is the
- *                     sum over the groups too (fixed order, in double)
+ *                     sum over the groups too (fixed order; float32 in double, bfloat16 by adding
+ *                     the groups' rounded gradients in float32)
  * Everything else is as for grkan_fwd / grkan_bwd.  grkan_bwd_model asks `alloc(bytes, alloc_context)` once,
  * during the call, for its workspace: device memory, 16-byte aligned, that stays untouched until the
  * enqueued work has finished.  `alloc` must not throw; NULL from it gives GRKAN_ERR_WORKSPACE.

@@ -335,8 +335,9 @@ struct BwdArgs {
 // so that the chip as a whole keeps about 4 MB of loads in flight (measured
 // optimum of this memory system for a streaming read/write mix; both deeper
 // per-wave prefetch and more resident waves were measured slower).
-// LOOSE: the overlapped walk (a flat walk whose vectors are aligned to their elements only).
-template <typename IO, int VEC, bool FIXED, bool LANECOEF, int M, int N, bool LOOSE = false>
+// LOOSE: the overlapped walk (a flat walk whose vectors are aligned to their elements only).  CBF: bfloat16
+// coefficients.
+template <typename IO, int VEC, bool FIXED, bool LANECOEF, int M, int N, bool LOOSE = false, bool CBF = false>
 __global__ __launch_bounds__(kThreadsPerWg) void grkan_fwd_kernel(const FwdArgs a)
 {
     static_assert(FIXED || !LANECOEF, "per-lane coefficients need fixed columns");
@@ -350,11 +351,11 @@ __global__ __launch_bounds__(kThreadsPerWg) void grkan_fwd_kernel(const FwdArgs 
     // fixed column inside the wave's block of whole groups (vector registers)
     int cg;
     if constexpr (LANECOEF)
-        cg = (int)(((uint32_t)id.g * (uint32_t)p.dg + fixed_col_elem(p, fixed_lane_col(p, id.w, lane).ccol)) /
+        cg = (int)(((uint32_t)id.g * (uint32_t)p.dg + fixed_col_elem(p, fixed_lane_col(p, id.w, lane).ccol, LOOSE)) /
                    (uint32_t)a.dgc);
     else
         cg = p.dg == a.dgc ? id.g : (int)((uint32_t)id.g * (uint32_t)p.dg / (uint32_t)a.dgc);
-    const Coef<M, N> c = load_coef<M, N, !LANECOEF>(a.coef, cg);
+    const Coef<M, N> c = load_coef<M, N, !LANECOEF, CBF>(a.coef, cg);
     const int32_t n_it = full_visits(p, id.w);
     const bool tail = owns_tail(p, id.w) && lane < p.rem;
     constexpr int64_t ES = sizeof(IO);
@@ -374,7 +375,7 @@ __global__ __launch_bounds__(kThreadsPerWg) void grkan_fwd_kernel(const FwdArgs 
     if constexpr (FIXED) {
         const uint64_t base0 = (uint64_t)(fixed_base0(p, id.g, id.w) * ES);
         const uint64_t step = (uint64_t)(fixed_step(p) * ES);
-        uint32_t lo = fixed_lane_offset(p, id.w, lane) * (uint32_t)ES;
+        uint32_t lo = fixed_lane_offset(p, id.w, lane, LOOSE) * (uint32_t)ES;
         // chunk `i` of this wave: scalar base + lane offset
         auto xin = [&](int32_t i) { return (gcptr_t)uniform_u64(x0 + base0 + (uint64_t)(uint32_t)i * step) + lo; };
         auto yout = [&](int32_t i) { return (gptr_t)uniform_u64(y0 + base0 + (uint64_t)(uint32_t)i * step) + lo; };
@@ -430,7 +431,7 @@ __global__ __launch_bounds__(kThreadsPerWg) void grkan_fwd_kernel(const FwdArgs 
 }
 
 // Backward, stage 1 (see the file header).
-template <typename IO, int VEC, bool FIXED, bool LANECOEF, int M, int N, bool LOOSE = false>
+template <typename IO, int VEC, bool FIXED, bool LANECOEF, int M, int N, bool LOOSE = false, bool CBF = false>
 __global__ __launch_bounds__(kThreadsPerWg) void grkan_bwd_stage1_kernel(const BwdArgs a)
 {
     static_assert(FIXED || !LANECOEF, "per-lane coefficients need fixed columns");
@@ -441,11 +442,11 @@ __global__ __launch_bounds__(kThreadsPerWg) void grkan_bwd_stage1_kernel(const B
     const WaveId id = wave_id(p, (int32_t)blockIdx.x, wv);
     int cg;
     if constexpr (LANECOEF)
-        cg = (int)(((uint32_t)id.g * (uint32_t)p.dg + fixed_col_elem(p, fixed_lane_col(p, id.w, lane).ccol)) /
+        cg = (int)(((uint32_t)id.g * (uint32_t)p.dg + fixed_col_elem(p, fixed_lane_col(p, id.w, lane).ccol, LOOSE)) /
                    (uint32_t)a.dgc);
     else
         cg = p.dg == a.dgc ? id.g : (int)((uint32_t)id.g * (uint32_t)p.dg / (uint32_t)a.dgc);
-    const Coef<M, N> c = load_coef<M, N, !LANECOEF>(a.coef, cg);
+    const Coef<M, N> c = load_coef<M, N, !LANECOEF, CBF>(a.coef, cg);
     const int32_t n_it = full_visits(p, id.w);
     const bool tail = owns_tail(p, id.w) && lane < p.rem;
     constexpr int64_t ES = sizeof(IO);
@@ -475,7 +476,7 @@ __global__ __launch_bounds__(kThreadsPerWg) void grkan_bwd_stage1_kernel(const B
     if constexpr (FIXED) {
         const uint64_t base0 = (uint64_t)(fixed_base0(p, id.g, id.w) * ES);
         const uint64_t step = (uint64_t)(fixed_step(p) * ES);
-        uint32_t lo = fixed_lane_offset(p, id.w, lane) * (uint32_t)ES;
+        uint32_t lo = fixed_lane_offset(p, id.w, lane, LOOSE) * (uint32_t)ES;
         // chunk `i` of this wave: scalar base + lane offset
         auto xin = [&](int32_t i) { return (gcptr_t)uniform_u64(x0 + base0 + (uint64_t)(uint32_t)i * step) + lo; };
         auto dyin = [&](int32_t i) { return (gcptr_t)uniform_u64(dy0 + base0 + (uint64_t)(uint32_t)i * step) + lo; };
@@ -644,6 +645,30 @@ __global__ __launch_bounds__(kStage2MaxThreads) void grkan_bwd_stage2_kernel(con
     const int T = blockDim.x; // 64 or 256
     if (G_shared > 0 && g >= G_shared) {
         const int k = g - G_shared;
+        if (bf16) {
+            // bfloat16: every group's gradient is rounded, then the rounded ones are added in float32 (what
+            // converting and summing the groups' gradients gives); a wavefront takes every T / 64th group
+            float t = 0.0f;
+            for (int c = tid / kWave; c < G_shared; c += T / kWave) {
+                double s = 0.0;
+#pragma unroll 4
+                for (int r = tid & (kWave - 1); r < rows_per_group; r += kWave)
+                    s += (double)partial[((int64_t)c * rows_per_group + r) * kNumCoef + k];
+                for (int d = kWave / 2; d > 0; d /= 2)
+                    s += __shfl_xor(s, d);
+                t += widen_one<bf16_t>(narrow_one<bf16_t>((float)s));
+            }
+            if ((tid & (kWave - 1)) == 0)
+                block_sum[0][tid / kWave] = (double)t;
+            __syncthreads();
+            if (tid == 0) {
+                float v = 0.0f;
+                for (int b = 0; b < T / kWave; ++b)
+                    v += (float)block_sum[0][b];
+                store_coef_grad(dA, k, (double)v, bf16);
+            }
+            return;
+        }
         double s = 0.0;
 #pragma unroll 8
         for (int64_t r = tid; r < (int64_t)G_shared * rows_per_group; r += T)
@@ -760,84 +785,76 @@ using FwdKernel = void (*)(const FwdArgs);
 using BwdKernel = void (*)(const BwdArgs);
 using Stage2Kernel = void (*)(const float *, int32_t, void *, void *, int32_t, int32_t);
 
-template <typename IO, int VEC, int M, int N> static FwdKernel fwd_variant(bool fixed, bool lane_coef)
+template <typename IO, int VEC, int M, int N, bool CBF> static FwdKernel fwd_variant(bool fixed, bool lane_coef)
 {
     if (lane_coef)
-        return grkan_fwd_kernel<IO, VEC, true, true, M, N>;
-    return fixed ? grkan_fwd_kernel<IO, VEC, true, false, M, N> : grkan_fwd_kernel<IO, VEC, false, false, M, N>;
+        return grkan_fwd_kernel<IO, VEC, true, true, M, N, false, CBF>;
+    return fixed ? grkan_fwd_kernel<IO, VEC, true, false, M, N, false, CBF>
+                 : grkan_fwd_kernel<IO, VEC, false, false, M, N, false, CBF>;
 }
-template <typename IO, int VEC, int M, int N> static BwdKernel bwd_variant(bool fixed, bool lane_coef)
+template <typename IO, int VEC, int M, int N, bool CBF> static BwdKernel bwd_variant(bool fixed, bool lane_coef)
 {
     if (lane_coef)
-        return grkan_bwd_stage1_kernel<IO, VEC, true, true, M, N>;
-    return fixed ? grkan_bwd_stage1_kernel<IO, VEC, true, false, M, N>
-                 : grkan_bwd_stage1_kernel<IO, VEC, false, false, M, N>;
+        return grkan_bwd_stage1_kernel<IO, VEC, true, true, M, N, false, CBF>;
+    return fixed ? grkan_bwd_stage1_kernel<IO, VEC, true, false, M, N, false, CBF>
+                 : grkan_bwd_stage1_kernel<IO, VEC, false, false, M, N, false, CBF>;
 }
 
-template <int M, int N> static FwdKernel select_fwd(grkan_dtype_t io, int vec, bool fixed, bool lane_coef, bool overlapped)
+// What a launch needs of the kernel besides the degrees.
+struct Pick {
+    grkan_dtype_t io;
+    int vec;
+    bool fixed, lane_coef, overlapped, coef_bf16;
+};
+
+template <typename IO, int M, int N, bool CBF = false> static FwdKernel fwd_of_type(const Pick &k)
 {
-    if (overlapped) // full vectors only
-        return io == GRKAN_F32    ? grkan_fwd_kernel<float, 4, true, true, M, N, true>
-               : io == GRKAN_BF16 ? grkan_fwd_kernel<bf16_t, 8, true, true, M, N, true>
-                                  : grkan_fwd_kernel<f16_t, 8, true, true, M, N, true>;
-    switch (io) {
-    case GRKAN_F32:
-        switch (vec) {
-        case 4: return fwd_variant<float, 4, M, N>(fixed, lane_coef);
-        case 2: return fwd_variant<float, 2, M, N>(fixed, lane_coef);
-        case 1: return fwd_variant<float, 1, M, N>(fixed, lane_coef);
-        }
-        break;
-    case GRKAN_BF16:
-        switch (vec) {
-        case 8: return fwd_variant<bf16_t, 8, M, N>(fixed, lane_coef);
-        case 4: return fwd_variant<bf16_t, 4, M, N>(fixed, lane_coef);
-        case 2: return fwd_variant<bf16_t, 2, M, N>(fixed, lane_coef);
-        case 1: return fwd_variant<bf16_t, 1, M, N>(fixed, lane_coef);
-        }
-        break;
-    case GRKAN_F16:
-        switch (vec) {
-        case 8: return fwd_variant<f16_t, 8, M, N>(fixed, lane_coef);
-        case 4: return fwd_variant<f16_t, 4, M, N>(fixed, lane_coef);
-        case 2: return fwd_variant<f16_t, 2, M, N>(fixed, lane_coef);
-        case 1: return fwd_variant<f16_t, 1, M, N>(fixed, lane_coef);
-        }
-        break;
+    constexpr int kFull = 16 / (int)sizeof(IO);
+    if (k.overlapped) // full vectors only
+        return grkan_fwd_kernel<IO, kFull, true, true, M, N, true, CBF>;
+    if constexpr (kFull == 8)
+        if (k.vec == 8)
+            return fwd_variant<IO, 8, M, N, CBF>(k.fixed, k.lane_coef);
+    switch (k.vec) {
+    case 4: return fwd_variant<IO, 4, M, N, CBF>(k.fixed, k.lane_coef);
+    case 2: return fwd_variant<IO, 2, M, N, CBF>(k.fixed, k.lane_coef);
+    case 1: return fwd_variant<IO, 1, M, N, CBF>(k.fixed, k.lane_coef);
     }
     return nullptr;
 }
 
-template <int M, int N> static BwdKernel select_bwd(grkan_dtype_t io, int vec, bool fixed, bool lane_coef, bool overlapped)
+template <typename IO, int M, int N, bool CBF = false> static BwdKernel bwd_of_type(const Pick &k)
 {
-    if (overlapped)
-        return io == GRKAN_F32    ? grkan_bwd_stage1_kernel<float, 4, true, true, M, N, true>
-               : io == GRKAN_BF16 ? grkan_bwd_stage1_kernel<bf16_t, 8, true, true, M, N, true>
-                                  : grkan_bwd_stage1_kernel<f16_t, 8, true, true, M, N, true>;
-    switch (io) {
-    case GRKAN_F32:
-        switch (vec) {
-        case 4: return bwd_variant<float, 4, M, N>(fixed, lane_coef);
-        case 2: return bwd_variant<float, 2, M, N>(fixed, lane_coef);
-        case 1: return bwd_variant<float, 1, M, N>(fixed, lane_coef);
-        }
-        break;
-    case GRKAN_BF16:
-        switch (vec) {
-        case 8: return bwd_variant<bf16_t, 8, M, N>(fixed, lane_coef);
-        case 4: return bwd_variant<bf16_t, 4, M, N>(fixed, lane_coef);
-        case 2: return bwd_variant<bf16_t, 2, M, N>(fixed, lane_coef);
-        case 1: return bwd_variant<bf16_t, 1, M, N>(fixed, lane_coef);
-        }
-        break;
-    case GRKAN_F16:
-        switch (vec) {
-        case 8: return bwd_variant<f16_t, 8, M, N>(fixed, lane_coef);
-        case 4: return bwd_variant<f16_t, 4, M, N>(fixed, lane_coef);
-        case 2: return bwd_variant<f16_t, 2, M, N>(fixed, lane_coef);
-        case 1: return bwd_variant<f16_t, 1, M, N>(fixed, lane_coef);
-        }
-        break;
+    constexpr int kFull = 16 / (int)sizeof(IO);
+    if (k.overlapped)
+        return grkan_bwd_stage1_kernel<IO, kFull, true, true, M, N, true, CBF>;
+    if constexpr (kFull == 8)
+        if (k.vec == 8)
+            return bwd_variant<IO, 8, M, N, CBF>(k.fixed, k.lane_coef);
+    switch (k.vec) {
+    case 4: return bwd_variant<IO, 4, M, N, CBF>(k.fixed, k.lane_coef);
+    case 2: return bwd_variant<IO, 2, M, N, CBF>(k.fixed, k.lane_coef);
+    case 1: return bwd_variant<IO, 1, M, N, CBF>(k.fixed, k.lane_coef);
+    }
+    return nullptr;
+}
+
+template <int M, int N> static FwdKernel select_fwd(const Pick &k)
+{
+    switch (k.io) {
+    case GRKAN_F32: return fwd_of_type<float, M, N>(k);
+    case GRKAN_BF16: return k.coef_bf16 ? fwd_of_type<bf16_t, M, N, true>(k) : fwd_of_type<bf16_t, M, N>(k);
+    case GRKAN_F16: return fwd_of_type<f16_t, M, N>(k);
+    }
+    return nullptr;
+}
+
+template <int M, int N> static BwdKernel select_bwd(const Pick &k)
+{
+    switch (k.io) {
+    case GRKAN_F32: return bwd_of_type<float, M, N>(k);
+    case GRKAN_BF16: return k.coef_bf16 ? bwd_of_type<bf16_t, M, N, true>(k) : bwd_of_type<bf16_t, M, N>(k);
+    case GRKAN_F16: return bwd_of_type<f16_t, M, N>(k);
     }
     return nullptr;
 }
@@ -847,8 +864,8 @@ template <int M, int N> static BwdKernel select_bwd(grkan_dtype_t io, int vec, b
 // units of the same family.
 struct DegreeOps {
     int m, n;
-    FwdKernel (*fwd)(grkan_dtype_t, int, bool, bool, bool);
-    BwdKernel (*bwd)(grkan_dtype_t, int, bool, bool, bool);
+    FwdKernel (*fwd)(const Pick &);
+    BwdKernel (*bwd)(const Pick &);
     Stage2Kernel stage2;
 };
 
@@ -930,11 +947,11 @@ static Want bwd_want(grkan_dtype_t io, int m, int64_t rows, int32_t D, int num_c
 template <typename Select>
 static grkan_status_t plan_resident(int64_t rows, int32_t D, int32_t G, grkan_dtype_t io, int32_t align,
                                     const DeviceInfo &info, int dev, Want want, bool forward, Select select,
-                                    bool may_overlap, grkan_plan_t *pl, Walk *walk, const void **kernel)
+                                    bool may_overlap, bool coef_bf16, grkan_plan_t *pl, Walk *walk, const void **kernel)
 {
     int per_cu = want.group_walk;
     if (may_overlap && make_overlapped(rows, D, G, io, info.num_cu, want.flat_rows, forward, pl, walk)) {
-        *kernel = reinterpret_cast<const void *>(select(io, pl->vec, true, true, true));
+        *kernel = reinterpret_cast<const void *>(select(Pick{io, pl->vec, true, true, true, coef_bf16}));
         const int fit = resident_wg_per_cu(*kernel, dev);
         if (fit <= 0)
             return GRKAN_ERR_LAUNCH;
@@ -958,7 +975,8 @@ static grkan_status_t plan_resident(int64_t rows, int32_t D, int32_t G, grkan_dt
                 return st;
         }
     }
-    *kernel = reinterpret_cast<const void *>(select(io, pl->vec, pl->fixed_col != 0, pl->lane_coef != 0, false));
+    *kernel = reinterpret_cast<const void *>(
+        select(Pick{io, pl->vec, pl->fixed_col != 0, pl->lane_coef != 0, false, coef_bf16}));
     if (!*kernel)
         return GRKAN_ERR_LAUNCH;
     const int fit = resident_wg_per_cu(*kernel, dev);
@@ -969,7 +987,8 @@ static grkan_status_t plan_resident(int64_t rows, int32_t D, int32_t G, grkan_dt
         st = make_plan(rows, D, G, io, align, info.num_cu, fit, forward, pl, walk);
         if (st != GRKAN_OK)
             return st;
-        *kernel = reinterpret_cast<const void *>(select(io, pl->vec, pl->fixed_col != 0, pl->lane_coef != 0, false));
+        *kernel = reinterpret_cast<const void *>(
+            select(Pick{io, pl->vec, pl->fixed_col != 0, pl->lane_coef != 0, false, coef_bf16}));
         if (!*kernel || (pl->lane_coef != was_flat && resident_wg_per_cu(*kernel, dev) <= 0))
             return GRKAN_ERR_LAUNCH;
     }
@@ -1010,9 +1029,10 @@ extern "C" size_t grkan_bwd_workspace_bytes(int64_t rows, int32_t D, int32_t G, 
         for (int align = elem_size(io); align <= 16; align *= 2) {
             grkan_plan_t pl;
             const void *kernel = nullptr;
-            for (int overlap = 0; overlap < 2; ++overlap) {
-                if (plan_resident(rows, D, G, io, align, info, dev, want, false, ops.bwd, overlap != 0, &pl, nullptr,
-                                  &kernel) != GRKAN_OK)
+            for (int v = 0; v < (io == GRKAN_BF16 ? 4 : 2); ++v) {
+                const int overlap = v & 1, coef_bf16 = v >> 1;
+                if (plan_resident(rows, D, G, io, align, info, dev, want, false, ops.bwd, overlap != 0, coef_bf16 != 0,
+                                  &pl, nullptr, &kernel) != GRKAN_OK)
                     return 0;
                 const size_t b = workspace_for(pl, G, ops.m + 1 + ops.n);
                 need = b > need ? b : need;
@@ -1085,7 +1105,7 @@ static grkan_status_t fwd_impl(const void *x, const CoefRows &coef, void *y, int
     const void *kernel = nullptr;
     const size_t bytes = (size_t)rows * (size_t)D * (size_t)es;
     st = plan_resident(rows, D, G, io, common_alignment({x, y}), info, dev, fwd_want(io), true, ops->fwd,
-                       disjoint(x, y, bytes), &pl, &a.walk, &kernel);
+                       disjoint(x, y, bytes), coef.bf16 != 0, &pl, &a.walk, &kernel);
     if (st != GRKAN_OK)
         return st;
     a.x = static_cast<const char *>(x);
@@ -1112,7 +1132,7 @@ extern "C" grkan_status_t grkan_fwd_model(const void *x, const void *A, const vo
                                           grkan_dtype_t io, grkan_dtype_t coef_dtype, int32_t shared_numerator,
                                           void *hip_stream)
 {
-    if (coef_dtype != GRKAN_F32 && coef_dtype != GRKAN_BF16)
+    if (coef_dtype != GRKAN_F32 && !(coef_dtype == GRKAN_BF16 && io == GRKAN_BF16))
         return GRKAN_ERR_DTYPE;
     return fwd_impl(x, coef_rows(A, B, m, shared_numerator != 0, coef_dtype), y, rows, D, G, m, n, io, hip_stream);
 }
@@ -1181,15 +1201,15 @@ static grkan_status_t bwd_impl(const void *x, const void *dy, const CoefRows &co
     bool may_overlap = disjoint(x, dx, bytes) && disjoint(dy, dx, bytes);
     const Want want = bwd_want(io, m, rows, D, info.num_cu);
     st = plan_resident(rows, D, G, io, common_alignment({x, dy, dx}), info, dev, want, false, ops->bwd, may_overlap,
-                       &pl, &a.walk, &kernel);
+                       coef.bf16 != 0, &pl, &a.walk, &kernel);
     if (st != GRKAN_OK)
         return st;
     size_t need = workspace_for(pl, G, m + 1 + n);
     // a workspace that is too small for the overlapped walk may do for the other
     const size_t limit = ws.own_scratch ? kScratchBytes : ws.alloc ? SIZE_MAX : ws.bytes;
     if (a.walk.gvecs > 0 && need > limit) {
-        st = plan_resident(rows, D, G, io, common_alignment({x, dy, dx}), info, dev, want, false, ops->bwd, false, &pl,
-                           &a.walk, &kernel);
+        st = plan_resident(rows, D, G, io, common_alignment({x, dy, dx}), info, dev, want, false, ops->bwd, false,
+                           coef.bf16 != 0, &pl, &a.walk, &kernel);
         if (st != GRKAN_OK)
             return st;
         need = workspace_for(pl, G, m + 1 + n);
@@ -1264,7 +1284,7 @@ extern "C" grkan_status_t grkan_bwd_model(const void *x, const void *dy, const v
                                           grkan_dtype_t io, grkan_dtype_t coef_dtype, int32_t shared_numerator,
                                           void *hip_stream)
 {
-    if (coef_dtype != GRKAN_F32 && coef_dtype != GRKAN_BF16)
+    if (coef_dtype != GRKAN_F32 && !(coef_dtype == GRKAN_BF16 && io == GRKAN_BF16))
         return GRKAN_ERR_DTYPE;
     if (!alloc)
         return GRKAN_ERR_NULL;

@@ -310,7 +310,7 @@ static int64_t cover_errors(const Walk &p, bool fixed, int es)
                 const int64_t base0 = fixed_base0(p, id.g, id.w);
                 const int64_t step = fixed_step(p);
                 for (int32_t lane = 0; lane < kWave; ++lane) {
-                    const uint64_t lo_bytes = (uint64_t)fixed_lane_offset(p, id.w, lane) * (uint64_t)es;
+                    const uint64_t lo_bytes = (uint64_t)fixed_lane_offset(p, id.w, lane, false) * (uint64_t)es;
                     if (lo_bytes >> 32) {
                         ++bad; // the kernels hold this offset in 32 bits
                         continue;
@@ -397,7 +397,7 @@ extern "C" int64_t grkan_overlapped_cover_errors(int64_t rows, int32_t D, int32_
             const WaveId id = wave_id(p, b, wv);
             const int32_t n_it = full_visits(p, id.w);
             for (int32_t lane = 0; lane < kWave; ++lane) {
-                const uint64_t lo = fixed_lane_offset(p, id.w, lane);
+                const uint64_t lo = fixed_lane_offset(p, id.w, lane, true);
                 if ((lo * es) >> 32)
                     ++bad;
                 const uint32_t ccol = fixed_lane_col(p, id.w, lane).ccol;

@@ -191,8 +191,9 @@ std::optional<Tensor> rational(const Tensor &x, const Tensor &A, const Tensor &B
     if (!plain_context() || !on_current_gpu(x) || !plain(x, x.device()) || !plain(A, x.device()) || !plain(B, x.device()))
         return std::nullopt;
     if (!io_of(x) || A.scalar_type() != B.scalar_type() ||
-        (A.scalar_type() != at::kFloat && A.scalar_type() != at::kBFloat16) || x.dim() < 1 || B.dim() != 2 || A.dim() < 1 ||
-        A.dim() > 2 || (A.dim() == 2 && A.size(0) != B.size(0)))
+        (A.scalar_type() != at::kFloat &&
+         !(A.scalar_type() == at::kBFloat16 && x.scalar_type() == at::kBFloat16)) ||
+        x.dim() < 1 || B.dim() != 2 || A.dim() < 1 || A.dim() > 2 || (A.dim() == 2 && A.size(0) != B.size(0)))
         return std::nullopt;
     const int64_t D = x.size(-1), G = B.size(0), m = A.size(-1) - 1, n = B.size(1);
     const bool degrees = (m == 5 && n == 4) || (m == 3 && n == 2) || (m == 7 && n == 6);

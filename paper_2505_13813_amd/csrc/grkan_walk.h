@@ -170,29 +170,28 @@ GRKAN_HD LaneCol fixed_lane_col(const Walk &p, int32_t w, int32_t lane)
     return lc;
 }
 
-// Element a lane's vector starts at, from the row's (or the column block's) start.
-GRKAN_HD uint32_t fixed_col_elem(const Walk &p, uint32_t ccol)
+// Element a lane's vector starts at, from the row's (or the column block's) start.  `overlapped`: p.gvecs > 0,
+// passed so that a kernel built for one kind of walk holds no trace of the other.
+GRKAN_HD uint32_t fixed_col_elem(const Walk &p, uint32_t ccol, bool overlapped)
 {
-    if (p.gvecs == 0)
+    if (!overlapped)
         return ccol * (uint32_t)p.vec;
     const uint32_t g = ccol / (uint32_t)p.gvecs, j = ccol - g * (uint32_t)p.gvecs;
     const uint32_t at = j * (uint32_t)p.vec, most = (uint32_t)(p.gdim - p.vec);
     return g * (uint32_t)p.gdim + (at < most ? at : most);
 }
 
-// Leading elements of the vector that the vector before it holds too (0 outside the overlapped walk).
+// Overlapped walk: leading elements of the vector that the vector before it holds too.
 GRKAN_HD uint32_t overlap_skip(const Walk &p, uint32_t ccol)
 {
-    if (p.gvecs == 0)
-        return 0;
     const uint32_t j = ccol % (uint32_t)p.gvecs;
     return j + 1 == (uint32_t)p.gvecs ? (uint32_t)(p.gvecs * p.vec - p.gdim) : 0u;
 }
 
-GRKAN_HD uint32_t fixed_lane_offset(const Walk &p, int32_t w, int32_t lane)
+GRKAN_HD uint32_t fixed_lane_offset(const Walk &p, int32_t w, int32_t lane, bool overlapped)
 {
     const LaneCol lc = fixed_lane_col(p, w, lane);
-    return lc.rrow * (uint32_t)p.D + fixed_col_elem(p, lc.ccol);
+    return lc.rrow * (uint32_t)p.D + fixed_col_elem(p, lc.ccol, overlapped);
 }
 
 } // namespace grkan

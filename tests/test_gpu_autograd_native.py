@@ -40,14 +40,14 @@ def test_same_bits_as_the_python_function(rows, D, G, dtype):
 @pytest.mark.parametrize("rows,D,G", SHAPES)
 def test_shared_numerator_and_bfloat16_coefficients(rows, D, G, coef):
     """The module's parameters as they are against their expanded float32 rows through the Python function: the
-    same outputs, the numerator's gradient summed over the groups (in double here, rounded once: 2^-22 of the
-    magnitudes' sum for float32, 2^-8 of the value for bfloat16)."""
+    same outputs, the numerator's gradient summed over the groups (float32: in double, 2^-22 of the magnitudes'
+    sum; bfloat16: of the groups' rounded gradients, rounded once more: 2^-8 of the value)."""
     import torch
 
     from paper_2505_13813_amd import nn as gnn
 
     unit = gnn.GroupRational(G).to("cuda:0")
-    x, dy, A, B = _inputs(torch, rows, D, G, 5, 4, torch.float32)
+    x, dy, A, B = _inputs(torch, rows, D, G, 5, 4, getattr(torch, coef))
     with torch.no_grad():
         unit.numerator.copy_(A[0])
         unit.denominator.copy_(B)
@@ -61,7 +61,7 @@ def test_shared_numerator_and_bfloat16_coefficients(rows, D, G, coef):
     assert torch.equal(y, ref) and torch.equal(got[0], dx)
     assert got[1].dtype == unit.numerator.dtype and got[1].shape == unit.numerator.shape
     assert torch.equal(got[2], dB.to(unit.denominator.dtype))
-    want = dA.double().sum(0)
+    want = dA.to(unit.numerator.dtype).double().sum(0)
     bound = 2.0 ** -22 * dA.abs().sum(0).double() + (2.0 ** -8 * want.abs() if coef == "bfloat16" else 0.0)
     assert bool(((got[1].double() - want).abs() <= bound + 1e-30).all())
 
@@ -79,6 +79,10 @@ def test_views_empty_inputs_and_hooks():
     (r,) = torch.autograd.grad(gnn.GroupRationalFunction.apply(wide[:, ::2], A, B).sum(), [wide])
     assert torch.equal(g, r)
     assert gnn.group_rational(x[:0], A, B).shape == (0, 96)
+    # float32 activations with bfloat16 coefficients are converted first
+    unit = gnn.GroupRational(4).to("cuda:0").to(torch.bfloat16)
+    rows_A, rows_B = (t.detach().to(torch.float32).contiguous() for t in unit.coefficient_rows())
+    assert torch.equal(unit(x), gnn.GroupRationalFunction.apply(x, rows_A, rows_B))
     # saved tensors go through the caller's hooks, and changing one before the backward pass is an error
     packed = []
     with torch.autograd.graph.saved_tensors_hooks(lambda t: (packed.append(t.shape), t)[1], lambda t: t):
