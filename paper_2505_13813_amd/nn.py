@@ -4,12 +4,15 @@ conventions, the GR-KAN linear layer and the KAT MLP block.
 
 The rational function runs in this package's kernels; the matrix products are
 torch's (library GEMMs), except where the one-kernel layer grkan_linear_fwd is
-selected (GRKANLinear(fused=...)).  Conventions taken from the FlashKAT paper:
+selected (GRKANLinear(fused=...)) and for the weight and bias gradients of
+bfloat16 training (grkan_linear_wgrad).  Plain calls run as native autograd
+functions; what those do not take runs in the Python ones here.  Conventions taken from the FlashKAT paper:
   * GR-KAN(x) = W F(x): the rational function is applied to the INPUT of each
     linear layer (Eq. "GR_KAN").
   * the groups use one common set of numerator coefficients and have their own
-    denominator coefficients (Sec. "Results"): one numerator row, broadcast to
-    the kernel's [G, m+1] layout; autograd's expand sums dA over the groups.
+    denominator coefficients (Sec. "Results"): one numerator row, read by the
+    kernels as it is, dA summed over the groups (in the Python functions it is
+    broadcast to [G, m+1] and autograd's expand sums).
   * the first rational of an MLP block starts as the identity, the second as a
     Swish (Sec. "Results").  The paper prints no Swish coefficients, so they
     are obtained here by a (linearised) least-squares fit on [-3, 3].
