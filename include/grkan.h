@@ -259,6 +259,17 @@ grkan_status_t grkan_linear_fwd(const void *x, const float *A, const float *B, c
 double grkan_linear_estimate_us(int64_t rows, int32_t D_in, int32_t D_out);
 
 /*
+ * The same layer on the parameters as a bfloat16 model keeps them, for callers that keep no converted or packed copy
+ * of them between calls: x, A, B, W, bias (or NULL) and out all bfloat16; shared_numerator as for grkan_fwd_model.
+ * The results are those of grkan_linear_fwd on float32 copies of A, B and bias, bit for bit.
+ * Alignment: x, W and out 16 bytes, bias 8, A and B 4 (else GRKAN_ERR_ALIGN).
+ */
+grkan_status_t grkan_linear_fwd_model(const void *x, const void *A, const void *B, const void *W,
+                                      const void *bias, void *out,
+                                      int64_t rows, int32_t D_in, int32_t D_out, int32_t G,
+                                      int32_t m, int32_t n, int32_t shared_numerator, void *hip_stream);
+
+/*
  * The same layer with the weights in a packed copy, for callers whose weights do
  * not change between calls (inference): the kernel's weight fetches then read
  * whole cache lines in sequence (5 - 8 % of the layer's time at the paper's wide

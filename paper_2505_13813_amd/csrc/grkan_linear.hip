@@ -67,10 +67,10 @@ constexpr int kXBuf = kXRows * kXPitch; // 18432
 struct LinArgs {
     const char *x;     // bfloat16 [rows, K]
     const char *W;     // bfloat16 [Nout, K]
-    const float *bias; // float32 [Nout] or NULL
+    const void *bias;  // float32 [Nout] or NULL (MODEL: bfloat16)
     char *out;         // OUT [rows, Nout]
-    const float *A;    // [G, m + 1]
-    const float *B;    // [G, n]
+    const void *A;     // float32 [G, m + 1] (MODEL: bfloat16, rows a_stride apart)
+    const void *B;     // float32 [G, n] (MODEL: bfloat16)
     int64_t rows;
     int32_t K;
     int32_t Nout;
@@ -79,6 +79,7 @@ struct LinArgs {
     int32_t nblocks;   // ceil(Nout / BN)
     int32_t wtiles;    // packed W only: 16-row tiles per stage
     int32_t n_major;   // small kernel: tiles of one channel block share an XCD (else: of one token block)
+    int32_t a_stride;  // MODEL: m + 1, or 0 where all groups share one numerator row
 };
 
 // LDS of the small kernel: four x buffers of a 64-k block for each group of WN of the NW wavefronts, and a
@@ -248,6 +249,56 @@ template <> struct OutPack<bf16_out> {
     }
 };
 
+// The coefficient rows of group g as they are kept: float32, or (MODEL) bfloat16 rows that are whole 32-bit words and
+// are widened when they are used (exactly), so that a call needs no converted copies of them.  Read through the
+// constant address space (nothing writes A and B while the kernels run), where g uniform means scalar loads.
+template <bool MODEL, int M, int N> struct RowWords {
+    static constexpr int kA = MODEL ? (M + 1) / 2 : M + 1, kB = MODEL ? N / 2 : N;
+    static_assert(!MODEL || (M % 2 == 1 && N % 2 == 0), "bfloat16 coefficient rows are read in 32-bit words");
+    uint32_t a[kA], b[kB];
+
+    __device__ __forceinline__ void load(const LinArgs &args, int g)
+    {
+        typedef const __attribute__((address_space(4))) uint32_t *cword_ptr;
+        const cword_ptr pa = (cword_ptr)(reinterpret_cast<uintptr_t>(args.A) + (MODEL ? (size_t)g * args.a_stride * 2u : (size_t)g * (M + 1) * 4u));
+        const cword_ptr pb = (cword_ptr)(reinterpret_cast<uintptr_t>(args.B) + (size_t)g * kB * 4u);
+#pragma unroll
+        for (int i = 0; i < kA; ++i)
+            a[i] = pa[i];
+#pragma unroll
+        for (int i = 0; i < kB; ++i)
+            b[i] = pb[i];
+    }
+    static __device__ __forceinline__ float value(const uint32_t *w, int i)
+    {
+        if constexpr (MODEL)
+            return __builtin_bit_cast(float, i % 2 == 0 ? w[i / 2] << 16 : w[i / 2] & 0xffff0000u);
+        else
+            return __builtin_bit_cast(float, w[i]);
+    }
+    __device__ __forceinline__ void to(Coef<M, N> &c) const
+    {
+#pragma unroll
+        for (int i = 0; i <= M; ++i)
+            c.a[i] = value(a, i);
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            c.b[i] = value(b, i);
+    }
+};
+
+// four consecutive elements of the bias, float32 or (MODEL) bfloat16
+template <bool MODEL> __device__ __forceinline__ f32x4 bias_of(const void *bias, int32_t o)
+{
+    if constexpr (MODEL) {
+        const u32x2 w = *(const u32x2 *)(static_cast<const char *>(bias) + (int64_t)o * 2);
+        return f32x4{__builtin_bit_cast(float, w[0] << 16), __builtin_bit_cast(float, w[0] & 0xffff0000u),
+                     __builtin_bit_cast(float, w[1] << 16), __builtin_bit_cast(float, w[1] & 0xffff0000u)};
+    } else {
+        return *(const f32x4 *)(static_cast<const char *>(bias) + (int64_t)o * 4);
+    }
+}
+
 // Number of multiples of `period` in [lo, hi] (the x refills, one per stage start, among a range of steps).
 constexpr int multiples_in(int lo, int hi, int period)
 {
@@ -267,7 +318,9 @@ constexpr int multiples_in(int lo, int hi, int period)
 // brings (16 rows x 32 k, pieces already permuted) is contiguous: the fetch then reads eight whole
 // cache lines in sequence instead of sixteen half lines D_in * 2 bytes apart (5 - 8 % of the kernel's
 // time at the wide layer).  Rows past Nout are zeros there.
-template <int NW, int NT, typename OUT, bool NEDGE, bool PACKED, int M, int N>
+//
+// MODEL: coefficients and bias in bfloat16, as a bfloat16 model keeps them (RowWords).
+template <int NW, int NT, typename OUT, bool NEDGE, bool PACKED, bool MODEL, int M, int N>
 __global__ __launch_bounds__(64 * NW, 1) void grkan_linear_fwd_kernel(const LinArgs a)
 {
     static_assert(M == 5 && N == 4 && kMT == 7, "rational_piece is written for degrees (5, 4) and 7-tile steps");
@@ -407,21 +460,15 @@ __global__ __launch_bounds__(64 * NW, 1) void grkan_linear_fwd_kernel(const LinA
     // vector memory path, into vector registers, with a wait on the vector-memory counter (and so on
     // the x and W loads just issued) in front of the first use.  (A quotient of an integer division
     // is formed by vector instructions, hence the readfirstlane.)
-    typedef const __attribute__((address_space(4))) float *cfloat_ptr;
-    Coef<M, N> c, c_next;
-    auto coef_for = [&](Coef<M, N> &dst, uint32_t kbyte_pair) {
+    Coef<M, N> c;
+    RowWords<MODEL, M, N> c_next;
+    auto coef_for = [&](RowWords<MODEL, M, N> &dst, uint32_t kbyte_pair) {
         const int g = __builtin_amdgcn_readfirstlane((int)((kbyte_pair / 2u + (uint32_t)xhalf * 32u) / (uint32_t)a.dgc));
-        const cfloat_ptr pa = (cfloat_ptr)(uintptr_t)(a.A + (size_t)g * (M + 1));
-        const cfloat_ptr pb = (cfloat_ptr)(uintptr_t)(a.B + (size_t)g * N);
-#pragma unroll
-        for (int i = 0; i <= M; ++i)
-            dst.a[i] = pa[i];
-#pragma unroll
-        for (int i = 0; i < N; ++i)
-            dst.b[i] = pb[i];
+        dst.load(a, g);
     };
     uint32_t pp = rot; // the pair the matrix products work on
-    coef_for(c, pp * 128u);
+    coef_for(c_next, pp * 128u);
+    c_next.to(c);
 
     u32x4 xq[U]; // this lane's 16-byte pieces (8 k each, of U rows) of the pair F works on next
 
@@ -448,7 +495,8 @@ __global__ __launch_bounds__(64 * NW, 1) void grkan_linear_fwd_kernel(const LinA
 #pragma unroll
         for (int u = 0; u < PPS; ++u)
             xq[u] = gload16(x_base + kp, x_lane[u]);
-        coef_for(c, kp);
+        coef_for(c_next, kp);
+        c_next.to(c);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
@@ -578,7 +626,7 @@ __global__ __launch_bounds__(64 * NW, 1) void grkan_linear_fwd_kernel(const LinA
         // pair.  (The coefficients requested in the first stage
         // are for F during the next pair, which works on the pair after it.)
         stage(std::integral_constant<int, 1>{}, xsel, kXBuf - xsel, pp * 128u + 64u, p1 * 128u, p1 * 128u + 64u, p2 * 128u, 0u);
-        c = c_next;
+        c_next.to(c);
         xsel = kXBuf - xsel;
         pp = p1;
     }
@@ -606,7 +654,7 @@ __global__ __launch_bounds__(64 * NW, 1) void grkan_linear_fwd_kernel(const LinA
         for (int nt = 0; nt < NT; ++nt) {
             bv[nt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
             if (a.bias)
-                bv[nt] = *(const f32x4 *)(a.bias + n0 + wave * WN + nt * 16 + (lane >> 4) * 4);
+                bv[nt] = bias_of<MODEL>(a.bias, n0 + wave * WN + nt * 16 + (lane >> 4) * 4);
         }
         // every fetch into the operand buffers has landed (the last stages prefetch past the end of
         // the walk, which wraps around) and every wavefront has read its last operands
@@ -648,7 +696,7 @@ __global__ __launch_bounds__(64 * NW, 1) void grkan_linear_fwd_kernel(const LinA
                 continue;
             f32x4 bv = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
             if (a.bias)
-                bv = *(const f32x4 *)(a.bias + o);
+                bv = bias_of<MODEL>(a.bias, o);
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
                 const int64_t token = m0 + mt * 16 + (lane & 15);
@@ -674,7 +722,8 @@ __global__ __launch_bounds__(64 * NW, 1) void grkan_linear_fwd_kernel(const LinA
 //     units it has fetched by F of them in place, one block ahead of their use.  (With LDS-direct loads in
 //     flight the compiler can wait for a load into registers only by waiting for everything.)  With WN = 1
 //     a wavefront reads what it wrote itself and the loop has no barrier.
-template <int NW, int MT, int NT, int WN, typename OUT, bool PACKED, int M, int N>
+//   * MODEL: coefficients and bias in bfloat16 (RowWords).
+template <int NW, int MT, int NT, int WN, typename OUT, bool PACKED, bool MODEL, int M, int N>
 __global__ __launch_bounds__(64 * NW, 1) void grkan_linear_small_kernel(const LinArgs a)
 {
     constexpr int WK = NW / WN;
@@ -781,7 +830,6 @@ __global__ __launch_bounds__(64 * NW, 1) void grkan_linear_small_kernel(const Li
     };
 
     // ---- coefficients of the groups of the wave's units (one group per 32 k)
-    typedef const __attribute__((address_space(4))) float *cfloat_ptr;
     constexpr int kHalves = PU > MT ? 2 : 1; // halves of the 64 k the wave's units lie in
     Coef<M, N> c[kHalves];
     int cur_g[kHalves];
@@ -791,14 +839,9 @@ __global__ __launch_bounds__(64 * NW, 1) void grkan_linear_small_kernel(const Li
             const uint32_t k = kbyte(i) / 2u + (uint32_t)((wn * PU) / MT + h) * 32u;
             const int g = __builtin_amdgcn_readfirstlane((int)(k / (uint32_t)a.dgc));
             if (first || g != cur_g[h]) {
-                const cfloat_ptr pa = (cfloat_ptr)(uintptr_t)(a.A + (size_t)g * (M + 1));
-                const cfloat_ptr pb = (cfloat_ptr)(uintptr_t)(a.B + (size_t)g * N);
-#pragma unroll
-                for (int j = 0; j <= M; ++j)
-                    c[h].a[j] = pa[j];
-#pragma unroll
-                for (int j = 0; j < N; ++j)
-                    c[h].b[j] = pb[j];
+                RowWords<MODEL, M, N> rows;
+                rows.load(a, g);
+                rows.to(c[h]);
                 cur_g[h] = g;
             }
             // In vector registers from here on: an instruction with a scalar operand issues at 0.6 of the rate
@@ -992,7 +1035,7 @@ __global__ __launch_bounds__(64 * NW, 1) void grkan_linear_small_kernel(const Li
         for (int g = 1; g < kSlabs; ++g)
             v += *(const __attribute__((address_space(3))) f32x4 *)(uintptr_t)(src + (uint32_t)g * kSlab);
         if (a.bias)
-            v += *(const f32x4 *)(a.bias + o);
+            v += bias_of<MODEL>(a.bias, o);
         OutPack<OUT>::store((gptr_t)(a.out + ((m0 + r) * a.Nout + o) * (int)sizeof(OUT)), v);
     }
 }
@@ -1073,28 +1116,28 @@ static const SmallVariant *pick_small(int64_t rows, int32_t D_in, int32_t D_out,
     return pick;
 }
 
-template <typename OUT, bool PACKED> static LinKernel select_small(SmallVariant v)
+template <typename OUT, bool PACKED, bool MODEL = false> static LinKernel select_small(SmallVariant v)
 {
     if (v.mt == 1 && v.nt == 4 && v.wn == 1)
-        return grkan_linear_small_kernel<8, 1, 4, 1, OUT, PACKED, 5, 4>;
+        return grkan_linear_small_kernel<8, 1, 4, 1, OUT, PACKED, MODEL, 5, 4>;
     if (v.mt == 2 && v.nt == 4 && v.wn == 2)
-        return grkan_linear_small_kernel<8, 2, 4, 2, OUT, PACKED, 5, 4>;
+        return grkan_linear_small_kernel<8, 2, 4, 2, OUT, PACKED, MODEL, 5, 4>;
     if (v.mt == 4 && v.nt == 3 && v.wn == 4)
-        return grkan_linear_small_kernel<8, 4, 3, 4, OUT, PACKED, 5, 4>;
+        return grkan_linear_small_kernel<8, 4, 3, 4, OUT, PACKED, MODEL, 5, 4>;
     if (v.mt == 4 && v.nt == 3 && v.wn == 8)
-        return grkan_linear_small_kernel<16, 4, 3, 8, OUT, PACKED, 5, 4>;
+        return grkan_linear_small_kernel<16, 4, 3, 8, OUT, PACKED, MODEL, 5, 4>;
     return nullptr;
 }
 
-template <typename OUT, bool PACKED> static LinKernel select_kernel(Variant v, bool nedge)
+template <typename OUT, bool PACKED, bool MODEL = false> static LinKernel select_kernel(Variant v, bool nedge)
 {
     if (v.nw == 8 && v.nt == 6)
-        return grkan_linear_fwd_kernel<8, 6, OUT, false, PACKED, 5, 4>;
+        return grkan_linear_fwd_kernel<8, 6, OUT, false, PACKED, MODEL, 5, 4>;
     if (v.nw == 8 && v.nt == 3)
-        return grkan_linear_fwd_kernel<8, 3, OUT, false, PACKED, 5, 4>;
+        return grkan_linear_fwd_kernel<8, 3, OUT, false, PACKED, MODEL, 5, 4>;
     if (v.nw == 4 && v.nt == 3)
-        return nedge ? grkan_linear_fwd_kernel<4, 3, OUT, true, PACKED, 5, 4>
-                     : grkan_linear_fwd_kernel<4, 3, OUT, false, PACKED, 5, 4>;
+        return nedge ? grkan_linear_fwd_kernel<4, 3, OUT, true, PACKED, MODEL, 5, 4>
+                     : grkan_linear_fwd_kernel<4, 3, OUT, false, PACKED, MODEL, 5, 4>;
     return nullptr;
 }
 
@@ -1105,12 +1148,13 @@ static size_t lds_bytes(Variant v) { return (size_t)2 * kXBuf + (size_t)2 * v.bn
 static bool allow_lds(const void *kernel, size_t bytes)
 {
     static std::mutex mu;
-    static const void *done[64][32];
+    constexpr int kKernels = 64;
+    static const void *done[64][kKernels];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64)
         return false;
     std::lock_guard<std::mutex> lock(mu);
-    for (int i = 0; i < 32; ++i) {
+    for (int i = 0; i < kKernels; ++i) {
         if (done[dev][i] == kernel)
             return true;
         if (!done[dev][i]) {
@@ -1167,11 +1211,17 @@ static grkan_status_t linear_shape_status(int64_t rows, int32_t D_in, int32_t D_
     return GRKAN_OK;
 }
 
-static grkan_status_t linear_fwd_impl(const void *x, const float *A, const float *B, const void *W, bool packed,
-                                      const float *bias, void *out, int64_t rows, int32_t D_in, int32_t D_out,
+// What the operands of a call look like: the weights plain or packed, or (plain) everything in bfloat16 as a model
+// keeps it, with one numerator row per group or one for all.
+enum class Operands { plain, packed, model, model_shared };
+
+static grkan_status_t linear_fwd_impl(const void *x, const void *A, const void *B, const void *W, Operands operands,
+                                      const void *bias, void *out, int64_t rows, int32_t D_in, int32_t D_out,
                                       int32_t G, int32_t m, int32_t n, grkan_dtype_t io, grkan_dtype_t out_dtype,
                                       void *hip_stream)
 {
+    const bool packed = operands == Operands::packed;
+    const bool model = operands == Operands::model || operands == Operands::model_shared;
     if (io != GRKAN_BF16 || (out_dtype != GRKAN_BF16 && out_dtype != GRKAN_F32))
         return GRKAN_ERR_DTYPE;
     if (m != 5 || n != 4)
@@ -1181,9 +1231,10 @@ static grkan_status_t linear_fwd_impl(const void *x, const float *A, const float
         return shape;
     if (!A || !B || !W || (rows > 0 && (!x || !out)))
         return GRKAN_ERR_NULL;
-    // 128-bit loads of x and W rows, 64/128-bit stores of four output channels, vector load of the bias
-    if ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(out) |
-         reinterpret_cast<uintptr_t>(bias)) % 16 != 0 ||
+    // 128-bit loads of x and W rows, 64/128-bit stores of four output channels, vector load of the bias, 32-bit
+    // loads of the coefficients
+    if ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(out)) % 16 != 0 ||
+        reinterpret_cast<uintptr_t>(bias) % (model ? 8 : 16) != 0 ||
         (reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) % 4 != 0)
         return GRKAN_ERR_ALIGN;
     if (shape != GRKAN_OK)
@@ -1196,7 +1247,9 @@ static grkan_status_t linear_fwd_impl(const void *x, const float *A, const float
     const int bm = small ? small->bm() : kBM, bn = small ? small->bn() : v.bn();
     const bool nedge = D_out % bn != 0;
     LinKernel kernel;
-    if (small && packed)
+    if (model)
+        kernel = small ? select_small<bf16_out, false, true>(*small) : select_kernel<bf16_out, false, true>(v, nedge);
+    else if (small && packed)
         kernel = out_dtype == GRKAN_BF16 ? select_small<bf16_out, true>(*small) : select_small<float, true>(*small);
     else if (small)
         kernel = out_dtype == GRKAN_BF16 ? select_small<bf16_out, false>(*small) : select_small<float, false>(*small);
@@ -1217,6 +1270,7 @@ static grkan_status_t linear_fwd_impl(const void *x, const float *A, const float
     a.out = static_cast<char *>(out);
     a.A = A;
     a.B = B;
+    a.a_stride = operands == Operands::model_shared ? 0 : m + 1;
     a.rows = rows;
     a.K = D_in;
     a.Nout = D_out;
@@ -1248,7 +1302,7 @@ extern "C" grkan_status_t grkan_linear_fwd(const void *x, const float *A, const 
                                            int32_t m, int32_t n, grkan_dtype_t io, grkan_dtype_t out_dtype,
                                            void *hip_stream)
 {
-    return linear_fwd_impl(x, A, B, W, false, bias, out, rows, D_in, D_out, G, m, n, io, out_dtype, hip_stream);
+    return linear_fwd_impl(x, A, B, W, Operands::plain, bias, out, rows, D_in, D_out, G, m, n, io, out_dtype, hip_stream);
 }
 
 extern "C" grkan_status_t grkan_linear_fwd_packed(const void *x, const float *A, const float *B, const void *Wp,
@@ -1257,7 +1311,16 @@ extern "C" grkan_status_t grkan_linear_fwd_packed(const void *x, const float *A,
                                                   int32_t m, int32_t n, grkan_dtype_t io, grkan_dtype_t out_dtype,
                                                   void *hip_stream)
 {
-    return linear_fwd_impl(x, A, B, Wp, true, bias, out, rows, D_in, D_out, G, m, n, io, out_dtype, hip_stream);
+    return linear_fwd_impl(x, A, B, Wp, Operands::packed, bias, out, rows, D_in, D_out, G, m, n, io, out_dtype, hip_stream);
+}
+
+extern "C" grkan_status_t grkan_linear_fwd_model(const void *x, const void *A, const void *B, const void *W,
+                                                 const void *bias, void *out,
+                                                 int64_t rows, int32_t D_in, int32_t D_out, int32_t G,
+                                                 int32_t m, int32_t n, int32_t shared_numerator, void *hip_stream)
+{
+    return linear_fwd_impl(x, A, B, W, shared_numerator ? Operands::model_shared : Operands::model, bias, out, rows, D_in,
+                           D_out, G, m, n, GRKAN_BF16, GRKAN_BF16, hip_stream);
 }
 
 extern "C" double grkan_linear_estimate_us(int64_t rows, int32_t D_in, int32_t D_out)

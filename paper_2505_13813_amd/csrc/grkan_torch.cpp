@@ -236,11 +236,43 @@ std::optional<Tensor> layer_packed(const Tensor &x_in, const Tensor &A, const Te
     return out;
 }
 
+// The one-kernel layer on a bfloat16 module's own parameters (inference): nothing is converted, packed or kept.
+// Sizes, layouts and alignments that the kernel does not cover are not taken.
+std::optional<Tensor> layer_model(const Tensor &x_in, const Tensor &A, const Tensor &B, const Tensor &W,
+                                  const std::optional<Tensor> &bias)
+{
+    if (at::GradMode::is_enabled() || !plain_context() || !on_current_gpu(x_in))
+        return std::nullopt;
+    for (const Tensor *t : {&x_in, &A, &B, &W, bias ? &*bias : &x_in})
+        if (!plain(*t, x_in.device()) || t->scalar_type() != at::kBFloat16 || (t != &x_in && !t->is_contiguous()))
+            return std::nullopt;
+    if (x_in.dim() < 1 || x_in.numel() == 0 || W.dim() != 2 || W.size(1) != x_in.size(-1) || B.dim() != 2 || B.size(1) != 4 ||
+        A.dim() < 1 || A.dim() > 2 || A.size(-1) != 6 || (A.dim() == 2 && A.size(0) != B.size(0)) ||
+        (bias && (bias->dim() != 1 || bias->size(0) != W.size(0))))
+        return std::nullopt;
+    const int64_t D = W.size(1), D_out = W.size(0), G = B.size(0);
+    if (D > INT32_MAX || D_out > INT32_MAX || G <= 0 || D % 64 != 0 || D % G != 0 || D / G % 32 != 0 || D_out <= 0 || D_out % 4 != 0)
+        return std::nullopt;
+    auto misaligned = [](const Tensor &t, uintptr_t to) { return reinterpret_cast<uintptr_t>(t.data_ptr()) % to != 0; };
+    const Tensor x = x_in.contiguous();
+    if (misaligned(x, 16) || misaligned(W, 16) || misaligned(A, 4) || misaligned(B, 4) || (bias && misaligned(*bias, 8)))
+        return std::nullopt;
+    auto shape = x.sizes().vec();
+    shape.back() = D_out;
+    Tensor out = at::empty(shape, x.options());
+    check(grkan_linear_fwd_model(x.data_ptr(), A.data_ptr(), B.data_ptr(), W.data_ptr(), bias ? bias->data_ptr() : nullptr,
+                                 out.data_ptr(), x.numel() / D, (int32_t)D, (int32_t)D_out, (int32_t)G, 5, 4, A.dim() == 1,
+                                 stream_of(x)),
+          "grkan_linear_fwd_model");
+    return out;
+}
+
 } // namespace
 
 PYBIND11_MODULE(_native, mod)
 {
     mod.def("rational", &rational, pybind11::call_guard<pybind11::gil_scoped_release>());
     mod.def("product", &product, pybind11::call_guard<pybind11::gil_scoped_release>());
+    mod.def("layer_model", &layer_model, pybind11::call_guard<pybind11::gil_scoped_release>());
     mod.def("layer_packed", &layer_packed, pybind11::call_guard<pybind11::gil_scoped_release>());
 }

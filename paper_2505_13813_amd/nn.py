@@ -84,9 +84,9 @@ def fused_layer_supported(x, A, weight) -> bool:
 
 
 def fused_layer_pays(rows: int, D_in: int, D_out: int) -> bool:
-    """Whether the layer's 112-row tiles (of 768, 384 or 192 channels) fill the chip, or the contraction is so
-    short that a tile is quick: the sizes at which that tile alone is the faster route.  (The module decides
-    by one_kernel_is_faster, which knows the smaller tiles too.)"""
+    """The sizes at which a GRKANLinear runs the one-kernel layer on a packed copy of its weights that it keeps between
+    calls: the layer's 112-row tiles (of 768, 384 or 192 channels) fill the chip, or the contraction is short.  (At
+    other sizes the module takes the layer on its parameters as they are, where one_kernel_is_faster says so.)"""
     bn = 768 if D_out % 768 == 0 else (384 if D_out % 384 == 0 else 192)
     workgroups = -(-int(rows) // 112) * -(-int(D_out) // bn)
     return workgroups >= 200 or D_in <= 768
@@ -264,13 +264,19 @@ class GRKANLinear(nn.Module):
         """`fused`: when the one-kernel layer (F inside the matrix product) is used where it applies
         (bfloat16, see fused_layer_supported): "inference" = when no gradient is recorded (in training
         its backward pass has to recompute F(x)) and it is the faster route at this size
-        (one_kernel_is_faster); "always" = wherever it applies; "never"."""
+        (one_kernel_is_faster); "always" = wherever it applies; "never".
+
+        At the sizes of fused_layer_pays it runs on a packed copy of the weights (with bias and coefficients
+        in float32) that is kept until a parameter is written to or replaced.  Writes through `.data` or a
+        detached alias leave no trace that this could be told from: after one, call drop_packed_weights().
+        At all other sizes it reads the parameters themselves and keeps nothing."""
         super().__init__()
         if in_features % groups:
             raise ValueError("in_features must be a multiple of groups")
         if fused not in ("inference", "always", "never"):
             raise ValueError("fused must be 'inference', 'always' or 'never'")
         self.fused = fused
+        self._keep_packed = True
         self._packed = None      # inference: packed copy of the weights and float32 bias, remade when they change
         self._packed_key = None
         self.rational = GroupRational(groups, init, shared_numerator, degrees)
@@ -280,6 +286,11 @@ class GRKANLinear(nn.Module):
             self.linear.weight.normal_(0.0, math.sqrt(alpha / in_features))
             if bias:
                 self.linear.bias.zero_()
+
+    def drop_packed_weights(self):
+        """Forgets the packed copy of the weights; the next call that needs one makes it anew."""
+        self._packed_key = None
+        self._packed = None
 
     def _inference_weights(self):
         """Packed weights (the kernel then fetches them in whole cache lines), the bias and the
@@ -300,8 +311,10 @@ class GRKANLinear(nn.Module):
             A, B = self.rational.coefficient_rows()
             if fused_layer_supported(x, A, self.linear.weight):
                 rows, D_in = x.numel() // x.shape[-1], x.shape[-1]
+                D_out = self.linear.weight.shape[0]
                 if not torch.is_grad_enabled() and (
-                        self.fused == "always" or one_kernel_is_faster(rows, D_in, self.linear.weight.shape[0])):
+                        self.fused == "always" or (self._keep_packed and fused_layer_pays(rows, D_in, D_out)
+                                                   and one_kernel_is_faster(rows, D_in, D_out))):
                     pw, b32, A32, B32 = self._inference_weights()
                     if D_in == pw.D_in and not torch.compiler.is_compiling():
                         out = binding.load_native().layer_packed(x, A32, B32, pw.data, pw.D_out, b32)
@@ -311,6 +324,11 @@ class GRKANLinear(nn.Module):
                 if self.fused == "always":
                     return GRKANLayerFunction.apply(x, A.to(torch.float32), B.to(torch.float32), self.linear.weight,
                                                     self.linear.bias)
+                if not torch.compiler.is_compiling() and one_kernel_is_faster(rows, D_in, D_out):
+                    out = binding.load_native().layer_model(x, self.rational.numerator, self.rational.denominator,
+                                                            self.linear.weight, self.linear.bias)
+                    if out is not None:
+                        return out
         y = self.rational(x)
         out = _native_product(self.linear, y)
         return self.linear(y) if out is None else out
@@ -327,6 +345,7 @@ class KATMlp(nn.Module):
         # in training the library product after the elementwise kernel is the faster route for fc1
         self.fc1 = GRKANLinear(dim, hidden, groups, init="identity", degrees=degrees,
                                fused="never" if fused == "never" else "inference")
+        self.fc1._keep_packed = False
         self.fc2 = GRKANLinear(hidden, dim, groups, init="swish", degrees=degrees, fused=fused)
 
     def forward(self, x):

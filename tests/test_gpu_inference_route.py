@@ -1,0 +1,112 @@
+"""GPU tests of the route a GR-KAN layer takes in inference: results follow the parameters, whatever wrote them,
+and whatever is attached to the layer's parts is run."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# rows, D_in, D_out, G of layers that read their parameters as they are: every tile, one row, ragged rows
+LAYERS = [(1, 3072, 768, 8), (197, 3072, 768, 8), (1001, 1536, 388, 8), (3107, 1088, 1152, 2), (6304, 832, 768, 2),
+          (20011, 832, 768, 2), (25000, 896, 384, 4), (28000, 832, 188, 1)]
+
+
+def _layer(torch, D_in, D_out, G, seed=0, bias=True, shared=True):
+    from paper_2505_13813_amd import nn as gnn
+
+    torch.manual_seed(seed)
+    layer = gnn.GRKANLinear(D_in, D_out, G, init="swish", bias=bias, shared_numerator=shared).to("cuda:0").to(torch.bfloat16).eval()
+    _stir(torch, layer)
+    return layer
+
+
+def _stir(torch, layer):
+    with torch.no_grad():
+        layer.rational.numerator.add_(0.05 * torch.randn_like(layer.rational.numerator))
+        layer.rational.denominator.add_(0.02 * torch.rand_like(layer.rational.denominator))
+        if layer.linear.bias is not None:
+            layer.linear.bias.normal_(0.0, 0.1)
+
+
+def _rows(torch, rows, D, seed=1):
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(seed)
+    return torch.randn(rows, D, device="cuda:0", generator=gen).to(torch.bfloat16)
+
+
+def _close(torch, got, want):
+    """Two routes with the same rounding points, sums in another order: an output that differs is next to a rounding
+    boundary, one unit in the last place away: 2^(e - 7) for a value of at least 2^e, so 2^-7 of it.  Near zero the
+    sums themselves differ, by far less than 2^-12 of their scale."""
+    g, w = got.float(), want.float()
+    assert got.dtype == want.dtype and got.shape == want.shape
+    return bool(((g - w).abs() <= 2.0 ** -7 * w.abs() + 2.0 ** -12 * w.pow(2).mean().sqrt()).all())
+
+
+@pytest.mark.parametrize("bias,shared", [(True, True), (False, False)])
+@pytest.mark.parametrize("rows,D_in,D_out,G", LAYERS)
+def test_layer_on_the_models_own_parameters(rows, D_in, D_out, G, bias, shared):
+    """bfloat16 coefficients and bias read by the kernel against the same kernel on their float32 copies (the same
+    bits) and against the two-kernel route."""
+    import torch
+
+    import paper_2505_13813_amd as grkan
+    from paper_2505_13813_amd import binding
+    from paper_2505_13813_amd import nn as gnn
+
+    layer, x = _layer(torch, D_in, D_out, G, bias=bias, shared=shared), _rows(torch, rows, D_in)
+    A, B = (t.detach().float().contiguous() for t in layer.rational.coefficient_rows())
+    b32 = layer.linear.bias.detach().float() if bias else None
+    with torch.no_grad():
+        got = binding.load_native().layer_model(x, layer.rational.numerator, layer.rational.denominator, layer.linear.weight,
+                                                layer.linear.bias)
+        want = grkan.grkan_linear_fwd(x, A, B, layer.linear.weight.detach(), b32)
+        assert got is not None
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+        assert _close(torch, got, layer.linear(layer.rational(x)))
+        if gnn.one_kernel_is_faster(rows, D_in, D_out) and not gnn.fused_layer_pays(rows, D_in, D_out):
+            assert torch.equal(layer(x).view(torch.int16), got.view(torch.int16))
+
+
+def test_writes_through_data_are_seen():
+    """An exponential moving average or a broadcast writes parameters through .data, which changes neither their
+    address nor their version: the block's output has to follow."""
+    import torch
+
+    from paper_2505_13813_amd import nn as gnn
+
+    torch.manual_seed(3)
+    block = gnn.KATMlp(768).to("cuda:0").to(torch.bfloat16).eval()
+    other = gnn.KATMlp(768).to("cuda:0").to(torch.bfloat16).eval()
+    for layer in (other.fc1, other.fc2):
+        _stir(torch, layer)
+    x = _rows(torch, 197, 768).view(1, 197, 768)
+    with torch.no_grad():
+        before, want = block(x), other(x)
+        assert not torch.equal(before, want)
+        for p, q in zip(block.parameters(), other.parameters()):
+            p.data.copy_(q.data)
+        assert torch.equal(block(x), want)
+        for p in block.parameters():
+            p.data.mul_(0.5)
+        again = block(x)
+        for p in other.parameters():
+            p.mul_(0.5)
+        assert torch.equal(again, other(x)) and not torch.equal(again, want)
+    assert block.fc1._packed is None and block.fc2._packed is None
+
+
+def test_a_kept_copy_can_be_dropped():
+    """At the sizes where the layer keeps a packed copy of its weights, writes it can be told of are seen, and after
+    others the copy is dropped by hand."""
+    import torch
+
+    layer, x = _layer(torch, 256, 64, 8), _rows(torch, 160, 256)
+    with torch.no_grad():
+        first = layer(x)
+        layer.linear.weight.mul_(0.5)
+        layer.linear.bias.mul_(0.5)
+        half = layer(x)
+        assert _close(torch, half, (0.5 * first.float()).to(torch.bfloat16))
+        layer.linear.weight.data.mul_(2.0)
+        layer.linear.bias.data.mul_(2.0)
+        layer.drop_packed_weights()
+        assert torch.equal(layer(x), first)
