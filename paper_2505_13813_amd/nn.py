@@ -148,20 +148,30 @@ def _native_product(linear, y):
     """The linear layer on y with grkan_linear_wgrad in its backward pass, or None where that route is not
     taken: plain bfloat16 training on the GPU, at sizes it pays for, with nothing attached to the linear layer
     that its own call would run or change (hooks, parametrisations, autocast, tracing, tensor subclasses)."""
+    if not _only_a(nn.Linear, linear):
+        return None
     w, b = linear.weight, linear.bias
-    if (type(linear) is not nn.Linear or y.dtype != torch.bfloat16 or not torch.is_grad_enabled() or not w.requires_grad
+    if (y.dtype != torch.bfloat16 or not torch.is_grad_enabled() or not w.requires_grad
             or type(w) is not nn.Parameter or (b is not None and type(b) is not nn.Parameter) or type(y) is not torch.Tensor
-            or "forward" in linear.__dict__ or linear._forward_hooks or linear._forward_pre_hooks or linear._backward_hooks
-            or linear._backward_pre_hooks or _global_hooks() or torch.is_autocast_enabled()
+            or torch.is_autocast_enabled()
             or torch.compiler.is_compiling() or not wgrad_pays(y.numel() // y.shape[-1], w.shape[1], w.shape[0])):
         return None
     return binding.load_native().product(y, w, b)
 
 
-def _global_hooks() -> bool:
+def _only_a(cls, module) -> bool:
+    """Whether calling `module` runs cls.forward and nothing else, so that a route past the call changes nothing: no
+    subclass (an adapter, a parametrisation), no forward of its own, no hooks on it or on every module."""
     m = nn.modules.module
-    return bool(m._global_forward_hooks or m._global_forward_pre_hooks or m._global_backward_hooks
-                or m._global_backward_pre_hooks)
+    return (type(module) is cls and "forward" not in module.__dict__
+            and not (module._forward_hooks or module._forward_pre_hooks or module._backward_hooks
+                     or module._backward_pre_hooks or m._global_forward_hooks or m._global_forward_pre_hooks
+                     or m._global_backward_hooks or m._global_backward_pre_hooks))
+
+
+def _autocast_elsewhere() -> bool:
+    """Whether autocast would have torch's linear compute in another type than bfloat16."""
+    return torch.is_autocast_enabled() and torch.get_autocast_dtype("cuda") != torch.bfloat16
 
 
 def group_rational(x, A, B):
@@ -246,7 +256,8 @@ class GroupRational(nn.Module):
         return float(np.mean([second_moment(A[g], B[g]) for g in range(self.groups)]))
 
     def forward(self, x):
-        if not torch.compiler.is_compiling():
+        if (not torch.compiler.is_compiling() and "coefficient_rows" not in self.__dict__
+                and type(self).coefficient_rows is GroupRational.coefficient_rows):
             # the parameters as they are: one numerator row for all groups, float32 or bfloat16
             y = binding.load_native().rational(x, self.numerator, self.denominator)
             if y is not None:
@@ -292,11 +303,13 @@ class GRKANLinear(nn.Module):
         self._packed_key = None
         self._packed = None
 
+    def _inference_params(self):
+        return self.linear.weight, self.linear.bias, self.rational.numerator, self.rational.denominator
+
     def _inference_weights(self):
         """Packed weights (the kernel then fetches them in whole cache lines), the bias and the
         coefficient rows in float32, cached until a parameter is written to or replaced."""
-        params = (self.linear.weight, self.linear.bias, self.rational.numerator, self.rational.denominator)
-        key = tuple(None if p is None else (p.data_ptr(), p._version, p.device) for p in params)
+        key = tuple(None if p is None else (p.data_ptr(), p._version, p.device) for p in self._inference_params())
         if self._packed_key != key:
             w, b = self.linear.weight, self.linear.bias
             A, B = self.rational.coefficient_rows()
@@ -307,24 +320,27 @@ class GRKANLinear(nn.Module):
         return self._packed
 
     def forward(self, x):
-        if self.fused == "always" or (self.fused == "inference" and not torch.is_grad_enabled()):
+        if ((self.fused == "always" or (self.fused == "inference" and not torch.is_grad_enabled()))
+                and _only_a(nn.Linear, self.linear) and _only_a(GroupRational, self.rational) and not _autocast_elsewhere()):
             A, B = self.rational.coefficient_rows()
             if fused_layer_supported(x, A, self.linear.weight):
                 rows, D_in = x.numel() // x.shape[-1], x.shape[-1]
                 D_out = self.linear.weight.shape[0]
-                if not torch.is_grad_enabled() and (
-                        self.fused == "always" or (self._keep_packed and fused_layer_pays(rows, D_in, D_out)
-                                                   and one_kernel_is_faster(rows, D_in, D_out))):
+                faster = one_kernel_is_faster(rows, D_in, D_out)
+                # (a tensor put in a parameter's place for one call may sit where the last one did)
+                keep = self._keep_packed and all(type(p) is nn.Parameter for p in self._inference_params() if p is not None)
+                if not torch.is_grad_enabled() and keep and (
+                        self.fused == "always" or (fused_layer_pays(rows, D_in, D_out) and faster)):
                     pw, b32, A32, B32 = self._inference_weights()
                     if D_in == pw.D_in and not torch.compiler.is_compiling():
                         out = binding.load_native().layer_packed(x, A32, B32, pw.data, pw.D_out, b32)
                         if out is not None:
                             return out
                     return binding.grkan_linear_fwd(x.contiguous(), A32, B32, pw, b32, out_dtype=x.dtype)
-                if self.fused == "always":
+                if self.fused == "always" and torch.is_grad_enabled():
                     return GRKANLayerFunction.apply(x, A.to(torch.float32), B.to(torch.float32), self.linear.weight,
                                                     self.linear.bias)
-                if not torch.compiler.is_compiling() and one_kernel_is_faster(rows, D_in, D_out):
+                if not torch.compiler.is_compiling() and (faster or self.fused == "always"):
                     out = binding.load_native().layer_model(x, self.rational.numerator, self.rational.denominator,
                                                             self.linear.weight, self.linear.bias)
                     if out is not None:

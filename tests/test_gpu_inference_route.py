@@ -110,3 +110,100 @@ def test_a_kept_copy_can_be_dropped():
         layer.linear.bias.data.mul_(2.0)
         layer.drop_packed_weights()
         assert torch.equal(layer(x), first)
+
+
+# one size that reads the parameters as they are, and one that keeps a packed copy
+SIZES = [(197, 3072, 768), (160, 256, 64)]
+
+
+def _two_kernels(torch, layer, x):
+    """The layer's own parts, called one after the other."""
+    return layer.linear(layer.rational(x))
+
+
+@pytest.mark.parametrize("rows,D_in,D_out", SIZES)
+def test_hooks_on_the_layers_parts_run(rows, D_in, D_out):
+    import torch
+
+    layer, x = _layer(torch, D_in, D_out, 8), _rows(torch, rows, D_in)
+    seen = []
+    with torch.no_grad():
+        for part in (layer.linear, layer.rational):
+            for register in ("register_forward_hook", "register_forward_pre_hook"):
+                handle = getattr(part, register)(lambda *a: seen.append(register))
+                layer(x)
+                handle.remove()
+                assert seen.pop() == register and not seen
+        handle = layer.linear.register_forward_hook(lambda m, args, out: out + 1)
+        assert torch.equal(layer(x), _two_kernels(torch, layer, x))
+        handle.remove()
+        handle = torch.nn.modules.module.register_module_forward_hook(lambda m, args, out: seen.append(type(m).__name__))
+        layer(x)
+        handle.remove()
+        assert {"Linear", "GroupRational"} <= set(seen)
+        # a weight computed in a pre-hook, and one computed on every access
+        torch.nn.utils.weight_norm(layer.linear)
+        layer.linear.weight_g.mul_(2.0)
+        assert torch.equal(layer(x), _two_kernels(torch, layer, x))
+        torch.nn.utils.remove_weight_norm(layer.linear)
+
+        class Doubled(torch.nn.Module):
+            def forward(self, w):
+                return 2 * w
+
+        before = _two_kernels(torch, layer, x)
+        torch.nn.utils.parametrize.register_parametrization(layer.linear, "weight", Doubled())
+        after = layer(x)
+        assert torch.equal(after, _two_kernels(torch, layer, x)) and not torch.equal(after, before)
+        for p in layer.linear.parametrizations.weight.parameters():
+            p.mul_(0.5)
+        assert not torch.equal(layer(x), after)
+
+
+@pytest.mark.parametrize("rows,D_in,D_out", SIZES)
+def test_replaced_parts_are_called(rows, D_in, D_out):
+    """A linear layer with an adapter, one without a weight of its own, a rational with other coefficient rows, a
+    forward set on the module, tensors in the parameters' place."""
+    import torch
+
+    from paper_2505_13813_amd import nn as gnn
+
+    class Adapter(torch.nn.Linear):
+        def forward(self, x):
+            return super().forward(x) + x[..., :1]
+
+    class Clamped(gnn.GroupRational):
+        def coefficient_rows(self):
+            A, B = super().coefficient_rows()
+            return A, B.clamp(min=0.01)
+
+    layer, x = _layer(torch, D_in, D_out, 8), _rows(torch, rows, D_in)
+    with torch.no_grad():
+        plain = layer.linear
+        adapted = Adapter(D_in, D_out).to("cuda:0").to(torch.bfloat16)
+        adapted.load_state_dict(plain.state_dict())
+        for part in (adapted, torch.nn.Sequential(plain)):
+            layer.linear = part
+            assert torch.equal(layer(x), _two_kernels(torch, layer, x))
+        layer.linear = plain
+        plain.forward = lambda t: torch.nn.functional.linear(t, plain.weight)
+        assert torch.equal(layer(x), _two_kernels(torch, layer, x))
+        del plain.forward
+        # another set of parameters for one call: the module's own are as they were afterwards
+        base = layer(x)
+        other = {k: 0.5 * v for k, v in layer.state_dict().items()}
+        swapped = torch.func.functional_call(layer, other, (x,))
+        want = _layer(torch, D_in, D_out, 8)
+        want.load_state_dict(other)
+        assert _close(torch, swapped, want(x)) and torch.equal(layer(x), base)
+        rows_of = layer.rational
+        layer.rational = Clamped(8, "swish").to("cuda:0").to(torch.bfloat16)
+        A, B = layer.rational.coefficient_rows()
+        f = gnn.GroupRationalFunction.apply(x, A.float().contiguous(), B.float().contiguous())
+        assert torch.equal(layer.rational(x), f) and torch.equal(layer(x), layer.linear(f))
+        layer.rational = rows_of
+        # torch's linear would compute in float16 here
+        with torch.autocast("cuda", dtype=torch.float16):
+            assert layer(x).dtype == torch.float16
+        with torch.autocast("cuda", dtype=torch.bfloat16):
+            assert torch.equal(layer(x), base)
