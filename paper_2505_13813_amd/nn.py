@@ -320,34 +320,41 @@ class GRKANLinear(nn.Module):
         return self._packed
 
     def forward(self, x):
-        if ((self.fused == "always" or (self.fused == "inference" and not torch.is_grad_enabled()))
-                and _only_a(nn.Linear, self.linear) and _only_a(GroupRational, self.rational) and not _autocast_elsewhere()):
-            A, B = self.rational.coefficient_rows()
-            if fused_layer_supported(x, A, self.linear.weight):
-                rows, D_in = x.numel() // x.shape[-1], x.shape[-1]
-                D_out = self.linear.weight.shape[0]
-                faster = one_kernel_is_faster(rows, D_in, D_out)
-                # (a tensor put in a parameter's place for one call may sit where the last one did)
-                keep = self._keep_packed and all(type(p) is nn.Parameter for p in self._inference_params() if p is not None)
-                if not torch.is_grad_enabled() and keep and (
-                        self.fused == "always" or (fused_layer_pays(rows, D_in, D_out) and faster)):
-                    pw, b32, A32, B32 = self._inference_weights()
-                    if D_in == pw.D_in and not torch.compiler.is_compiling():
-                        out = binding.load_native().layer_packed(x, A32, B32, pw.data, pw.D_out, b32)
-                        if out is not None:
-                            return out
-                    return binding.grkan_linear_fwd(x.contiguous(), A32, B32, pw, b32, out_dtype=x.dtype)
-                if self.fused == "always" and torch.is_grad_enabled():
-                    return GRKANLayerFunction.apply(x, A.to(torch.float32), B.to(torch.float32), self.linear.weight,
-                                                    self.linear.bias)
-                if not torch.compiler.is_compiling() and (faster or self.fused == "always"):
-                    out = binding.load_native().layer_model(x, self.rational.numerator, self.rational.denominator,
-                                                            self.linear.weight, self.linear.bias)
-                    if out is not None:
-                        return out
+        out = self._one_kernel(x)
+        if out is not None:
+            return out
         y = self.rational(x)
         out = _native_product(self.linear, y)
         return self.linear(y) if out is None else out
+
+    def _one_kernel(self, x):
+        """The layer's output from the one kernel, or None where that route is not taken.  (What the native entries
+        do not take - alignment, forward-mode differentiation, function transforms - is left to the two kernels.)"""
+        grad, always = torch.is_grad_enabled(), self.fused == "always"
+        if (self.fused == "never" or (grad and not always) or not _only_a(nn.Linear, self.linear)
+                or not _only_a(GroupRational, self.rational) or _autocast_elsewhere()):
+            return None
+        A, B = self.rational.coefficient_rows()
+        weight = self.linear.weight
+        if not fused_layer_supported(x, A, weight) or x.shape[-1] != weight.shape[1]:
+            return None
+        if grad:
+            return GRKANLayerFunction.apply(x, A.to(torch.float32), B.to(torch.float32), weight, self.linear.bias)
+        rows, D_in, D_out = x.numel() // x.shape[-1], x.shape[-1], weight.shape[0]
+        if not always and not one_kernel_is_faster(rows, D_in, D_out):
+            return None
+        compiling = torch.compiler.is_compiling()
+        # (a tensor put in a parameter's place for one call may sit where the last one did)
+        if (self._keep_packed and (always or fused_layer_pays(rows, D_in, D_out))
+                and all(type(p) is nn.Parameter for p in self._inference_params() if p is not None)):
+            pw, b32, A32, B32 = self._inference_weights()
+            if compiling:
+                return binding.grkan_linear_fwd(x.contiguous(), A32, B32, pw, b32, out_dtype=x.dtype)
+            return binding.load_native().layer_packed(x, A32, B32, pw.data, pw.D_out, b32)
+        if compiling:
+            return None
+        return binding.load_native().layer_model(x, self.rational.numerator, self.rational.denominator, weight,
+                                                 self.linear.bias)
 
 
 class KATMlp(nn.Module):

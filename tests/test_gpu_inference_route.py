@@ -207,3 +207,27 @@ def test_replaced_parts_are_called(rows, D_in, D_out):
             assert layer(x).dtype == torch.float16
         with torch.autocast("cuda", dtype=torch.bfloat16):
             assert torch.equal(layer(x), base)
+
+
+@pytest.mark.parametrize("rows,D_in,D_out", SIZES)
+def test_what_the_native_entries_leave_alone_runs_in_two_kernels(rows, D_in, D_out):
+    """An input that starts at an odd element, one of no rows, a strided one; forward-mode differentiation is refused
+    by the Python function instead of losing its tangent."""
+    import torch
+
+    layer, x = _layer(torch, D_in, D_out, 8), _rows(torch, rows, D_in)
+    flat = torch.empty(rows * D_in + 1, device="cuda:0", dtype=torch.bfloat16)
+    odd = flat[1:].view(rows, D_in)
+    odd.copy_(x)
+    with torch.no_grad():
+        assert torch.equal(layer(odd), _two_kernels(torch, layer, odd))
+        assert layer(x[:0]).shape == (0, D_out)
+        wide = torch.empty(rows, 2 * D_in, device="cuda:0", dtype=torch.bfloat16)
+        wide[:, ::2] = x
+        assert torch.equal(layer(wide[:, ::2]), layer(x))
+        with torch.autograd.forward_ad.dual_level():
+            dual = torch.autograd.forward_ad.make_dual(x, torch.ones_like(x))
+            with pytest.raises((RuntimeError, NotImplementedError)):
+                layer(dual)
+        with pytest.raises((RuntimeError, NotImplementedError)):
+            torch.func.vmap(layer)(torch.stack([x, x]))
