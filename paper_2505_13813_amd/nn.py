@@ -313,7 +313,10 @@ class GRKANLinear(nn.Module):
         if self._packed_key != key:
             w, b = self.linear.weight, self.linear.bias
             A, B = self.rational.coefficient_rows()
-            self._packed = (binding.grkan_linear_pack_w(w.detach().contiguous()),
+            w = w.detach().contiguous()
+            if w.data_ptr() % 16:  # a view into a larger buffer
+                w = w.clone()
+            self._packed = (binding.grkan_linear_pack_w(w),
                             None if b is None else b.detach().to(torch.float32).contiguous(),
                             A.detach().to(torch.float32).contiguous(), B.detach().to(torch.float32).contiguous())
             self._packed_key = key
@@ -344,9 +347,10 @@ class GRKANLinear(nn.Module):
         if not always and not one_kernel_is_faster(rows, D_in, D_out):
             return None
         compiling = torch.compiler.is_compiling()
-        # (a tensor put in a parameter's place for one call may sit where the last one did)
+        # (a tensor put in a parameter's place for one call may sit where the last one did; inference tensors have no
+        # version)
         if (self._keep_packed and (always or fused_layer_pays(rows, D_in, D_out))
-                and all(type(p) is nn.Parameter for p in self._inference_params() if p is not None)):
+                and all(type(p) is nn.Parameter and not p.is_inference() for p in self._inference_params() if p is not None)):
             pw, b32, A32, B32 = self._inference_weights()
             if compiling:
                 return binding.grkan_linear_fwd(x.contiguous(), A32, B32, pw, b32, out_dtype=x.dtype)
