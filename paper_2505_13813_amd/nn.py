@@ -26,6 +26,7 @@ functions; what those do not take runs in the Python ones here.  Conventions tak
 from __future__ import annotations
 
 import math
+import weakref
 from functools import lru_cache
 from typing import Tuple
 
@@ -266,6 +267,40 @@ class GroupRational(nn.Module):
         return group_rational(x, A.to(torch.float32), B.to(torch.float32))
 
 
+class _Packed(tuple):
+    """(PackedWeight, bias, A rows, B rows) of one state of a layer's parameters, with the event after which other
+    streams than the one it was made on may read it.  Not part of a copied or saved module."""
+
+    def __new__(cls, rational, params):
+        w, b = (None if p is None else p.detach() for p in params[:2])
+        A, B = rational.coefficient_rows()
+        w = w.contiguous()
+        if w.data_ptr() % 16:  # a view into a larger buffer
+            w = w.clone()
+        self = super().__new__(cls, (binding.grkan_linear_pack_w(w), None if b is None else b.to(torch.float32).contiguous(),
+                                     A.detach().to(torch.float32).contiguous(), B.detach().to(torch.float32).contiguous()))
+        self._params = tuple(None if p is None else weakref.ref(p) for p in params)
+        self._key = cls._key_of(params)
+        return self
+
+    @staticmethod
+    def _key_of(params):
+        return tuple(None if p is None else (p.data_ptr(), p._version, p.device) for p in params)
+
+    def is_of(self, params) -> bool:
+        return self._key == self._key_of(params) and all(r is p if p is None else r is not None and r() is p
+                                                         for r, p in zip(self._params, params))
+
+    def tensors(self):
+        return [t for t in (self[0].data, *self[1:]) if t is not None]
+
+    def __deepcopy__(self, memo):
+        return None
+
+    def __reduce__(self):
+        return type(None), ()
+
+
 class GRKANLinear(nn.Module):
     """GR-KAN(x) = W F(x) + bias (Eq. "GR_KAN"), variance-preserving init."""
 
@@ -287,9 +322,7 @@ class GRKANLinear(nn.Module):
         if fused not in ("inference", "always", "never"):
             raise ValueError("fused must be 'inference', 'always' or 'never'")
         self.fused = fused
-        self._keep_packed = True
-        self._packed = None      # inference: packed copy of the weights and float32 bias, remade when they change
-        self._packed_key = None
+        self._packed = None  # _Packed
         self.rational = GroupRational(groups, init, shared_numerator, degrees)
         self.linear = nn.Linear(in_features, out_features, bias=bias)
         alpha = 1.0 / self.rational.second_moment()  # Var[x] / E[F(x)^2] with Var[x] = 1
@@ -298,29 +331,30 @@ class GRKANLinear(nn.Module):
             if bias:
                 self.linear.bias.zero_()
 
+    _keep_packed = True
+
     def drop_packed_weights(self):
         """Forgets the packed copy of the weights; the next call that needs one makes it anew."""
-        self._packed_key = None
         self._packed = None
 
     def _inference_params(self):
         return self.linear.weight, self.linear.bias, self.rational.numerator, self.rational.denominator
 
     def _inference_weights(self):
-        """Packed weights (the kernel then fetches them in whole cache lines), the bias and the
-        coefficient rows in float32, cached until a parameter is written to or replaced."""
-        key = tuple(None if p is None else (p.data_ptr(), p._version, p.device) for p in self._inference_params())
-        if self._packed_key != key:
-            w, b = self.linear.weight, self.linear.bias
-            A, B = self.rational.coefficient_rows()
-            w = w.detach().contiguous()
-            if w.data_ptr() % 16:  # a view into a larger buffer
-                w = w.clone()
-            self._packed = (binding.grkan_linear_pack_w(w),
-                            None if b is None else b.detach().to(torch.float32).contiguous(),
-                            A.detach().to(torch.float32).contiguous(), B.detach().to(torch.float32).contiguous())
-            self._packed_key = key
-        return self._packed
+        """Packed weights (the kernel then fetches them in whole cache lines), the bias and the coefficient rows in
+        float32, kept until a parameter is written to or replaced."""
+        params = self._inference_params()
+        stream = torch.cuda.current_stream(params[0].device)
+        packed = self._packed
+        if packed is None or not packed.is_of(params):
+            packed = _Packed(self.rational, params)
+            packed.stream, packed.made = stream, stream.record_event()
+            self._packed = packed
+        elif packed.stream != stream:
+            stream.wait_event(packed.made)
+            for t in packed.tensors():
+                t.record_stream(stream)
+        return packed
 
     def forward(self, x):
         out = self._one_kernel(x)

@@ -258,3 +258,35 @@ def test_parameters_of_every_kind(rows, D_in, D_out):
         assert _close(torch, other(x), want)
         other.linear.bias.add_(1.0)
         assert _close(torch, other(x), _two_kernels(torch, other, x))
+
+
+def test_kept_copy_on_other_streams():
+    """A second stream waits for the packing, and memory of a copy that is replaced is not handed out while another
+    stream still reads it."""
+    import torch
+
+    layer, x = _layer(torch, 768, 384, 8), _rows(torch, 300, 768)
+    side = torch.cuda.Stream()
+    with torch.no_grad():
+        want = layer(x)
+        layer.drop_packed_weights()
+        junk = [torch.full_like(t, 77) for t in layer._inference_weights().tensors()]   # what freed memory holds
+        layer.drop_packed_weights()
+        del junk
+        torch.cuda.synchronize()
+        torch.cuda._sleep(20_000_000)
+        first = layer(x)                                  # packs, behind the wait
+        with torch.cuda.stream(side):
+            second = layer(x)
+        torch.cuda.synchronize()
+        assert torch.equal(first, want) and torch.equal(second, want)
+
+        sizes = [(t.shape, t.dtype) for t in layer._packed.tensors()]
+        with torch.cuda.stream(side):
+            torch.cuda._sleep(20_000_000)
+            old = layer(x)
+        layer.linear.weight.mul_(0.5)
+        layer(x)                                          # replaces the copy
+        junk = [torch.full(s, 77, dtype=d, device="cuda:0") for s, d in sizes * 2]
+        torch.cuda.synchronize()
+        assert torch.equal(old, want) and junk
