@@ -344,6 +344,9 @@ class GRKANLinear(nn.Module):
         """Packed weights (the kernel then fetches them in whole cache lines), the bias and the coefficient rows in
         float32, kept until a parameter is written to or replaced."""
         params = self._inference_params()
+        if torch.cuda.is_current_stream_capturing():
+            # part of the graph, so that a replay follows the parameters and its memory is the graph's own
+            return _Packed(self.rational, params)
         stream = torch.cuda.current_stream(params[0].device)
         packed = self._packed
         if packed is None or not packed.is_of(params):

@@ -290,3 +290,31 @@ def test_kept_copy_on_other_streams():
         junk = [torch.full(s, 77, dtype=d, device="cuda:0") for s, d in sizes * 2]
         torch.cuda.synchronize()
         assert torch.equal(old, want) and junk
+
+
+def test_captured_call_follows_the_parameters():
+    """A graph captured with the kept copy in place packs for itself: replays see writes to the parameters, and
+    nothing that is kept lives in the graph's memory."""
+    import torch
+
+    for fresh in (False, True):
+        layer, x = _layer(torch, 768, 384, 8), _rows(torch, 300, 768)
+        with torch.no_grad():
+            layer(x)
+            torch.cuda.synchronize()
+            if fresh:
+                layer.drop_packed_weights()
+            kept = layer._packed
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph):
+                out = layer(x)
+            assert layer._packed is kept
+            for step in range(4):
+                layer.linear.weight.mul_(0.7)
+                layer.rational.denominator.add_(0.01)
+                x.copy_(_rows(torch, 300, 768, seed=9 + step))
+                want = layer(x)
+                torch.cuda.synchronize()
+                graph.replay()
+                torch.cuda.synchronize()
+                assert torch.equal(out, want)
