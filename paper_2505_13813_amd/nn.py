@@ -313,8 +313,9 @@ class GRKANLinear(nn.Module):
         (one_kernel_is_faster); "always" = wherever it applies; "never".
 
         At the sizes of fused_layer_pays it runs on a packed copy of the weights (with bias and coefficients
-        in float32) that is kept until a parameter is written to or replaced.  Writes through `.data` or a
-        detached alias leave no trace that this could be told from: after one, call drop_packed_weights().
+        in float32) that is kept until a parameter is written to or replaced, the module is moved, converted or
+        switched between training and evaluation, or a state is loaded.  Writes through `.data` or a detached alias
+        leave no trace that this could be told from: after one, call drop_packed_weights() (or train() / eval()).
         At all other sizes it reads the parameters themselves and keeps nothing."""
         super().__init__()
         if in_features % groups:
@@ -335,6 +336,22 @@ class GRKANLinear(nn.Module):
 
     def drop_packed_weights(self):
         """Forgets the packed copy of the weights; the next call that needs one makes it anew."""
+        self._packed = None
+
+    def train(self, mode: bool = True):
+        self.drop_packed_weights()
+        return super().train(mode)
+
+    def _apply(self, *args, **kwargs):
+        self.drop_packed_weights()
+        return super()._apply(*args, **kwargs)
+
+    def _load_from_state_dict(self, *args, **kwargs):
+        self.drop_packed_weights()
+        return super()._load_from_state_dict(*args, **kwargs)
+
+    def __setstate__(self, state):
+        super().__setstate__(state)
         self._packed = None
 
     def _inference_params(self):

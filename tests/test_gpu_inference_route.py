@@ -318,3 +318,38 @@ def test_captured_call_follows_the_parameters():
                 graph.replay()
                 torch.cuda.synchronize()
                 assert torch.equal(out, want)
+
+
+def test_copied_saved_and_moved_modules():
+    import copy
+    import io
+
+    import torch
+
+    layer, x = _layer(torch, 256, 64, 8), _rows(torch, 160, 256)
+    with torch.no_grad():
+        want = layer(x)
+        other = copy.deepcopy(layer)
+        assert other._packed is None and torch.equal(other(x), want)
+        buffer = io.BytesIO()
+        torch.save(layer, buffer)
+        buffer.seek(0)
+        other = torch.load(buffer, weights_only=False)
+        assert other._packed is None and torch.equal(other(x), want)
+        for p in layer.parameters():
+            p.data.mul_(0.5)
+        half = layer.eval()(x)
+        assert not torch.equal(half, want)
+        layer.load_state_dict(other.state_dict(), assign=True)
+        assert torch.equal(layer(x), want)
+        layer.cpu()
+        layer.linear.weight.data.mul_(2.0)
+        layer.linear.bias.data.zero_()
+        layer.to("cuda:0")
+        assert torch.equal(layer(x), _layer_like(torch, layer)(x))
+
+
+def _layer_like(torch, layer):
+    other = _layer(torch, layer.linear.in_features, layer.linear.out_features, layer.rational.groups)
+    other.load_state_dict(layer.state_dict())
+    return other
