@@ -87,7 +87,8 @@ def fused_layer_supported(x, A, weight) -> bool:
 def fused_layer_pays(rows: int, D_in: int, D_out: int) -> bool:
     """The sizes at which a GRKANLinear runs the one-kernel layer on a packed copy of its weights that it keeps between
     calls: the layer's 112-row tiles (of 768, 384 or 192 channels) fill the chip, or the contraction is short.  (At
-    other sizes the module takes the layer on its parameters as they are, where one_kernel_is_faster says so.)"""
+    other sizes the module in evaluation mode takes the layer on its parameters as they are, where
+    one_kernel_is_faster says so.)"""
     bn = 768 if D_out % 768 == 0 else (384 if D_out % 384 == 0 else 192)
     workgroups = -(-int(rows) // 112) * -(-int(D_out) // bn)
     return workgroups >= 200 or D_in <= 768
@@ -316,7 +317,7 @@ class GRKANLinear(nn.Module):
         in float32) that is kept until a parameter is written to or replaced, the module is moved, converted or
         switched between training and evaluation, or a state is loaded.  Writes through `.data` or a detached alias
         leave no trace that this could be told from: after one, call drop_packed_weights() (or train() / eval()).
-        At all other sizes it reads the parameters themselves and keeps nothing."""
+        At all other sizes, in evaluation mode, it reads the parameters themselves and keeps nothing."""
         super().__init__()
         if in_features % groups:
             raise ValueError("in_features must be a multiple of groups")
@@ -409,7 +410,9 @@ class GRKANLinear(nn.Module):
             if compiling:
                 return binding.grkan_linear_fwd(x.contiguous(), A32, B32, pw, b32, out_dtype=x.dtype)
             return binding.load_native().layer_packed(x, A32, B32, pw.data, pw.D_out, b32)
-        if compiling:
+        # In training mode a pass without a gradient may be the first half of one with (reentrant checkpointing): both
+        # take the same kernels.
+        if compiling or (self.training and not always):
             return None
         return binding.load_native().layer_model(x, self.rational.numerator, self.rational.denominator, weight,
                                                  self.linear.bias)

@@ -353,3 +353,25 @@ def _layer_like(torch, layer):
     other = _layer(torch, layer.linear.in_features, layer.linear.out_features, layer.rational.groups)
     other.load_state_dict(layer.state_dict())
     return other
+
+
+def test_checkpointed_block_recomputes_what_it_returned():
+    """Reentrant checkpointing runs a training block without a gradient first and again with one: the same kernels
+    both times, and nothing packed."""
+    import torch
+
+    from paper_2505_13813_amd import nn as gnn
+
+    torch.manual_seed(5)
+    block = gnn.KATMlp(768).to("cuda:0").to(torch.bfloat16)
+    for layer in (block.fc1, block.fc2):
+        _stir(torch, layer)
+    x = _rows(torch, 197, 768).requires_grad_()
+    plain = block(x)
+    got = torch.utils.checkpoint.checkpoint(block, x, use_reentrant=True)
+    assert torch.equal(got, plain)
+    dy = torch.randn_like(plain)
+    (want,) = torch.autograd.grad(plain, [x], dy)
+    got.backward(dy)
+    assert torch.equal(x.grad, want)
+    assert block.fc1._packed is None and block.fc2._packed is None
