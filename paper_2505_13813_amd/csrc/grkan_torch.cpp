@@ -6,6 +6,7 @@
 // Every entry returns "not taken" (an empty optional) for anything but plain dense tensors on the current
 // GPU outside of tracing, function transforms, forward-mode differentiation and dispatch modes; the caller
 // then takes the Python route, which handles or refuses the call as it always did.
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/custom_function.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/csrc/jit/frontend/tracer.h>
@@ -60,9 +61,17 @@ std::optional<grkan_dtype_t> io_of(const Tensor &t)
     }
 }
 
+// A status of the library as the exception the Python functions raise for it.
 void check(grkan_status_t st, const char *where)
 {
-    TORCH_CHECK(st == GRKAN_OK, where, ": ", grkan_status_string(st), " (status ", (int)st, ")");
+    if (st == GRKAN_OK)
+        return;
+    pybind11::gil_scoped_acquire gil;
+    const pybind11::object type = pybind11::module_::import("paper_2505_13813_amd.binding").attr("GrkanError");
+    PyErr_SetObject(type.ptr(), type((int)st, where).ptr());
+    python_error error;
+    error.persist(); // (in the backward pass it crosses threads)
+    throw error;
 }
 
 // A workspace from torch's allocator (its streams and lifetimes), handed out during one call of the C ABI.

@@ -1,0 +1,85 @@
+"""GPU tests of where the C++ autograd route meets Python: exceptions keep their types, saved-tensor hooks and
+checkpointing see what they saw before, and what is not a plain tensor stays with the Python functions."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _unit(torch, dtype, D=96, G=4):
+    from paper_2505_13813_amd import nn as gnn
+
+    torch.manual_seed(0)
+    unit = gnn.GroupRational(G, "swish").to("cuda:0").to(dtype)
+    return unit, torch.randn(600, D, device="cuda:0").to(dtype).requires_grad_()
+
+
+def _layer(torch):
+    from paper_2505_13813_amd import nn as gnn
+
+    torch.manual_seed(1)
+    layer = gnn.GRKANLinear(192, 392, 2, init="swish").to("cuda:0").to(torch.bfloat16)
+    return layer, torch.randn(3, 200, 192, device="cuda:0").to(torch.bfloat16).requires_grad_()
+
+
+@pytest.mark.parametrize("early_stop", [True, False])
+def test_checkpointing_with_saved_tensor_hooks(early_stop):
+    """Non-reentrant checkpointing ends its recomputation with an exception of its own out of a saved-tensor hook,
+    which has to come back as it is."""
+    import torch
+    from torch.utils.checkpoint import checkpoint, set_checkpoint_early_stop
+
+    for part, x in (_unit(torch, torch.float32), _unit(torch, torch.bfloat16), _layer(torch)):
+        leaves = [x] + list(part.parameters())
+        want_y = part(x)
+        dy = torch.randn_like(want_y)
+        want = torch.autograd.grad(want_y, leaves, dy)
+        with set_checkpoint_early_stop(early_stop):
+            y = checkpoint(part, x, use_reentrant=False)
+        got = torch.autograd.grad(y, leaves, dy)
+        assert torch.equal(y, want_y) and all(torch.equal(g, w) for g, w in zip(got, want))
+
+
+def test_exceptions_keep_their_types():
+    import torch
+
+    import paper_2505_13813_amd as grkan
+    from paper_2505_13813_amd import binding
+
+    class Refused(Exception):
+        pass
+
+    def refuse(t):
+        raise Refused("no")
+
+    for part, x in (_unit(torch, torch.float32), _layer(torch)):
+        with pytest.raises(Refused), torch.autograd.graph.saved_tensors_hooks(refuse, lambda t: t):
+            part(x)
+        with torch.autograd.graph.saved_tensors_hooks(lambda t: t, refuse):
+            y = part(x)
+        with pytest.raises(Refused):
+            y.sum().backward()
+
+    unit, _ = _unit(torch, torch.float32, 3072, 8)
+    big = torch.zeros(1 << 15, 3072, device="cuda:0")
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (64 << 20)) / total)
+    try:
+        with pytest.raises(torch.OutOfMemoryError):
+            unit(big)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+
+
+def test_a_status_of_the_library_is_a_grkan_error():
+    import torch
+
+    import paper_2505_13813_amd as grkan
+    from paper_2505_13813_amd import binding
+
+    x = torch.zeros(16, 64, device="cuda:0", dtype=torch.bfloat16)
+    A, B = torch.zeros(2, 6, device="cuda:0"), torch.zeros(2, 4, device="cuda:0")
+    pw = grkan.grkan_linear_pack_w(torch.zeros(64, 64, device="cuda:0", dtype=torch.bfloat16))
+    with torch.no_grad(), pytest.raises(grkan.GrkanError) as e:
+        binding.load_native().layer_packed(x, A, B, pw.data, 62, None)   # not a multiple of 4: refused on the host
+    assert e.value.status == 8
