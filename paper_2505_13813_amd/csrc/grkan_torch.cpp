@@ -3,9 +3,9 @@
 // the Python functions; what goes is the host time around it (argument marshalling, and small kernels that
 // expand, convert and sum the coefficients of a model).
 //
-// Every entry returns "not taken" (an empty optional) for anything but plain dense tensors on the current
-// GPU outside of tracing, function transforms, forward-mode differentiation and dispatch modes; the caller
-// then takes the Python route, which handles or refuses the call as it always did.
+// Every entry returns "not taken" (an empty optional) for anything but plain dense tensors (no subclass) on the
+// current GPU outside of tracing, function transforms, forward-mode differentiation, dispatch modes and function
+// modes; the caller then takes the Python route, which handles or refuses the call as it always did.
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/custom_function.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -13,12 +13,14 @@
 #include <torch/csrc/utils/pybind.h>
 
 #include <ATen/ATen.h>
+#include <ATen/PythonTorchFunctionTLS.h>
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
 
 #include <exception>
+#include <initializer_list>
 #include <optional>
 
 #include "../../include/grkan.h"
@@ -276,12 +278,70 @@ std::optional<Tensor> layer_model(const Tensor &x_in, const Tensor &A, const Ten
     return out;
 }
 
+// No function mode, or device contexts alone (torch.set_default_device: they act on factory functions only).
+bool no_function_mode()
+{
+    if (!at::impl::torch_function_mode_enabled())
+        return true;
+    const pybind11::object device_context = pybind11::module_::import("torch.utils._device").attr("DeviceContext");
+    for (const pybind11::handle mode : pybind11::module_::import("torch.overrides").attr("_get_current_function_mode_stack")())
+        if (reinterpret_cast<PyObject *>(Py_TYPE(mode.ptr())) != device_context.ptr())
+            return false;
+    return true;
+}
+
+// The arguments of an entry as tensors; `taken` is false if one is a tensor subclass (or no tensor at all), or if a
+// function mode would see the calls of the Python route.
+struct Arguments {
+    bool taken = no_function_mode();
+
+    Tensor tensor(pybind11::handle h)
+    {
+        if (!taken || !THPVariable_CheckExact(h.ptr())) {
+            taken = false;
+            return Tensor();
+        }
+        return THPVariable_Unpack(h.ptr());
+    }
+    std::optional<Tensor> optional(pybind11::handle h)
+    {
+        return h.is_none() ? std::nullopt : std::optional<Tensor>(tensor(h));
+    }
+    template <typename Entry> std::optional<Tensor> call(Entry &&entry) const
+    {
+        if (!taken)
+            return std::nullopt;
+        pybind11::gil_scoped_release no_gil;
+        return entry();
+    }
+};
+
 } // namespace
 
 PYBIND11_MODULE(_native, mod)
 {
-    mod.def("rational", &rational, pybind11::call_guard<pybind11::gil_scoped_release>());
-    mod.def("product", &product, pybind11::call_guard<pybind11::gil_scoped_release>());
-    mod.def("layer_model", &layer_model, pybind11::call_guard<pybind11::gil_scoped_release>());
-    mod.def("layer_packed", &layer_packed, pybind11::call_guard<pybind11::gil_scoped_release>());
+    using pybind11::handle;
+    mod.def("rational", [](handle x_, handle A_, handle B_) {
+        Arguments args;
+        const Tensor x = args.tensor(x_), A = args.tensor(A_), B = args.tensor(B_);
+        return args.call([&] { return rational(x, A, B); });
+    });
+    mod.def("product", [](handle y_, handle W_, handle bias_) {
+        Arguments args;
+        const Tensor y = args.tensor(y_), W = args.tensor(W_);
+        const std::optional<Tensor> bias = args.optional(bias_);
+        return args.call([&] { return product(y, W, bias); });
+    });
+    mod.def("layer_model", [](handle x_, handle A_, handle B_, handle W_, handle bias_) {
+        Arguments args;
+        const Tensor x = args.tensor(x_), A = args.tensor(A_), B = args.tensor(B_), W = args.tensor(W_);
+        const std::optional<Tensor> bias = args.optional(bias_);
+        return args.call([&] { return layer_model(x, A, B, W, bias); });
+    });
+    mod.def("layer_packed", [](handle x_, handle A_, handle B_, handle Wp_, int64_t D_out, handle bias_) {
+        Arguments args;
+        const Tensor x = args.tensor(x_), A = args.tensor(A_), B = args.tensor(B_), Wp = args.tensor(Wp_);
+        const std::optional<Tensor> bias = args.optional(bias_);
+        return args.call([&] { return layer_packed(x, A, B, Wp, D_out, bias); });
+    });
 }

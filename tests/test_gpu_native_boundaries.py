@@ -83,3 +83,43 @@ def test_a_status_of_the_library_is_a_grkan_error():
     with torch.no_grad(), pytest.raises(grkan.GrkanError) as e:
         binding.load_native().layer_packed(x, A, B, pw.data, 62, None)   # not a multiple of 4: refused on the host
     assert e.value.status == 8
+
+
+def test_subclasses_and_function_modes_stay_with_the_python_functions():
+    """A tensor subclass comes back as one, a function mode sees the linear layer's call; a default device (which is
+    a function mode too) changes nothing."""
+    import torch
+    from torch.overrides import TorchFunctionMode
+
+    from paper_2505_13813_amd import nn as gnn
+
+    class Tagged(torch.Tensor):
+        pass
+
+    class Log(TorchFunctionMode):
+        def __init__(self):
+            super().__init__()
+            self.seen = []
+
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            self.seen.append(getattr(func, "__name__", str(func)))
+            return func(*args, **(kwargs or {}))
+
+    for dtype in (torch.float32, torch.bfloat16):
+        unit, x = _unit(torch, dtype)
+        tagged = x.detach().as_subclass(Tagged)
+        A, B = (t.detach().float().contiguous() for t in unit.coefficient_rows())
+        assert type(unit(tagged)) is Tagged and type(gnn.group_rational(tagged, A, B)) is Tagged
+        assert torch.equal(unit(tagged), unit(x))
+    layer, x = _layer(torch)
+    want = layer(x)
+    assert "Product" in want.grad_fn.name()
+    with Log() as log:
+        got = layer(x)
+    assert "linear" in log.seen and torch.equal(got, want)
+    layer.eval()
+    with torch.no_grad(), Log() as log:
+        got = layer(x)
+    assert "linear" in log.seen and torch.equal(got, want)
+    with torch.device("cuda:0"):
+        assert "Product" in layer(x).grad_fn.name()
