@@ -112,6 +112,21 @@ Sizes sizes_of(const Tensor &x, const Tensor &A, const Tensor &B)
     return Sizes{x.numel() / D, (int32_t)D, (int32_t)B.size(0), (int32_t)A.size(-1) - 1, (int32_t)B.size(1), A.dim() == 1};
 }
 
+// The operands of a backward pass as they come back from saved-tensor hooks, which may return anything: what the
+// Python function checks in front of the kernels.
+void check_saved(const Tensor &x, const Tensor &dy, const Tensor &A, const Tensor &B)
+{
+    TORCH_CHECK_VALUE(x.is_cuda() && A.device() == x.device() && B.device() == x.device(),
+                      "grkan runs on the GPU only: tensors must be on one HIP device");
+    TORCH_CHECK_VALUE(x.is_contiguous() && A.is_contiguous() && B.is_contiguous(), "tensors must be contiguous");
+    TORCH_CHECK_TYPE(A.scalar_type() == B.scalar_type() &&
+                         (A.scalar_type() == at::kFloat || (A.scalar_type() == at::kBFloat16 && x.scalar_type() == at::kBFloat16)),
+                     "A and B must be float32");
+    TORCH_CHECK_VALUE(B.dim() == 2 && (A.dim() == 1 || (A.dim() == 2 && A.size(0) == B.size(0))), "A must be [G, m+1] and B [G, n]");
+    TORCH_CHECK_VALUE(dy.sizes() == x.sizes() && dy.scalar_type() == x.scalar_type() && dy.device() == x.device(),
+                      "dy must match x");
+}
+
 // y = F(x); A [G, m+1] or, shared by the groups, [m+1].
 struct Rational : public torch::autograd::Function<Rational> {
     static Tensor forward(AutogradContext *ctx, const Tensor &x_in, const Tensor &A_in, const Tensor &B_in)
@@ -134,8 +149,7 @@ struct Rational : public torch::autograd::Function<Rational> {
             return {Tensor(), Tensor(), Tensor()};
         at::AutoGradMode no_grad(false);
         const Tensor dy = grads[0].contiguous();
-        TORCH_CHECK_VALUE(dy.sizes() == x.sizes() && dy.scalar_type() == x.scalar_type() && dy.device() == x.device(),
-                          "dy must match x");
+        check_saved(x, dy, A, B);
         const Sizes s = sizes_of(x, A, B);
         Tensor dx = at::empty_like(x), dA = at::empty_like(A), dB = at::empty_like(B);
         Scratch scratch{x.options().dtype(at::kByte), Tensor(), nullptr};
@@ -166,25 +180,28 @@ struct Product : public torch::autograd::Function<Product> {
             return {Tensor(), Tensor(), Tensor()};
         const bool want_y = ctx->needs_input_grad(0), want_w = ctx->needs_input_grad(1);
         const bool want_b = ctx->saved_data["has_bias"].toBool() && ctx->needs_input_grad(2);
-        const int64_t D_in = W.size(1), D_out = W.size(0);
+        const int64_t D_in = y.size(-1), D_out = dout.size(-1);
         Tensor dout2 = dout.reshape({-1, D_out}), y2 = y.reshape({-1, D_in});
         Tensor dy, dW, db;
         if (want_y)
             dy = dout2.mm(W).view(y.sizes());
-        // with a graph of the backward pass wanted, operations that torch can differentiate
-        if (want_w && !at::GradMode::is_enabled() && plain(dout2, y.device()) && dout2.scalar_type() == at::kBFloat16) {
+        // With a graph of the backward pass wanted, operations that torch can differentiate; and what a saved-tensor
+        // hook made of y is left to torch if it is not what was saved.
+        if (want_w && !at::GradMode::is_enabled() && dout2.is_cuda() && plain(dout2, dout2.device()) &&
+            plain(y2, dout2.device()) && dout2.scalar_type() == at::kBFloat16 && y2.scalar_type() == at::kBFloat16 &&
+            y2.size(0) == dout2.size(0)) {
             dout2 = dout2.contiguous();
             y2 = y2.contiguous();
             const size_t need = grkan_linear_wgrad_workspace_bytes(dout2.size(0), (int32_t)D_in, (int32_t)D_out);
             if (need > 0 && reinterpret_cast<uintptr_t>(dout2.data_ptr()) % 16 == 0 &&
                 reinterpret_cast<uintptr_t>(y2.data_ptr()) % 16 == 0) {
-                const Tensor ws = at::empty({(int64_t)need}, y.options().dtype(at::kByte));
-                dW = at::empty({D_out, D_in}, W.options());
+                const Tensor ws = at::empty({(int64_t)need}, dout2.options().dtype(at::kByte));
+                dW = at::empty({D_out, D_in}, dout2.options());
                 if (want_b)
-                    db = at::empty({D_out}, W.options());
+                    db = at::empty({D_out}, dout2.options());
                 check(grkan_linear_wgrad(dout2.data_ptr(), y2.data_ptr(), dW.data_ptr(), want_b ? db.data_ptr() : nullptr,
                                          ws.data_ptr(), need, dout2.size(0), (int32_t)D_in, (int32_t)D_out, GRKAN_BF16,
-                                         stream_of(y)),
+                                         stream_of(dout2)),
                       "grkan_linear_wgrad");
             }
         }

@@ -123,3 +123,41 @@ def test_subclasses_and_function_modes_stay_with_the_python_functions():
     assert "linear" in log.seen and torch.equal(got, want)
     with torch.device("cuda:0"):
         assert "Product" in layer(x).grad_fn.name()
+
+
+def test_what_saved_tensor_hooks_return_is_checked():
+    """The backward pass reads what the caller's hooks give back by address: tensors of another layout, type, size or
+    device are refused as the Python function refuses them (the product's are left to torch)."""
+    import torch
+
+    from paper_2505_13813_amd import binding
+    from paper_2505_13813_amd import nn as gnn
+
+    strided = lambda t: t.new_empty(*t.shape, 2)[..., 0].copy_(t)
+    for change in (strided, lambda t: t.cpu(), lambda t: t.half(), lambda t: t[:1], lambda t: t.flatten(), lambda t: t[0]):
+        x, A, B = (torch.randn(*s, device="cuda:0", requires_grad=True) for s in ((64, 96), (4, 6), (4, 4)))
+        for which in range(3):
+            def unpack(packed):
+                i, t = packed
+                return change(t) if i == which else t
+
+            for route in (gnn.group_rational, gnn.GroupRationalFunction.apply):
+                order = iter(range(3))
+                with torch.autograd.graph.saved_tensors_hooks(lambda t: (next(order), t), unpack):
+                    y = route(x, A, B)
+                with pytest.raises((ValueError, TypeError, RuntimeError)):
+                    y.sum().backward()
+
+    y = torch.randn(600, 96, device="cuda:0").to(torch.bfloat16).requires_grad_()
+    W = torch.randn(64, 96, device="cuda:0").to(torch.bfloat16).requires_grad_()
+    dout = torch.randn(600, 64, device="cuda:0").to(torch.bfloat16)
+    want = torch.autograd.grad(torch.nn.functional.linear(y, W), [W], dout)[0]
+    for change in (lambda t: t, strided, lambda t: t.cpu(), lambda t: t.float(), lambda t: t[:8]):
+        with torch.autograd.graph.saved_tensors_hooks(lambda t: t, lambda t: change(t) if t.shape == y.shape else t):
+            out = binding.load_native().product(y, W, None)
+        if change(y).shape == y.shape and change(y).is_cuda and change(y).dtype == y.dtype:
+            (got,) = torch.autograd.grad(out, [W], dout)
+            assert float((got.float() - want.float()).norm()) <= 2.0 ** -7 * float(want.float().norm())
+        else:
+            with pytest.raises(RuntimeError):
+                torch.autograd.grad(out, [W], dout)
