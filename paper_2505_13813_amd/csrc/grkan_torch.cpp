@@ -162,11 +162,12 @@ struct Rational : public torch::autograd::Function<Rational> {
     }
 };
 
-// out = y W^T + bias with dW and dbias from grkan_linear_wgrad; saves what torch's linear saves.
+// out = y W^T + bias with dW and dbias from grkan_linear_wgrad; saves what torch's linear saves: each operand where
+// the gradient of the other is wanted.
 struct Product : public torch::autograd::Function<Product> {
     static Tensor forward(AutogradContext *ctx, const Tensor &y, const Tensor &W, const std::optional<Tensor> &bias)
     {
-        ctx->save_for_backward({y, W});
+        ctx->save_for_backward({W.requires_grad() ? y : Tensor(), y.requires_grad() ? W : Tensor()});
         ctx->saved_data["has_bias"] = bias.has_value();
         return at::linear(y, W, bias);
     }
@@ -180,11 +181,15 @@ struct Product : public torch::autograd::Function<Product> {
             return {Tensor(), Tensor(), Tensor()};
         const bool want_y = ctx->needs_input_grad(0), want_w = ctx->needs_input_grad(1);
         const bool want_b = ctx->saved_data["has_bias"].toBool() && ctx->needs_input_grad(2);
-        const int64_t D_in = y.size(-1), D_out = dout.size(-1);
-        Tensor dout2 = dout.reshape({-1, D_out}), y2 = y.reshape({-1, D_in});
-        Tensor dy, dW, db;
-        if (want_y)
-            dy = dout2.mm(W).view(y.sizes());
+        const int64_t D_out = dout.size(-1);
+        Tensor dout2 = dout.reshape({-1, D_out}), y2, dy, dW, db;
+        if (want_y) {
+            auto shape = dout.sizes().vec();
+            shape.back() = W.size(1);
+            dy = dout2.mm(W).view(shape);
+        }
+        if (want_w)
+            y2 = y.reshape({-1, y.size(-1)});
         // With a graph of the backward pass wanted, operations that torch can differentiate; and what a saved-tensor
         // hook made of y is left to torch if it is not what was saved.
         if (want_w && !at::GradMode::is_enabled() && dout2.is_cuda() && plain(dout2, dout2.device()) &&
@@ -192,6 +197,7 @@ struct Product : public torch::autograd::Function<Product> {
             y2.size(0) == dout2.size(0)) {
             dout2 = dout2.contiguous();
             y2 = y2.contiguous();
+            const int64_t D_in = y2.size(1);
             const size_t need = grkan_linear_wgrad_workspace_bytes(dout2.size(0), (int32_t)D_in, (int32_t)D_out);
             if (need > 0 && reinterpret_cast<uintptr_t>(dout2.data_ptr()) % 16 == 0 &&
                 reinterpret_cast<uintptr_t>(y2.data_ptr()) % 16 == 0) {

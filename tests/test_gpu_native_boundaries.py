@@ -161,3 +161,32 @@ def test_what_saved_tensor_hooks_return_is_checked():
         else:
             with pytest.raises(RuntimeError):
                 torch.autograd.grad(out, [W], dout)
+
+
+def test_the_product_saves_what_torchs_linear_saves():
+    """A weight whose input takes no gradient may be written to between the passes (an optimizer step in between two
+    backward passes); an expanded upstream gradient (a sum's) and each subset of wanted gradients."""
+    import torch
+
+    from paper_2505_13813_amd import binding
+
+    y = torch.randn(4, 150, 96, device="cuda:0").to(torch.bfloat16)
+    W = torch.randn(64, 96, device="cuda:0").to(torch.bfloat16).requires_grad_()
+    b = torch.randn(64, device="cuda:0").to(torch.bfloat16).requires_grad_()
+    near = lambda g, w: float((g.float() - w.float()).norm()) <= 2.0 ** -7 * float(w.float().norm())
+    out = binding.load_native().product(y, W, b)
+    want = torch.autograd.grad(torch.nn.functional.linear(y, W, b).sum(), [W, b])
+    with torch.no_grad():
+        W.add_(1.0)
+    got = torch.autograd.grad(out.sum(), [W, b])
+    assert all(near(g, w) for g, w in zip(got, want))
+
+    leaves = [y.clone().requires_grad_(), W, b]
+    for chosen in ([0], [1], [2], [0, 2], [0, 1, 2]):
+        inputs = [leaves[i] for i in chosen]
+        got = torch.autograd.grad(binding.load_native().product(*leaves).sum(), inputs)
+        want = torch.autograd.grad(torch.nn.functional.linear(*leaves).sum(), inputs)
+        assert all(g.shape == w.shape and near(g, w) for g, w in zip(got, want))
+    out = binding.load_native().product(leaves[0], W.detach(), None)
+    assert near(torch.autograd.grad(out.sum(), [leaves[0]])[0], torch.autograd.grad(
+        torch.nn.functional.linear(leaves[0], W.detach()).sum(), [leaves[0]])[0])
