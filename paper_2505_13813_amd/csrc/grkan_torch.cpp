@@ -22,6 +22,7 @@
 #include <exception>
 #include <initializer_list>
 #include <optional>
+#include <tuple>
 
 #include "../../include/grkan.h"
 
@@ -127,6 +128,20 @@ void check_saved(const Tensor &x, const Tensor &dy, const Tensor &A, const Tenso
                       "dy must match x");
 }
 
+// Gradients of a backward pass that was asked for a graph of itself and has none: differentiating them with respect to
+// what they depend on is an error instead of leaving it out.
+struct Undifferentiable : public torch::autograd::Function<Undifferentiable> {
+    static variable_list forward(AutogradContext *, const Tensor &dx, const Tensor &dA, const Tensor &dB, const Tensor &,
+                                 const Tensor &, const Tensor &, const Tensor &)
+    {
+        return {dx.view_as(dx), dA.view_as(dA), dB.view_as(dB)};
+    }
+    static variable_list backward(AutogradContext *, const variable_list &)
+    {
+        TORCH_CHECK(false, "the group-wise rational function is not differentiable twice");
+    }
+};
+
 // y = F(x); A [G, m+1] or, shared by the groups, [m+1].
 struct Rational : public torch::autograd::Function<Rational> {
     static Tensor forward(AutogradContext *ctx, const Tensor &x_in, const Tensor &A_in, const Tensor &B_in)
@@ -147,8 +162,17 @@ struct Rational : public torch::autograd::Function<Rational> {
         const Tensor &x = saved[0], &A = saved[1], &B = saved[2];
         if (!grads[0].defined())
             return {Tensor(), Tensor(), Tensor()};
-        at::AutoGradMode no_grad(false);
-        const Tensor dy = grads[0].contiguous();
+        const bool graph_wanted = at::GradMode::is_enabled();
+        Tensor dx, dA, dB;
+        {
+            at::AutoGradMode no_grad(false);
+            std::tie(dx, dA, dB) = gradients(x, grads[0].contiguous(), A, B);
+        }
+        return graph_wanted ? Undifferentiable::apply(dx, dA, dB, x, A, B, grads[0]) : variable_list{dx, dA, dB};
+    }
+
+    static std::tuple<Tensor, Tensor, Tensor> gradients(const Tensor &x, const Tensor &dy, const Tensor &A, const Tensor &B)
+    {
         check_saved(x, dy, A, B);
         const Sizes s = sizes_of(x, A, B);
         Tensor dx = at::empty_like(x), dA = at::empty_like(A), dB = at::empty_like(B);

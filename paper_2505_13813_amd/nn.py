@@ -56,6 +56,27 @@ def _workspace(x, rows: int, D: int, G: int) -> torch.Tensor:
     return ws
 
 
+class _Undifferentiable(torch.autograd.Function):
+    """Gradients of a backward pass that was asked for a graph of itself and has none: differentiating them with
+    respect to what they depend on is an error instead of leaving it out."""
+
+    @staticmethod
+    def forward(ctx, dx, dA, dB, x, A, B, dy):
+        return dx.view_as(dx), dA.view_as(dA), dB.view_as(dB)
+
+    @staticmethod
+    def backward(ctx, *_):
+        raise RuntimeError("the group-wise rational function is not differentiable twice")
+
+
+def _rational_gradients(x, dy, A, B):
+    """(dx, dA, dB) of F in a backward pass."""
+    D = int(x.shape[-1])
+    ws = _workspace(x, int(x.numel() // D) if D else 0, D, int(A.shape[0]))
+    grads = binding.grkan_bwd(x, dy.contiguous(), A, B, workspace=ws)
+    return _Undifferentiable.apply(*grads, x, A, B, dy) if torch.is_grad_enabled() else grads
+
+
 class GroupRationalFunction(torch.autograd.Function):
     """y = F(x) group-wise; backward through grkan_bwd (nothing but x, A, B is saved)."""
 
@@ -70,10 +91,7 @@ class GroupRationalFunction(torch.autograd.Function):
     @staticmethod
     def backward(ctx, dy):
         x, A, B = ctx.saved_tensors
-        D = int(x.shape[-1])
-        ws = _workspace(x, int(x.numel() // D) if D else 0, D, int(A.shape[0]))
-        dx, dA, dB = binding.grkan_bwd(x, dy.contiguous(), A, B, workspace=ws)
-        return dx, dA, dB
+        return _rational_gradients(x, dy, A, B)
 
 
 def fused_layer_supported(x, A, weight) -> bool:
@@ -128,12 +146,11 @@ class GRKANLayerFunction(torch.autograd.Function):
         x, A, B, weight = ctx.saved_tensors
         D_in, D_out = int(x.shape[-1]), int(weight.shape[0])
         dout2 = dout.contiguous().view(-1, D_out)
-        y = binding.grkan_fwd(x, A, B).view(-1, D_in)      # F(x), recomputed
+        # F(x), recomputed (with a graph of its own where one of this pass is wanted)
+        y = (GroupRationalFunction.apply if torch.is_grad_enabled() else binding.grkan_fwd)(x, A, B).view(-1, D_in)
         dW = dout2.t().mm(y)
         dF = dout2.mm(weight).view(x.shape)
-        rows = int(x.numel() // D_in) if D_in else 0
-        ws = _workspace(x, rows, D_in, int(A.shape[0]))
-        dx, dA, dB = binding.grkan_bwd(x, dF, A, B, workspace=ws)
+        dx, dA, dB = _rational_gradients(x, dF, A, B)
         dbias = dout2.sum(0).to(ctx.bias_dtype) if ctx.has_bias else None
         return dx, dA, dB, dW, dbias
 

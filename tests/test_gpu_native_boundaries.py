@@ -190,3 +190,38 @@ def test_the_product_saves_what_torchs_linear_saves():
     out = binding.load_native().product(leaves[0], W.detach(), None)
     assert near(torch.autograd.grad(out.sum(), [leaves[0]])[0], torch.autograd.grad(
         torch.nn.functional.linear(leaves[0], W.detach()).sum(), [leaves[0]])[0])
+
+
+def test_a_second_derivative_is_refused():
+    """create_graph=True gives the first derivatives; differentiating them raises instead of leaving out their
+    dependence on x and the coefficients (a gradient penalty through a layer, say)."""
+    import torch
+
+    from paper_2505_13813_amd import nn as gnn
+
+    x, A, B = (torch.randn(*s, device="cuda:0", requires_grad=True) for s in ((64, 96), (4, 6), (4, 4)))
+    dy = torch.randn(64, 96, device="cuda:0", requires_grad=True)
+    for route in (gnn.group_rational, gnn.GroupRationalFunction.apply):
+        first = torch.autograd.grad(route(x, A, B), [x, A, B], dy)
+        again = torch.autograd.grad(route(x, A, B), [x, A, B], dy, create_graph=True)
+        assert all(torch.equal(f, g) and not f.requires_grad for f, g in zip(first, again))
+        for g in again:
+            with pytest.raises(RuntimeError, match="not differentiable twice"):
+                torch.autograd.grad(g.sum(), [x, dy], allow_unused=True, retain_graph=True)
+
+    for fused in ("inference", "always"):
+        layer, x = _layer(torch)
+        layer.fused = fused
+        out = layer(x)
+        (dx,) = torch.autograd.grad(out.float().square().sum(), [x], create_graph=True)
+        with pytest.raises(RuntimeError, match="not differentiable twice"):
+            (out.float().sum() + dx.float().square().sum()).backward()
+        # the weight's gradient is differentiable: out = F(x) W^T, dW = up^T F(x)
+        up = torch.randn_like(out).requires_grad_()
+        (dW,) = torch.autograd.grad(layer(x), [layer.linear.weight], up, create_graph=True)
+        du, dx = torch.autograd.grad(dW.float().sum(), [up, x])
+        f = layer.rational(x)
+        want_u = f.float().sum(-1, keepdim=True).expand_as(up)
+        (want_x,) = torch.autograd.grad(f, [x], up.detach().float().sum(-1, keepdim=True).expand_as(f).to(f.dtype))
+        for got, want in ((du, want_u), (dx, want_x)):
+            assert float((got.float() - want.float()).norm()) <= 2e-2 * float(want.float().norm())
