@@ -1075,10 +1075,9 @@ struct SmallVariant {
     int bn() const { return 16 * nt * wn; }
 };
 
-// One round of up to 256 workgroups (one per compute unit) takes a time that depends on the tile and D_in
-// only, and the time of a layer is that times the rounds, to within 15 % over 1 .. 12,608 rows of 3072 -> 768,
-// 1536 -> 384, 768 -> 192 and 768 -> 3072 (measured on MI355X, us per round at D_in = 768 / 1536 / 3072, the
-// chip filled):
+// A round of workgroups (one per compute unit) takes a time that depends on the tile and D_in only, and the time of a
+// layer is that times the rounds: to within 25 % at all, and 15 % at nine in ten, of 266 sizes of nineteen layer shapes
+// and 1 .. 25,216 rows (measured on MI355X, us per round at D_in = 768 / 1536 / 3072, the chip filled):
 //   16 x 64: 6.6 / 7.8 / 11.7    32 x 128: 8.5 / 12.2 / 20.5    64 x 192: 13.2 / 21 / 36
 //   64 x 384: 15.8 / 24.5 / 45   112 x 768: 41 / - / 133   112 x 384: - / 43 / -   112 x 192: 24 / - / -
 static const SmallVariant kSmall[] = {
@@ -1087,12 +1086,18 @@ static const SmallVariant kSmall[] = {
     {8, 4, 3, 4, 5.7, 10.1},
     {16, 4, 3, 8, 6.0, 12.7},
 };
-constexpr int kRound = 256;
+// Whether the tiles of one channel block share an XCD (else: those of one token block); the small tiles only.
+static bool is_n_major(int64_t rows, int32_t D_out) { return rows < D_out; }
 
-static double rounds_us(int64_t rows, int32_t D_in, int32_t D_out, int bm, int bn, double fixed_us, double us_per_1k)
+// The blocks of one side are dealt out to the 8 XCDs of 32 compute units, each with all tiles of the other side, and the
+// XCD that gets the most sets the rounds: 85 x 3 tiles fit 256 units, but five XCDs get 11 x 3 of them (9,456 rows of
+// 1152 -> 1152 in tiles of 112 x 384: 70 us, 44 in tiles of 64 x 384).
+static double rounds_us(int64_t rows, int32_t D_in, int32_t D_out, int bm, int bn, bool n_major, double fixed_us,
+                        double us_per_1k)
 {
-    const int64_t wgs = ((rows + bm - 1) / bm) * (((int64_t)D_out + bn - 1) / bn);
-    return (double)((wgs + kRound - 1) / kRound) * (fixed_us + us_per_1k * D_in / 1024.0);
+    const int64_t mb = (rows + bm - 1) / bm, nb = ((int64_t)D_out + bn - 1) / bn;
+    const int64_t per_xcd = n_major ? (nb + 7) / 8 * mb : (mb + 7) / 8 * nb;
+    return (double)((per_xcd + 31) / 32) * (fixed_us + us_per_1k * D_in / 1024.0);
 }
 
 // The tile for a layer: the one with the least estimated time.  A layer of few rows takes many small tiles
@@ -1101,11 +1106,11 @@ static double rounds_us(int64_t rows, int32_t D_in, int32_t D_out, int bm, int b
 static const SmallVariant *pick_small(int64_t rows, int32_t D_in, int32_t D_out, double *estimate_us)
 {
     const Variant v = pick_variant(D_out);
-    double best = v.nt == 6 ? rounds_us(rows, D_in, D_out, kBM, v.bn(), 10.5, 40.0)
-                            : rounds_us(rows, D_in, D_out, kBM, v.bn(), 5.0, 24.0);
+    double best = v.nt == 6 ? rounds_us(rows, D_in, D_out, kBM, v.bn(), false, 10.5, 40.0)
+                            : rounds_us(rows, D_in, D_out, kBM, v.bn(), false, 5.0, 24.0);
     const SmallVariant *pick = nullptr;
     for (const SmallVariant &s : kSmall) {
-        const double t = rounds_us(rows, D_in, D_out, s.bm(), s.bn(), s.fixed_us, s.us_per_1k);
+        const double t = rounds_us(rows, D_in, D_out, s.bm(), s.bn(), is_n_major(rows, D_out), s.fixed_us, s.us_per_1k);
         if (t < best) {
             best = t;
             pick = &s;
@@ -1278,7 +1283,7 @@ static grkan_status_t linear_fwd_impl(const void *x, const void *A, const void *
     const int64_t mblocks = (rows + bm - 1) / bm;
     const int64_t nblocks = (D_out + bn - 1) / bn;
     // small kernel: the tiles that share the larger operand's slice on one XCD
-    a.n_major = small && rows < D_out;
+    a.n_major = small && is_n_major(rows, D_out);
     const int64_t grid = a.n_major ? ((nblocks + 7) / 8) * 8 * mblocks : ((mblocks + 7) / 8) * 8 * nblocks;
     if (mblocks > INT32_MAX / 2 || grid > INT32_MAX)
         return GRKAN_ERR_UNSUPPORTED;

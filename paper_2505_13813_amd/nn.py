@@ -114,13 +114,19 @@ def fused_layer_pays(rows: int, D_in: int, D_out: int) -> bool:
 
 @lru_cache(maxsize=1024)
 def one_kernel_is_faster(rows: int, D_in: int, D_out: int) -> bool:
-    """Whether the one-kernel layer is the faster route in inference (measured on MI355X, bfloat16, 50 - 25,216
-    rows of ten layer shapes).  The two kernels take about 11 us + the elementwise pass at 5.5 TB/s + the
-    library product at 950 TFLOP/s, and 50 us of host time, so that one launch of up to 25 us is faster
-    whatever the device times are (3072 -> 768: 197 rows 21.6 us against 54 us of wall time, 6,304 rows 56
-    against 59, 12,608 rows 107 against 96, 25,216 rows 133 against 197)."""
-    two_us = 11.0 + rows * D_in * 4 / 5.5e6 + 2.0 * rows * D_in * D_out / 0.95e9
-    return binding.grkan_linear_estimate_us(rows, D_in, D_out) <= max(25.0, two_us)
+    """Whether the one-kernel layer is the faster route in inference, by its own estimate and one of the two kernels:
+    the elementwise pass at 5.5 TB/s and the library product in whole rounds of 256 x 256 or 128 x 128 tiles, and no
+    less than the 27 us of host time that two launches take.  (Measured on MI355X, bfloat16, at 266 sizes: nineteen
+    layer shapes, 1 - 25,216 rows.  Nowhere was the route that this takes more than 4 % slower than the two kernels;
+    at fifteen sizes it passes by a gain of 5 % or more, most of them where the library's own choice of tile is a poor
+    one.  3072 -> 768: 197 rows 12.4 us against 27.7, 1,576 35.7 against 28.1, 6,304 47 against 51, 25,216 128 against
+    195; 768 -> 3072: 1,576 rows 19 against 28, 6,304 44 against 56, 12,608 85 against 71.)"""
+    def product_us(tile, us_per_1k):
+        rounds = -(-(-(-rows // tile) * -(-D_out // tile)) // 256)
+        return rounds * (6.0 + us_per_1k * D_in / 1024)
+
+    two_us = rows * D_in * 4 / 5.5e6 + min(product_us(256, 24.0), product_us(128, 4.0))
+    return binding.grkan_linear_estimate_us(rows, D_in, D_out) <= max(27.0, two_us)
 
 
 class GRKANLayerFunction(torch.autograd.Function):

@@ -87,3 +87,19 @@ def test_fused_layer_size_rule():
     assert not fused_layer_pays(6304, 1536, 384)
     assert fused_layer_pays(197, 768, 192)             # short contraction: one launch instead of two
     assert fused_layer_pays(6000, 3072, 3072)          # many channel blocks make up for few tokens
+
+
+def test_one_kernel_rule():
+    """Sizes at which both routes were measured: one kernel / two kernels in us."""
+    from paper_2505_13813_amd.nn import one_kernel_is_faster
+
+    for rows, D_in, D_out in ((1, 3072, 768), (197, 3072, 768), (6304, 3072, 768), (25216, 3072, 768), (1576, 768, 3072),
+                              (6304, 768, 3072), (3152, 1536, 384), (25216, 1536, 384)):
+        assert one_kernel_is_faster(rows, D_in, D_out)
+    for rows, D_in, D_out in ((1576, 3072, 768),       # 35.7 / 28.1
+                              (9456, 3072, 768),       # 93 / 70
+                              (12608, 768, 3072),      # 85 / 71
+                              (25216, 768, 3072),      # 165 / 140
+                              (25216, 4096, 1024),     # 306 / 236
+                              (9456, 1152, 1152)):     # 44 / 40: 85 x 3 tiles of 112 x 384 are more than one round of the XCDs
+        assert not one_kernel_is_faster(rows, D_in, D_out)
