@@ -162,11 +162,16 @@ class GRKANLayerFunction(torch.autograd.Function):
 
 
 def wgrad_pays(rows: int, D_in: int, D_out: int) -> bool:
-    """Whether grkan_linear_wgrad is the faster route for the gradients of a bfloat16 product (measured on
-    MI355X against the library's product and column sum): it was at every size tried from 640 rows up
-    (25,216 rows: 384 x 1536 50 us against 184, 768 x 3072 143 against 308; 1,000 rows of 384 x 1536 20 against
-    23) as long as its 192 x 192 tiles fit the chip's 256 compute units once."""
-    return rows >= 512 and D_in % 8 == 0 and D_out % 8 == 0 and -(-D_in // 192) * -(-D_out // 192) <= 256
+    """Whether grkan_linear_wgrad is the faster route for the gradients of a bfloat16 product, measured on MI355X
+    against the library's product and column sum at thirty-one shapes of 1 - 256 tiles (192 x 192, one per compute
+    unit at a time) and 512 - 25,216 rows.  Up to 128 tiles, where each unit gets a range of rows of at least one: faster
+    everywhere (25,216 rows: 384 x 1536 45 us against 171, 768 x 3072 125 against 270, 2048 x 2048 224 against 369;
+    640 rows: 16 against 28, 26 against 28, 26.7 against 27.9; 512 rows: the same, but 27 against 26 from 96 tiles on).
+    From 129 tiles on the rows are not split: with 132 - 210 tiles the units that get none make it lose at some row
+    counts (25,216 rows of 1024 x 4096: 413 against 340), with 225 - 256 it is faster again (443 against 562)."""
+    tiles = -(-D_in // 192) * -(-D_out // 192)
+    return (D_in % 8 == 0 and D_out % 8 == 0 and rows >= (512 if tiles <= 64 else 640)
+            and (tiles <= 128 or 224 <= tiles <= 256))
 
 
 def _native_product(linear, y):

@@ -103,3 +103,14 @@ def test_one_kernel_rule():
                               (25216, 4096, 1024),     # 306 / 236
                               (9456, 1152, 1152)):     # 44 / 40: 85 x 3 tiles of 112 x 384 are more than one round of the XCDs
         assert not one_kernel_is_faster(rows, D_in, D_out)
+
+
+def test_weight_gradient_rule():
+    from paper_2505_13813_amd.nn import wgrad_pays
+
+    assert wgrad_pays(512, 192, 768) and wgrad_pays(512, 768, 3072) and wgrad_pays(640, 2048, 2048)
+    assert wgrad_pays(25216, 384, 1536) and wgrad_pays(25216, 2880, 2880) and wgrad_pays(25216, 3072, 3072)
+    assert not wgrad_pays(511, 192, 768) and not wgrad_pays(512, 1152, 3072)     # 27.3 us against 26.2
+    assert not wgrad_pays(25216, 1024, 4096)                                     # 132 tiles: 413 us against 340
+    assert not wgrad_pays(12608, 2688, 2880)                                     # 210 tiles: 218 us against 213
+    assert not wgrad_pays(25216, 3136, 3072) and not wgrad_pays(25216, 384, 1532)
