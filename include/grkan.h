@@ -259,6 +259,12 @@ grkan_status_t grkan_linear_fwd(const void *x, const float *A, const float *B, c
 double grkan_linear_estimate_us(int64_t rows, int32_t D_in, int32_t D_out);
 
 /*
+ * Host-only: the tile grkan_linear_fwd runs these sizes in, rows x channels.  GRKAN_ERR_SHAPE for sizes that are not
+ * positive.
+ */
+grkan_status_t grkan_linear_tile(int64_t rows, int32_t D_in, int32_t D_out, int32_t *tile_rows, int32_t *tile_channels);
+
+/*
  * The same layer on the parameters as a bfloat16 model keeps them, for callers that keep no converted or packed copy
  * of them between calls: x, A, B, W, bias (or NULL) and out all bfloat16; shared_numerator as for grkan_fwd_model.
  * The results are those of grkan_linear_fwd on float32 copies of A, B and bias, bit for bit.

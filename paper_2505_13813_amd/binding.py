@@ -97,6 +97,8 @@ def load_library():
     lib.grkan_linear_wgrad_workspace_bytes.restype = sz
     lib.grkan_linear_estimate_us.argtypes = [i64, i32, i32]
     lib.grkan_linear_estimate_us.restype = ctypes.c_double
+    lib.grkan_linear_tile.argtypes = [i64, i32, i32, ctypes.POINTER(i32), ctypes.POINTER(i32)]
+    lib.grkan_linear_tile.restype = ctypes.c_int
     lib.grkan_linear_packed_w_bytes.argtypes = [i32, i32]
     lib.grkan_linear_packed_w_bytes.restype = ctypes.c_size_t
     lib.grkan_linear_pack_w.argtypes = [vp, vp, i32, i32, vp]
@@ -363,6 +365,15 @@ def grkan_linear_fwd(x, A, B, W, bias=None, out=None, out_dtype=None, stream=Non
 def grkan_linear_estimate_us(rows: int, D_in: int, D_out: int) -> float:
     """Estimated device time of grkan_linear_fwd in microseconds (host only)."""
     return float(load_library().grkan_linear_estimate_us(int(rows), int(D_in), int(D_out)))
+
+
+def grkan_linear_tile(rows: int, D_in: int, D_out: int) -> Tuple[int, int]:
+    """(rows, channels) of the tile that grkan_linear_fwd runs these sizes in (host only)."""
+    bm, bn = ctypes.c_int32(), ctypes.c_int32()
+    st = load_library().grkan_linear_tile(int(rows), int(D_in), int(D_out), ctypes.byref(bm), ctypes.byref(bn))
+    if st:
+        raise GrkanError(st, "grkan_linear_tile")
+    return bm.value, bn.value
 
 
 def grkan_linear_wgrad(dout, y, bias: bool = True, stream=None):

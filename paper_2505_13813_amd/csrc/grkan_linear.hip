@@ -1337,6 +1337,19 @@ extern "C" double grkan_linear_estimate_us(int64_t rows, int32_t D_in, int32_t D
     return us;
 }
 
+extern "C" grkan_status_t grkan_linear_tile(int64_t rows, int32_t D_in, int32_t D_out, int32_t *tile_rows,
+                                            int32_t *tile_channels)
+{
+    if (!tile_rows || !tile_channels)
+        return GRKAN_ERR_NULL;
+    if (rows <= 0 || D_in <= 0 || D_out <= 0)
+        return GRKAN_ERR_SHAPE;
+    const SmallVariant *const small = pick_small(rows, D_in, D_out, nullptr);
+    *tile_rows = small ? small->bm() : kBM;
+    *tile_channels = small ? small->bn() : pick_variant(D_out).bn();
+    return GRKAN_OK;
+}
+
 extern "C" size_t grkan_linear_packed_w_bytes(int32_t D_in, int32_t D_out)
 {
     if (D_in <= 0 || D_out <= 0 || D_in % 64 != 0 || D_out % 4 != 0 || (int64_t)D_in * 2 * 768 >= ((int64_t)1 << 32))

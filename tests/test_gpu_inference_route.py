@@ -4,9 +4,10 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
-# rows, D_in, D_out, G of layers that read their parameters as they are: every tile, one row, ragged rows
-LAYERS = [(1, 3072, 768, 8), (197, 3072, 768, 8), (1001, 1536, 388, 8), (3107, 1088, 1152, 2), (6304, 832, 768, 2),
-          (20011, 832, 768, 2), (25000, 896, 384, 4), (28000, 832, 188, 1)]
+# rows, D_in, D_out, G of layers that read their parameters as they are, in every tile; one row, ragged rows
+LAYERS = [(1, 3072, 768, 8, (16, 64)), (197, 3072, 768, 8, (16, 64)), (1001, 1536, 388, 8, (32, 128)),
+          (3107, 1088, 572, 2, (64, 192)), (6304, 832, 768, 2, (64, 384)), (20011, 832, 768, 2, (112, 768)),
+          (25000, 896, 384, 4, (112, 384)), (28000, 832, 188, 1, (112, 192))]
 
 
 def _layer(torch, D_in, D_out, G, seed=0, bias=True, shared=True):
@@ -42,8 +43,8 @@ def _close(torch, got, want):
 
 
 @pytest.mark.parametrize("bias,shared", [(True, True), (False, False)])
-@pytest.mark.parametrize("rows,D_in,D_out,G", LAYERS)
-def test_layer_on_the_models_own_parameters(rows, D_in, D_out, G, bias, shared):
+@pytest.mark.parametrize("rows,D_in,D_out,G,tile", LAYERS)
+def test_layer_on_the_models_own_parameters(rows, D_in, D_out, G, tile, bias, shared):
     """bfloat16 coefficients and bias read by the kernel against the same kernel on their float32 copies (the same
     bits) and against the two-kernel route."""
     import torch
@@ -52,6 +53,7 @@ def test_layer_on_the_models_own_parameters(rows, D_in, D_out, G, bias, shared):
     from paper_2505_13813_amd import binding
     from paper_2505_13813_amd import nn as gnn
 
+    assert binding.grkan_linear_tile(rows, D_in, D_out) == tile
     layer, x = _layer(torch, D_in, D_out, G, bias=bias, shared=shared), _rows(torch, rows, D_in)
     A, B = (t.detach().float().contiguous() for t in layer.rational.coefficient_rows())
     b32 = layer.linear.bias.detach().float() if bias else None

@@ -295,27 +295,32 @@ def test_packed_weights_full_size_bit_identical():
 
 
 SMALL_TILES = [
-    # rows, D_in, D_out, G      the tile the sizes select, and the edge they sit on
-    (1, 64, 4, 2),              # 16 x 64: one row, one block of the contraction for eight groups of wavefronts
-    (17, 576, 68, 18),          # 16 x 64: nine blocks for eight groups, d_g = 32, one row and one quad past a tile
-    (33, 704, 60, 1),           # 16 x 64: eleven blocks, a partial channel tile
-    (1001, 192, 388, 6),        # 32 x 128: three blocks for four groups, ragged rows and channels
-    (1500, 640, 384, 10),       # 32 x 128: ten blocks, d_g = 64
-    (3107, 128, 388, 4),        # 64 x 192: one block per group of wavefronts, ragged rows and channels
-    (3100, 320, 572, 10),       # 64 x 192: five blocks for two groups, d_g = 32
-    (6307, 128, 764, 4),        # 64 x 384: ragged rows and channels
-    (6240, 448, 768, 7),        # 64 x 384: seven blocks, whole channel tiles
+    # rows, D_in, D_out, G, tile        the edge they sit on
+    (1, 64, 4, 2, (32, 128)),         # one row, one block of the contraction for four groups of wavefronts
+    (17, 192, 68, 6, (16, 64)),       # three blocks for eight groups, d_g = 32, one row and one quad past a tile
+    (47, 448, 188, 7, (16, 64)),      # seven blocks for eight groups, ragged rows and channels
+    (17, 576, 68, 18, (16, 64)),      # nine blocks for eight groups, d_g = 32, one row and one quad past a tile
+    (33, 704, 60, 1, (16, 64)),       # eleven blocks, a partial channel tile
+    (1001, 192, 388, 6, (32, 128)),   # three blocks for four groups, ragged rows and channels
+    (1500, 640, 384, 10, (32, 128)),  # ten blocks, d_g = 64
+    (3107, 64, 388, 2, (64, 192)),    # one block for two groups of wavefronts, ragged rows and channels
+    (3107, 128, 388, 4, (64, 192)),   # one block per group
+    (3100, 320, 572, 10, (64, 192)),  # five blocks for two groups, d_g = 32
+    (6307, 64, 768, 2, (64, 384)),    # one block for two groups, ragged rows
+    (6307, 128, 764, 4, (64, 384)),   # one block per group
+    (6240, 448, 768, 7, (64, 384)),   # seven blocks, whole channel tiles
 ]
 
 
-@pytest.mark.parametrize("rows,D_in,D_out,G", SMALL_TILES)
-def test_fused_layer_small_tiles(oracle, rows, D_in, D_out, G):
+@pytest.mark.parametrize("rows,D_in,D_out,G,tile", SMALL_TILES)
+def test_fused_layer_small_tiles(oracle, rows, D_in, D_out, G, tile):
     """Inputs of few rows run in smaller tiles: every output against the oracle, and the packed weights
     bit for bit against the plain ones."""
     import torch
 
     import paper_2505_13813_amd as grkan
 
+    assert grkan.binding.grkan_linear_tile(rows, D_in, D_out) == tile
     case = custom_linear_case(rows * 3 + D_in + D_out + G, rows, D_in, D_out, G, bias=bool(rows % 2))
     check(oracle, case, "f32" if rows % 2 else "bf16", "small tile %dx%d -> %d G=%d" % (rows, D_in, D_out, G),
           threads=8, full=rows > 200)

@@ -105,6 +105,21 @@ def test_one_kernel_rule():
         assert not one_kernel_is_faster(rows, D_in, D_out)
 
 
+def test_tile_query():
+    """Tiles by size, without a GPU; the sizes that the tests of the small tiles rely on among them."""
+    from test_gpu_linear import SMALL_TILES
+
+    from paper_2505_13813_amd import binding
+
+    for rows, D_in, D_out, _, tile in SMALL_TILES:
+        assert binding.grkan_linear_tile(rows, D_in, D_out) == tile
+    assert binding.grkan_linear_tile(25216, 3072, 768) == (112, 768)
+    assert binding.grkan_linear_tile(25216, 1536, 384) == (112, 384)
+    assert binding.grkan_linear_tile(25216, 768, 192) == (112, 192)
+    with pytest.raises(binding.GrkanError):
+        binding.grkan_linear_tile(0, 768, 192)
+
+
 def test_weight_gradient_rule():
     from paper_2505_13813_amd.nn import wgrad_pays
 
