@@ -86,10 +86,7 @@ __device__ __forceinline__ uint64_t uniform_u64(uint64_t v)
 // formed by a vector instruction need up to five wait states.
 __device__ __forceinline__ void load_to_lds(uint64_t base, uint32_t lane_off, uint32_t lds_at)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :
-                 : "s"(lds_at), "v"(lane_off), "s"(base)
-                 : "memory", "m0");
+    asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %1, %2" : : "{m0}"(lds_at), "v"(lane_off), "s"(base) : "memory");
 }
 
 __device__ __forceinline__ s16x4 read_transposed(uint32_t addr)
