@@ -201,9 +201,10 @@ __global__ __launch_bounds__(512, 1) void grkan_linear_wgrad_kernel(const Args a
         fetch(1);
     for (int32_t t = 0; t < mine; ++t) {
         // this wavefront's part of stage t has landed (the loads of stage t + 1 may be in flight; the stage
-        // before the last waits for everything, because the last may have gone through registers)
+        // before the last waits for everything, because the last may have gone through registers), and so have its
+        // reads of the buffer that is refilled next, wherever the compiler put the instructions that use them
         if (t + 2 < mine)
-            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * kLoads) : "memory");
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * kLoads) : "memory");
         else
             asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
         if (t + 2 < mine)
