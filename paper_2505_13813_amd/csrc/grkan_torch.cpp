@@ -272,10 +272,19 @@ std::optional<Tensor> product(const Tensor &y, const Tensor &W, const std::optio
     return Product::apply(y, W, bias);
 }
 
-// The one-kernel layer on packed weights (inference): all operands as the module keeps them.
+// The one-kernel layer on packed weights (inference): all operands as the module keeps them.  `made_on`: the stream
+// (its address) the kept copies were made on, -1 for copies that this call may read wherever it runs; on another stream,
+// and under capture, the caller has something to do first and the call is not taken.
 std::optional<Tensor> layer_packed(const Tensor &x_in, const Tensor &A, const Tensor &B, const Tensor &Wp, int64_t D_out,
-                                   const std::optional<Tensor> &bias)
+                                   const std::optional<Tensor> &bias, int64_t made_on)
 {
+    if (made_on != -1 && on_current_gpu(x_in)) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        void *const stream = stream_of(x_in);
+        if (reinterpret_cast<int64_t>(stream) != made_on ||
+            hipStreamIsCapturing(static_cast<hipStream_t>(stream), &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)
+            return std::nullopt;
+    }
     if (!plain_context() || !on_current_gpu(x_in) || !plain(x_in, x_in.device()) || x_in.scalar_type() != at::kBFloat16 ||
         x_in.numel() == 0 || !plain(A, x_in.device()) || !plain(B, x_in.device()) || !plain(Wp, x_in.device()) ||
         (bias && !plain(*bias, x_in.device())))
@@ -385,10 +394,11 @@ PYBIND11_MODULE(_native, mod)
         const std::optional<Tensor> bias = args.optional(bias_);
         return args.call([&] { return layer_model(x, A, B, W, bias); });
     });
-    mod.def("layer_packed", [](handle x_, handle A_, handle B_, handle Wp_, int64_t D_out, handle bias_) {
+    mod.def("layer_packed", [](handle x_, handle A_, handle B_, handle Wp_, int64_t D_out, handle bias_,
+                                int64_t made_on) {
         Arguments args;
         const Tensor x = args.tensor(x_), A = args.tensor(A_), B = args.tensor(B_), Wp = args.tensor(Wp_);
         const std::optional<Tensor> bias = args.optional(bias_);
-        return args.call([&] { return layer_packed(x, A, B, Wp, D_out, bias); });
+        return args.call([&] { return layer_packed(x, A, B, Wp, D_out, bias, made_on); });
     });
 }

@@ -33,6 +33,7 @@ from typing import Tuple
 import numpy as np
 import torch
 from torch import nn
+from torch.nn.modules import module as every_module
 
 from . import binding
 
@@ -97,9 +98,14 @@ class GroupRationalFunction(torch.autograd.Function):
 def fused_layer_supported(x, A, weight) -> bool:
     """Shapes and types the one-kernel layer (grkan_linear_fwd) covers: bfloat16 x and W on the GPU,
     degrees (5, 4), D_in a multiple of 64, d_g a multiple of 32, D_out a multiple of 4."""
-    D_in, G = int(x.shape[-1]), int(A.shape[0])
-    return (x.is_cuda and x.dtype == torch.bfloat16 and weight.dtype == torch.bfloat16 and int(A.shape[1]) == 6
-            and D_in % 64 == 0 and D_in % G == 0 and (D_in // G) % 32 == 0 and int(weight.shape[0]) % 4 == 0)
+    return _fused_shapes(x, int(A.shape[0]), int(A.shape[1]), weight)
+
+
+def _fused_shapes(x, G: int, numerator_columns: int, weight) -> bool:
+    D_in = x.shape[-1]
+    return (D_in % 64 == 0 and D_in % G == 0 and (D_in // G) % 32 == 0 and weight.shape[0] % 4 == 0
+            and numerator_columns == M_DEGREE + 1 and x.is_cuda and x.dtype == torch.bfloat16
+            and weight.dtype == torch.bfloat16)
 
 
 def fused_layer_pays(rows: int, D_in: int, D_out: int) -> bool:
@@ -192,11 +198,11 @@ def _native_product(linear, y):
 def _only_a(cls, module) -> bool:
     """Whether calling `module` runs cls.forward and nothing else, so that a route past the call changes nothing: no
     subclass (an adapter, a parametrisation), no forward of its own, no hooks on it or on every module."""
-    m = nn.modules.module
     return (type(module) is cls and "forward" not in module.__dict__
             and not (module._forward_hooks or module._forward_pre_hooks or module._backward_hooks
-                     or module._backward_pre_hooks or m._global_forward_hooks or m._global_forward_pre_hooks
-                     or m._global_backward_hooks or m._global_backward_pre_hooks))
+                     or module._backward_pre_hooks or every_module._global_forward_hooks
+                     or every_module._global_forward_pre_hooks or every_module._global_backward_hooks
+                     or every_module._global_backward_pre_hooks))
 
 
 def _autocast_elsewhere() -> bool:
@@ -297,8 +303,11 @@ class GroupRational(nn.Module):
 
 
 class _Packed(tuple):
-    """(PackedWeight, bias, A rows, B rows) of one state of a layer's parameters, with the event after which other
-    streams than the one it was made on may read it.  Not part of a copied or saved module."""
+    """(PackedWeight, bias, A rows, B rows) of one state of a layer's parameters, with the stream it was made on and the
+    event after which others may read it (made_on = -1: made during a capture, for the call that made it).  Not part of a
+    copied or saved module."""
+
+    made_on, stream, made = -1, None, None
 
     def __new__(cls, rational, params):
         w, b = (None if p is None else p.detach() for p in params[:2])
@@ -308,17 +317,17 @@ class _Packed(tuple):
             w = w.clone()
         self = super().__new__(cls, (binding.grkan_linear_pack_w(w), None if b is None else b.to(torch.float32).contiguous(),
                                      A.detach().to(torch.float32).contiguous(), B.detach().to(torch.float32).contiguous()))
-        self._params = tuple(None if p is None else weakref.ref(p) for p in params)
-        self._key = cls._key_of(params)
+        self._made_of = tuple((None, 0, 0) if p is None else (weakref.ref(p), p.data_ptr(), p._version) for p in params)
         return self
 
-    @staticmethod
-    def _key_of(params):
-        return tuple(None if p is None else (p.data_ptr(), p._version, p.device) for p in params)
-
     def is_of(self, params) -> bool:
-        return self._key == self._key_of(params) and all(r is p if p is None else r is not None and r() is p
-                                                         for r, p in zip(self._params, params))
+        for p, (ref, address, version) in zip(params, self._made_of):
+            if p is None or ref is None:
+                if p is not None or ref is not None:
+                    return False
+            elif ref() is not p or p.data_ptr() != address or p._version != version:
+                return False
+        return True
 
     def tensors(self):
         return [t for t in (self[0].data, *self[1:]) if t is not None]
@@ -383,23 +392,40 @@ class GRKANLinear(nn.Module):
         super().__setstate__(state)
         self._packed = None
 
-    def _inference_params(self):
-        return self.linear.weight, self.linear.bias, self.rational.numerator, self.rational.denominator
-
-    def _inference_weights(self):
+    def _inference_weights(self, params):
         """Packed weights (the kernel then fetches them in whole cache lines), the bias and the coefficient rows in
-        float32, kept until a parameter is written to or replaced."""
-        params = self._inference_params()
+        float32, kept until a parameter is written to or replaced; None where no copy can be kept: a tensor put in a
+        parameter's place for one call may sit where the last one did, and inference tensors have no version."""
+        packed = self._packed
+        if packed is not None and packed.is_of(params):
+            return packed
+        if not all(type(p) is nn.Parameter and not p.is_inference() for p in params if p is not None):
+            return None
+        packed = _Packed(self.rational, params)
+        if not torch.cuda.is_current_stream_capturing():
+            packed.stream = torch.cuda.current_stream(params[0].device)
+            packed.made = packed.stream.record_event()
+            packed.made_on = packed.stream.cuda_stream
+            self._packed = packed
+        return packed
+
+    def _packed_layer(self, x, packed, params):
+        """The layer on the packed weights; None where the native entry does not take the call."""
+        entry = binding.load_native().layer_packed
+        pw, b32, A32, B32 = packed
+        out = entry(x, A32, B32, pw.data, pw.D_out, b32, packed.made_on)
+        if out is None and packed.made_on != -1:
+            pw, b32, A32, B32 = self._readable_here(packed, params)
+            out = entry(x, A32, B32, pw.data, pw.D_out, b32, -1)
+        return out
+
+    def _readable_here(self, packed, params):
+        """The kept copy ordered behind its packing on whatever stream this is; under capture one that is part of the
+        graph, so that a replay follows the parameters and its memory is the graph's own."""
         if torch.cuda.is_current_stream_capturing():
-            # part of the graph, so that a replay follows the parameters and its memory is the graph's own
             return _Packed(self.rational, params)
         stream = torch.cuda.current_stream(params[0].device)
-        packed = self._packed
-        if packed is None or not packed.is_of(params):
-            packed = _Packed(self.rational, params)
-            packed.stream, packed.made = stream, stream.record_event()
-            self._packed = packed
-        elif packed.stream != stream:
+        if stream != packed.stream:
             stream.wait_event(packed.made)
             for t in packed.tensors():
                 t.record_stream(stream)
@@ -416,34 +442,42 @@ class GRKANLinear(nn.Module):
     def _one_kernel(self, x):
         """The layer's output from the one kernel, or None where that route is not taken.  (What the native entries
         do not take - alignment, forward-mode differentiation, function transforms - is left to the two kernels.)"""
-        grad, always = torch.is_grad_enabled(), self.fused == "always"
-        if (self.fused == "never" or (grad and not always) or not _only_a(nn.Linear, self.linear)
-                or not _only_a(GroupRational, self.rational) or _autocast_elsewhere()):
+        fused, grad = self.fused, torch.is_grad_enabled()
+        always = fused == "always"
+        if fused == "never" or (grad and not always) or x.dtype is not torch.bfloat16:
             return None
-        A, B = self.rational.coefficient_rows()
-        weight = self.linear.weight
-        if not fused_layer_supported(x, A, weight) or x.shape[-1] != weight.shape[1]:
+        linear, rational = self._modules.get("linear"), self._modules.get("rational")
+        if not _only_a(nn.Linear, linear) or not _only_a(GroupRational, rational) or _autocast_elsewhere():
+            return None
+        weight, bias = linear._parameters.get("weight"), linear._parameters.get("bias")
+        numerator, denominator = rational._parameters.get("numerator"), rational._parameters.get("denominator")
+        if weight is None or numerator is None or denominator is None:
+            return None
+        if not x.dim() or not x.shape[-1]:
+            return None
+        D_in, D_out = x.shape[-1], weight.shape[0]
+        if not _fused_shapes(x, denominator.shape[0], numerator.shape[-1], weight) or D_in != weight.shape[1]:
             return None
         if grad:
-            return GRKANLayerFunction.apply(x, A.to(torch.float32), B.to(torch.float32), weight, self.linear.bias)
-        rows, D_in, D_out = x.numel() // x.shape[-1], x.shape[-1], weight.shape[0]
+            A, B = rational.coefficient_rows()
+            return GRKANLayerFunction.apply(x, A.to(torch.float32), B.to(torch.float32), weight, bias)
+        rows = x.numel() // D_in
         if not always and not one_kernel_is_faster(rows, D_in, D_out):
             return None
         compiling = torch.compiler.is_compiling()
-        # (a tensor put in a parameter's place for one call may sit where the last one did; inference tensors have no
-        # version)
-        if (self._keep_packed and (always or fused_layer_pays(rows, D_in, D_out))
-                and all(type(p) is nn.Parameter and not p.is_inference() for p in self._inference_params() if p is not None)):
-            pw, b32, A32, B32 = self._inference_weights()
-            if compiling:
-                return binding.grkan_linear_fwd(x.contiguous(), A32, B32, pw, b32, out_dtype=x.dtype)
-            return binding.load_native().layer_packed(x, A32, B32, pw.data, pw.D_out, b32)
+        if self._keep_packed and (always or fused_layer_pays(rows, D_in, D_out)):
+            params = (weight, bias, numerator, denominator)
+            packed = self._inference_weights(params)
+            if packed is not None:
+                if compiling:
+                    pw, b32, A32, B32 = packed if packed.made_on == -1 else self._readable_here(packed, params)
+                    return binding.grkan_linear_fwd(x.contiguous(), A32, B32, pw, b32, out_dtype=x.dtype)
+                return self._packed_layer(x, packed, params)
         # In training mode a pass without a gradient may be the first half of one with (reentrant checkpointing): both
         # take the same kernels.
         if compiling or (self.training and not always):
             return None
-        return binding.load_native().layer_model(x, self.rational.numerator, self.rational.denominator, weight,
-                                                 self.linear.bias)
+        return binding.load_native().layer_model(x, numerator, denominator, weight, bias)
 
 
 class KATMlp(nn.Module):

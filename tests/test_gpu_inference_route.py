@@ -272,7 +272,8 @@ def test_kept_copy_on_other_streams():
     with torch.no_grad():
         want = layer(x)
         layer.drop_packed_weights()
-        junk = [torch.full_like(t, 77) for t in layer._inference_weights().tensors()]   # what freed memory holds
+        layer(x)
+        junk = [torch.full_like(t, 77) for t in layer._packed.tensors()]   # what freed memory holds
         layer.drop_packed_weights()
         del junk
         torch.cuda.synchronize()

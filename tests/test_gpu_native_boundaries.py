@@ -81,7 +81,7 @@ def test_a_status_of_the_library_is_a_grkan_error():
     A, B = torch.zeros(2, 6, device="cuda:0"), torch.zeros(2, 4, device="cuda:0")
     pw = grkan.grkan_linear_pack_w(torch.zeros(64, 64, device="cuda:0", dtype=torch.bfloat16))
     with torch.no_grad(), pytest.raises(grkan.GrkanError) as e:
-        binding.load_native().layer_packed(x, A, B, pw.data, 62, None)   # not a multiple of 4: refused on the host
+        binding.load_native().layer_packed(x, A, B, pw.data, 62, None, -1)   # not a multiple of 4: refused on the host
     assert e.value.status == 8
 
 
