@@ -225,3 +225,61 @@ def test_a_second_derivative_is_refused():
         (want_x,) = torch.autograd.grad(f, [x], up.detach().float().sum(-1, keepdim=True).expand_as(f).to(f.dtype))
         for got, want in ((du, want_u), (dx, want_x)):
             assert float((got.float() - want.float()).norm()) <= 2e-2 * float(want.float().norm())
+
+
+def _step(torch, block, x, dy):
+    y = block(x)
+    return (y.detach(),) + torch.autograd.grad(y, [x] + list(block.parameters()), dy)
+
+
+def test_streams_threads_and_capture():
+    """A training step of the block on a stream of its own behind work that makes its input, in two threads at once,
+    and captured in a graph: the bits of the eager step on the default stream."""
+    import threading
+
+    import torch
+
+    from paper_2505_13813_amd import nn as gnn
+
+    torch.manual_seed(2)
+    block = gnn.KATMlp(256, groups=4).to("cuda:0").to(torch.bfloat16)
+    inputs = [torch.randn(700, 256, device="cuda:0").to(torch.bfloat16) for _ in range(4)]
+    dy = torch.randn(700, 256, device="cuda:0").to(torch.bfloat16)
+    want = [_step(torch, block, t.clone().requires_grad_(), dy) for t in inputs]
+    same = lambda got, ref: all(torch.equal(g, r) for g, r in zip(got, ref))
+    torch.cuda.synchronize()
+
+    results = [None] * len(inputs)
+
+    def on_a_stream(i):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            x = torch.zeros_like(inputs[i])
+            torch.cuda._sleep(5_000_000)
+            x.copy_(inputs[i])
+            results[i] = _step(torch, block, x.requires_grad_(), dy)
+            torch.cuda.current_stream().synchronize()
+
+    threads = [threading.Thread(target=on_a_stream, args=(i,)) for i in range(len(inputs))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert all(same(got, ref) for got, ref in zip(results, want))
+
+    x = inputs[0].clone().requires_grad_()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        _step(torch, block, x, dy)
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = _step(torch, block, x, dy)
+    for t, ref in zip(inputs + inputs, want + want):
+        with torch.no_grad():
+            x.copy_(t)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert same(out, ref)
+        assert same(_step(torch, block, t.clone().requires_grad_(), dy), ref)
