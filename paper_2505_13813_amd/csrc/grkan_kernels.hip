@@ -614,13 +614,14 @@ __global__ __launch_bounds__(kThreadsPerWg) void grkan_bwd_stage1_kernel(const B
 // T thread sums go through LDS, each block of 64 of them is added in thread
 // order, then the blocks in block order.  Every order is fixed by T and the row
 // count; dA / dB are overwritten.
+// With one numerator row shared by the groups (G_shared > 0) the workgroups below
+// G_shared write dB only, and M + 1 more, of four wavefronts, add one numerator
+// sum each over the rows of all groups the same way.
 constexpr int kStage2MaxThreads = 4 * kWave;
 
 static int stage2_threads(int32_t rows_per_group) { return rows_per_group > kWave ? kStage2MaxThreads : kWave; }
 
-//
-// With one numerator row shared by the groups (G_shared > 0) the workgroups below G_shared write dB only, and
-// M + 1 more, of four wavefronts, add one numerator sum each over the rows of all groups the same way.
+// A coefficient's gradient in the coefficients' type.
 __device__ __forceinline__ void store_coef_grad(void *p, int32_t i, double v, int32_t bf16)
 {
     if (bf16)

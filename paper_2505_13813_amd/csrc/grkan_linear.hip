@@ -250,7 +250,8 @@ template <> struct OutPack<bf16_out> {
 };
 
 // The coefficient rows of group g as they are kept: float32, or (MODEL) bfloat16 rows that are whole 32-bit words and
-// are widened when they are used (exactly), so that a call needs no converted copies of them.  Read through the
+// are widened when they are used (exactly), so that a call needs no converted copies of them (at the time of kept float32
+// copies: 6,304 rows of 3072 -> 768 47.7 us against 46.2, of 768 -> 3072 44.5 against 43.5).  Read through the
 // constant address space (nothing writes A and B while the kernels run), where g uniform means scalar loads.
 template <bool MODEL, int M, int N> struct RowWords {
     static constexpr int kA = MODEL ? (M + 1) / 2 : M + 1, kB = MODEL ? N / 2 : N;

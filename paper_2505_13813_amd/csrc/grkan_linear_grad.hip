@@ -24,11 +24,12 @@
 //     in place of a pass over dOut.
 //
 // Measured on one MI355X, both gradients, 25,216 rows, against the library's product + column sum (us):
-//   384 x 1536: 49.6 against 162 + 22     1536 x 384: 49.4 against 140 + 34     192 x 768: 29 against 166 + 15
-//   768 x 3072: 143 against 281 + 26      3072 x 768: 144 against 239 + 41
-// (600 - 830 TFLOP/s.)  What bounds it: the transposing reads (98 KB per stage, about 900 of the stage's 1152
-// matrix-instruction clocks), the loads into LDS (49 KB per stage: 43 of about 53 B per clock and CU), and
-// the partial tiles (38 MB written and read again).
+//   384 x 1536: 46 against 171     192 x 768: 28 against 189     768 x 3072: 124 against 270     3072 x 768: 125 against 305
+// What bounds it: at 384 x 1536 (25 stages for each workgroup) the matrix cores are busy 37 %
+// of the time and the wavefronts wait 40 % of theirs: the transposing reads (98 KB per stage at 109 B per clock and CU:
+// 900 of the stage's 1152 matrix-instruction clocks) and the loads into LDS (49 KB per stage at about 53) go on beside
+// the matrix instructions, filling the pipeline and the partial tile's way out do not; 7 - 9 of the 46 us are the second
+// kernel, which reads the 37 MB of partial tiles.  No bank conflicts, and both operands are read from memory once.
 #include <hip/hip_runtime.h>
 
 #include <mutex>

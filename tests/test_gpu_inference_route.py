@@ -62,7 +62,9 @@ def test_layer_on_the_models_own_parameters(rows, D_in, D_out, G, tile, bias, sh
                                                 layer.linear.bias)
         want = grkan.grkan_linear_fwd(x, A, B, layer.linear.weight.detach(), b32)
         assert got is not None
-        assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+        again = binding.load_native().layer_model(x, layer.rational.numerator, layer.rational.denominator,
+                                                  layer.linear.weight, layer.linear.bias)
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16)) and torch.equal(got, again)
         assert _close(torch, got, layer.linear(layer.rational(x)))
         if gnn.one_kernel_is_faster(rows, D_in, D_out) and not gnn.fused_layer_pays(rows, D_in, D_out):
             assert torch.equal(layer(x).view(torch.int16), got.view(torch.int16))
