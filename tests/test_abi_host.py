@@ -150,3 +150,23 @@ def test_packed_weight_size_is_host_arithmetic():
     assert f(100, 768) == 0 and f(3072, 770) == 0 and f(0, 768) == 0 and f(3072, -4) == 0
     assert lib.grkan_linear_pack_w(None, None, 3072, 768, None) == 1                  # null pointers
     assert lib.grkan_linear_pack_w(None, None, 100, 768, None) == 8                   # shape not covered
+
+
+def test_layer_on_a_models_parameters_rejects_on_the_host():
+    """grkan_linear_fwd_model: every operand is bfloat16, so coefficients need 4 bytes and the bias 8; nothing is
+    launched for these calls, nor for no rows."""
+    lib = binding.load_library()
+    f = lib.grkan_linear_fwd_model
+    f.argtypes = [ctypes.c_void_p] * 6 + [ctypes.c_int64] + [ctypes.c_int32] * 6 + [ctypes.c_void_p]
+    f.restype = ctypes.c_int
+    good = [16, 4, 4, 16, 8, 16, 4, 192, 64, 6, 5, 4, 1, None]
+
+    def status(**changes):
+        names = ("x", "A", "B", "W", "bias", "out", "rows", "D_in", "D_out", "G", "m", "n", "shared", "stream")
+        return f(*[changes.get(n, v) for n, v in zip(names, good)])
+
+    assert status(rows=0) == 0 and status(rows=0, x=None, out=None, bias=None) == 0
+    assert all(status(**{p: None}) == 1 for p in ("x", "A", "B", "W", "out"))
+    assert all(status(**{p: v}) == 4 for p, v in (("x", 8), ("A", 2), ("B", 2), ("W", 8), ("bias", 4), ("out", 8)))
+    assert status(m=3, n=2) == 3 and status(D_in=190) == 2
+    assert status(D_in=96, G=3) == 8 and status(D_in=192, G=12) == 8 and status(D_out=66) == 8
