@@ -272,6 +272,40 @@ std::optional<Tensor> product(const Tensor &y, const Tensor &W, const std::optio
     return Product::apply(y, W, bias);
 }
 
+// What layer_packed reads of a layer's parameters: the packed weights, the bias, and a row of coefficients for every
+// group, in float32.
+std::optional<std::tuple<Tensor, std::optional<Tensor>, Tensor, Tensor>>
+pack_layer(const Tensor &W_in, const std::optional<Tensor> &bias, const Tensor &A, const Tensor &B)
+{
+    if (!plain_context() || !on_current_gpu(W_in))
+        return std::nullopt;
+    for (const Tensor *t : {&W_in, &A, &B, bias ? &*bias : &W_in})
+        if (!plain(*t, W_in.device()))
+            return std::nullopt;
+    if (W_in.scalar_type() != at::kBFloat16 || W_in.dim() != 2 || A.dim() < 1 || A.dim() > 2 || B.dim() != 2 ||
+        W_in.size(0) > INT32_MAX || W_in.size(1) > INT32_MAX)
+        return std::nullopt;
+    at::AutoGradMode no_grad(false);
+    Tensor W = W_in.detach().contiguous();
+    if (reinterpret_cast<uintptr_t>(W.data_ptr()) % 16 != 0) // a view into a larger buffer
+        W = W.clone();
+    const int32_t D_out = (int32_t)W.size(0), D_in = (int32_t)W.size(1);
+    const size_t bytes = grkan_linear_packed_w_bytes(D_in, D_out);
+    if (bytes == 0)
+        return std::nullopt;
+    const Tensor data = at::empty({(int64_t)bytes}, W.options().dtype(at::kByte));
+    check(grkan_linear_pack_w(W.data_ptr(), data.data_ptr(), D_in, D_out, stream_of(W)), "grkan_linear_pack_w");
+    // copies, not views of float32 parameters, which may be written to or resized behind them
+    auto float32 = [](const Tensor &t, at::IntArrayRef shape) {
+        Tensor out = at::empty(shape, t.options().dtype(at::kFloat));
+        return out.copy_(t.detach().expand(shape));
+    };
+    std::optional<Tensor> b32;
+    if (bias)
+        b32 = float32(*bias, bias->sizes());
+    return std::make_tuple(data, b32, float32(A, {B.size(0), A.size(-1)}), float32(B, B.sizes()));
+}
+
 // The one-kernel layer on packed weights (inference): all operands as the module keeps them.  `made_on`: the stream
 // (its address) the kept copies were made on, -1 for copies that this call may read wherever it runs; on another stream,
 // and under capture, the caller has something to do first and the call is not taken.
@@ -363,7 +397,7 @@ struct Arguments {
     {
         return h.is_none() ? std::nullopt : std::optional<Tensor>(tensor(h));
     }
-    template <typename Entry> std::optional<Tensor> call(Entry &&entry) const
+    template <typename Entry> auto call(Entry &&entry) const -> decltype(entry())
     {
         if (!taken)
             return std::nullopt;
@@ -393,6 +427,12 @@ PYBIND11_MODULE(_native, mod)
         const Tensor x = args.tensor(x_), A = args.tensor(A_), B = args.tensor(B_), W = args.tensor(W_);
         const std::optional<Tensor> bias = args.optional(bias_);
         return args.call([&] { return layer_model(x, A, B, W, bias); });
+    });
+    mod.def("pack_layer", [](handle W_, handle bias_, handle A_, handle B_) {
+        Arguments args;
+        const Tensor W = args.tensor(W_), A = args.tensor(A_), B = args.tensor(B_);
+        const std::optional<Tensor> bias = args.optional(bias_);
+        return args.call([&] { return pack_layer(W, bias, A, B); });
     });
     mod.def("layer_packed", [](handle x_, handle A_, handle B_, handle Wp_, int64_t D_out, handle bias_,
                                 int64_t made_on) {

@@ -309,14 +309,14 @@ class _Packed(tuple):
 
     made_on, stream, made = -1, None, None
 
-    def __new__(cls, rational, params):
-        w, b = (None if p is None else p.detach() for p in params[:2])
-        A, B = rational.coefficient_rows()
-        w = w.contiguous()
-        if w.data_ptr() % 16:  # a view into a larger buffer
-            w = w.clone()
-        self = super().__new__(cls, (binding.grkan_linear_pack_w(w), None if b is None else b.to(torch.float32).contiguous(),
-                                     A.detach().to(torch.float32).contiguous(), B.detach().to(torch.float32).contiguous()))
+    @classmethod
+    def of(cls, params):
+        """The copies, or None where the parameters are not plain tensors on the current GPU."""
+        copies = binding.load_native().pack_layer(*params)
+        if copies is None:
+            return None
+        data, b32, A32, B32 = copies
+        self = cls((binding.PackedWeight(data, *params[0].shape), b32, A32, B32))
         self._made_of = tuple((None, 0, 0) if p is None else (weakref.ref(p), p.data_ptr(), p._version) for p in params)
         return self
 
@@ -401,8 +401,8 @@ class GRKANLinear(nn.Module):
             return packed
         if not all(type(p) is nn.Parameter and not p.is_inference() for p in params if p is not None):
             return None
-        packed = _Packed(self.rational, params)
-        if not torch.cuda.is_current_stream_capturing():
+        packed = _Packed.of(params)
+        if packed is not None and not torch.cuda.is_current_stream_capturing():
             packed.stream = torch.cuda.current_stream(params[0].device)
             packed.made = packed.stream.record_event()
             packed.made_on = packed.stream.cuda_stream
@@ -415,7 +415,10 @@ class GRKANLinear(nn.Module):
         pw, b32, A32, B32 = packed
         out = entry(x, A32, B32, pw.data, pw.D_out, b32, packed.made_on)
         if out is None and packed.made_on != -1:
-            pw, b32, A32, B32 = self._readable_here(packed, params)
+            packed = self._readable_here(packed, params)
+            if packed is None:
+                return None
+            pw, b32, A32, B32 = packed
             out = entry(x, A32, B32, pw.data, pw.D_out, b32, -1)
         return out
 
@@ -423,7 +426,7 @@ class GRKANLinear(nn.Module):
         """The kept copy ordered behind its packing on whatever stream this is; under capture one that is part of the
         graph, so that a replay follows the parameters and its memory is the graph's own."""
         if torch.cuda.is_current_stream_capturing():
-            return _Packed(self.rational, params)
+            return _Packed.of(params)
         stream = torch.cuda.current_stream(params[0].device)
         if stream != packed.stream:
             stream.wait_event(packed.made)
@@ -451,7 +454,7 @@ class GRKANLinear(nn.Module):
             return None
         weight, bias = linear._parameters.get("weight"), linear._parameters.get("bias")
         numerator, denominator = rational._parameters.get("numerator"), rational._parameters.get("denominator")
-        if weight is None or numerator is None or denominator is None:
+        if weight is None or numerator is None or denominator is None or "coefficient_rows" in rational.__dict__:
             return None
         if not x.dim() or not x.shape[-1]:
             return None
@@ -470,7 +473,11 @@ class GRKANLinear(nn.Module):
             packed = self._inference_weights(params)
             if packed is not None:
                 if compiling:
-                    pw, b32, A32, B32 = packed if packed.made_on == -1 else self._readable_here(packed, params)
+                    if packed.made_on != -1:
+                        packed = self._readable_here(packed, params)
+                    if packed is None:
+                        return None
+                    pw, b32, A32, B32 = packed
                     return binding.grkan_linear_fwd(x.contiguous(), A32, B32, pw, b32, out_dtype=x.dtype)
                 return self._packed_layer(x, packed, params)
         # In training mode a pass without a gradient may be the first half of one with (reentrant checkpointing): both
