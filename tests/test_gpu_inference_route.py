@@ -297,13 +297,14 @@ def test_kept_copy_on_other_streams():
         assert torch.equal(old, want) and junk
 
 
-def test_captured_call_follows_the_parameters():
+@pytest.mark.parametrize("rows,D_in,D_out", [(300, 768, 384), (197, 3072, 768)])
+def test_captured_call_follows_the_parameters(rows, D_in, D_out):
     """A graph captured with the kept copy in place packs for itself: replays see writes to the parameters, and
     nothing that is kept lives in the graph's memory."""
     import torch
 
     for fresh in (False, True):
-        layer, x = _layer(torch, 768, 384, 8), _rows(torch, 300, 768)
+        layer, x = _layer(torch, D_in, D_out, 8), _rows(torch, rows, D_in)
         with torch.no_grad():
             layer(x)
             torch.cuda.synchronize()
@@ -317,7 +318,7 @@ def test_captured_call_follows_the_parameters():
             for step in range(4):
                 layer.linear.weight.mul_(0.7)
                 layer.rational.denominator.add_(0.01)
-                x.copy_(_rows(torch, 300, 768, seed=9 + step))
+                x.copy_(_rows(torch, rows, D_in, seed=9 + step))
                 want = layer(x)
                 torch.cuda.synchronize()
                 graph.replay()
