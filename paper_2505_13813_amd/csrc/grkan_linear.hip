@@ -1078,7 +1078,7 @@ struct SmallVariant {
 
 // A round of workgroups (one per compute unit) takes a time that depends on the tile and D_in only, and the time of a
 // layer is that times the rounds: to within 25 % at all, and 15 % at nine in ten, of 266 sizes of nineteen layer shapes
-// and 1 .. 25,216 rows (measured on MI355X, us per round at D_in = 768 / 1536 / 3072, the chip filled):
+// and 1 .. 25,216 rows (packed weights; measured on MI355X, us per round at D_in = 768 / 1536 / 3072, the chip filled):
 //   16 x 64: 6.6 / 7.8 / 11.7    32 x 128: 8.5 / 12.2 / 20.5    64 x 192: 13.2 / 21 / 36
 //   64 x 384: 15.8 / 24.5 / 45   112 x 768: 41 / - / 133   112 x 384: - / 43 / -   112 x 192: 24 / - / -
 static const SmallVariant kSmall[] = {
