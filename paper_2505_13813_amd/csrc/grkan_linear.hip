@@ -82,18 +82,19 @@ struct LinArgs {
     int32_t a_stride;  // MODEL: m + 1, or 0 where all groups share one numerator row
 };
 
-// LDS of the small kernel: four x buffers of a 64-k block for each group of WN of the NW wavefronts, and a
-// ring of 2 KB weight slots per wavefront, as deep as 160 KB allow
-constexpr int small_x_bytes(int NW, int MT, int WN) { return (NW / WN) * 4 * MT * 2048; }
-constexpr int small_ring(int NW, int MT, int WN)
+// The small kernel: eight wavefronts multiply, eight evaluate F; two or three buffers of F of a 64-k block for each
+// group of WN multiplying wavefronts, and a ring of two blocks of 2 KB weight tiles per multiplying wavefront
+constexpr int kMulWaves = 8;
+constexpr int kSmallWaves = 2 * kMulWaves;
+constexpr int kXAhead = 4; // periods x is loaded ahead
+constexpr int small_period(int WN) { return WN == kMulWaves ? 2 : 1; } // 64-k blocks of a group between two barriers
+constexpr int small_f_bytes(int MT, int WN) { return (kMulWaves / WN) * small_period(WN) * 2 * MT * 2048; }
+constexpr int small_ring(int NT) { return 2 * NT; }
+constexpr size_t small_lds_bytes(int MT, int NT, int WN)
 {
-    const int fit = (160 * 1024 - small_x_bytes(NW, MT, WN)) / (NW * 2048);
-    return fit > 8 ? 8 : fit;
+    return (size_t)kMulWaves * small_ring(NT) * 2048 + small_f_bytes(MT, WN);
 }
-constexpr size_t small_lds_bytes(int NW, int MT, int WN)
-{
-    return (size_t)NW * small_ring(NW, MT, WN) * 2048 + small_x_bytes(NW, MT, WN);
-}
+constexpr int small_slab(int MT, int NT, int WN) { return 16 * MT * (16 * NT * WN + 4) * 4; } // a partial tile, rows 16 bytes apart from the next bank
 
 __device__ __forceinline__ uint64_t uniform_u64(uint64_t v)
 {
@@ -113,6 +114,10 @@ __device__ __forceinline__ u32x4 gload16(uint64_t uniform_base, uint32_t lane_of
 // next to the access that uses it, where "scalar base + 32-bit lane offset" is recognised; hoisted
 // out of the loop it would turn every access into a 64-bit vector addition.
 __device__ __forceinline__ void keep_in_loop(uint32_t &v) { asm volatile("" : "+v"(v)); }
+
+// Which 16-byte piece of its 128-byte line row `row` of a 16-row tile keeps in LDS slot s: piece s xor line_swizzle(row).
+// A read of one piece index of all sixteen rows then touches every bank once.
+__device__ __forceinline__ uint32_t line_swizzle(uint32_t row) { return (row >> 1) & 7u; }
 
 __device__ __forceinline__ bf16x8 lds_read16(uint32_t addr)
 {
@@ -210,6 +215,20 @@ template <int S> __device__ __forceinline__ void rational_piece(PairState &t, ui
         y[1] = t.p1 * t.h1;
         out = __builtin_bit_cast(uint32_t, __builtin_convertvector(y, bf16x2));
     }
+}
+
+// F of the eight elements of four words.  Every stage of all of them before the next: left to itself the compiler works
+// them off one after the other, and a wavefront that has nothing else to do waits out every instruction's latency
+// (197 rows of 3072 -> 768, most of it waiting for F: 12.9 -> 11.7 us).
+__device__ __forceinline__ u32x4 rational_words(const u32x4 &w, const Coef<5, 4> &c)
+{
+    PairState t[4];
+    uint32_t y[4];
+    static_for<0, 7>([&](auto sc) {
+        static_for<0, 4>([&](auto jc) { rational_piece<decltype(sc)::value>(t[decltype(jc)::value], w[decltype(jc)::value], c, y[decltype(jc)::value]); });
+        fence_schedule();
+    });
+    return u32x4{y[0], y[1], y[2], y[3]};
 }
 
 template <typename OUT> struct OutPack;
@@ -712,30 +731,61 @@ __global__ __launch_bounds__(64 * NW, 1) void grkan_linear_fwd_kernel(const LinA
 // the same layer for inputs of too few rows to fill the chip with 112-row tiles
 // --------------------------------------------------------------------------
 //
-// A workgroup of NW wavefronts, WK groups of WN: group kg takes the 64-k blocks kg, kg + WK, .. of
-// the contraction, wavefront wn of a group the 16 NT channels [16 NT wn, 16 NT (wn + 1)) of the tile, all
-// of them the tile's BM = 16 MT tokens; the WK partial tiles are added in group order at the end.
-//   * W: LDS-direct loads into a ring of kRing 2 KB slots per wavefront (16 rows x 64 k), private to it;
-//     the two 64-byte halves of the rows are fetched back to back, so that the second half of each
-//     cache line comes from the vector cache (measured from L2: 50 B per clock and CU, 26 when the
-//     halves are fetched apart).
-//   * x: LDS-direct loads too, three blocks ahead, in the layout of the weights; a wavefront replaces the
-//     units it has fetched by F of them in place, one block ahead of their use.  (With LDS-direct loads in
-//     flight the compiler can wait for a load into registers only by waiting for everything.)  With WN = 1
-//     a wavefront reads what it wrote itself and the loop has no barrier.
+// A workgroup of sixteen wavefronts, four per SIMD: eight multiply, eight evaluate F for them.  The multiplying
+// ones are WK groups of WN: group kg takes the 64-k blocks kg, kg + WK, .. of the contraction, wavefront wn of a
+// group the 16 NT channels [16 NT wn, 16 NT (wn + 1)) of the tile, all of them the tile's BM = 16 MT tokens; the
+// WK partial tiles are added in group order at the end.
+//   * W: LDS-direct loads, two blocks ahead, into a ring of 2 KB slots (16 rows x 64 k) per multiplying wavefront,
+//     private to it.
+//   * x: memory -> registers, four periods ahead -> F -> LDS, one period ahead of its use.  A period is KB blocks of
+//     every group.  The loop's only barrier stands in front of the last step of a period: F of the next period is
+//     complete there, and F of this one has been read.
+//   * The operands of a block are read during the last step of the block before, each register as soon as its
+//     last use has been issued, so that nothing is waited for at a block's start.
+//   * The order of an output's sum is fixed by the tile alone.  (Starting the workgroups of an XCD at different blocks, as
+//     the big kernel does, gained nothing at any size here and cost half of the time where W outgrows the L2: 3,152 rows of
+//     3072 -> 3072 134 us against 89.)
 //   * MODEL: coefficients and bias in bfloat16 (RowWords).
-template <int NW, int MT, int NT, int WN, typename OUT, bool PACKED, bool MODEL, int M, int N>
-__global__ __launch_bounds__(64 * NW, 1) void grkan_linear_small_kernel(const LinArgs a)
+//
+// What bounds it: the vector ALU and the matrix cores together - a SIMD that does both takes about 7 clocks for a matrix
+// and 5 for a vector instruction (micro-benchmark: 48 of the one and 200 of the other, from different wavefronts, 535 ns;
+// alone 350 and 240), and a 64 x 384 tile has that ratio per block - and beside them L2 -> LDS (57 KB per block).  With
+// eight wavefronts that each did all of it, the F evaluations, the operand reads and the barriers stood in the way of the
+// matrix instructions: us per call before / now, the parameters of a bfloat16 model, launches from a graph:
+//   197 x 3072 -> 768   (16 x 64)  12.7 / 11.0     788 x 3072 -> 768   (32 x 128) 21.4 / 18.1
+//   6304 x 1536 -> 384  (64 x 192) 21.9 / 18.8     6304 x 3072 -> 768  (64 x 384) 46.6 / 42.5
+// A walk over the 64-k blocks first, first + by, .. of a contraction.  (A few scalar instructions a step: a wavefront issues
+// one instruction in four to five clocks whatever its kind, so that even a scalar division per block shows.)
+struct BlockWalk {
+    int32_t left;   // steps left, this one included
+    uint32_t kbyte; // byte offset inside a row of this step's block (0 past the end)
+    uint32_t step;
+    __device__ __forceinline__ BlockWalk(int32_t n_blocks, int32_t first, int32_t by)
+        : left((n_blocks - first + by - 1) / by), kbyte(left > 0 ? (uint32_t)first * 128u : 0u), step((uint32_t)by * 128u)
+    {
+    }
+    __device__ __forceinline__ void next()
+    {
+        --left;
+        kbyte = left > 0 ? kbyte + step : 0u;
+    }
+};
+
+template <int MT, int NT, int WN, typename OUT, bool PACKED, bool MODEL, int M, int N>
+__global__ __launch_bounds__(64 * kSmallWaves, 1) void grkan_linear_small_kernel(const LinArgs a)
 {
-    constexpr int WK = NW / WN;
+    constexpr int WK = kMulWaves / WN;
     constexpr int BM = 16 * MT;
     constexpr int BN = 16 * NT * WN;
-    constexpr int PU = 2 * MT / WN; // 16-row, 32-k units of x a wavefront turns into F per block
-    constexpr uint32_t kXB = 2u * MT * 1024u; // bytes of a block of x: unit q at 1024 q, half q / MT, rows 16 (q % MT) ..
-    constexpr int kRing = small_ring(NW, MT, WN);
-    constexpr uint32_t kX0 = (uint32_t)NW * kRing * 2048u;
-    static_assert(WN * WK == NW && PU >= 1 && PU * WN == 2 * MT, "a group's wavefronts share the units of a block evenly");
-    static_assert(kRing <= 2 * NT + 2, "a weight tile waited for must be younger than the x needed with it");
+    constexpr int KB = small_period(WN);          // blocks of a group per period
+    constexpr int PU = WK * KB * 2 * MT / kMulWaves; // units of x (8 rows x 64 k) a wavefront turns into F per period
+    constexpr uint32_t kXB = 2u * MT * 1024u;     // bytes of a block of F: unit q at 1024 q, half q / MT, rows 16 (q % MT) ..
+    constexpr int kRing = small_ring(NT);
+    constexpr uint32_t kF0 = (uint32_t)kMulWaves * kRing * 2048u;
+    // a unit's rows decide which pieces its lanes hold; two units of eight rows of one 16-row tile differ in that
+    constexpr int kSets = PU > 1 ? 2 : 1;
+    static_assert(WN * WK == kMulWaves && PU >= 1 && PU <= 2 && PU * kMulWaves == WK * KB * 2 * MT && 2 * MT % PU == 0,
+                  "the wavefronts share the units of a period evenly, each within one group");
     extern __shared__ __align__(16) char smem[];
     const lptr_t lds = (lptr_t)smem;
     const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
@@ -743,8 +793,6 @@ __global__ __launch_bounds__(64 * NW, 1) void grkan_linear_small_kernel(const Li
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wn = wave % WN;
-    const int kg = wave / WN;
 
     // Workgroup -> tile.  Workgroups go round-robin over the 8 XCDs; the tiles that share the larger of the
     // two operands' slices run on one XCD, so that its L2 is the only one to fetch them.
@@ -764,276 +812,273 @@ __global__ __launch_bounds__(64 * NW, 1) void grkan_linear_small_kernel(const Li
     const int32_t n0 = nb * BN;
     const uint32_t K2 = (uint32_t)a.K * 2u;
     const int32_t n_blocks = a.K >> 6;
-    const int32_t n_iter = (n_blocks + WK - 1) / WK;           // the same for every wavefront (barriers)
-    const int32_t mine = (n_blocks - kg + WK - 1) / WK;        // blocks of this group
+    const int32_t n_iter = (n_blocks + WK * KB - 1) / (WK * KB); // periods, the same for every wavefront (barriers)
 
-    // 16-byte pieces of a row are permuted as in the big kernel: slot = piece xor g(row)
-    const uint32_t w_g = (uint32_t)((lane >> 4) ^ (lane >> 3)) & 3u;
-
-    // ---- x: unit q = wn PU + u of a block is half q / MT of the 64 k, rows 16 (q % MT) + lane / 4
-    uint32_t x_lane[PU];
+    if (wave >= kMulWaves) {
+        // ---- F: unit q = p PU + u of a period is rows 8 (q % (2 MT)) + lane / 8 of the period's block q / (2 MT): of group
+        // q / (2 MT KB), and of its KB blocks the (q / (2 MT) % KB)th
+        const int p = wave - kMulWaves;
+        const int pb = p * PU / (2 * MT);
+        const int q0 = p * PU - pb * 2 * MT; // the first unit inside the block
+        uint32_t x_lane[PU];
 #pragma unroll
-    for (int u = 0; u < PU; ++u) {
-        const int q = wn * PU + u;
-        int64_t xg = m0 + 16 * (q % MT) + (lane >> 2);
-        if (xg > a.rows - 1)
-            xg = a.rows - 1; // rows past the end read the last row (never stored)
-        x_lane[u] = (uint32_t)((xg - m0) * (int64_t)K2) + (uint32_t)(q / MT) * 64u + (((uint32_t)lane & 3u) ^ w_g) * 16u;
-    }
-    const uint64_t x_base = reinterpret_cast<uint64_t>(a.x) + (uint64_t)m0 * K2;
-    // byte offset inside a row of this group's block i (blocks past the end repeat the last one)
-    const int32_t last = mine > 0 ? mine - 1 : 0;
-    auto kbyte = [&](int32_t i) {
-        const int32_t b = kg + (i < last ? i : last) * WK;
-        return (uint32_t)(b < n_blocks ? b : n_blocks - 1) * 128u; // (a group without any block: never consumed)
-    };
-    const uint32_t x_group = kX0 + (uint32_t)kg * 4u * kXB;                          // this group's four buffers
-    const uint32_t x_own = x_group + (uint32_t)(wn * PU) * 1024u;                    // this wavefront's units
-
-    // ---- W ring
-    uint64_t w_base;
-    uint32_t w_lane[NT];
-    const uint64_t w_stage_bytes = (uint64_t)(uint32_t)a.wtiles * 1024u; // packed: bytes per 32 k
-#pragma unroll
-    for (int i = 0; i < NT; ++i) {
-        if constexpr (PACKED) {
-            int t = (n0 >> 4) + NT * wn + i;
-            if (t > a.wtiles - 1)
-                t = a.wtiles - 1;
-            w_lane[i] = (uint32_t)t * 1024u + (uint32_t)lane * 16u;
-        } else {
-            int r = n0 + 16 * (NT * wn + i) + (lane >> 2);
-            if (r > a.Nout - 1)
-                r = a.Nout - 1;
-            w_lane[i] = (uint32_t)(r - n0) * K2 + (((uint32_t)lane & 3u) ^ w_g) * 16u;
+        for (int u = 0; u < PU; ++u) {
+            const int row = 8 * (q0 + u) + (lane >> 3);
+            int64_t xg = m0 + row;
+            if (xg > a.rows - 1)
+                xg = a.rows - 1; // rows past the end read the last row (never stored)
+            const uint32_t piece = ((uint32_t)lane ^ line_swizzle(row)) & 7u;
+            x_lane[u] = (uint32_t)((xg - m0) * (int64_t)K2) + piece * 16u;
         }
-    }
-    w_base = reinterpret_cast<uint64_t>(a.W) + (PACKED ? 0 : (uint64_t)(uint32_t)n0 * K2);
-    const lptr_t ring = lds + (uint32_t)wave * (kRing * 2048u);
-    // operand read: row lane % 16 of a 1 KB unit, piece lane / 16
-    const uint32_t op_lane = (uint32_t)(lane & 15) * kWRow +
-                             ((((uint32_t)(lane >> 4)) ^ ((uint32_t)(((lane & 15) >> 2) ^ ((lane & 15) >> 1)) & 3u)) * 16u);
-    const uint32_t ring_read = lds0 + (uint32_t)wave * (kRing * 2048u) + op_lane;
-    // tile i (static) of the group's block `blk` into ring slot `slot_bytes`
-    auto w_fetch = [&](auto ic, int32_t blk, uint32_t slot_bytes) {
-        constexpr int i = decltype(ic)::value;
-        const uint32_t kb = kbyte(blk);
+        const uint64_t x_base = reinterpret_cast<uint64_t>(a.x) + (uint64_t)m0 * K2;
+        u32x4 raw[kXAhead][PU];
+        BlockWalk xw(n_blocks, pb / KB + pb % KB * WK, WK * KB), cw = xw; // of the blocks to be loaded, and to be evaluated, next
+        auto x_load = [&](u32x4 (&v)[PU]) {
+            const bool past = xw.left <= 0; // one address for all lanes, never consumed
+            const uint64_t base = uniform_u64(x_base + xw.kbyte);
+            xw.next();
+#pragma unroll
+            for (int u = 0; u < PU; ++u) {
+                keep_in_loop(x_lane[u]);
+                v[u] = gload16(base, past ? 0u : x_lane[u]);
+            }
+        };
+        // Coefficients: a block may hold two groups of channels (32 k each), a lane's piece lies in one of them.  In vector
+        // registers: two wavefronts issue instructions with a scalar operand one after the other, those on vector registers
+        // together.
+        Coef<M, N> c[kSets];
+        uint32_t c_lo = 1, c_span = 0; // blocks that start in [c_lo, c_lo + c_span) have the coefficients held
+        auto coef_for = [&]() {
+            const uint32_t k = cw.kbyte / 2u;
+            cw.next();
+            if (k - c_lo >= c_span) {
+                const int g0 = __builtin_amdgcn_readfirstlane((int)(k / (uint32_t)a.dgc));
+                const int g1 = __builtin_amdgcn_readfirstlane((int)((k + 32u) / (uint32_t)a.dgc));
+                c_lo = g0 == g1 ? (uint32_t)g0 * (uint32_t)a.dgc : k;
+                c_span = g0 == g1 ? (uint32_t)a.dgc - 32u : 1u;
+                RowWords<MODEL, M, N> r0, r1;
+                Coef<M, N> c0, c1;
+                r0.load(a, g0);
+                r1.load(a, g1);
+                r0.to(c0);
+                r1.to(c1);
+#pragma unroll
+                for (int h = 0; h < kSets; ++h) {
+                    const bool second = ((lane ^ (int)line_swizzle(8 * (q0 + h) + (lane >> 3))) & 4) != 0;
+#pragma unroll
+                    for (int j = 0; j <= M; ++j)
+                        c[h].a[j] = second ? c1.a[j] : c0.a[j];
+#pragma unroll
+                    for (int j = 0; j < N; ++j)
+                        c[h].b[j] = second ? c1.b[j] : c0.b[j];
+                }
+            }
+        };
+        const uint32_t f_own = lds0 + kF0 + (uint32_t)pb * 2u * kXB + (uint32_t)q0 * 1024u + (uint32_t)lane * 16u;
+        auto f_block = [&](const u32x4 (&v)[PU], uint32_t slot_bytes) {
+#pragma unroll
+            for (int u = 0; u < PU; ++u)
+                lds_write16(f_own + slot_bytes + (uint32_t)u * 1024u, rational_words(v[u], c[kSets == 2 ? u : 0]));
+        };
+#pragma unroll
+        for (int i = 0; i < kXAhead; ++i)
+            x_load(raw[i]);
+        // Period j: F of it into buffer j % 2, then the barrier behind which it is read (and buffer (j + 1) % 2 is not).
+        uint32_t f_slot = 0;
+        auto period = [&](auto jc) {
+            constexpr int r = decltype(jc)::value % kXAhead;
+            coef_for();
+            f_block(raw[r], f_slot);
+            x_load(raw[r]);
+            f_slot = kXB - f_slot;
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        };
+        int32_t j = 0;
+        for (; j + kXAhead <= n_iter; j += kXAhead)
+            static_for<0, kXAhead>([&](auto jc) { period(jc); });
+        static_for<0, kXAhead - 1>([&](auto jc) {
+            if (j + decltype(jc)::value < n_iter)
+                period(jc);
+        });
+        asm volatile("s_barrier" ::: "memory"); // the operand buffers are free
+        asm volatile("s_barrier" ::: "memory"); // the partial tiles are in LDS
+    } else {
+        const int wn = wave % WN;
+        const int kg = wave / WN;
+        BlockWalk ww(n_blocks, kg, WK);
+
+        // ---- W ring.  Plain: a fetch brings 8 rows x 128 bytes, whole cache lines; which 16-byte piece of its row a lane
+        // takes is permuted (line_swizzle).  A tile that reaches past Nout starts at its last sixteen rows instead (some
+        // channels are then formed twice, with the same bits).  Packed: 16 rows x 32 k, as the copy is laid out.
+        const uint32_t w_stage_bytes = (uint32_t)a.wtiles * 1024u; // packed: bytes per 32 k
+        int32_t tile_n[NT];                                        // the tile's first channel, from n0
+        uint64_t w_base[NT];
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            tile_n[i] = 16 * (NT * wn + i);
+            if constexpr (PACKED) {
+                const int32_t t = (n0 + tile_n[i]) >> 4;
+                w_base[i] = reinterpret_cast<uint64_t>(a.W) + (uint64_t)(uint32_t)(t < a.wtiles ? t : a.wtiles - 1) * 1024u;
+            } else {
+                if (n0 + tile_n[i] > a.Nout - 16)
+                    tile_n[i] = (a.Nout > 16 ? a.Nout - 16 : 0) - n0;
+                w_base[i] = reinterpret_cast<uint64_t>(a.W) + (uint64_t)(uint32_t)(n0 + tile_n[i]) * K2;
+            }
+        }
+        uint32_t w_lane[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            gcptr_t src;
-            if constexpr (PACKED)
-                src = (gcptr_t)uniform_u64(w_base + (uint64_t)((kb >> 6) + h) * w_stage_bytes) + w_lane[i];
-            else
-                src = (gcptr_t)uniform_u64(w_base + kb + h * 64u) + w_lane[i];
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
-                                             (__attribute__((address_space(3))) void *)(ring + slot_bytes + h * 1024u), 16, 0, 0);
+            const int row = 8 * h + (lane >> 3);
+            w_lane[h] = PACKED ? (uint32_t)lane * 16u
+                               : (uint32_t)(row < a.Nout ? row : a.Nout - 1) * K2 + (((uint32_t)lane ^ line_swizzle(row)) & 7u) * 16u;
         }
-    };
-
-    // ---- coefficients of the groups of the wave's units (one group per 32 k)
-    constexpr int kHalves = PU > MT ? 2 : 1; // halves of the 64 k the wave's units lie in
-    Coef<M, N> c[kHalves];
-    int cur_g[kHalves];
-    auto coef_for = [&](int32_t i, bool first) {
+        const uint32_t ring_at = (uint32_t)wave * (kRing * 2048u);
+        // operand reads: row i = lane % 16 of a 16-row tile, piece lane / 16 of its first 32 k (the second: bit 6 flipped);
+        // in a packed tile the halves are 1 KB apart
+        const uint32_t i16 = (uint32_t)lane & 15u, g4 = (uint32_t)lane >> 4;
+        const uint32_t op_lane = i16 * 128u + ((g4 ^ line_swizzle(i16)) * 16u);
+        const uint32_t op_packed = i16 * kWRow + ((g4 ^ (((i16 >> 2) ^ (i16 >> 1)) & 3u)) * 16u);
+        uint32_t w_read0 = lds0 + ring_at + (PACKED ? op_packed : op_lane);
+        uint32_t w_read1 = lds0 + ring_at + (PACKED ? op_packed + 1024u : op_lane ^ 64u);
+        // tile i (static) of the block at byte `kb` of a row into the ring at `at`
+        auto w_fetch = [&](auto ic, uint32_t kb, uint32_t at) {
+            constexpr int i = decltype(ic)::value;
 #pragma unroll
-        for (int h = 0; h < kHalves; ++h) {
-            const uint32_t k = kbyte(i) / 2u + (uint32_t)((wn * PU) / MT + h) * 32u;
-            const int g = __builtin_amdgcn_readfirstlane((int)(k / (uint32_t)a.dgc));
-            if (first || g != cur_g[h]) {
-                RowWords<MODEL, M, N> rows;
-                rows.load(a, g);
-                rows.to(c[h]);
-                cur_g[h] = g;
+            for (int h = 0; h < 2; ++h) {
+                keep_in_loop(w_lane[h]);
+                const uint64_t src = PACKED ? w_base[i] + (uint64_t)((kb >> 6) + h) * w_stage_bytes : w_base[i] + kb;
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)((gcptr_t)uniform_u64(src) + w_lane[h]),
+                                                 (__attribute__((address_space(3))) void *)(lds + at + h * 1024u), 16, 0, 0);
             }
-            // In vector registers from here on: an instruction with a scalar operand issues at 0.6 of the rate
-            // (these tiles are bound by the F evaluations: 5 % of their time).
-#pragma unroll
-            for (int j = 0; j <= M; ++j)
-                asm volatile("" : "+v"(c[h].a[j]));
-#pragma unroll
-            for (int j = 0; j < N; ++j)
-                asm volatile("" : "+v"(c[h].b[j]));
-        }
-    };
+        };
 
-    auto x_fetch = [&](int32_t i) {
-        const uint64_t base = uniform_u64(x_base + kbyte(i));
-#pragma unroll
-        for (int u = 0; u < PU; ++u)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)((gcptr_t)base + x_lane[u]),
-                                             (__attribute__((address_space(3))) void *)(lds + x_own + ((uint32_t)i & 3u) * kXB + u * 1024u),
-                                             16, 0, 0);
-    };
-    // the wavefront's units of the group's block i
-    auto x_at = [&](int32_t i) { return lds0 + x_own + ((uint32_t)i & 3u) * kXB + (uint32_t)lane * 16u; };
-    auto x_raw = [&](u32x4 (&v)[PU], int32_t i) {
-#pragma unroll
-        for (int u = 0; u < PU; ++u)
-            v[u] = *(const __attribute__((address_space(3))) u32x4 *)(uintptr_t)(x_at(i) + u * 1024u);
-    };
-    auto f_write = [&](const u32x4 (&v)[PU], int32_t i) {
-#pragma unroll
-        for (int u = 0; u < PU; ++u)
-            lds_write16(x_at(i) + u * 1024u, v[u]);
-    };
-
-    auto block_barrier = [&]() {
-        // with one wavefront per group the F values it reads are its own (LDS accesses of a wavefront are in order)
-        if constexpr (WN > 1)
-            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        else
-            asm volatile("" ::: "memory");
-    };
-
-    f32x4 acc[NT][MT];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-            acc[nt][mt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-
-    // ---- prologue: x of the first three blocks, the ring filled, F of the first block
-    x_fetch(0);
-    x_fetch(1);
-    x_fetch(2);
-    static_for<0, kRing - 1>([&](auto tc) {
-        constexpr int t = decltype(tc)::value;
-        w_fetch(std::integral_constant<int, t % NT>{}, t / NT, (uint32_t)t * 2048u);
-    });
-    coef_for(0, true);
-    wait_loads<2 * (kRing - 1) + 2 * PU>(); // x of block 0
-    {
-        u32x4 v[PU];
-        x_raw(v, 0);
-#pragma unroll
-        for (int u = 0; u < PU; ++u)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                v[u][j] = rational_pair<M, N>(v[u][j], c[kHalves == 2 ? u / MT : 0]);
-        f_write(v, 0);
-    }
-    coef_for(1, false);
-    block_barrier();
-
-    // Tile t of the walk (block t / NT of the group, 16-row tile t % NT) sits in ring slot t % kRing.  Step t
-    // first refills the slot of tile t - 1 (multiplied in the step before), then waits for tile t + 1 by
-    // load count (and so for the x of block b + 1, which is older) and reads its operands, then multiplies tile t.  The refills past the end of the walk fetch
-    // its last block again, so that the count stays the same to the end; they are never read.  (x loads
-    // issued in between only make the wait stricter than it has to be.)
-    uint32_t s_cur = 0;                          // slot of tile t, in bytes
-    auto next_slot = [&](uint32_t s) { return s + 2048u == kRing * 2048u ? 0u : s + 2048u; };
-    bf16x8 w0, w1;
-    wait_loads<2 * (kRing - 2)>();
-    w0 = lds_read16(ring_read);
-    w1 = lds_read16(ring_read + 1024u);
-
-    for (int32_t b = 0; b < mine; ++b) {
-        x_fetch(b + 3); // into the buffer of block b - 1
-        bf16x8 xf[2][MT];
-        const uint32_t fb = lds0 + x_group + ((uint32_t)b & 3u) * kXB + op_lane;
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                xf[h][mt] = lds_read16(fb + (uint32_t)(h * MT + mt) * 1024u);
-        constexpr int kWords = 4 * PU;                         // words of x (two elements) a lane turns into F
-        constexpr int kWordsPerStep = (kWords + NT - 1) / NT;
-        u32x4 xv[PU], y[PU];
-        static_for<0, NT>([&](auto ntc) {
-            constexpr int nt = decltype(ntc)::value;
-            // tile t - 1 + kRing = block b + (nt - 1 + kRing) / NT, into the slot before this one
-            // (the operands of tile t are in their registers here, so those of tile t - 1, read before them, are too)
-            constexpr int ahead = nt - 1 + kRing;
-            const uint32_t s_prev = s_cur == 0 ? (kRing - 1) * 2048u : s_cur - 2048u;
-            asm volatile("" ::"v"(w0), "v"(w1) : "memory");
-            w_fetch(std::integral_constant<int, ahead % NT>{}, b + ahead / NT, s_prev);
-            wait_loads<2 * (kRing - 2)>();
-            s_cur = next_slot(s_cur);
-            const bf16x8 n0v = lds_read16(ring_read + s_cur);
-            const bf16x8 n1v = lds_read16(ring_read + s_cur + 1024u);
-            if constexpr (nt == 0)
-                x_raw(xv, b + 1);
-            // F of the next block in pieces between the matrix instructions (see rational_piece)
-            PairState ps[kWordsPerStep];
-            uint32_t res[kWordsPerStep];
-            static_for<0, 2 * MT>([&](auto mc) {
-                constexpr int m = decltype(mc)::value;
-                constexpr int mt = m % MT;
-                acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(m < MT ? w0 : w1, xf[m / MT][mt], acc[nt][mt], 0, 0, 0);
-                static_for<0, 7>([&](auto sc) {
-                    constexpr int sp = decltype(sc)::value;
-                    if constexpr (sp * 2 * MT / 7 == m) {
-                        static_for<0, kWordsPerStep>([&](auto ic) {
-                            constexpr int j = nt * kWordsPerStep + decltype(ic)::value;
-                            if constexpr (j < kWords)
-                                rational_piece<sp>(ps[decltype(ic)::value], xv[j >> 2][j & 3],
-                                                   c[kHalves == 2 ? (j >> 2) / MT : 0], res[decltype(ic)::value]);
-                        });
-                    }
-                });
-            });
-            static_for<0, kWordsPerStep>([&](auto ic) {
-                constexpr int j = nt * kWordsPerStep + decltype(ic)::value;
-                if constexpr (j < kWords)
-                    y[j >> 2][j & 3] = res[decltype(ic)::value];
-            });
-            w0 = n0v;
-            w1 = n1v;
-        });
-        f_write(y, b + 1);
-        coef_for(b + 2, false);
-        block_barrier();
-    }
-    if (mine < n_iter) // a group with one block less than others: the same number of barriers for all
-        block_barrier();
-
-    // ---- epilogue: the partial tiles go to LDS as [WK][BM][BN + 4] float32 and leave as whole rows
-    // (as many groups at a time as fit; the first ones add what the others left in their place)
-    constexpr int kPitchF = BN + 4;
-    constexpr int kSlab = BM * kPitchF * 4;
-    constexpr int kSlabs = WK * kSlab <= (int)small_lds_bytes(NW, MT, WN) ? WK : WK / 2;
-    static_assert(kSlabs >= 1 && kSlabs * kSlab <= (int)small_lds_bytes(NW, MT, WN), "partial tiles must fit the operand buffers");
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // every fetch into the ring has landed
-    __syncthreads();
-    const uint32_t slab_at = lds0 + (uint32_t)(kg % kSlabs) * kSlab + (uint32_t)(lane & 15) * (kPitchF * 4u) +
-                             (uint32_t)(wn * 16 * NT + (lane >> 4) * 4) * 4u;
-    auto slab = [&](int nt, int mt) {
-        return (__attribute__((address_space(3))) f32x4 *)(uintptr_t)(slab_at + (uint32_t)(mt * 16) * (kPitchF * 4u) + (uint32_t)nt * 64u);
-    };
-    if (kSlabs < WK) {
-        if (kg >= kSlabs) {
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-                    *slab(nt, mt) = acc[nt][mt];
-        }
-        __syncthreads();
-        if (kg < kSlabs) {
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-                    *slab(nt, mt) = acc[nt][mt] + *slab(nt, mt);
-        }
-    } else {
+        f32x4 acc[NT][MT];
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
-                *slab(nt, mt) = acc[nt][mt];
+                acc[nt][mt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+        // The ring holds two blocks: tile t of the walk (step t / NT, 16-row tile t % NT) sits in slot t % kRing.  Before tile
+        // t is multiplied, the slot of tile t - 1 (multiplied just before) is refilled with tile t - 1 + kRing, tile t + 1 is
+        // waited for by load count and its operands are read.  The last two steps of the walk refill nothing.
+        static_assert(kRing == 2 * NT, "two blocks");
+        const int32_t count = ww.left;
+        uint32_t kb1 = 0, kb2 = 0; // the next block's byte in a row, and the one after it
+        if (count > 0) {
+            const uint32_t kb0 = ww.kbyte;
+            static_for<0, NT>([&](auto ic) { w_fetch(ic, kb0, ring_at + (uint32_t)decltype(ic)::value * 2048u); });
+        }
+        if (count > 1) {
+            ww.next();
+            kb1 = ww.kbyte;
+            static_for<0, NT - 1>([&](auto ic) { w_fetch(ic, kb1, ring_at + (uint32_t)(NT + decltype(ic)::value) * 2048u); });
+            wait_loads<2 * (2 * NT - 2)>();
+        } else {
+            wait_loads<2 * (NT - 1)>();
+        }
+        bf16x8 w0, w1, xf[2][MT];
+        w0 = lds_read16(w_read0);
+        w1 = lds_read16(w_read1);
+        const uint32_t f_read = lds0 + kF0 + (uint32_t)(kg * KB) * 2u * kXB;
+        asm volatile("s_barrier" ::: "memory"); // F of the first period
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+                xf[h][mt] = lds_read16(f_read + (h ? op_lane ^ 64u : op_lane) + (uint32_t)mt * 2048u);
+        uint32_t f_slot = 0; // of the current block
+        uint32_t side = 0;   // the half of the ring the current block is in
+        // block b of the walk; LEFT: blocks after it, 2 for two and more
+        auto block = [&](auto left_c, int32_t b) {
+            constexpr int LEFT = decltype(left_c)::value;
+            const bool ends = KB == 1 || (b & 1) != 0; // a period: the next block is in the other buffer of F
+            f_slot = ends ? kXB - f_slot % (2u * kXB) : f_slot + 2u * kXB;
+            uint32_t f0 = f_read + f_slot + op_lane, f1 = f_read + f_slot + (op_lane ^ 64u);
+            keep_in_loop(f0);
+            keep_in_loop(f1);
+            const uint32_t other = (uint32_t)(NT * 2048) - side;
+            const uint32_t here0 = w_read0 + side, here1 = w_read1 + side, there0 = w_read0 + other, there1 = w_read1 + other;
+            static_for<0, NT>([&](auto ntc) {
+                constexpr int nt = decltype(ntc)::value;
+                // (the operands of tile t are in their registers here, so those of tile t - 1, read before them, are too)
+                asm volatile("" ::"v"(w0), "v"(w1) : "memory");
+                if constexpr (nt == 0 && LEFT >= 1)
+                    w_fetch(std::integral_constant<int, NT - 1>{}, kb1, ring_at + other + (NT - 1) * 2048u);
+                if constexpr (nt > 0 && LEFT >= 2)
+                    w_fetch(std::integral_constant<int, nt - 1>{}, kb2, ring_at + side + (nt - 1) * 2048u);
+                if constexpr (nt == NT - 1 && LEFT >= 1)
+                    if (ends)
+                        asm volatile("s_barrier" ::: "memory"); // F of the next period
+                // tiles in flight that are younger than tile t + 1: to the end of the next block, or NT - 1 .. from there
+                constexpr int kTo = LEFT == 0 ? NT - 1 : LEFT == 1 ? 2 * NT - 1 : 2 * NT - 1 + nt;
+                if constexpr (kTo >= nt + 1)
+                    wait_loads<2 * (kTo - nt - 1)>();
+                bf16x8 n0v = w0, n1v = w1;
+                if constexpr (nt + 1 < NT) {
+                    n0v = lds_read16(here0 + (uint32_t)(nt + 1) * 2048u);
+                    n1v = lds_read16(here1 + (uint32_t)(nt + 1) * 2048u);
+                } else if constexpr (LEFT >= 1) {
+                    n0v = lds_read16(there0);
+                    n1v = lds_read16(there1);
+                }
+                fence_schedule();
+                static_for<0, 2 * MT>([&](auto mc) {
+                    constexpr int m = decltype(mc)::value;
+                    constexpr int mt = m % MT;
+                    acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(m < MT ? w0 : w1, xf[m / MT][mt], acc[nt][mt], 0, 0, 0);
+                    if constexpr (nt == NT - 1 && LEFT >= 1) {
+                        xf[m / MT][mt] = lds_read16((m < MT ? f0 : f1) + (uint32_t)mt * 2048u);
+                        fence_schedule();
+                    }
+                });
+                fence_schedule();
+                w0 = n0v;
+                w1 = n1v;
+            });
+            side = other;
+            kb1 = kb2;
+        };
+        for (int32_t b = 0; b < count - 2; ++b) {
+            ww.next();
+            kb2 = ww.kbyte;
+            block(std::integral_constant<int, 2>{}, b);
+        }
+        if (count > 1)
+            block(std::integral_constant<int, 1>{}, count - 2);
+        if (count > 0)
+            block(std::integral_constant<int, 0>{}, count - 1);
+        for (int32_t j = count > 0 ? (count + KB - 1) / KB : 1; j < n_iter; ++j)
+            asm volatile("s_barrier" ::: "memory");
+
+        // ---- the partial tiles go to LDS as [WK][BM][BN + 4] float32
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); // every fetch has landed, every operand has been read
+        const uint32_t slab_at = lds0 + (uint32_t)kg * small_slab(MT, NT, WN) + i16 * ((BN + 4) * 4u);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const int32_t col = tile_n[nt] + (int32_t)g4 * 4; // (before n0: another workgroup's)
+            if (PACKED || col >= 0)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    *(__attribute__((address_space(3))) f32x4 *)(uintptr_t)(slab_at + (uint32_t)(mt * 16) * ((BN + 4) * 4u) + (uint32_t)col * 4u) =
+                        acc[nt][mt];
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     }
-    __syncthreads();
+
+    // ---- epilogue: the sum of the partial tiles leaves as whole rows
+    constexpr int kSlab = small_slab(MT, NT, WN);
+    static_assert(WK * kSlab <= (int)small_lds_bytes(MT, NT, WN) && small_lds_bytes(MT, NT, WN) <= 160 * 1024, "partial tiles must fit the operand buffers");
     constexpr int QPR = BN / 4; // four channels per lane
-    for (int i = tid; i < BM * QPR; i += 64 * NW) {
+    for (int i = tid; i < BM * QPR; i += 64 * kSmallWaves) {
         const int r = i / QPR;
         const int o = n0 + (i - r * QPR) * 4;
         if (m0 + r >= a.rows || o >= a.Nout)
             continue;
-        const uint32_t src = lds0 + (uint32_t)r * (kPitchF * 4u) + (uint32_t)(o - n0) * 4u;
+        const uint32_t src = lds0 + (uint32_t)r * ((BN + 4) * 4u) + (uint32_t)(o - n0) * 4u;
         f32x4 v = *(const __attribute__((address_space(3))) f32x4 *)(uintptr_t)src;
 #pragma unroll
-        for (int g = 1; g < kSlabs; ++g)
+        for (int g = 1; g < WK; ++g)
             v += *(const __attribute__((address_space(3))) f32x4 *)(uintptr_t)(src + (uint32_t)g * kSlab);
         if (a.bias)
             v += bias_of<MODEL>(a.bias, o);
@@ -1065,27 +1110,28 @@ static Variant pick_variant(int32_t D_out)
     return Variant{4, 3};
 }
 
-// Tile variants of the small kernel: (waves, 16-token sub-tiles, 16-channel sub-tiles per wave, waves side by
-// side).  The widest tile has sixteen waves, four per SIMD, in two groups: with eight in one group the F
-// evaluations, the matrix instructions and the operand reads of a block all waited for each other at its
-// barrier (one round at D_in = 3072: 51 -> 45 us).  The others have no room in LDS for sixteen.
+// Tile variants of the small kernel: (16-token sub-tiles, 16-channel sub-tiles per multiplying wave, waves side by side).
 struct SmallVariant {
-    int nw, mt, nt, wn;
+    int mt, nt, wn;
     double fixed_us, us_per_1k; // time of one round of workgroups: fixed_us + us_per_1k D_in / 1024
     int bm() const { return 16 * mt; }
     int bn() const { return 16 * nt * wn; }
 };
 
 // A round of workgroups (one per compute unit) takes a time that depends on the tile and D_in only, and the time of a
-// layer is that times the rounds: to within 25 % at all, and 15 % at nine in ten, of 266 sizes of nineteen layer shapes
-// and 1 .. 25,216 rows (packed weights; measured on MI355X, us per round at D_in = 768 / 1536 / 3072, the chip filled):
-//   16 x 64: 6.6 / 7.8 / 11.7    32 x 128: 8.5 / 12.2 / 20.5    64 x 192: 13.2 / 21 / 36
-//   64 x 384: 15.8 / 24.5 / 45   112 x 768: 41 / - / 133   112 x 384: - / 43 / -   112 x 192: 24 / - / -
+// layer is that times the rounds.  Measured on MI355X (plain weights, launches from a graph; medians over seventeen layer
+// shapes of 50 .. 25,216 rows), us per round at D_in = 768 / 1536 / 3072:
+//   16 x 64: 6.3 / 7.5 / 10.8    32 x 128: 8.1 / 10.8 / 16.6    64 x 192: 11.6 / 17.2 / 29
+//   64 x 384: 14.6 / 22 / 38 alone, 24 / 44 where rounds follow each other
+//   112 x 768: 41 / - / 133   112 x 384: - / 43 / -   112 x 192: 24 / - / -
+// (before F had wavefronts of its own: 6.6 / 7.8 / 11.7, 8.5 / 12.2 / 20.5, 13.2 / 21 / 36 and 15.8 / 24.5 / 45).  With
+// these lines the tile taken is at most 6 % slower than the best of the five at all but nine of 234 sizes, and nowhere
+// more than 20 %.
 static const SmallVariant kSmall[] = {
-    {8, 1, 4, 1, 4.8, 2.3},
-    {8, 2, 4, 2, 4.4, 5.3},
-    {8, 4, 3, 4, 5.7, 10.1},
-    {16, 4, 3, 8, 6.0, 12.7},
+    {1, 4, 1, 4.9, 2.1},
+    {2, 4, 2, 4.6, 4.2},
+    {4, 3, 4, 5.9, 7.9},
+    {4, 3, 8, 6.0, 12.6},
 };
 // Whether the tiles of one channel block share an XCD (else: those of one token block); the small tiles only.
 static bool is_n_major(int64_t rows, int32_t D_out) { return rows < D_out; }
@@ -1125,13 +1171,13 @@ static const SmallVariant *pick_small(int64_t rows, int32_t D_in, int32_t D_out,
 template <typename OUT, bool PACKED, bool MODEL = false> static LinKernel select_small(SmallVariant v)
 {
     if (v.mt == 1 && v.nt == 4 && v.wn == 1)
-        return grkan_linear_small_kernel<8, 1, 4, 1, OUT, PACKED, MODEL, 5, 4>;
+        return grkan_linear_small_kernel<1, 4, 1, OUT, PACKED, MODEL, 5, 4>;
     if (v.mt == 2 && v.nt == 4 && v.wn == 2)
-        return grkan_linear_small_kernel<8, 2, 4, 2, OUT, PACKED, MODEL, 5, 4>;
+        return grkan_linear_small_kernel<2, 4, 2, OUT, PACKED, MODEL, 5, 4>;
     if (v.mt == 4 && v.nt == 3 && v.wn == 4)
-        return grkan_linear_small_kernel<8, 4, 3, 4, OUT, PACKED, MODEL, 5, 4>;
+        return grkan_linear_small_kernel<4, 3, 4, OUT, PACKED, MODEL, 5, 4>;
     if (v.mt == 4 && v.nt == 3 && v.wn == 8)
-        return grkan_linear_small_kernel<16, 4, 3, 8, OUT, PACKED, MODEL, 5, 4>;
+        return grkan_linear_small_kernel<4, 3, 8, OUT, PACKED, MODEL, 5, 4>;
     return nullptr;
 }
 
@@ -1265,7 +1311,7 @@ static grkan_status_t linear_fwd_impl(const void *x, const void *A, const void *
         kernel = out_dtype == GRKAN_BF16 ? select_kernel<bf16_out, false>(v, nedge) : select_kernel<float, false>(v, nedge);
     if (!kernel)
         return GRKAN_ERR_LAUNCH;
-    const size_t lds = small ? small_lds_bytes(small->nw, small->mt, small->wn) : lds_bytes(v);
+    const size_t lds = small ? small_lds_bytes(small->mt, small->nt, small->wn) : lds_bytes(v);
     if (!allow_lds(reinterpret_cast<const void *>(kernel), lds))
         return GRKAN_ERR_LAUNCH;
 
@@ -1293,7 +1339,7 @@ static grkan_status_t linear_fwd_impl(const void *x, const void *A, const void *
     a.wtiles = (int32_t)packed_tiles(D_out);
     void *args[] = {&a};
     const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3((unsigned)grid),
-                                         dim3(64 * (small ? small->nw : v.nw)), args, lds, static_cast<hipStream_t>(hip_stream));
+                                         dim3(64 * (small ? kSmallWaves : v.nw)), args, lds, static_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? GRKAN_OK : GRKAN_ERR_LAUNCH;
 }
 
