@@ -322,6 +322,32 @@ grkan_status_t grkan_linear_wgrad(const void *dout, const void *y, void *dW, voi
                                   grkan_dtype_t io, void *hip_stream);
 
 /*
+ * The hidden activation of a KAT MLP block in training: the product that makes or receives it and the second layer's
+ * rational function on it, in one kernel each way, on a bfloat16 model's own parameters.
+ *
+ *   grkan_hidden_fwd:  h[r, o] = sum_k W[o, k] y[r, k] (+ bias[o])     f = F(h)
+ *   grkan_hidden_bwd:  dF[r, c] = sum_k dout[r, k] W[k, c]             dh, dA, dB = backward of F at h
+ *
+ * h is rounded to bfloat16 and F evaluated on what is kept, as grkan_fwd on it; dF is rounded to bfloat16 too.  F's degrees are
+ * (5, 4); y / dout [rows, K], W [N, K] forward and [K, N] backward, h, f, dh [rows, N], bias [N] or NULL, A [G, 6] (or
+ * [6], shared_numerator), B [G, 4] and their gradients: DEVICE, bfloat16, contiguous; all but A, B, dA and dB 16-byte
+ * aligned.  dA and dB are overwritten; a shared numerator's are the groups' rounded gradients, added in float32 (as
+ * grkan_bwd_model).  Sums have a fixed order.
+ * grkan_hidden_supported: K of 192, 256 or 384, N a multiple of 384 (K = 256: of 256) and at most 32 times that, N / G a
+ * multiple of 32, at most 2^30 rows.  Anything else is GRKAN_ERR_UNSUPPORTED.
+ * workspace: grkan_hidden_workspace_bytes() bytes of device scratch, untouched until the enqueued work has finished.
+ */
+int32_t grkan_hidden_supported(int32_t K, int32_t N, int32_t G);
+size_t grkan_hidden_workspace_bytes(int64_t rows, int32_t K, int32_t N, int32_t G);
+grkan_status_t grkan_hidden_fwd(const void *y, const void *W, const void *bias, const void *A, const void *B,
+                                void *h, void *f, int64_t rows, int32_t K, int32_t N, int32_t G,
+                                int32_t shared_numerator, void *hip_stream);
+grkan_status_t grkan_hidden_bwd(const void *dout, const void *W, const void *h, const void *A, const void *B,
+                                void *dh, void *dA, void *dB, void *workspace, size_t workspace_bytes,
+                                int64_t rows, int32_t K, int32_t N, int32_t G, int32_t shared_numerator,
+                                void *hip_stream);
+
+/*
  * grkan_bwd for callers that cannot allocate device memory or pass a workspace:
  * code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Same arguments, results and kernels as grkan_bwd (bit-identical

@@ -95,6 +95,14 @@ def load_library():
     lib.grkan_linear_wgrad.restype = ctypes.c_int
     lib.grkan_linear_wgrad_workspace_bytes.argtypes = [i64, i32, i32]
     lib.grkan_linear_wgrad_workspace_bytes.restype = sz
+    lib.grkan_hidden_supported.argtypes = [i32, i32, i32]
+    lib.grkan_hidden_supported.restype = i32
+    lib.grkan_hidden_workspace_bytes.argtypes = [i64, i32, i32, i32]
+    lib.grkan_hidden_workspace_bytes.restype = sz
+    lib.grkan_hidden_fwd.argtypes = [vp, vp, vp, vp, vp, vp, vp, i64, i32, i32, i32, i32, vp]
+    lib.grkan_hidden_fwd.restype = ctypes.c_int
+    lib.grkan_hidden_bwd.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp, sz, i64, i32, i32, i32, i32, vp]
+    lib.grkan_hidden_bwd.restype = ctypes.c_int
     lib.grkan_linear_estimate_us.argtypes = [i64, i32, i32]
     lib.grkan_linear_estimate_us.restype = ctypes.c_double
     lib.grkan_linear_tile.argtypes = [i64, i32, i32, ctypes.POINTER(i32), ctypes.POINTER(i32)]

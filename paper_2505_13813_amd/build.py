@@ -10,7 +10,7 @@ PKG = Path(__file__).resolve().parent
 CSRC = PKG / "csrc"
 LIB = PKG / "libgrkan.so"
 SOURCES = [CSRC / "grkan_kernels.hip", CSRC / "grkan_plan.cpp", CSRC / "grkan_alg1_baseline.hip",
-           CSRC / "grkan_linear.hip", CSRC / "grkan_linear_grad.hip"]
+           CSRC / "grkan_linear.hip", CSRC / "grkan_linear_grad.hip", CSRC / "grkan_hidden.hip"]
 HEADERS = [CSRC / "grkan_walk.h", CSRC / "grkan_plan.h", CSRC / "grkan_elem.h", PKG.parent / "include" / "grkan.h",
            PKG.parent / "include" / "grkan_alg1.h"]
 

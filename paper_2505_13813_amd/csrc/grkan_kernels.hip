@@ -36,63 +36,6 @@
 
 namespace grkan {
 
-// Eq. "grad_x", "grad_a", "grad_b" for one element; returns dx and adds this
-// element's M + 1 + N terms to acc (acc[0..M] numerator, acc[M+1..M+N]
-// denominator, the latter with the opposite sign until negate_b_sums is
-// applied).  P/Q^2 is formed as (P r) r with r = 1/Q, so Q^2 is never computed.
-// MASKED: `skip` keeps the element out of the sums (powers and weights become zeros, whatever x is).
-template <bool WIDE, int M, int N, bool MASKED = false>
-__device__ __forceinline__ float bwd_elem(float x, float d, const Coef<M, N> &c, float (&acc)[M + 1 + N], bool skip = false)
-{
-    // x^k: squares for even k, one more factor x for odd k
-    constexpr int K = M > N ? M : N;
-    const float xs = MASKED && skip ? 0.0f : x;
-    float pw[K + 1];
-    pw[0] = 1.0f;
-    pw[1] = xs;
-#pragma unroll
-    for (int k = 2; k <= K; ++k)
-        pw[k] = (k % 2 == 0) ? pw[k / 2] * pw[k / 2] : pw[k - 1] * xs;
-
-    const float p = numerator_of(x, c);
-
-    float dp = c.da[M];
-#pragma unroll
-    for (int i = M - 1; i >= 1; --i)
-        dp = fmaf(dp, x, c.da[i]);
-
-    const float aden = aden_of<WIDE>(x, c);
-
-    float dh = c.db[N - 1];
-#pragma unroll
-    for (int j = N - 2; j >= 0; --j)
-        dh = fmaf(dh, x, c.db[j]);
-
-    const float q = 1.0f + fabsf(aden);
-    const float r = __builtin_amdgcn_rcpf(q);
-
-    const float t = d * r; // dy / Q
-    const float ts = MASKED && skip ? 0.0f : t;
-    acc[0] += ts;
-#pragma unroll
-    for (int i = 1; i <= M; ++i)
-        acc[i] = fmaf(ts, pw[i], acc[i]);
-
-    // s / Q with s = sign(Aden), sign(0) = 0: r > 0, so the sign is copied onto it bitwise
-    const float sr = aden != 0.0f ? __builtin_copysignf(r, aden) : 0.0f;
-    // acc[M+1..] collect +dy s P x^j / Q^2; the minus sign of Eq. "grad_b" is
-    // applied once per lane after the loop (negate_b_sums)
-    const float wb = t * (p * sr); // (dy / Q) (P s / Q) = dy s P / Q^2
-    const float ws = MASKED && skip ? 0.0f : wb;
-#pragma unroll
-    for (int j = 1; j <= N; ++j)
-        acc[M + j] = fmaf(ws, pw[j], acc[M + j]);
-
-    // dx = dy (P'/Q - s Aden' P/Q^2) = (dy/Q) P' - (dy s P/Q^2) Aden'
-    const float dx = fmaf(t, dp, -(wb * dh));
-    return dx;
-}
-
 // Global-memory (address space 1) byte pointers.  The loop-carried chunk base
 // is wave-uniform; passing its two halves through readfirstlane keeps it in
 // scalar registers, so that the memory instructions take the "scalar base +
@@ -118,13 +61,6 @@ __device__ __forceinline__ uint64_t uniform_u64(uint64_t v)
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
     return ((uint64_t)hi << 32) | lo;
-}
-
-template <int M, int N> __device__ __forceinline__ void negate_b_sums(float (&acc)[M + 1 + N])
-{
-#pragma unroll
-    for (int k = M + 1; k < M + 1 + N; ++k)
-        acc[k] = -acc[k];
 }
 
 // --------------------------------------------------------------------------
@@ -283,28 +219,6 @@ __device__ __forceinline__ void store_vec(gptr_t p, const float (&in)[VEC])
     } else {
         __builtin_nontemporal_store(r, (__attribute__((address_space(1))) Raw *)p);
     }
-}
-
-// --------------------------------------------------------------------------
-// wavefront sum with DPP: quad swaps, half-row and row mirrors, then the two
-// row broadcasts; the total of all 64 lanes ends in lane 63.
-// --------------------------------------------------------------------------
-template <int CTRL, int ROW_MASK> __device__ __forceinline__ float dpp_get(float v)
-{
-    // lanes whose row is masked off receive 0
-    return __builtin_bit_cast(
-        float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROW_MASK, 0xf, false));
-}
-
-__device__ __forceinline__ float wave_sum(float v)
-{
-    v += dpp_get<0xB1, 0xf>(v);  // quad_perm [1,0,3,2]
-    v += dpp_get<0x4E, 0xf>(v);  // quad_perm [2,3,0,1]
-    v += dpp_get<0x141, 0xf>(v); // row_half_mirror
-    v += dpp_get<0x140, 0xf>(v); // row_mirror: every lane of a row holds the row's sum
-    v += dpp_get<0x142, 0xa>(v); // row_bcast:15 into rows 1 and 3
-    v += dpp_get<0x143, 0xc>(v); // row_bcast:31 into rows 2 and 3
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
 // --------------------------------------------------------------------------
@@ -1175,6 +1089,22 @@ struct Workspace {
     void *alloc_context;
 };
 
+grkan_status_t run_stage2(const float *partial, int32_t rows_per_group, const CoefRows &coef, void *dA, void *dB, int32_t G,
+                          int32_t m, int32_t n, hipStream_t stream)
+{
+    const DegreeOps *const ops = degree_ops(m, n);
+    if (!ops)
+        return GRKAN_ERR_DEGREE;
+    int32_t G_shared = coef.a_stride == 0 ? G : 0;
+    int32_t bf16 = coef.bf16;
+    void *args[] = {&partial, &rows_per_group, &dA, &dB, &G_shared, &bf16};
+    const int threads = G_shared > 0 ? kStage2MaxThreads : stage2_threads(rows_per_group);
+    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(ops->stage2),
+                                         dim3((unsigned)G + (G_shared > 0 ? (unsigned)(m + 1) : 0u)), dim3(threads), args, 0,
+                                         stream);
+    return e == hipSuccess ? GRKAN_OK : GRKAN_ERR_LAUNCH;
+}
+
 static grkan_status_t bwd_impl(const void *x, const void *dy, const CoefRows &coef, void *dx, void *dA, void *dB,
                                const Workspace &ws, int64_t rows, int32_t D, int32_t G, int32_t m, int32_t n,
                                grkan_dtype_t io, void *hip_stream)
@@ -1246,16 +1176,7 @@ static grkan_status_t bwd_impl(const void *x, const void *dy, const CoefRows &co
     // Stage 1 writes every workspace row stage 2 reads (one per workgroup and group, zeros included),
     // so nothing has to be cleared beforehand; with no rows there are no workspace rows and stage 2
     // writes zeros.
-    const float *partial = a.partial;
-    int32_t rows_per_group = pl.partials_per_group;
-    int32_t G_shared = coef.a_stride == 0 ? G : 0;
-    int32_t bf16 = coef.bf16;
-    void *args2[] = {&partial, &rows_per_group, &dA, &dB, &G_shared, &bf16};
-    const int threads = G_shared > 0 ? kStage2MaxThreads : stage2_threads(rows_per_group);
-    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(ops->stage2),
-                                         dim3((unsigned)G + (G_shared > 0 ? (unsigned)(m + 1) : 0u)), dim3(threads), args2, 0,
-                                         stream);
-    return e == hipSuccess ? GRKAN_OK : GRKAN_ERR_LAUNCH;
+    return run_stage2(a.partial, pl.partials_per_group, coef, dA, dB, G, m, n, stream);
 }
 
 } // namespace grkan

@@ -27,5 +27,11 @@ bool make_overlapped(int64_t rows, int32_t D, int32_t G, grkan_dtype_t io, int32
 grkan_status_t walk_from_plan(int64_t rows, int32_t D, int32_t G, grkan_dtype_t io,
                               const grkan_plan_t &pl, Walk *walk);
 
+// Stage 2 of the backward pass (grkan_kernels.hip): adds `rows_per_group` workspace rows of m + 1 + n sums for each of the
+// G groups into dA / dB, which it overwrites; coef says whether the numerator is shared and of which type they are.
+struct CoefRows;
+grkan_status_t run_stage2(const float *partial, int32_t rows_per_group, const CoefRows &coef, void *dA, void *dB, int32_t G,
+                          int32_t m, int32_t n, struct ihipStream_t *stream);
+
 } // namespace grkan
 #endif // GRKAN_PLAN_H_

@@ -7,6 +7,7 @@
 // current GPU outside of tracing, function transforms, forward-mode differentiation, dispatch modes and function
 // modes; the caller then takes the Python route, which handles or refuses the call as it always did.
 #include <torch/csrc/Exceptions.h>
+#include <torch/csrc/autograd/autograd.h>
 #include <torch/csrc/autograd/custom_function.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/csrc/jit/frontend/tracer.h>
@@ -186,6 +187,25 @@ struct Rational : public torch::autograd::Function<Rational> {
     }
 };
 
+// dW [D_out, D_in] and, where wanted, dbias [D_out] of out = y W^T + bias from the bfloat16 kernel, if it takes them.
+bool weight_gradients(Tensor dout2, Tensor y2, bool want_b, Tensor &dW, Tensor &db)
+{
+    dout2 = dout2.contiguous();
+    y2 = y2.contiguous();
+    const int64_t D_in = y2.size(1), D_out = dout2.size(1);
+    const size_t need = grkan_linear_wgrad_workspace_bytes(dout2.size(0), (int32_t)D_in, (int32_t)D_out);
+    if (need == 0 || reinterpret_cast<uintptr_t>(dout2.data_ptr()) % 16 != 0 || reinterpret_cast<uintptr_t>(y2.data_ptr()) % 16 != 0)
+        return false;
+    const Tensor ws = at::empty({(int64_t)need}, dout2.options().dtype(at::kByte));
+    dW = at::empty({D_out, D_in}, dout2.options());
+    if (want_b)
+        db = at::empty({D_out}, dout2.options());
+    check(grkan_linear_wgrad(dout2.data_ptr(), y2.data_ptr(), dW.data_ptr(), want_b ? db.data_ptr() : nullptr, ws.data_ptr(), need,
+                             dout2.size(0), (int32_t)D_in, (int32_t)D_out, GRKAN_BF16, stream_of(dout2)),
+          "grkan_linear_wgrad");
+    return true;
+}
+
 // out = y W^T + bias with dW and dbias from grkan_linear_wgrad; saves what torch's linear saves: each operand where
 // the gradient of the other is wanted.
 struct Product : public torch::autograd::Function<Product> {
@@ -218,28 +238,126 @@ struct Product : public torch::autograd::Function<Product> {
         // hook made of y is left to torch if it is not what was saved.
         if (want_w && !at::GradMode::is_enabled() && dout2.is_cuda() && plain(dout2, dout2.device()) &&
             plain(y2, dout2.device()) && dout2.scalar_type() == at::kBFloat16 && y2.scalar_type() == at::kBFloat16 &&
-            y2.size(0) == dout2.size(0)) {
-            dout2 = dout2.contiguous();
-            y2 = y2.contiguous();
-            const int64_t D_in = y2.size(1);
-            const size_t need = grkan_linear_wgrad_workspace_bytes(dout2.size(0), (int32_t)D_in, (int32_t)D_out);
-            if (need > 0 && reinterpret_cast<uintptr_t>(dout2.data_ptr()) % 16 == 0 &&
-                reinterpret_cast<uintptr_t>(y2.data_ptr()) % 16 == 0) {
-                const Tensor ws = at::empty({(int64_t)need}, dout2.options().dtype(at::kByte));
-                dW = at::empty({D_out, D_in}, dout2.options());
-                if (want_b)
-                    db = at::empty({D_out}, dout2.options());
-                check(grkan_linear_wgrad(dout2.data_ptr(), y2.data_ptr(), dW.data_ptr(), want_b ? db.data_ptr() : nullptr,
-                                         ws.data_ptr(), need, dout2.size(0), (int32_t)D_in, (int32_t)D_out, GRKAN_BF16,
-                                         stream_of(dout2)),
-                      "grkan_linear_wgrad");
-            }
-        }
+            y2.size(0) == dout2.size(0))
+            weight_gradients(dout2, y2, want_b, dW, db);
         if (want_w && !dW.defined())
             dW = dout2.t().mm(y2);
         if (want_b && !db.defined())
             db = dout2.sum(0);
         return {dy, dW, db};
+    }
+};
+
+// The two GR-KAN layers of an MLP block: f1 = F1(x), h = f1 W1^T + b1 and f2 = F2(h) in one kernel (and so are the product
+// with W2 and F2's gradients in the backward pass: dF2 is never written), out = f2 W2^T + b2.  Saves what the layers by
+// themselves save.  `wgrad1`, `wgrad2`: whether the layers' weight gradients take grkan_linear_wgrad at this size.
+struct Block : public torch::autograd::Function<Block> {
+    static Tensor forward(AutogradContext *ctx, const Tensor &x_in, const Tensor &A1, const Tensor &B1, const Tensor &W1,
+                          const Tensor &A2, const Tensor &B2, const Tensor &W2, const std::optional<Tensor> &b1,
+                          const std::optional<Tensor> &b2, bool wgrad1, bool wgrad2)
+    {
+        const Tensor x = x_in.contiguous();
+        const Sizes s1 = sizes_of(x, A1, B1);
+        const int64_t hidden = W1.size(0);
+        Tensor f1 = at::empty_like(x, at::MemoryFormat::Contiguous);
+        check(grkan_fwd_model(x.data_ptr(), A1.data_ptr(), B1.data_ptr(), f1.data_ptr(), s1.rows, s1.D, s1.G, s1.m, s1.n, GRKAN_BF16,
+                              GRKAN_BF16, s1.shared, stream_of(x)),
+              "grkan_fwd");
+        Tensor h = at::empty({s1.rows, hidden}, x.options()), f2 = at::empty({s1.rows, hidden}, x.options());
+        check(grkan_hidden_fwd(f1.data_ptr(), W1.data_ptr(), b1 ? b1->data_ptr() : nullptr, A2.data_ptr(), B2.data_ptr(), h.data_ptr(),
+                               f2.data_ptr(), s1.rows, s1.D, (int32_t)hidden, (int32_t)B2.size(0), A2.dim() == 1, stream_of(x)),
+              "grkan_hidden_fwd");
+        ctx->save_for_backward({x, A1, B1, W1, A2, B2, W2, b1 ? *b1 : Tensor(), b2 ? *b2 : Tensor(), f1, h, f2});
+        ctx->saved_data["biases"] = (int64_t)(b1 ? 1 : 0) + (b2 ? 2 : 0);
+        ctx->saved_data["wgrad"] = (int64_t)(wgrad1 ? 1 : 0) + (wgrad2 ? 2 : 0);
+        auto shape = x.sizes().vec();
+        shape.back() = W2.size(0);
+        return at::linear(f2, W2, b2).view(shape);
+    }
+
+    // A saved tensor as its hooks returned it, in the form the kernels read.
+    static Tensor as_saved(const Tensor &t, const Tensor &like, at::IntArrayRef sizes)
+    {
+        TORCH_CHECK_VALUE(t.defined() && t.device() == like.device() && t.layout() == at::kStrided, "grkan runs on the GPU only: tensors must be on one HIP device");
+        TORCH_CHECK_TYPE(t.scalar_type() == at::kBFloat16, "saved tensors must be bfloat16");
+        TORCH_CHECK_VALUE(t.sizes() == sizes, "a saved tensor has another shape");
+        const Tensor c = t.contiguous();
+        return reinterpret_cast<uintptr_t>(c.data_ptr()) % 16 == 0 ? c : c.clone();
+    }
+
+    static variable_list backward(AutogradContext *ctx, const variable_list &grads)
+    {
+        const auto saved = ctx->get_saved_variables();
+        variable_list out(11);
+        if (!grads[0].defined())
+            return out;
+        const int64_t biases = ctx->saved_data["biases"].toInt(), wgrad = ctx->saved_data["wgrad"].toInt();
+        const bool has1 = (biases & 1) != 0, has2 = (biases & 2) != 0;
+        const Tensor &x_ = saved[0], &A1 = saved[1], &B1 = saved[2], &W1_ = saved[3], &A2 = saved[4], &B2 = saved[5], &W2_ = saved[6];
+        const std::optional<Tensor> b1 = has1 ? std::optional<Tensor>(saved[7]) : std::nullopt;
+        const std::optional<Tensor> b2 = has2 ? std::optional<Tensor>(saved[8]) : std::nullopt;
+        if (at::GradMode::is_enabled()) {
+            // a graph of this pass is wanted: the same through the layers' own functions, of which it is made
+            const Tensor y = Product::apply(Rational::apply(Product::apply(Rational::apply(x_, A1, B1), W1_, b1), A2, B2), W2_, b2);
+            std::vector<int> of{0, 1, 2, 3, 4, 5, 6};
+            if (has1)
+                of.push_back(7);
+            if (has2)
+                of.push_back(8);
+            variable_list inputs;
+            std::vector<int> at;
+            for (size_t i = 0; i < of.size(); ++i)
+                if (ctx->needs_input_grad(i) && saved[of[i]].requires_grad()) {
+                    inputs.push_back(saved[of[i]]);
+                    at.push_back(of[i]);
+                }
+            if (!inputs.empty()) {
+                const variable_list got = torch::autograd::grad({y}, inputs, {grads[0]}, true, true, true);
+                for (size_t i = 0; i < at.size(); ++i)
+                    out[at[i]] = got[i];
+            }
+            return out;
+        }
+        const bool want_b1 = has1 && ctx->needs_input_grad(7), want_b2 = has2 && ctx->needs_input_grad(has1 ? 8 : 7);
+        const bool want_w1 = ctx->needs_input_grad(3), want_w2 = ctx->needs_input_grad(6);
+        const bool want_first = ctx->needs_input_grad(0) || ctx->needs_input_grad(1) || ctx->needs_input_grad(2);
+        const bool want_dh = want_first || want_w1 || want_b1 || ctx->needs_input_grad(4) || ctx->needs_input_grad(5);
+        const Tensor x = as_saved(x_, grads[0], x_.sizes());
+        const int64_t D = x.size(-1), rows = x.numel() / D, hidden = W1_.size(0);
+        const Tensor dout = as_saved(grads[0].reshape({rows, W2_.size(0)}), x, {rows, W2_.size(0)});
+        const Tensor f2 = as_saved(saved[11], x, {rows, hidden});
+        gradients_of(dout, f2, want_w2, want_b2, (wgrad & 2) != 0, out[6], out[8]);
+        if (!want_dh)
+            return out;
+        const Tensor W2 = as_saved(W2_, x, {D, hidden}), h = as_saved(saved[10], x, {rows, hidden});
+        check_saved(h, h, A2, B2);
+        Tensor dh = at::empty_like(h);
+        out[4] = at::empty_like(A2);
+        out[5] = at::empty_like(B2);
+        {
+            const int32_t G = (int32_t)B2.size(0);
+            const size_t need = grkan_hidden_workspace_bytes(rows, (int32_t)D, (int32_t)hidden, G);
+            const Tensor ws = at::empty({(int64_t)need}, x.options().dtype(at::kByte));
+            check(grkan_hidden_bwd(dout.data_ptr(), W2.data_ptr(), h.data_ptr(), A2.data_ptr(), B2.data_ptr(), dh.data_ptr(),
+                                   out[4].data_ptr(), out[5].data_ptr(), ws.data_ptr(), need, rows, (int32_t)D, (int32_t)hidden, G,
+                                   A2.dim() == 1, stream_of(x)),
+                  "grkan_hidden_bwd");
+        }
+        if (want_w1 || want_b1)
+            gradients_of(dh, as_saved(saved[9], x, x.sizes()).view({rows, D}), want_w1, want_b1, (wgrad & 1) != 0, out[3], out[7]);
+        if (want_first)
+            std::tie(out[0], out[1], out[2]) = Rational::gradients(x, dh.mm(W1_).view(x.sizes()), A1, B1);
+        return out;
+    }
+
+    static void gradients_of(const Tensor &dout, const Tensor &y, bool want_w, bool want_b, bool wgrad, Tensor &dW, Tensor &db)
+    {
+        if (want_w && wgrad && weight_gradients(dout, y, want_b, dW, db))
+            return;
+        if (want_w)
+            dW = dout.t().mm(y);
+        if (want_b)
+            db = dout.sum(0);
     }
 };
 
@@ -270,6 +388,34 @@ std::optional<Tensor> product(const Tensor &y, const Tensor &W, const std::optio
         W.dim() != 2 || y.dim() < 1 || y.size(-1) != W.size(1) || !W.is_contiguous())
         return std::nullopt;
     return Product::apply(y, W, bias);
+}
+
+// The MLP block in training, with a gradient wanted for its input and every parameter.  (Hooks and the like on its
+// modules are the caller's to check.)
+std::optional<Tensor> block(const Tensor &x, const Tensor &A1, const Tensor &B1, const Tensor &W1, const std::optional<Tensor> &b1,
+                            const Tensor &A2, const Tensor &B2, const Tensor &W2, const std::optional<Tensor> &b2, bool wgrad1,
+                            bool wgrad2)
+{
+    if (!plain_context() || !on_current_gpu(x))
+        return std::nullopt;
+    for (const Tensor *t : {&x, &A1, &B1, &W1, &A2, &B2, &W2, b1 ? &*b1 : &W1, b2 ? &*b2 : &W2})
+        if (!plain(*t, x.device()) || t->scalar_type() != at::kBFloat16 || !t->requires_grad() || (t != &x && !t->is_contiguous()))
+            return std::nullopt;
+    if (x.dim() < 1 || x.numel() == 0 || W1.dim() != 2 || W2.dim() != 2 || x.size(-1) != W1.size(1) || W2.size(1) != W1.size(0) ||
+        W2.size(0) != W1.size(1) || (b1 && (b1->dim() != 1 || b1->size(0) != W1.size(0))) || (b2 && (b2->dim() != 1 || b2->size(0) != W2.size(0))))
+        return std::nullopt;
+    auto coefficients = [](const Tensor &A, const Tensor &B, int64_t channels) {
+        return B.dim() == 2 && B.size(1) == 4 && A.dim() >= 1 && A.dim() <= 2 && A.size(-1) == 6 &&
+               (A.dim() == 1 || A.size(0) == B.size(0)) && B.size(0) > 0 && channels % B.size(0) == 0;
+    };
+    const int64_t D = W1.size(1), hidden = W1.size(0);
+    if (D > INT32_MAX || hidden > INT32_MAX || !coefficients(A1, B1, D) || !coefficients(A2, B2, hidden) ||
+        x.numel() / D > ((int64_t)1 << 30) || !grkan_hidden_supported((int32_t)D, (int32_t)hidden, (int32_t)B2.size(0)))
+        return std::nullopt;
+    for (const Tensor *t : {&W1, &W2, b1 ? &*b1 : &W1})
+        if (reinterpret_cast<uintptr_t>(t->data_ptr()) % 16 != 0)
+            return std::nullopt;
+    return Block::apply(x, A1, B1, W1, A2, B2, W2, b1, b2, wgrad1, wgrad2);
 }
 
 // What layer_packed reads of a layer's parameters: the packed weights, the bias, and a row of coefficients for every
@@ -421,6 +567,15 @@ PYBIND11_MODULE(_native, mod)
         const Tensor y = args.tensor(y_), W = args.tensor(W_);
         const std::optional<Tensor> bias = args.optional(bias_);
         return args.call([&] { return product(y, W, bias); });
+    });
+    mod.def("block", [](handle x_, handle A1_, handle B1_, handle W1_, handle b1_, handle A2_, handle B2_, handle W2_, handle b2_,
+                        bool wgrad1, bool wgrad2) {
+        Arguments args;
+        const Tensor x = args.tensor(x_), A1 = args.tensor(A1_), B1 = args.tensor(B1_), W1 = args.tensor(W1_);
+        const std::optional<Tensor> b1 = args.optional(b1_);
+        const Tensor A2 = args.tensor(A2_), B2 = args.tensor(B2_), W2 = args.tensor(W2_);
+        const std::optional<Tensor> b2 = args.optional(b2_);
+        return args.call([&] { return block(x, A1, B1, W1, b1, A2, B2, W2, b2, wgrad1, wgrad2); });
     });
     mod.def("layer_model", [](handle x_, handle A_, handle B_, handle W_, handle bias_) {
         Arguments args;

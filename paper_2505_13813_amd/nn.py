@@ -495,11 +495,40 @@ class KATMlp(nn.Module):
                  degrees: Tuple[int, int] = (M_DEGREE, N_DEGREE), fused: str = "inference"):
         super().__init__()
         hidden = 4 * dim if hidden is None else hidden
-        # in training the library product after the elementwise kernel is the faster route for fc1
+        # in training a product after the elementwise kernel is the faster route for fc1
         self.fc1 = GRKANLinear(dim, hidden, groups, init="identity", degrees=degrees,
                                fused="never" if fused == "never" else "inference")
         self.fc1._keep_packed = False
         self.fc2 = GRKANLinear(hidden, dim, groups, init="swish", degrees=degrees, fused=fused)
 
     def forward(self, x):
-        return self.fc2(self.fc1(x))
+        out = self._native_block(x)
+        return self.fc2(self.fc1(x)) if out is None else out
+
+    def _native_block(self, x):
+        """The block in bfloat16 training as one native autograd function (the hidden activation's product and rational
+        function in one kernel each way), or None where that route is not taken: where calling the two layers would do
+        anything else than their parts do, or a parameter or x takes no gradient.  A pass without a gradient in training
+        mode may be the first half of one with (reentrant checkpointing): both take the same kernels."""
+        if x.dtype is not torch.bfloat16 or not (torch.is_grad_enabled() or self.training) or not x.requires_grad:
+            return None
+        if torch.is_autocast_enabled() or torch.compiler.is_compiling():
+            return None
+        params = []
+        for fc in (self._modules.get("fc1"), self._modules.get("fc2")):
+            if not _only_a(GRKANLinear, fc) or fc.fused == "always":
+                return None
+            linear, rational = fc._modules.get("linear"), fc._modules.get("rational")
+            if not _only_a(nn.Linear, linear) or not _only_a(GroupRational, rational) or "coefficient_rows" in rational.__dict__:
+                return None
+            params += [rational._parameters.get("numerator"), rational._parameters.get("denominator"),
+                       linear._parameters.get("weight"), linear._parameters.get("bias")]
+        for i, p in enumerate(params):
+            if type(p) is not nn.Parameter and not (p is None and i % 4 == 3):
+                return None
+        dim = x.shape[-1] if x.dim() else 0
+        hidden = params[2].shape[0] if params[2].dim() else 0
+        if not dim or not hidden:
+            return None
+        pays = wgrad_pays(x.numel() // dim, dim, hidden)
+        return binding.load_native().block(x, *params, pays, pays)
