@@ -333,7 +333,7 @@ grkan_status_t grkan_linear_wgrad(const void *dout, const void *y, void *dW, voi
  * [6], shared_numerator), B [G, 4] and their gradients: DEVICE, bfloat16, contiguous; all but A, B, dA and dB 16-byte
  * aligned.  dA and dB are overwritten; a shared numerator's are the groups' rounded gradients, added in float32 (as
  * grkan_bwd_model).  Sums have a fixed order.
- * grkan_hidden_supported: K of 192, 256 or 384, N a multiple of 384 (K = 256: of 256) and at most 32 times that, N / G a
+ * grkan_hidden_supported: K of 192, 256, 384, 512, 640 or 768, N a multiple of 256 (K = 192 and 384: of 384) and at most 32 times that, N / G a
  * multiple of 32, at most 2^30 rows.  Anything else is GRKAN_ERR_UNSUPPORTED.
  * workspace: grkan_hidden_workspace_bytes() bytes of device scratch, untouched until the enqueued work has finished.
  */

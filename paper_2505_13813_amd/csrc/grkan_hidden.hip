@@ -5,7 +5,7 @@
 //   forward    h = X W^T + bias  (bfloat16, kept for the backward pass),  f = F(h)
 //   backward   dF = dY W  (bfloat16, never written),  dh = dF F'(h),  dA, dB
 //
-// Both products contract over the block's width K (192 .. 384) into the wide hidden dimension N = 4 K: 25,216 tokens of
+// Both products contract over the block's width K (192 .. 768) into the wide hidden dimension N = 4 K: 25,216 tokens of
 // 384 -> 1536 are 30 GFLOP, 20 us at the matrix cores' rate, around 77 MB of result.  A library product runs this
 // short contraction at 420 - 560 TFLOP/s and leaves the result to be read again.
 //
@@ -38,7 +38,6 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef const __attribute__((address_space(1))) char *gcptr_t;
 typedef __attribute__((address_space(1))) char *gptr_t;
 
-constexpr int kTileRows = 32;   // tokens of a tile
 constexpr int kM = 5, kN = 4, kSums = kM + 1 + kN;
 
 struct Args {
@@ -56,11 +55,11 @@ struct Args {
 
 // The shape of a variant.  KS: contraction in steps of 32; KR: of these in registers, the others in LDS; NT: 16-channel
 // tiles of a wavefront.
-template <int KS, int KR, int NT, int NW> struct Shape {
+template <int KS, int KR, int NT, int NW, int TR> struct Shape {
     static constexpr int K = 32 * KS, CW = 16 * NT;
     static constexpr int kPieces = K / 8;                                    // 16-byte pieces of a token's row
     static constexpr uint32_t kPitch = K * 2 + 16;                           // rows 16 bytes apart from the next bank
-    static constexpr uint32_t kXBuf = kTileRows * kPitch;
+    static constexpr uint32_t kXBuf = TR * kPitch;
     static constexpr int kKept = KS - KR > 2 ? KS - KR : 2;                  // steps a wavefront's own LDS holds (two while loading)
     static constexpr uint32_t kOwn = kKept * NT * 1024u;
     static constexpr size_t kLds = 2 * kXBuf + NW * kOwn;
@@ -159,10 +158,11 @@ __device__ __forceinline__ u32x4 rational8(const u32x4 &w, const Coef<kM, kN> &c
     return y;
 }
 
-template <int KS, int KR, int NT, int NW, bool BWD>
+template <int KS, int KR, int NT, int NW, int TR, bool BWD>
 __global__ __launch_bounds__(64 * NW, NW / 4) void hidden_kernel(const Args a)
 {
-    using S = Shape<KS, KR, NT, NW>;
+    using S = Shape<KS, KR, NT, NW, TR>;
+    constexpr int kTileRows = TR;
     extern __shared__ __align__(16) char smem[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
     const int tid = threadIdx.x;
@@ -419,15 +419,15 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void hidden_kernel(const Args a)
 using Kernel = void (*)(const Args);
 
 struct Variant {
-    int32_t K, CW, waves;
+    int32_t K, CW, waves, tile_rows;
     size_t lds;
     Kernel fwd, bwd;
 };
 
-template <int KS, int KR, int NT, int NW> static constexpr Variant variant()
+template <int KS, int KR, int NT, int NW, int TR = 32> static constexpr Variant variant()
 {
-    using S = Shape<KS, KR, NT, NW>;
-    return Variant{S::K, S::CW, NW, S::kLds, hidden_kernel<KS, KR, NT, NW, false>, hidden_kernel<KS, KR, NT, NW, true>};
+    using S = Shape<KS, KR, NT, NW, TR>;
+    return Variant{S::K, S::CW, NW, TR, S::kLds, hidden_kernel<KS, KR, NT, NW, TR, false>, hidden_kernel<KS, KR, NT, NW, TR, true>};
 }
 
 // us at 25,216 rows, forward / backward (two 16-channel tiles a wavefront but for the last column; twelve wavefronts are
@@ -435,7 +435,10 @@ template <int KS, int KR, int NT, int NW> static constexpr Variant variant()
 //   K = 192: 12 wavefronts 20.3 / 37.9   8: 21.9 / 37.6                                 8 of 96 channels 24.2 / 44.5
 //   K = 256:  8 wavefronts 26.5 / 46.2  16: 25.7 / 66 (spills)                          8 of 64 channels 27.9 / 46.9
 //   K = 384: 12 wavefronts 44.1 / 69.9 (two steps of the weights in LDS)  8: 47.0 / 75.2   8 of 64 channels 44.0 / 78.4
-static const Variant kVariants[] = {variant<6, 6, 2, 12>(), variant<8, 8, 2, 8>(), variant<12, 10, 2, 12>()};
+//   K = 512:  8 wavefronts 81.6 / 110 (library product + rational function of its own: 116 / 147)
+//   K = 640:  8 wavefronts 112 / 155 (129 / 177)    K = 768: 8 wavefronts 164 / 237 (167 / 223); 6,304 rows 48 / 72 (65 / 68)
+static const Variant kVariants[] = {variant<6, 6, 2, 12>(), variant<8, 8, 2, 8>(), variant<12, 10, 2, 12>(), variant<16, 14, 2, 8>(),
+                                    variant<20, 16, 2, 8>(), variant<24, 18, 2, 8, 16>()};
 
 // The variant of a shape, or NULL: whole slabs of eight wavefronts, each within one coefficient group.
 static const Variant *variant_of(int32_t K, int32_t N, int32_t G)
@@ -465,7 +468,7 @@ static bool allow_lds(const Variant &v)
 static void divide(const Variant &v, int64_t rows, int32_t N, Args *a)
 {
     a->slabs = N / (v.waves * v.CW);
-    a->tiles = (int32_t)((rows + kTileRows - 1) / kTileRows);
+    a->tiles = (int32_t)((rows + v.tile_rows - 1) / v.tile_rows);
     const int32_t most = 8 * (32 / a->slabs), few = (a->tiles + 7) / 8 * 8;
     a->parts = few < most ? few : most;
 }

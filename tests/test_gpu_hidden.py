@@ -10,7 +10,8 @@ BF16 = 2.0 ** -8  # half a unit in the last place, relative
 # rows, K, N, G: one token, ragged last tiles, one tile, fewer tiles than parts, several tiles per part; one and several slabs,
 # groups of one and of several wavefronts, more than one group per wavefront's neighbours
 SHAPES = [(1, 192, 768, 8), (33, 192, 384, 4), (4133, 192, 768, 2), (31, 256, 256, 8), (2100, 256, 1024, 8), (4111, 256, 768, 24),
-          (32, 384, 384, 1), (47, 384, 1536, 8), (2090, 384, 1536, 48), (4001, 384, 768, 8)]
+          (32, 384, 384, 1), (47, 384, 1536, 8), (2090, 384, 1536, 48), (4001, 384, 768, 8), (75, 512, 512, 4),
+          (1040, 640, 768, 8), (531, 768, 1024, 8)]
 
 
 def _operands(torch, rows, K, N, G):

@@ -7,11 +7,11 @@ STATUS = {"NULL": 1, "SHAPE": 2, "ALIGN": 4, "WORKSPACE": 5, "UNSUPPORTED": 8}
 
 def test_supported_shapes():
     lib = binding.load_library()
-    for K, N, G, yes in ((192, 768, 8, 1), (256, 1024, 8, 1), (384, 1536, 8, 1), (384, 384, 12, 1), (256, 256, 1, 1),
+    for K, N, G, yes in ((192, 768, 8, 1), (256, 1024, 8, 1), (384, 1536, 8, 1), (384, 384, 12, 1), (256, 256, 1, 1), (512, 2048, 8, 1), (640, 2560, 8, 1),
                          (192, 768, 32, 0),                       # d_g = 24
                          (384, 1024, 8, 0), (192, 200, 1, 0),     # no whole slabs
                          (192, 384 * 33, 1, 0),                   # more slabs than an XCD has compute units
-                         (320, 1280, 8, 0), (768, 3072, 8, 0), (384, 1536, 7, 0), (384, 1536, 0, 0), (0, 0, 0, 0)):
+                         (320, 1280, 8, 0), (768, 3072, 8, 1), (896, 3584, 8, 0), (384, 1536, 7, 0), (384, 1536, 0, 0), (0, 0, 0, 0)):
         assert lib.grkan_hidden_supported(K, N, G) == yes, (K, N, G)
         assert (lib.grkan_hidden_workspace_bytes(1000, K, N, G) > 0) == bool(yes)
     # [G][parts x wavefronts of a part in the group][10 sums]: 64 parts of 4 slabs, d_g = 192 in wavefronts of 32
