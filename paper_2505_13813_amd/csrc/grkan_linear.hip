@@ -752,8 +752,7 @@ __global__ __launch_bounds__(64 * NW, 1) void grkan_linear_fwd_kernel(const LinA
 // alone 350 and 240), and a 64 x 384 tile has that ratio per block - and beside them L2 -> LDS (57 KB per block).  With
 // eight wavefronts that each did all of it, the F evaluations, the operand reads and the barriers stood in the way of the
 // matrix instructions: us per call before / now, the parameters of a bfloat16 model, launches from a graph:
-//   197 x 3072 -> 768   (16 x 64)  12.7 / 11.0     788 x 3072 -> 768   (32 x 128) 21.4 / 18.1
-//   6304 x 1536 -> 384  (64 x 192) 21.9 / 18.8     6304 x 3072 -> 768  (64 x 384) 46.6 / 42.5
+//   788 x 3072 -> 768 (32 x 128) 21.4 / 17.5    6304 x 1536 -> 384 (64 x 192) 21.9 / 18.8    6304 x 3072 -> 768 (64 x 384) 46.6 / 42.5
 // A walk over the 64-k blocks first, first + by, .. of a contraction.  (A few scalar instructions a step: a wavefront issues
 // one instruction in four to five clocks whatever its kind, so that even a scalar division per block shows.)
 struct BlockWalk {
@@ -771,6 +770,75 @@ struct BlockWalk {
     }
 };
 
+// The coefficients of group g1 where `second`, else of g0, in vector registers (two wavefronts issue instructions with a
+// scalar operand one after the other, those on vector registers together).
+template <bool MODEL, int M, int N>
+__device__ __forceinline__ void select_coefficients(const LinArgs &a, int g0, int g1, bool second, Coef<M, N> &c)
+{
+    RowWords<MODEL, M, N> r0, r1;
+    Coef<M, N> c0, c1;
+    r0.load(a, g0);
+    r1.load(a, g1);
+    r0.to(c0);
+    r1.to(c1);
+#pragma unroll
+    for (int j = 0; j <= M; ++j)
+        c.a[j] = second ? c1.a[j] : c0.a[j];
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+        c.b[j] = second ? c1.b[j] : c0.b[j];
+}
+
+// The 16-row weight tiles of a wavefront, tile i at channel n0 + 16 (first + i), and how they come to LDS and are read
+// there: 2 KB per tile and 64-k block.  Plain: a fetch brings 8 rows x 128 bytes, whole cache lines; which 16-byte piece of
+// its row a lane takes is permuted (line_swizzle).  A tile that reaches past Nout starts at its last sixteen rows instead
+// (some channels are then formed twice, with the same bits).  Packed: 16 rows x 32 k, as the copy is laid out.
+template <int NT, bool PACKED> struct WeightTiles {
+    uint64_t base[NT];
+    int32_t tile_n[NT];   // the tile's first channel, from n0
+    uint32_t stage_bytes; // packed: bytes per 32 k
+    uint32_t lane_at[2];
+    uint32_t op_lane, read0, read1; // operand reads: row lane % 16, piece lane / 16 of the first 32 k, and of the second
+    __device__ __forceinline__ WeightTiles(const LinArgs &a, int32_t n0, int first, int lane, uint32_t K2)
+        : stage_bytes((uint32_t)a.wtiles * 1024u)
+    {
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            tile_n[i] = 16 * (first + i);
+            if constexpr (PACKED) {
+                const int32_t t = (n0 + tile_n[i]) >> 4;
+                base[i] = reinterpret_cast<uint64_t>(a.W) + (uint64_t)(uint32_t)(t < a.wtiles ? t : a.wtiles - 1) * 1024u;
+            } else {
+                if (n0 + tile_n[i] > a.Nout - 16)
+                    tile_n[i] = (a.Nout > 16 ? a.Nout - 16 : 0) - n0;
+                base[i] = reinterpret_cast<uint64_t>(a.W) + (uint64_t)(uint32_t)(n0 + tile_n[i]) * K2;
+            }
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int row = 8 * h + (lane >> 3);
+            lane_at[h] = PACKED ? (uint32_t)lane * 16u
+                                : (uint32_t)(row < a.Nout ? row : a.Nout - 1) * K2 + (((uint32_t)lane ^ line_swizzle(row)) & 7u) * 16u;
+        }
+        // (in a packed tile the halves are 1 KB apart)
+        const uint32_t i16 = (uint32_t)lane & 15u, g4 = (uint32_t)lane >> 4;
+        op_lane = i16 * 128u + ((g4 ^ line_swizzle(i16)) * 16u);
+        read0 = PACKED ? i16 * kWRow + ((g4 ^ (((i16 >> 2) ^ (i16 >> 1)) & 3u)) * 16u) : op_lane;
+        read1 = PACKED ? read0 + 1024u : op_lane ^ 64u;
+    }
+    // tile i of the block at byte `kb` of a row to LDS at `at` (past: one address for all lanes, never read)
+    template <int i> __device__ __forceinline__ void fetch(uint32_t kb, bool past, lptr_t at)
+    {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            keep_in_loop(lane_at[h]);
+            const uint64_t src = PACKED ? base[i] + (uint64_t)((kb >> 6) + h) * stage_bytes : base[i] + kb;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)((gcptr_t)uniform_u64(src) + (past ? 0u : lane_at[h])),
+                                             (__attribute__((address_space(3))) void *)(at + h * 1024u), 16, 0, 0);
+        }
+    }
+};
+
 template <int MT, int NT, int WN, typename OUT, bool PACKED, bool MODEL, int M, int N>
 __global__ __launch_bounds__(64 * kSmallWaves, 1) void grkan_linear_small_kernel(const LinArgs a)
 {
@@ -783,8 +851,8 @@ __global__ __launch_bounds__(64 * kSmallWaves, 1) void grkan_linear_small_kernel
     constexpr int kRing = small_ring(NT);
     constexpr uint32_t kF0 = (uint32_t)kMulWaves * kRing * 2048u;
     // a unit's rows decide which pieces its lanes hold; two units of eight rows of one 16-row tile differ in that
-    constexpr int kSets = PU > 1 ? 2 : 1;
-    static_assert(WN * WK == kMulWaves && PU >= 1 && PU <= 2 && PU * kMulWaves == WK * KB * 2 * MT && 2 * MT % PU == 0,
+    constexpr int kSets = PU;
+    static_assert(WN * WK == kMulWaves && PU == 2 && PU * kMulWaves == WK * KB * 2 * MT && 2 * MT % PU == 0,
                   "the wavefronts share the units of a period evenly, each within one group");
     extern __shared__ __align__(16) char smem[];
     const lptr_t lds = (lptr_t)smem;
@@ -843,9 +911,7 @@ __global__ __launch_bounds__(64 * kSmallWaves, 1) void grkan_linear_small_kernel
                 v[u] = gload16(base, past ? 0u : x_lane[u]);
             }
         };
-        // Coefficients: a block may hold two groups of channels (32 k each), a lane's piece lies in one of them.  In vector
-        // registers: two wavefronts issue instructions with a scalar operand one after the other, those on vector registers
-        // together.
+        // Coefficients: a block may hold two groups of channels (32 k each), a lane's piece lies in one of them.
         Coef<M, N> c[kSets];
         uint32_t c_lo = 1, c_span = 0; // blocks that start in [c_lo, c_lo + c_span) have the coefficients held
         auto coef_for = [&]() {
@@ -856,29 +922,16 @@ __global__ __launch_bounds__(64 * kSmallWaves, 1) void grkan_linear_small_kernel
                 const int g1 = __builtin_amdgcn_readfirstlane((int)((k + 32u) / (uint32_t)a.dgc));
                 c_lo = g0 == g1 ? (uint32_t)g0 * (uint32_t)a.dgc : k;
                 c_span = g0 == g1 ? (uint32_t)a.dgc - 32u : 1u;
-                RowWords<MODEL, M, N> r0, r1;
-                Coef<M, N> c0, c1;
-                r0.load(a, g0);
-                r1.load(a, g1);
-                r0.to(c0);
-                r1.to(c1);
 #pragma unroll
-                for (int h = 0; h < kSets; ++h) {
-                    const bool second = ((lane ^ (int)line_swizzle(8 * (q0 + h) + (lane >> 3))) & 4) != 0;
-#pragma unroll
-                    for (int j = 0; j <= M; ++j)
-                        c[h].a[j] = second ? c1.a[j] : c0.a[j];
-#pragma unroll
-                    for (int j = 0; j < N; ++j)
-                        c[h].b[j] = second ? c1.b[j] : c0.b[j];
-                }
+                for (int h = 0; h < kSets; ++h)
+                    select_coefficients<MODEL, M, N>(a, g0, g1, ((lane ^ (int)line_swizzle(8 * (q0 + h) + (lane >> 3))) & 4) != 0, c[h]);
             }
         };
         const uint32_t f_own = lds0 + kF0 + (uint32_t)pb * 2u * kXB + (uint32_t)q0 * 1024u + (uint32_t)lane * 16u;
         auto f_block = [&](const u32x4 (&v)[PU], uint32_t slot_bytes) {
 #pragma unroll
             for (int u = 0; u < PU; ++u)
-                lds_write16(f_own + slot_bytes + (uint32_t)u * 1024u, rational_words(v[u], c[kSets == 2 ? u : 0]));
+                lds_write16(f_own + slot_bytes + (uint32_t)u * 1024u, rational_words(v[u], c[u]));
         };
 #pragma unroll
         for (int i = 0; i < kXAhead; ++i)
@@ -907,50 +960,11 @@ __global__ __launch_bounds__(64 * kSmallWaves, 1) void grkan_linear_small_kernel
         const int kg = wave / WN;
         BlockWalk ww(n_blocks, kg, WK);
 
-        // ---- W ring.  Plain: a fetch brings 8 rows x 128 bytes, whole cache lines; which 16-byte piece of its row a lane
-        // takes is permuted (line_swizzle).  A tile that reaches past Nout starts at its last sixteen rows instead (some
-        // channels are then formed twice, with the same bits).  Packed: 16 rows x 32 k, as the copy is laid out.
-        const uint32_t w_stage_bytes = (uint32_t)a.wtiles * 1024u; // packed: bytes per 32 k
-        int32_t tile_n[NT];                                        // the tile's first channel, from n0
-        uint64_t w_base[NT];
-#pragma unroll
-        for (int i = 0; i < NT; ++i) {
-            tile_n[i] = 16 * (NT * wn + i);
-            if constexpr (PACKED) {
-                const int32_t t = (n0 + tile_n[i]) >> 4;
-                w_base[i] = reinterpret_cast<uint64_t>(a.W) + (uint64_t)(uint32_t)(t < a.wtiles ? t : a.wtiles - 1) * 1024u;
-            } else {
-                if (n0 + tile_n[i] > a.Nout - 16)
-                    tile_n[i] = (a.Nout > 16 ? a.Nout - 16 : 0) - n0;
-                w_base[i] = reinterpret_cast<uint64_t>(a.W) + (uint64_t)(uint32_t)(n0 + tile_n[i]) * K2;
-            }
-        }
-        uint32_t w_lane[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int row = 8 * h + (lane >> 3);
-            w_lane[h] = PACKED ? (uint32_t)lane * 16u
-                               : (uint32_t)(row < a.Nout ? row : a.Nout - 1) * K2 + (((uint32_t)lane ^ line_swizzle(row)) & 7u) * 16u;
-        }
-        const uint32_t ring_at = (uint32_t)wave * (kRing * 2048u);
-        // operand reads: row i = lane % 16 of a 16-row tile, piece lane / 16 of its first 32 k (the second: bit 6 flipped);
-        // in a packed tile the halves are 1 KB apart
-        const uint32_t i16 = (uint32_t)lane & 15u, g4 = (uint32_t)lane >> 4;
-        const uint32_t op_lane = i16 * 128u + ((g4 ^ line_swizzle(i16)) * 16u);
-        const uint32_t op_packed = i16 * kWRow + ((g4 ^ (((i16 >> 2) ^ (i16 >> 1)) & 3u)) * 16u);
-        uint32_t w_read0 = lds0 + ring_at + (PACKED ? op_packed : op_lane);
-        uint32_t w_read1 = lds0 + ring_at + (PACKED ? op_packed + 1024u : op_lane ^ 64u);
+        WeightTiles<NT, PACKED> weights(a, n0, NT * wn, lane, K2);
+        const uint32_t ring_at = (uint32_t)wave * (kRing * 2048u), op_lane = weights.op_lane;
+        const uint32_t w_read0 = lds0 + ring_at + weights.read0, w_read1 = lds0 + ring_at + weights.read1;
         // tile i (static) of the block at byte `kb` of a row into the ring at `at`
-        auto w_fetch = [&](auto ic, uint32_t kb, uint32_t at) {
-            constexpr int i = decltype(ic)::value;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                keep_in_loop(w_lane[h]);
-                const uint64_t src = PACKED ? w_base[i] + (uint64_t)((kb >> 6) + h) * w_stage_bytes : w_base[i] + kb;
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)((gcptr_t)uniform_u64(src) + w_lane[h]),
-                                                 (__attribute__((address_space(3))) void *)(lds + at + h * 1024u), 16, 0, 0);
-            }
-        };
+        auto w_fetch = [&](auto ic, uint32_t kb, uint32_t at) { weights.template fetch<decltype(ic)::value>(kb, false, lds + at); };
 
         f32x4 acc[NT][MT];
 #pragma unroll
@@ -1053,10 +1067,10 @@ __global__ __launch_bounds__(64 * kSmallWaves, 1) void grkan_linear_small_kernel
 
         // ---- the partial tiles go to LDS as [WK][BM][BN + 4] float32
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); // every fetch has landed, every operand has been read
-        const uint32_t slab_at = lds0 + (uint32_t)kg * small_slab(MT, NT, WN) + i16 * ((BN + 4) * 4u);
+        const uint32_t slab_at = lds0 + (uint32_t)kg * small_slab(MT, NT, WN) + (uint32_t)(lane & 15) * ((BN + 4) * 4u);
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
-            const int32_t col = tile_n[nt] + (int32_t)g4 * 4; // (before n0: another workgroup's)
+            const int32_t col = weights.tile_n[nt] + (lane >> 4) * 4; // (before n0: another workgroup's)
             if (PACKED || col >= 0)
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt)
@@ -1083,6 +1097,174 @@ __global__ __launch_bounds__(64 * kSmallWaves, 1) void grkan_linear_small_kernel
         if (a.bias)
             v += bias_of<MODEL>(a.bias, o);
         OutPack<OUT>::store((gptr_t)(a.out + ((m0 + r) * a.Nout + o) * (int)sizeof(OUT)), v);
+    }
+}
+
+// --------------------------------------------------------------------------
+// the same layer for very few rows: tiles of 16 x 64
+// --------------------------------------------------------------------------
+//
+// Every workgroup evaluates F on its sixteen rows over all of the contraction, and that, not the few matrix instructions,
+// is most of its time (3.2 us of vector instructions at D_in = 3072).  All sixteen wavefronts therefore take part in it:
+// wavefront w takes the 64-k blocks w, w + 16, .. by itself, from x to the partial tile, and the loop has no barrier.
+// Weights and x come by LDS-direct loads, waited for by count: x of the next block while F of this one is evaluated,
+// its weights (8 KB) from then on.  x is read in the matrix cores' order, so that F(x) is an operand where it is
+// computed.  The sixteen partial tiles are added in wavefront order.
+// Before, with eight wavefronts for F and eight multiplying (as the small kernel): us per call before / now: 197 x 3072 -> 768
+// 11.0 / 10.1, 197 x 768 -> 768 5.9 / 5.5.
+constexpr int kFewWaves = 16;
+constexpr int kFewPitch = 68; // floats between the rows of a partial tile
+constexpr size_t kFewLds = (size_t)kFewWaves * (8192 + 2048);
+
+template <typename OUT, bool PACKED, bool MODEL, int M, int N>
+__global__ __launch_bounds__(64 * kFewWaves, 1) void grkan_linear_few_kernel(const LinArgs a)
+{
+    constexpr int NT = 4;
+    extern __shared__ __align__(16) char smem[];
+    const lptr_t lds = (lptr_t)smem;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    const int xcd = (int)blockIdx.x & 7; // workgroup -> tile as in the small kernel
+    const int slot = (int)blockIdx.x >> 3;
+    int mb, nb;
+    if (a.n_major) {
+        mb = slot % a.mblocks;
+        nb = (slot / a.mblocks) * 8 + xcd;
+    } else {
+        nb = slot % a.nblocks;
+        mb = (slot / a.nblocks) * 8 + xcd;
+    }
+    if (mb >= a.mblocks || nb >= a.nblocks)
+        return;
+    const int64_t m0 = (int64_t)mb * 16;
+    const int32_t n0 = nb * 64;
+    const uint32_t K2 = (uint32_t)a.K * 2u;
+    const BlockWalk walk(a.K >> 6, wave, kFewWaves);
+    const int32_t count = walk.left;
+
+    // ---- x: half u of a block's 2 KB is rows 8 u + lane / 8, 16-byte piece (lane % 8) xor line_swizzle(row)
+    BlockWalk xw = walk, cw = walk, ww = walk;
+    uint32_t x_lane[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int row = 8 * u + (lane >> 3);
+        int64_t xg = m0 + row;
+        if (xg > a.rows - 1)
+            xg = a.rows - 1; // rows past the end read the last row (never stored)
+        x_lane[u] = (uint32_t)((xg - m0) * (int64_t)K2) + (((uint32_t)lane ^ line_swizzle(row)) & 7u) * 16u;
+    }
+    const uint64_t x_base = reinterpret_cast<uint64_t>(a.x) + (uint64_t)m0 * K2;
+    const uint32_t x_own = (uint32_t)kFewWaves * 8192u + (uint32_t)wave * 2048u;
+    auto x_fetch = [&]() {
+        const uint64_t base = uniform_u64(x_base + xw.kbyte);
+        const bool past = xw.left <= 0; // one address for all lanes, never consumed
+        xw.next();
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            keep_in_loop(x_lane[u]);
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)((gcptr_t)base + (past ? 0u : x_lane[u])),
+                                             (__attribute__((address_space(3))) void *)(lds + x_own + u * 1024u), 16, 0, 0);
+        }
+    };
+    // Coefficients of the first and the second 32 k of a block, requested one block ahead (with D_in = 3072 in eight groups
+    // every block of a wavefront lies in another group).
+    RowWords<MODEL, M, N> rows[2];
+    uint32_t c_lo = 1, c_span = 0; // blocks that start in [c_lo, c_lo + c_span) have the coefficients held
+    auto coef_request = [&]() {
+        const uint32_t k = cw.kbyte / 2u;
+        cw.next();
+        if (k - c_lo >= c_span) {
+            const int g0 = __builtin_amdgcn_readfirstlane((int)(k / (uint32_t)a.dgc));
+            const int g1 = __builtin_amdgcn_readfirstlane((int)((k + 32u) / (uint32_t)a.dgc));
+            c_lo = g0 == g1 ? (uint32_t)g0 * (uint32_t)a.dgc : k;
+            c_span = g0 == g1 ? (uint32_t)a.dgc - 32u : 1u;
+            rows[0].load(a, g0);
+            rows[1].load(a, g1);
+        }
+    };
+
+    // ---- W: the fetches of the small kernel, a block at a time
+    WeightTiles<NT, PACKED> weights(a, n0, 0, lane, K2);
+    const uint32_t own = (uint32_t)wave * 8192u;
+    auto w_fetch = [&]() {
+        static_for<0, NT>([&](auto ic) {
+            weights.template fetch<decltype(ic)::value>(ww.kbyte, ww.left <= 0, lds + own + (uint32_t)decltype(ic)::value * 2048u);
+        });
+        ww.next();
+    };
+
+    f32x4 acc[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+        acc[nt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    x_fetch();
+    w_fetch();
+    coef_request();
+    for (int32_t b = 0; b < count; ++b) {
+        Coef<M, N> c[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) { // in vector registers (select_coefficients)
+            rows[h].to(c[h]);
+#pragma unroll
+            for (int j = 0; j <= M; ++j)
+                asm volatile("" : "+v"(c[h].a[j]));
+#pragma unroll
+            for (int j = 0; j < N; ++j)
+                asm volatile("" : "+v"(c[h].b[j]));
+        }
+        wait_loads<2 * NT>(); // x of this block, older than its weights
+        u32x4 x0 = __builtin_bit_cast(u32x4, lds_read16(lds0 + x_own + weights.op_lane));
+        u32x4 x1 = __builtin_bit_cast(u32x4, lds_read16(lds0 + x_own + (weights.op_lane ^ 64u)));
+        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(x0), "+v"(x1)::"memory"); // read before the next block's comes in its place
+        x_fetch();
+        coef_request();
+        const bf16x8 xf0 = __builtin_bit_cast(bf16x8, rational_words(x0, c[0]));
+        const bf16x8 xf1 = __builtin_bit_cast(bf16x8, rational_words(x1, c[1]));
+        bf16x8 w0[NT], w1[NT];
+        static_for<0, NT>([&](auto ic) {
+            constexpr int nt = decltype(ic)::value;
+            wait_loads<2 * (NT - 1 - nt) + 2>(); // (younger: the block's other tiles, the next block's x)
+            w0[nt] = lds_read16(lds0 + own + weights.read0 + (uint32_t)nt * 2048u);
+            w1[nt] = lds_read16(lds0 + own + weights.read1 + (uint32_t)nt * 2048u);
+        });
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(w0[nt]), "+v"(w1[nt])::"memory"); // read before the next block comes in its place
+        w_fetch();
+        fence_schedule();
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+            acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w0[nt], xf0, acc[nt], 0, 0, 0);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+            acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1[nt], xf1, acc[nt], 0, 0, 0);
+    }
+
+    // ---- the partial tiles go to LDS as [16][16][68] float32; their sum leaves as whole rows
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); // every fetch has landed, every operand has been read
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        const int32_t col = weights.tile_n[nt] + (lane >> 4) * 4; // (before n0: another workgroup's)
+        if (PACKED || col >= 0)
+            *(__attribute__((address_space(3))) f32x4 *)(uintptr_t)(lds0 + (uint32_t)((wave * 16 + (lane & 15)) * kFewPitch + col) * 4u) =
+                acc[nt];
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (tid < 16 * 16) {
+        const int row = tid >> 4;
+        const int o = n0 + (tid & 15) * 4;
+        if (m0 + row >= a.rows || o >= a.Nout)
+            return;
+        f32x4 v = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int g = 0; g < kFewWaves; ++g)
+            v += *(const __attribute__((address_space(3))) f32x4 *)(uintptr_t)(lds0 + (uint32_t)((g * 16 + row) * kFewPitch + (o - n0)) * 4u);
+        if (a.bias)
+            v += bias_of<MODEL>(a.bias, o);
+        OutPack<OUT>::store((gptr_t)(a.out + ((m0 + row) * a.Nout + o) * (int)sizeof(OUT)), v);
     }
 }
 
@@ -1121,14 +1303,14 @@ struct SmallVariant {
 // A round of workgroups (one per compute unit) takes a time that depends on the tile and D_in only, and the time of a
 // layer is that times the rounds.  Measured on MI355X (plain weights, launches from a graph; medians over seventeen layer
 // shapes of 50 .. 25,216 rows), us per round at D_in = 768 / 1536 / 3072:
-//   16 x 64: 6.3 / 7.5 / 10.8    32 x 128: 8.1 / 10.8 / 16.6    64 x 192: 11.6 / 17.2 / 29
+//   16 x 64: 5.5 / 6.8 / 10.1    32 x 128: 8.1 / 10.8 / 16.6    64 x 192: 11.6 / 17.2 / 29
 //   64 x 384: 14.6 / 22 / 38 alone, 24 / 44 where rounds follow each other
 //   112 x 768: 41 / - / 133   112 x 384: - / 43 / -   112 x 192: 24 / - / -
 // (before F had wavefronts of its own: 6.6 / 7.8 / 11.7, 8.5 / 12.2 / 20.5, 13.2 / 21 / 36 and 15.8 / 24.5 / 45).  With
 // these lines the tile taken is at most 6 % slower than the best of the five at all but nine of 234 sizes, and nowhere
 // more than 20 %.
 static const SmallVariant kSmall[] = {
-    {1, 4, 1, 4.9, 2.1},
+    {1, 4, 1, 4.8, 1.9},
     {2, 4, 2, 4.6, 4.2},
     {4, 3, 4, 5.9, 7.9},
     {4, 3, 8, 6.0, 12.6},
@@ -1171,7 +1353,7 @@ static const SmallVariant *pick_small(int64_t rows, int32_t D_in, int32_t D_out,
 template <typename OUT, bool PACKED, bool MODEL = false> static LinKernel select_small(SmallVariant v)
 {
     if (v.mt == 1 && v.nt == 4 && v.wn == 1)
-        return grkan_linear_small_kernel<1, 4, 1, OUT, PACKED, MODEL, 5, 4>;
+        return grkan_linear_few_kernel<OUT, PACKED, MODEL, 5, 4>;
     if (v.mt == 2 && v.nt == 4 && v.wn == 2)
         return grkan_linear_small_kernel<2, 4, 2, OUT, PACKED, MODEL, 5, 4>;
     if (v.mt == 4 && v.nt == 3 && v.wn == 4)
@@ -1311,7 +1493,7 @@ static grkan_status_t linear_fwd_impl(const void *x, const void *A, const void *
         kernel = out_dtype == GRKAN_BF16 ? select_kernel<bf16_out, false>(v, nedge) : select_kernel<float, false>(v, nedge);
     if (!kernel)
         return GRKAN_ERR_LAUNCH;
-    const size_t lds = small ? small_lds_bytes(small->mt, small->nt, small->wn) : lds_bytes(v);
+    const size_t lds = !small ? lds_bytes(v) : small->mt == 1 ? kFewLds : small_lds_bytes(small->mt, small->nt, small->wn);
     if (!allow_lds(reinterpret_cast<const void *>(kernel), lds))
         return GRKAN_ERR_LAUNCH;
 

@@ -125,7 +125,7 @@ def one_kernel_is_faster(rows: int, D_in: int, D_out: int) -> bool:
     less than the 27 us of host time that two launches take.  (Measured on MI355X, bfloat16, at 266 sizes: nineteen
     layer shapes, 1 - 25,216 rows.  Nowhere was the route that this takes more than 4 % slower than the two kernels;
     at fifteen sizes it passes by a gain of 5 % or more, most of them where the library's own choice of tile is a poor
-    one.  3072 -> 768: 197 rows 11.0 us against 27.7, 1,576 30 against 28.1, 6,304 42.5 against 51, 25,216 128 against
+    one.  3072 -> 768: 197 rows 10.1 us against 27.7, 1,576 30 against 28.1, 6,304 42.5 against 51, 25,216 128 against
     195; 768 -> 3072: 1,576 rows 15.5 against 28, 6,304 44 against 56, 12,608 85 against 71.)"""
     def product_us(tile, us_per_1k):
         rounds = -(-(-(-rows // tile) * -(-D_out // tile)) // 256)

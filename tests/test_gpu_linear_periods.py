@@ -10,9 +10,11 @@ pytestmark = pytest.mark.gpu
 
 PERIODS = [
     # rows, D_in, D_out, G, tile
-    (16, 512, 260, 2, (16, 64)),      # eight blocks, one each
-    (15, 2240, 68, 5, (16, 64)),      # 35 blocks: five periods, the last for three of eight groups
-    (31, 2624, 52, 41, (16, 64)),     # 41 blocks: six periods; d_g = 64
+    (16, 512, 260, 2, (16, 64)),      # eight blocks for sixteen wavefronts
+    (16, 1024, 64, 32, (16, 64)),     # one each; d_g = 32
+    (9, 1088, 132, 17, (16, 64)),     # two for the first; d_g = 64
+    (15, 2240, 68, 5, (16, 64)),      # 35 blocks: three for the first three
+    (31, 2624, 52, 41, (16, 64)),     # 41 blocks; d_g = 64
     (770, 576, 776, 6, (32, 128)),   # nine blocks for four groups, d_g = 96
     (801, 1280, 500, 40, (32, 128)),  # 20 blocks: five whole periods, d_g = 32
     (3072, 960, 396, 10, (64, 192)),  # 15 blocks: eight periods, the last for one of two groups; d_g = 96
