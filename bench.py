@@ -39,13 +39,13 @@ VALU_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12  # 39.3 T lane-operations/s: 256 CUs x 
 #                  SIMD in 4 clocks).  Micro-benchmarks of independent instruction streams on this chip give, per
 #                  wave instruction and SIMD: 1.05-1.4 ns (0.6-0.85 slot) when every operand is a vector register,
 #                  1.7-1.9 ns (1.0-1.1 slots) with a scalar-register or literal operand (the coefficients) and for
-#                  conversions / shifts, 3.45 ns (2.1 slots, about 8 clocks) for v_rcp_f32.  The hot loop's
+#                  conversions / shifts, 2.0 for v_ldexp / v_med3, 3.45 ns (2.1 slots, about 8 clocks) for v_rcp_f32.  The hot loop's
 #                  instructions (from the compiler's assembly) priced with these costs give the slot count.
 # The roofline fraction uses the slots; the plain count (every instruction one slot, the reciprocal too) would
 # put the kernel at 0.95 of the same peak and is an upper bound on what the peak means.
 BWD_VALU_16BIT = {
-    ("bf16", 3, 2): (29.52, 24.54), ("bf16", 5, 4): (43.97, 36.64), ("bf16", 7, 6): (57.93, 48.74),
-    ("f16", 3, 2): (29.58, 25.02), ("f16", 5, 4): (44.03, 36.87), ("f16", 7, 6): (57.98, 48.73),
+    ("bf16", 3, 2): (27.75, 23.68), ("bf16", 5, 4): (42.97, 36.29), ("bf16", 7, 6): (56.94, 48.39),
+    ("f16", 3, 2): (27.78, 24.16), ("f16", 5, 4): (43.03, 36.52), ("f16", 7, 6): (56.99, 48.38),
 }
 
 WORKLOAD_LABEL = {"tiny": "tiny [4,197,192]", "kat_t": "KAT-T", "kat_s": "KAT-S", "kat_b": "KAT-B",

@@ -437,6 +437,7 @@ template <int KS, int KR, int NT, int NW, int TR = 32> static constexpr Variant 
 //   K = 384: 12 wavefronts 44.1 / 69.9 (two steps of the weights in LDS)  8: 47.0 / 75.2   8 of 64 channels 44.0 / 78.4
 //   K = 512:  8 wavefronts 81.6 / 110 (library product + rational function of its own: 116 / 147)
 //   K = 640:  8 wavefronts 112 / 155 (129 / 177)    K = 768: 8 wavefronts 164 / 237 (167 / 223); 6,304 rows 48 / 72 (65 / 68)
+// (Before bwd_elem took the sign by a clamp; backward since: K = 192 0.5 %, 384 2.7 %, 768 1.3 % less.)
 static const Variant kVariants[] = {variant<6, 6, 2, 12>(), variant<8, 8, 2, 8>(), variant<12, 10, 2, 12>(), variant<16, 14, 2, 8>(),
                                     variant<20, 16, 2, 8>(), variant<24, 18, 2, 8, 16>()};
 
