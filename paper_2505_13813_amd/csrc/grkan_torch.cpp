@@ -7,7 +7,6 @@
 // current GPU outside of tracing, function transforms, forward-mode differentiation, dispatch modes and function
 // modes; the caller then takes the Python route, which handles or refuses the call as it always did.
 #include <torch/csrc/Exceptions.h>
-#include <torch/csrc/autograd/autograd.h>
 #include <torch/csrc/autograd/custom_function.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/csrc/jit/frontend/tracer.h>
@@ -20,6 +19,7 @@
 #include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
 
+#include <algorithm>
 #include <exception>
 #include <initializer_list>
 #include <optional>
@@ -163,13 +163,19 @@ struct Rational : public torch::autograd::Function<Rational> {
         const Tensor &x = saved[0], &A = saved[1], &B = saved[2];
         if (!grads[0].defined())
             return {Tensor(), Tensor(), Tensor()};
+        return in_backward(x, grads[0].contiguous(), A, B);
+    }
+
+    // {dx, dA, dB} inside a backward pass; where a graph of it is wanted, behind Undifferentiable.
+    static variable_list in_backward(const Tensor &x, const Tensor &dy, const Tensor &A, const Tensor &B)
+    {
         const bool graph_wanted = at::GradMode::is_enabled();
         Tensor dx, dA, dB;
         {
             at::AutoGradMode no_grad(false);
-            std::tie(dx, dA, dB) = gradients(x, grads[0].contiguous(), A, B);
+            std::tie(dx, dA, dB) = gradients(x, dy, A, B);
         }
-        return graph_wanted ? Undifferentiable::apply(dx, dA, dB, x, A, B, grads[0]) : variable_list{dx, dA, dB};
+        return graph_wanted ? Undifferentiable::apply(dx, dA, dB, x, A, B, dy) : variable_list{dx, dA, dB};
     }
 
     static std::tuple<Tensor, Tensor, Tensor> gradients(const Tensor &x, const Tensor &dy, const Tensor &A, const Tensor &B)
@@ -293,48 +299,44 @@ struct Block : public torch::autograd::Function<Block> {
             return out;
         const int64_t biases = ctx->saved_data["biases"].toInt(), wgrad = ctx->saved_data["wgrad"].toInt();
         const bool has1 = (biases & 1) != 0, has2 = (biases & 2) != 0;
-        const Tensor &x_ = saved[0], &A1 = saved[1], &B1 = saved[2], &W1_ = saved[3], &A2 = saved[4], &B2 = saved[5], &W2_ = saved[6];
-        const std::optional<Tensor> b1 = has1 ? std::optional<Tensor>(saved[7]) : std::nullopt;
-        const std::optional<Tensor> b2 = has2 ? std::optional<Tensor>(saved[8]) : std::nullopt;
-        if (at::GradMode::is_enabled()) {
-            // a graph of this pass is wanted: the same through the layers' own functions, of which it is made
-            const Tensor y = Product::apply(Rational::apply(Product::apply(Rational::apply(x_, A1, B1), W1_, b1), A2, B2), W2_, b2);
-            std::vector<int> of{0, 1, 2, 3, 4, 5, 6};
-            if (has1)
-                of.push_back(7);
-            if (has2)
-                of.push_back(8);
-            variable_list inputs;
-            std::vector<int> at;
-            for (size_t i = 0; i < of.size(); ++i)
-                if (ctx->needs_input_grad(i) && saved[of[i]].requires_grad()) {
-                    inputs.push_back(saved[of[i]]);
-                    at.push_back(of[i]);
-                }
-            if (!inputs.empty()) {
-                const variable_list got = torch::autograd::grad({y}, inputs, {grads[0]}, true, true, true);
-                for (size_t i = 0; i < at.size(); ++i)
-                    out[at[i]] = got[i];
-            }
-            return out;
-        }
+        const Tensor &A1 = saved[1], &B1 = saved[2], &W1 = saved[3], &A2 = saved[4], &B2 = saved[5];
         const bool want_b1 = has1 && ctx->needs_input_grad(7), want_b2 = has2 && ctx->needs_input_grad(has1 ? 8 : 7);
         const bool want_w1 = ctx->needs_input_grad(3), want_w2 = ctx->needs_input_grad(6);
         const bool want_first = ctx->needs_input_grad(0) || ctx->needs_input_grad(1) || ctx->needs_input_grad(2);
         const bool want_dh = want_first || want_w1 || want_b1 || ctx->needs_input_grad(4) || ctx->needs_input_grad(5);
-        const Tensor x = as_saved(x_, grads[0], x_.sizes());
-        const int64_t D = x.size(-1), rows = x.numel() / D, hidden = W1_.size(0);
-        const Tensor dout = as_saved(grads[0].reshape({rows, W2_.size(0)}), x, {rows, W2_.size(0)});
-        const Tensor f2 = as_saved(saved[11], x, {rows, hidden});
+        const Tensor x = as_saved(saved[0], grads[0], saved[0].sizes());
+        const int64_t D = x.size(-1), rows = x.numel() / D, hidden = W1.size(0);
+        const Tensor W2 = as_saved(saved[6], x, {D, hidden});
+        const Tensor dout = as_saved(grads[0].reshape({rows, D}), x, {rows, D});
+        Tensor f1, h, f2;
+        // With a graph of this pass wanted, the activations are formed again, with their history, and every gradient by
+        // operations that torch differentiates, each from the one behind it.  (torch::autograd::grad of the block formed again would
+        // not stop at the block's inputs: on its way to a parameter it would walk their history too, and run their hooks.)
+        const bool graph = at::GradMode::is_enabled();
+        if (graph) {
+            check_saved(x, x, A1, B1);
+            f1 = Rational::apply(x, A1, B1).view({rows, D});
+            h = at::linear(f1, as_saved(W1, x, {hidden, D}), has1 ? std::optional<Tensor>(saved[7]) : std::nullopt);
+            check_saved(h, h, A2, B2);
+            f2 = Rational::apply(h, A2, B2);
+        } else {
+            f2 = as_saved(saved[11], x, {rows, hidden});
+        }
         gradients_of(dout, f2, want_w2, want_b2, (wgrad & 2) != 0, out[6], out[8]);
         if (!want_dh)
             return out;
-        const Tensor W2 = as_saved(W2_, x, {D, hidden}), h = as_saved(saved[10], x, {rows, hidden});
-        check_saved(h, h, A2, B2);
-        Tensor dh = at::empty_like(h);
-        out[4] = at::empty_like(A2);
-        out[5] = at::empty_like(B2);
-        {
+        Tensor dh;
+        if (graph) {
+            const variable_list d = Rational::in_backward(h, dout.mm(W2), A2, B2);
+            dh = d[0];
+            out[4] = d[1];
+            out[5] = d[2];
+        } else {
+            h = as_saved(saved[10], x, {rows, hidden});
+            check_saved(h, h, A2, B2);
+            dh = at::empty_like(h);
+            out[4] = at::empty_like(A2);
+            out[5] = at::empty_like(B2);
             const int32_t G = (int32_t)B2.size(0);
             const size_t need = grkan_hidden_workspace_bytes(rows, (int32_t)D, (int32_t)hidden, G);
             const Tensor ws = at::empty({(int64_t)need}, x.options().dtype(at::kByte));
@@ -343,16 +345,21 @@ struct Block : public torch::autograd::Function<Block> {
                                    A2.dim() == 1, stream_of(x)),
                   "grkan_hidden_bwd");
         }
-        if (want_w1 || want_b1)
-            gradients_of(dh, as_saved(saved[9], x, x.sizes()).view({rows, D}), want_w1, want_b1, (wgrad & 1) != 0, out[3], out[7]);
-        if (want_first)
-            std::tie(out[0], out[1], out[2]) = Rational::gradients(x, dh.mm(W1_).view(x.sizes()), A1, B1);
+        if (want_w1 || want_b1) {
+            if (!graph)
+                f1 = as_saved(saved[9], x, x.sizes()).view({rows, D});
+            gradients_of(dh, f1, want_w1, want_b1, (wgrad & 1) != 0, out[3], out[7]);
+        }
+        if (want_first) {
+            const variable_list d = Rational::in_backward(x, dh.mm(W1).view(x.sizes()), A1, B1);
+            std::copy(d.begin(), d.end(), out.begin());
+        }
         return out;
     }
 
     static void gradients_of(const Tensor &dout, const Tensor &y, bool want_w, bool want_b, bool wgrad, Tensor &dW, Tensor &db)
     {
-        if (want_w && wgrad && weight_gradients(dout, y, want_b, dW, db))
+        if (want_w && wgrad && !at::GradMode::is_enabled() && weight_gradients(dout, y, want_b, dW, db))
             return;
         if (want_w)
             dW = dout.t().mm(y);

@@ -1,0 +1,100 @@
+"""GPU tests of the MLP block's native training route at what surrounds it: graphs of the backward pass, shared weights, hooks,
+strided inputs, calls that write to its output, checkpointing.  The oracle is the block's two layers, called one by one."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _block(torch, dim=192, rows=600):
+    from paper_2505_13813_amd import nn as gnn
+
+    torch.manual_seed(dim)
+    block = gnn.KATMlp(dim).to("cuda:0")
+    with torch.no_grad():
+        for p in block.parameters():
+            p.add_(0.02 * torch.randn_like(p))
+    return block.to(torch.bfloat16), torch.randn(2, rows // 2, dim, device="cuda:0").to(torch.bfloat16).requires_grad_()
+
+
+def _layers(block):
+    return lambda x: block.fc2(block.fc1(x))
+
+
+def _near(got, want):
+    """The same function with its sums in another order: in the norm, a few roundings."""
+    return float((got.detach().double() - want.detach().double()).norm()) <= 2.0 ** -6 * float(want.detach().double().norm())
+
+
+def _gradients(torch, y, leaves, create_graph):
+    dy = 0.01 * torch.randn(y.shape, device=y.device, generator=torch.Generator(y.device).manual_seed(7)).to(y.dtype)
+    return torch.autograd.grad(y, leaves, dy, create_graph=create_graph, allow_unused=True)
+
+
+def _same_gradients(torch, block, call, leaves, create_graph=True):
+    """Of call(block) and of call(its layers): every gradient is there and near."""
+    y = call(block)
+    assert "Block" in _node_names(y.grad_fn)
+    got, want = _gradients(torch, y, leaves, create_graph), _gradients(torch, call(_layers(block)), leaves, create_graph)
+    for g, w in zip(got, want):
+        assert g is not None and w is not None and g.shape == w.shape and g.dtype == w.dtype and _near(g, w)
+
+
+def _node_names(node):
+    seen, todo = set(), [node]
+    while todo:
+        n = todo.pop()
+        if n is not None and n not in seen:
+            seen.add(n)
+            todo += [f for f, _ in n.next_functions]
+    return " ".join(n.name() for n in seen)
+
+
+@pytest.mark.parametrize("create_graph", [False, True])
+def test_weights_used_twice(create_graph):
+    """A block applied to its own output, and coefficients that both layers share: each use counts once."""
+    import torch
+
+    block, x = _block(torch)
+    _same_gradients(torch, block, lambda f: f(f(x)), [x] + list(block.parameters()), create_graph)
+    block.fc2.rational.numerator = block.fc1.rational.numerator
+    _same_gradients(torch, block, lambda f: f(x), [x] + list(block.parameters()), create_graph)
+    # x is made of one of the block's parameters
+    _same_gradients(torch, block, lambda f: f(x + block.fc2.linear.bias), [x] + list(block.parameters()), create_graph)
+
+
+@pytest.mark.parametrize("create_graph", [False, True])
+def test_tensor_hooks_run_once(create_graph):
+    """A hook on the input (not a leaf), or on a parameter, that halves its gradient."""
+    import torch
+
+    block, x = _block(torch)
+    leaves = [x] + list(block.parameters())
+
+    def hooked(f):
+        z = 2.0 * x
+        z.register_hook(lambda g: 0.5 * g)
+        return f(z)
+
+    handle = block.fc1.linear.weight.register_hook(lambda g: 0.5 * g)
+    try:
+        _same_gradients(torch, block, hooked, leaves, create_graph)
+    finally:
+        handle.remove()
+
+
+def test_second_derivatives_are_the_layers():
+    """Of dW2 with respect to what its F2(h) depends on, and of gradients taken one by one."""
+    import torch
+
+    block, x = _block(torch)
+    W1, W2, b1 = block.fc1.linear.weight, block.fc2.linear.weight, block.fc1.linear.bias
+
+    def second(f):
+        g, = _gradients(torch, f(x), [W2], True)
+        return torch.autograd.grad(g.float().pow(2).sum(), [W1, b1, x, block.fc1.rational.numerator])
+
+    assert all(_near(g, w) for g, w in zip(second(block), second(_layers(block))))
+    for leaf in [x] + list(block.parameters()):
+        got, = _gradients(torch, block(x), [leaf], True)
+        want, = _gradients(torch, _layers(block)(x), [leaf], True)
+        assert _near(got, want)
