@@ -258,11 +258,10 @@ struct Product : public torch::autograd::Function<Product> {
 // with W2 and F2's gradients in the backward pass: dF2 is never written), out = f2 W2^T + b2.  Saves what the layers by
 // themselves save.  `wgrad1`, `wgrad2`: whether the layers' weight gradients take grkan_linear_wgrad at this size.
 struct Block : public torch::autograd::Function<Block> {
-    static Tensor forward(AutogradContext *ctx, const Tensor &x_in, const Tensor &A1, const Tensor &B1, const Tensor &W1,
+    static Tensor forward(AutogradContext *ctx, const Tensor &x, const Tensor &A1, const Tensor &B1, const Tensor &W1,
                           const Tensor &A2, const Tensor &B2, const Tensor &W2, const std::optional<Tensor> &b1,
                           const std::optional<Tensor> &b2, bool wgrad1, bool wgrad2)
     {
-        const Tensor x = x_in.contiguous();
         const Sizes s1 = sizes_of(x, A1, B1);
         const int64_t hidden = W1.size(0);
         Tensor f1 = at::empty_like(x, at::MemoryFormat::Contiguous);
@@ -422,7 +421,8 @@ std::optional<Tensor> block(const Tensor &x, const Tensor &A1, const Tensor &B1,
     for (const Tensor *t : {&W1, &W2, b1 ? &*b1 : &W1})
         if (reinterpret_cast<uintptr_t>(t->data_ptr()) % 16 != 0)
             return std::nullopt;
-    return Block::apply(x, A1, B1, W1, A2, B2, W2, b1, b2, wgrad1, wgrad2);
+    // (a copy made inside the function would have no history for a graph of the backward pass)
+    return Block::apply(x.contiguous(), A1, B1, W1, A2, B2, W2, b1, b2, wgrad1, wgrad2);
 }
 
 // What layer_packed reads of a layer's parameters: the packed weights, the bias, and a row of coefficients for every

@@ -98,3 +98,14 @@ def test_second_derivatives_are_the_layers():
         got, = _gradients(torch, block(x), [leaf], True)
         want, = _gradients(torch, _layers(block)(x), [leaf], True)
         assert _near(got, want)
+
+
+@pytest.mark.parametrize("create_graph", [False, True])
+def test_strided_input(create_graph):
+    """A view of every other row, and a transposed one: dx is there, in the layout of the tensor that x is a view of."""
+    import torch
+
+    block, x = _block(torch)
+    leaves = [x] + list(block.parameters())
+    for view in (lambda t: t[:, ::2], lambda t: t.transpose(0, 1)):
+        _same_gradients(torch, block, lambda f: f(view(x)), leaves, create_graph)
