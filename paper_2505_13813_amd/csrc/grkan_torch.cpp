@@ -143,11 +143,11 @@ struct Undifferentiable : public torch::autograd::Function<Undifferentiable> {
     }
 };
 
-// y = F(x); A [G, m+1] or, shared by the groups, [m+1].
+// y = F(x); A [G, m+1] or, shared by the groups, [m+1]; all contiguous.  (A copy made in here would have no history: a second
+// derivative with respect to what it was made of would not reach Undifferentiable.)
 struct Rational : public torch::autograd::Function<Rational> {
-    static Tensor forward(AutogradContext *ctx, const Tensor &x_in, const Tensor &A_in, const Tensor &B_in)
+    static Tensor forward(AutogradContext *ctx, const Tensor &x, const Tensor &A, const Tensor &B)
     {
-        const Tensor x = x_in.contiguous(), A = A_in.contiguous(), B = B_in.contiguous();
         ctx->save_for_backward({x, A, B});
         const Sizes s = sizes_of(x, A, B);
         Tensor y = at::empty_like(x, at::MemoryFormat::Contiguous);
@@ -381,7 +381,7 @@ std::optional<Tensor> rational(const Tensor &x, const Tensor &A, const Tensor &B
     const bool degrees = (m == 5 && n == 4) || (m == 3 && n == 2) || (m == 7 && n == 6);
     if (!degrees || G <= 0 || D <= 0 || D > INT32_MAX || D % G != 0 || x.numel() == 0)
         return std::nullopt;
-    return Rational::apply(x, A, B);
+    return Rational::apply(x.contiguous(), A.contiguous(), B.contiguous());
 }
 
 // The product of a bfloat16 layer in training.  (Hooks and the like on the linear module are the caller's to check.)
@@ -421,7 +421,7 @@ std::optional<Tensor> block(const Tensor &x, const Tensor &A1, const Tensor &B1,
     for (const Tensor *t : {&W1, &W2, b1 ? &*b1 : &W1})
         if (reinterpret_cast<uintptr_t>(t->data_ptr()) % 16 != 0)
             return std::nullopt;
-    // (a copy made inside the function would have no history for a graph of the backward pass)
+    // (contiguous: as for Rational)
     return Block::apply(x.contiguous(), A1, B1, W1, A2, B2, W2, b1, b2, wgrad1, wgrad2);
 }
 

@@ -79,7 +79,8 @@ def _rational_gradients(x, dy, A, B):
 
 
 class GroupRationalFunction(torch.autograd.Function):
-    """y = F(x) group-wise; backward through grkan_bwd (nothing but x, A, B is saved)."""
+    """y = F(x) group-wise; backward through grkan_bwd (nothing but x, A, B is saved).  Of operands that are not contiguous it
+    saves copies, which have no history: callers that may be differentiated twice pass contiguous ones."""
 
     @staticmethod
     def forward(ctx, x, A, B):
@@ -216,7 +217,7 @@ def group_rational(x, A, B):
         y = binding.load_native().rational(x, A, B)
         if y is not None:
             return y
-    return GroupRationalFunction.apply(x, A, B)
+    return GroupRationalFunction.apply(x.contiguous(), A.contiguous(), B.contiguous())
 
 
 def _rational_np(x, a, b):
@@ -463,7 +464,8 @@ class GRKANLinear(nn.Module):
             return None
         if grad:
             A, B = rational.coefficient_rows()
-            return GRKANLayerFunction.apply(x, A.to(torch.float32), B.to(torch.float32), weight, bias)
+            operands = (x, A.to(torch.float32), B.to(torch.float32), weight)
+            return GRKANLayerFunction.apply(*(t.contiguous() for t in operands), bias)
         rows = x.numel() // D_in
         if not always and not one_kernel_is_faster(rows, D_in, D_out):
             return None

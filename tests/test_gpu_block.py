@@ -1,5 +1,7 @@
 """GPU tests of the MLP block's native training route at what surrounds it: graphs of the backward pass, shared weights, hooks,
 strided inputs, calls that write to its output, checkpointing.  The oracle is the block's two layers, called one by one."""
+import types
+
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -109,3 +111,35 @@ def test_strided_input(create_graph):
     leaves = [x] + list(block.parameters())
     for view in (lambda t: t[:, ::2], lambda t: t.transpose(0, 1)):
         _same_gradients(torch, block, lambda f: f(view(x)), leaves, create_graph)
+
+
+@pytest.mark.parametrize("route", ["native", "python", "layer"])
+def test_strided_operands_of_the_rational_function(route, monkeypatch):
+    """A second derivative through F is refused for strided operands as for contiguous ones (with frozen coefficients x is all
+    that could tell, with a frozen x the coefficients), and the first one is there."""
+    import torch
+
+    from paper_2505_13813_amd import nn as gnn
+
+    layer = gnn.GRKANLinear(64, 64, 2, init="swish", fused="always").cuda().to(torch.bfloat16).requires_grad_(False)
+    A, B = (t.detach().float().contiguous() for t in layer.rational.coefficient_rows())
+    if route == "python":
+        monkeypatch.setattr(gnn.binding, "load_native", lambda: types.SimpleNamespace(rational=lambda *_: None))
+    base = torch.randn(64, 128, device="cuda:0").to(torch.bfloat16).requires_grad_()
+    coefficients = torch.randn(2, 12, device="cuda:0").mul_(0.1).requires_grad_()
+
+    def of(x, a=A):
+        if route == "layer":
+            return layer(x)
+        return gnn.group_rational(x, a, B)
+
+    for x in (base[:, :64].contiguous(), base[:, :64], base.view(128, 64).t().contiguous().t()[:64]):
+        dx, = torch.autograd.grad(of(x).float().sum(), base, create_graph=True)
+        assert dx.shape == base.shape and float(dx.abs().sum()) > 0
+        with pytest.raises(RuntimeError, match="not differentiable twice"):
+            torch.autograd.grad(dx.float().sum() + base.float().pow(3).sum(), base)
+    if route != "layer":
+        x = base.detach()[:, :64].contiguous()
+        dA, = torch.autograd.grad(of(x, coefficients[:, ::2]).float().sum(), coefficients, create_graph=True)
+        with pytest.raises(RuntimeError, match="not differentiable twice"):
+            torch.autograd.grad(dA.sum() + coefficients.pow(3).sum(), coefficients)
