@@ -523,6 +523,8 @@ class KATMlp(nn.Module):
             linear, rational = fc._modules.get("linear"), fc._modules.get("rational")
             if not _only_a(nn.Linear, linear) or not _only_a(GroupRational, rational) or "coefficient_rows" in rational.__dict__:
                 return None
+            if "bias" not in linear._parameters:  # a buffer or a plain tensor, that only linear's own forward reads
+                return None
             params += [rational._parameters.get("numerator"), rational._parameters.get("denominator"),
                        linear._parameters.get("weight"), linear._parameters.get("bias")]
         for i, p in enumerate(params):

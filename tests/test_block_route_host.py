@@ -1,0 +1,63 @@
+"""Which calls of the MLP block and of its layers take the native routes, without a GPU: the native entries are replaced by ones
+that note their arguments."""
+import types
+
+import pytest
+import torch
+
+from paper_2505_13813_amd import nn as gnn
+
+
+@pytest.fixture
+def entries(monkeypatch):
+    """Calls of the native entries, as (name, arguments); all of them answer with the first argument."""
+    calls = []
+
+    def entry(name):
+        def call(*args):
+            calls.append((name, args))
+            return args[0]
+        return call
+
+    native = types.SimpleNamespace(**{name: entry(name) for name in ("block", "rational", "product", "layer_model")})
+    monkeypatch.setattr(gnn.binding, "load_native", lambda: native)
+    return calls
+
+
+def _block(**kwargs):
+    return gnn.KATMlp(64, **kwargs).to(torch.bfloat16)
+
+
+def _x(requires_grad=True):
+    return torch.randn(16, 64).to(torch.bfloat16).requires_grad_(requires_grad)
+
+
+def _foreign_bias(linear, kind):
+    """A bias that linear.bias finds and that is no parameter."""
+    bias = linear.bias.detach() + 1.0
+    del linear.bias
+    if kind == "buffer":
+        linear.register_buffer("bias", bias)
+    else:
+        linear.bias = bias
+    assert linear.bias is bias and "bias" not in linear._parameters
+
+
+def test_block_with_parameters_alone(entries):
+    block, x = _block(), _x()
+    block(x)
+    (name, args), = entries
+    assert name == "block" and args[0] is x and args[4] is block.fc1.linear.bias and args[8] is block.fc2.linear.bias
+    block.fc1.linear.bias = block.fc2.linear.bias = None  # layers without a bias
+    del entries[:]
+    block(x)
+    (name, args), = entries
+    assert name == "block" and args[4] is None and args[8] is None
+
+
+@pytest.mark.parametrize("fc", ["fc1", "fc2"])
+@pytest.mark.parametrize("kind", ["buffer", "tensor"])
+def test_block_leaves_a_bias_that_is_no_parameter_to_its_layers(entries, fc, kind):
+    block = _block()
+    _foreign_bias(getattr(block, fc).linear, kind)
+    assert block._native_block(_x()) is None and not entries
