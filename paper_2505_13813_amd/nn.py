@@ -457,6 +457,8 @@ class GRKANLinear(nn.Module):
         numerator, denominator = rational._parameters.get("numerator"), rational._parameters.get("denominator")
         if weight is None or numerator is None or denominator is None or "coefficient_rows" in rational.__dict__:
             return None
+        if bias is None and "bias" not in linear._parameters:  # a buffer or a plain tensor
+            return None
         if not x.dim() or not x.shape[-1]:
             return None
         D_in, D_out = x.shape[-1], weight.shape[0]

@@ -61,3 +61,21 @@ def test_block_leaves_a_bias_that_is_no_parameter_to_its_layers(entries, fc, kin
     block = _block()
     _foreign_bias(getattr(block, fc).linear, kind)
     assert block._native_block(_x()) is None and not entries
+
+
+@pytest.mark.parametrize("kind", [None, "buffer", "tensor"])
+@pytest.mark.parametrize("fused", ["inference", "always"])
+def test_layer_leaves_a_bias_that_is_no_parameter_to_its_parts(entries, monkeypatch, fused, kind):
+    monkeypatch.setattr(gnn, "_fused_shapes", lambda *_: True)  # (x is not on the GPU)
+    monkeypatch.setattr(gnn, "one_kernel_is_faster", lambda *_: True)
+    layer = gnn.GRKANLinear(64, 64, 2, fused=fused).to(torch.bfloat16).eval()
+    layer._keep_packed = False
+    if kind is not None:
+        _foreign_bias(layer.linear, kind)
+    x = _x(False)
+    with torch.no_grad():
+        out = layer(x)
+    if kind is None:
+        assert [name for name, _ in entries] == ["layer_model"] and entries[0][1][4] is layer.linear.bias
+    else:
+        assert [name for name, _ in entries] == ["rational"] and torch.equal(out, layer.linear(x))
