@@ -577,7 +577,9 @@ def main():
             kat = gnn.KATMlp(dim, groups=cfg.G, fused="never")
             mods = [("gelu_mlp", std), ("kat_mlp", kat)]
             if tdt == torch.bfloat16:
-                # the same block with the second layer's forward in the one-kernel layer (F inside the product)
+                # the same block as it comes (one autograd function in training, fused layers in inference), and with the
+                # second layer's forward in the one-kernel layer (F inside the product) in training too
+                mods.append(("kat_mlp_default", gnn.KATMlp(dim, groups=cfg.G)))
                 mods.append(("kat_mlp_fused_fc2", gnn.KATMlp(dim, groups=cfg.G, fused="always")))
             res = {}
             for name, mod in mods:

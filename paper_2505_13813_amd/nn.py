@@ -493,7 +493,12 @@ class GRKANLinear(nn.Module):
 
 class KATMlp(nn.Module):
     """The MLP of a KAT block: two GR-KAN layers, hidden width 4x by default;
-    the first rational starts as the identity, the second as Swish."""
+    the first rational starts as the identity, the second as Swish.
+
+    `fused`: of the second layer, as GRKANLinear has it (the first one is fused in evaluation mode only).  With the default,
+    "inference", bfloat16 training on the GPU runs the whole block as one autograd function where that applies
+    (_native_block), with the hidden activation's product and rational function in one kernel where that is faster; "never"
+    and "always" leave training to the two layers."""
 
     def __init__(self, dim: int, hidden: int | None = None, groups: int = 8,
                  degrees: Tuple[int, int] = (M_DEGREE, N_DEGREE), fused: str = "inference"):
@@ -520,7 +525,7 @@ class KATMlp(nn.Module):
             return None
         params = []
         for fc in (self._modules.get("fc1"), self._modules.get("fc2")):
-            if not _only_a(GRKANLinear, fc) or fc.fused == "always":
+            if not _only_a(GRKANLinear, fc) or fc.fused != "inference":
                 return None
             linear, rational = fc._modules.get("linear"), fc._modules.get("rational")
             if not _only_a(nn.Linear, linear) or not _only_a(GroupRational, rational) or "coefficient_rows" in rational.__dict__:

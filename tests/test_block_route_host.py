@@ -79,3 +79,16 @@ def test_layer_leaves_a_bias_that_is_no_parameter_to_its_parts(entries, monkeypa
         assert [name for name, _ in entries] == ["layer_model"] and entries[0][1][4] is layer.linear.bias
     else:
         assert [name for name, _ in entries] == ["rational"] and torch.equal(out, layer.linear(x))
+
+
+def test_never_fused_is_never_fused(entries):
+    """fused="never": neither layer's product is in one kernel with a rational function, in training as in inference."""
+    block = _block(fused="never")
+    for train in (True, False):
+        for grad in (True, False):
+            with torch.set_grad_enabled(grad):
+                block.train(train)(_x())
+    assert entries and {name for name, _ in entries} <= {"rational", "product"}
+    block = _block()
+    block.fc2.fused = "never"  # on one layer
+    assert block._native_block(_x()) is None
