@@ -212,6 +212,17 @@ bool weight_gradients(Tensor dout2, Tensor y2, bool want_b, Tensor &dW, Tensor &
     return true;
 }
 
+// torch's linear.  The result is no view of another tensor: torch refuses to write (y += x) to an output of an autograd
+// function that is one.
+Tensor linear_of_rows(const Tensor &y, const Tensor &W, const std::optional<Tensor> &bias)
+{
+    if (y.dim() <= 2 || y.numel() == 0)
+        return at::linear(y, W, bias);
+    auto shape = y.sizes().vec();
+    shape.back() = W.size(0);
+    return at::_unsafe_view(at::linear(y.reshape({-1, y.size(-1)}), W, bias), shape);
+}
+
 // out = y W^T + bias with dW and dbias from grkan_linear_wgrad; saves what torch's linear saves: each operand where
 // the gradient of the other is wanted.
 struct Product : public torch::autograd::Function<Product> {
@@ -219,7 +230,7 @@ struct Product : public torch::autograd::Function<Product> {
     {
         ctx->save_for_backward({W.requires_grad() ? y : Tensor(), y.requires_grad() ? W : Tensor()});
         ctx->saved_data["has_bias"] = bias.has_value();
-        return at::linear(y, W, bias);
+        return linear_of_rows(y, W, bias);
     }
 
     static variable_list backward(AutogradContext *ctx, const variable_list &grads)
@@ -275,9 +286,7 @@ struct Block : public torch::autograd::Function<Block> {
         ctx->save_for_backward({x, A1, B1, W1, A2, B2, W2, b1 ? *b1 : Tensor(), b2 ? *b2 : Tensor(), f1, h, f2});
         ctx->saved_data["biases"] = (int64_t)(b1 ? 1 : 0) + (b2 ? 2 : 0);
         ctx->saved_data["wgrad"] = (int64_t)(wgrad1 ? 1 : 0) + (wgrad2 ? 2 : 0);
-        auto shape = x.sizes().vec();
-        shape.back() = W2.size(0);
-        return at::linear(f2, W2, b2).view(shape);
+        return at::_unsafe_view(at::linear(f2, W2, b2), x.sizes());
     }
 
     // A saved tensor as its hooks returned it, in the form the kernels read.

@@ -143,3 +143,21 @@ def test_strided_operands_of_the_rational_function(route, monkeypatch):
         dA, = torch.autograd.grad(of(x, coefficients[:, ::2]).float().sum(), coefficients, create_graph=True)
         with pytest.raises(RuntimeError, match="not differentiable twice"):
             torch.autograd.grad(dA.sum() + coefficients.pow(3).sum(), coefficients)
+
+
+@pytest.mark.parametrize("lead", [(600,), (2, 300), (2, 3, 100)])
+@pytest.mark.parametrize("whole", [True, False])
+def test_writing_to_the_output(lead, whole):
+    """y = mlp(x); y += x, on the block and on a layer's product."""
+    import torch
+
+    block, x = _block(torch)
+    x = x.detach().reshape(*lead, x.shape[-1]).requires_grad_()
+    call = block if whole else _layers(block)
+    leaves = [x] + list(block.parameters())
+    want = call(x) + x
+    y = call(x)
+    assert ("Block" if whole else "Product") in y.grad_fn.name()
+    y += x
+    assert torch.equal(y, want)
+    assert all(torch.equal(g, w) for g, w in zip(_gradients(torch, y, leaves, False), _gradients(torch, want, leaves, False)))
