@@ -406,7 +406,7 @@ std::optional<Tensor> product(const Tensor &y, const Tensor &W, const std::optio
 }
 
 // The MLP block in training, with a gradient wanted for its input and every parameter.  (Hooks and the like on its
-// modules are the caller's to check.)
+// modules are the caller's to check.  In a pass without a graph nothing tells whether one is wanted for the input.)
 std::optional<Tensor> block(const Tensor &x, const Tensor &A1, const Tensor &B1, const Tensor &W1, const std::optional<Tensor> &b1,
                             const Tensor &A2, const Tensor &B2, const Tensor &W2, const std::optional<Tensor> &b2, bool wgrad1,
                             bool wgrad2)
@@ -414,7 +414,8 @@ std::optional<Tensor> block(const Tensor &x, const Tensor &A1, const Tensor &B1,
     if (!plain_context() || !on_current_gpu(x))
         return std::nullopt;
     for (const Tensor *t : {&x, &A1, &B1, &W1, &A2, &B2, &W2, b1 ? &*b1 : &W1, b2 ? &*b2 : &W2})
-        if (!plain(*t, x.device()) || t->scalar_type() != at::kBFloat16 || !t->requires_grad() || (t != &x && !t->is_contiguous()))
+        if (!plain(*t, x.device()) || t->scalar_type() != at::kBFloat16 || (t != &x && !t->is_contiguous()) ||
+            (!t->requires_grad() && (t != &x || at::GradMode::is_enabled())))
             return std::nullopt;
     if (x.dim() < 1 || x.numel() == 0 || W1.dim() != 2 || W2.dim() != 2 || x.size(-1) != W1.size(1) || W2.size(1) != W1.size(0) ||
         W2.size(0) != W1.size(1) || (b1 && (b1->dim() != 1 || b1->size(0) != W1.size(0))) || (b2 && (b2->dim() != 1 || b2->size(0) != W2.size(0))))

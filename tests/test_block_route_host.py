@@ -92,3 +92,15 @@ def test_never_fused_is_never_fused(entries):
     block = _block()
     block.fc2.fused = "never"  # on one layer
     assert block._native_block(_x()) is None
+
+
+def test_passes_without_a_gradient(entries):
+    """In training mode they take the block, whether or not x has lost its gradient; in evaluation mode the layers."""
+    block = _block()
+    for requires_grad in (True, False):
+        del entries[:]
+        with torch.no_grad():
+            block.train()(_x(requires_grad))
+            assert [name for name, _ in entries] == ["block"]
+            assert block.eval()._native_block(_x(requires_grad)) is None
+    assert block.train()._native_block(_x(False)) is None  # with a graph, and no gradient wanted for x

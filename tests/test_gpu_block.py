@@ -161,3 +161,31 @@ def test_writing_to_the_output(lead, whole):
     y += x
     assert torch.equal(y, want)
     assert all(torch.equal(g, w) for g, w in zip(_gradients(torch, y, leaves, False), _gradients(torch, want, leaves, False)))
+
+
+@pytest.mark.parametrize("reentrant", [True, False])
+def test_checkpointed_segment(reentrant):
+    """The block behind other operations in a checkpointed segment: its input takes no gradient while the segment runs without
+    one, and the same kernels run all the same."""
+    import torch
+    from torch.utils.checkpoint import checkpoint
+
+    block, x = _block(torch)
+    norm = torch.nn.LayerNorm(x.shape[-1]).to("cuda:0", torch.bfloat16)
+    seen = []
+
+    def segment(t):
+        t = block(norm(t))
+        seen.append(t.detach().clone())
+        return t
+
+    leaves = [x] + list(block.parameters()) + list(norm.parameters())
+    want_y = block(norm(x))
+    want = _gradients(torch, want_y, leaves, False)
+    y = checkpoint(segment, x, use_reentrant=reentrant)
+    assert torch.equal(y, want_y)
+    dy = 0.01 * torch.randn(y.shape, device=y.device, generator=torch.Generator(y.device).manual_seed(7)).to(y.dtype)
+    y.backward(dy)
+    # (without reentrance the second pass ends where the last saved tensor is there again)
+    assert len(seen) == (2 if reentrant else 1) and torch.equal(seen[0], seen[-1])
+    assert all(torch.equal(p.grad, w) for p, w in zip(leaves, want))
