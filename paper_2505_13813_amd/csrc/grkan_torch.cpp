@@ -292,9 +292,9 @@ struct Block : public torch::autograd::Function<Block> {
     // A saved tensor as its hooks returned it, in the form the kernels read.
     static Tensor as_saved(const Tensor &t, const Tensor &like, at::IntArrayRef sizes)
     {
-        TORCH_CHECK_VALUE(t.defined() && t.device() == like.device() && t.layout() == at::kStrided, "grkan runs on the GPU only: tensors must be on one HIP device");
+        TORCH_CHECK_VALUE(plain(t, like.device()) && t.is_cuda(), "grkan runs on the GPU only: tensors must be on one HIP device");
         TORCH_CHECK_TYPE(t.scalar_type() == at::kBFloat16, "saved tensors must be bfloat16");
-        TORCH_CHECK_VALUE(t.sizes() == sizes, "a saved tensor has another shape");
+        TORCH_CHECK_VALUE(t.sizes() == sizes && t.numel() > 0, "a saved tensor has another shape");
         const Tensor c = t.contiguous();
         return reinterpret_cast<uintptr_t>(c.data_ptr()) % 16 == 0 ? c : c.clone();
     }
@@ -333,25 +333,29 @@ struct Block : public torch::autograd::Function<Block> {
         gradients_of(dout, f2, want_w2, want_b2, (wgrad & 2) != 0, out[6], out[8]);
         if (!want_dh)
             return out;
-        Tensor dh;
-        if (graph) {
-            const variable_list d = Rational::in_backward(h, dout.mm(W2), A2, B2);
-            dh = d[0];
-            out[4] = d[1];
-            out[5] = d[2];
-        } else {
+        if (!graph) {
             h = as_saved(saved[10], x, {rows, hidden});
             check_saved(h, h, A2, B2);
+        }
+        const int32_t G = (int32_t)B2.size(0);
+        Tensor dh;
+        // (as the kernel reads them: a saved-tensor hook may have made float32 of them, which the rational function takes)
+        if (!graph && A2.scalar_type() == at::kBFloat16 && A2.size(-1) == 6 && B2.size(1) == 4 &&
+            grkan_hidden_supported((int32_t)D, (int32_t)hidden, G)) {
             dh = at::empty_like(h);
             out[4] = at::empty_like(A2);
             out[5] = at::empty_like(B2);
-            const int32_t G = (int32_t)B2.size(0);
             const size_t need = grkan_hidden_workspace_bytes(rows, (int32_t)D, (int32_t)hidden, G);
             const Tensor ws = at::empty({(int64_t)need}, x.options().dtype(at::kByte));
             check(grkan_hidden_bwd(dout.data_ptr(), W2.data_ptr(), h.data_ptr(), A2.data_ptr(), B2.data_ptr(), dh.data_ptr(),
                                    out[4].data_ptr(), out[5].data_ptr(), ws.data_ptr(), need, rows, (int32_t)D, (int32_t)hidden, G,
                                    A2.dim() == 1, stream_of(x)),
                   "grkan_hidden_bwd");
+        } else {
+            const variable_list d = Rational::in_backward(h, dout.mm(W2), A2, B2);
+            dh = d[0];
+            out[4] = d[1];
+            out[5] = d[2];
         }
         if (want_w1 || want_b1) {
             if (!graph)

@@ -189,3 +189,23 @@ def test_checkpointed_segment(reentrant):
     # (without reentrance the second pass ends where the last saved tensor is there again)
     assert len(seen) == (2 if reentrant else 1) and torch.equal(seen[0], seen[-1])
     assert all(torch.equal(p.grad, w) for p, w in zip(leaves, want))
+
+
+def test_coefficients_of_another_type_from_saved_tensor_hooks():
+    """Hooks that give the coefficients back in float32: the gradients are those of the layers under the same hooks.  And a numerator
+    of another degree is refused."""
+    import torch
+
+    block, x = _block(torch)
+    leaves = [x] + list(block.parameters())
+
+    def kept(f):
+        with torch.autograd.graph.saved_tensors_hooks(lambda t: t, lambda t: t.float() if t.numel() <= 32 else t):
+            return f(x)
+
+    got, want = (_gradients(torch, kept(f), leaves, False) for f in (block, _layers(block)))
+    assert all(_near(g, w) for g, w in zip(got, want))
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: t, lambda t: t[:4].contiguous() if t.shape == (6,) else t):
+        y = block(x)
+    with pytest.raises(Exception, match="grkan_bwd"):
+        _gradients(torch, y, leaves, False)
