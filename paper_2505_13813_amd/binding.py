@@ -97,6 +97,8 @@ def load_library():
     lib.grkan_linear_wgrad_workspace_bytes.restype = sz
     lib.grkan_hidden_supported.argtypes = [i32, i32, i32]
     lib.grkan_hidden_supported.restype = i32
+    lib.grkan_hidden_pays.argtypes = [i64, i32, i32, i32, i32]
+    lib.grkan_hidden_pays.restype = i32
     lib.grkan_hidden_workspace_bytes.argtypes = [i64, i32, i32, i32]
     lib.grkan_hidden_workspace_bytes.restype = sz
     lib.grkan_hidden_fwd.argtypes = [vp, vp, vp, vp, vp, vp, vp, i64, i32, i32, i32, i32, vp]

@@ -420,34 +420,66 @@ using Kernel = void (*)(const Args);
 
 struct Variant {
     int32_t K, CW, waves, tile_rows;
+    int32_t fwd_units, bwd_units; // compute units that have to get a workgroup for a large call to be the faster route (pays)
     size_t lds;
     Kernel fwd, bwd;
 };
 
-template <int KS, int KR, int NT, int NW, int TR = 32> static constexpr Variant variant()
+template <int KS, int KR, int NT, int NW, int TR = 32>
+static constexpr Variant variant(int32_t fwd_units, int32_t bwd_units)
 {
     using S = Shape<KS, KR, NT, NW, TR>;
-    return Variant{S::K, S::CW, NW, TR, S::kLds, hidden_kernel<KS, KR, NT, NW, TR, false>, hidden_kernel<KS, KR, NT, NW, TR, true>};
+    return Variant{S::K, S::CW, NW, TR, fwd_units, bwd_units, S::kLds,
+                   hidden_kernel<KS, KR, NT, NW, TR, false>, hidden_kernel<KS, KR, NT, NW, TR, true>};
 }
 
+// The contractions that are built: the widths 192, 384 and 768 of the model table, and of the other multiples of 64 those that
+// are multiples of 128.  (Any even number of steps fits the template; 320, 448, 576 and 704 are neither built nor measured, and
+// such a block runs its layers one by one.)
+//
 // us at 25,216 rows, forward / backward (two 16-channel tiles a wavefront but for the last column; twelve wavefronts are
 // three per SIMD of 168 registers each, eight are two of 256):
 //   K = 192: 12 wavefronts 20.3 / 37.9   8: 21.9 / 37.6                                 8 of 96 channels 24.2 / 44.5
 //   K = 256:  8 wavefronts 26.5 / 46.2  16: 25.7 / 66 (spills)                          8 of 64 channels 27.9 / 46.9
 //   K = 384: 12 wavefronts 44.1 / 69.9 (two steps of the weights in LDS)  8: 47.0 / 75.2   8 of 64 channels 44.0 / 78.4
-//   K = 512:  8 wavefronts 81.6 / 110 (library product + rational function of its own: 116 / 147)
-//   K = 640:  8 wavefronts 112 / 155 (129 / 177)    K = 768: 8 wavefronts 164 / 237 (167 / 223); 6,304 rows 48 / 72 (65 / 68)
+//   K = 512:  8 wavefronts 81.6 / 110   K = 640: 112 / 155   K = 768: 164 / 237
 // (Before bwd_elem took the sign by a clamp; backward since: K = 192 0.5 %, 384 2.7 %, 768 1.3 % less.)
-static const Variant kVariants[] = {variant<6, 6, 2, 12>(), variant<8, 8, 2, 8>(), variant<12, 10, 2, 12>(), variant<16, 14, 2, 8>(),
-                                    variant<20, 16, 2, 8>(), variant<24, 18, 2, 8, 16>()};
+static const Variant kVariants[] = {variant<6, 6, 2, 12>(0, 176), variant<8, 8, 2, 8>(0, 192), variant<12, 10, 2, 12>(0, 176),
+                                    variant<16, 14, 2, 8>(160, 192), variant<20, 16, 2, 8>(176, 192),
+                                    variant<24, 18, 2, 8, 16>(192, 208)};
 
-// The variant of a shape, or NULL: whole slabs of eight wavefronts, each within one coefficient group.
+// The variant of a shape, or NULL: whole slabs of the workgroup's wavefronts, each of these within one coefficient group.
 static const Variant *variant_of(int32_t K, int32_t N, int32_t G)
 {
     for (const Variant &v : kVariants)
         if (v.K == K && N > 0 && G > 0 && N % (v.waves * v.CW) == 0 && N / (v.waves * v.CW) <= 32 && N % G == 0 && N / G % v.CW == 0)
             return &v;
     return nullptr;
+}
+
+// Whether the kernel is the faster route than a library product and the rational function's own kernel.
+//
+// Large calls: a number of slabs that does not divide the 32 compute units of an XCD leaves units without a workgroup, and how
+// many of these the kernel can do without falls with K: the more of the weights is in LDS, the nearer it is to what it replaces.
+// Measured on MI355X in whole training blocks (forward and backward pass, 18 numbers of slabs, 6,304 - 50,432 rows; what the block
+// is slower, in per cent of its time, with the two kernels in place of the forward one, and of the backward one):
+//   units       240, 256             208 - 224            192 (12, 24 slabs)    176 (11, 22)          160 (20)              136 (17)
+//   K = 192     3 .. 16,  5 .. 17    6 .. 11,  6 .. 11    3 .. 9,   2 .. 5      4 .. 10,  3 .. 15     -1 .. 2, -4 .. -1     0 .. 3,   1 .. 7
+//   K = 256     3 .. 12,  5 .. 8     3 .. 16,  3 .. 9     4 .. 10,  1 .. 3      6 .. 11, -2 .. 3       3,      -5 .. -2     2 .. 5,  -9 .. -3
+//   K = 384     4 .. 15,  6 .. 15    8 .. 16,  5 .. 11    5 .. 9,   2 .. 5      6 .. 13,  1 .. 10      2 .. 3, -2 .. -1     4 .. 5,   0 .. 4
+//   K = 512     3 .. 14,  3 .. 9     2 .. 13,  3 .. 7     1 .. 11,  0 .. 6      5 .. 13, -1 .. 1       1 .. 3, -4 .. -3    -3 .. 8,  -8 .. -4
+//   K = 640     2 .. 10,  1 .. 12    2 .. 8,   1 .. 7     1 .. 7,   0 .. 5      0 .. 8,  -3 .. 0      -1 .. 0, -4          -1 .. 5,  -8 .. -5
+//   K = 768     2 .. 9,   1 .. 11   -1 .. 8,   0 .. 5     0 .. 6,  -1 .. 1     -2 .. 7,  -4 .. -1     -2,      -6 .. -5    -3 .. 2,  -9 .. -5
+// 768 -> 3072 is twelve slabs; us of the block with both kernels / the forward one / neither: 9,456 rows 430 / 419 / 421,
+// 25,216 1,032 / 1,015 / 1,047, 50,432 1,859 / 1,783 / 1,818.  (Timed by themselves, over the same buffers again and again, the
+// two kernels look up to a tenth better than in a block: the one finds in the caches what the other has just written.)
+//
+// Calls of less than 24 million hidden activations are bound by the host, which has one launch less to make: 768 -> 3072 211 /
+// 214 / 229 us at 3,152 rows (by themselves the kernels take 84 us there, the two of each direction 70), 299 / 302 / 321 at 6,304.
+static bool pays(const Variant &v, int64_t rows, int32_t N, bool backward)
+{
+    const int32_t slabs = N / (v.waves * v.CW), units = 8 * (32 / slabs) * slabs;
+    return rows * N < 24000000 || units >= (backward ? v.bwd_units : v.fwd_units);
 }
 
 static bool allow_lds(const Variant &v)
@@ -525,6 +557,12 @@ static grkan_status_t run(bool backward, const void *x, const void *W, const voi
 using namespace grkan;
 
 extern "C" int32_t grkan_hidden_supported(int32_t K, int32_t N, int32_t G) { return hidden::variant_of(K, N, G) != nullptr; }
+
+extern "C" int32_t grkan_hidden_pays(int64_t rows, int32_t K, int32_t N, int32_t G, int32_t backward)
+{
+    const hidden::Variant *const v = hidden::variant_of(K, N, G);
+    return v != nullptr && hidden::pays(*v, rows, N, backward != 0);
+}
 
 extern "C" size_t grkan_hidden_workspace_bytes(int64_t rows, int32_t K, int32_t N, int32_t G)
 {

@@ -265,8 +265,9 @@ struct Product : public torch::autograd::Function<Product> {
     }
 };
 
-// The two GR-KAN layers of an MLP block: f1 = F1(x), h = f1 W1^T + b1 and f2 = F2(h) in one kernel (and so are the product
-// with W2 and F2's gradients in the backward pass: dF2 is never written), out = f2 W2^T + b2.  Saves what the layers by
+// The two GR-KAN layers of an MLP block: f1 = F1(x), h = f1 W1^T + b1 and f2 = F2(h), out = f2 W2^T + b2.  Where it is the
+// faster route (grkan_hidden_pays, by direction) h and f2 come from one kernel, and in the backward pass the product with W2 and
+// F2's gradients, so that dF2 is never written; elsewhere from torch's product and the rational function.  Saves what the layers by
 // themselves save.  `wgrad1`, `wgrad2`: whether the layers' weight gradients take grkan_linear_wgrad at this size.
 struct Block : public torch::autograd::Function<Block> {
     static Tensor forward(AutogradContext *ctx, const Tensor &x, const Tensor &A1, const Tensor &B1, const Tensor &W1,
@@ -279,10 +280,19 @@ struct Block : public torch::autograd::Function<Block> {
         check(grkan_fwd_model(x.data_ptr(), A1.data_ptr(), B1.data_ptr(), f1.data_ptr(), s1.rows, s1.D, s1.G, s1.m, s1.n, GRKAN_BF16,
                               GRKAN_BF16, s1.shared, stream_of(x)),
               "grkan_fwd");
-        Tensor h = at::empty({s1.rows, hidden}, x.options()), f2 = at::empty({s1.rows, hidden}, x.options());
-        check(grkan_hidden_fwd(f1.data_ptr(), W1.data_ptr(), b1 ? b1->data_ptr() : nullptr, A2.data_ptr(), B2.data_ptr(), h.data_ptr(),
-                               f2.data_ptr(), s1.rows, s1.D, (int32_t)hidden, (int32_t)B2.size(0), A2.dim() == 1, stream_of(x)),
-              "grkan_hidden_fwd");
+        const int32_t G2 = (int32_t)B2.size(0);
+        Tensor h, f2 = at::empty({s1.rows, hidden}, x.options());
+        if (grkan_hidden_pays(s1.rows, s1.D, (int32_t)hidden, G2, 0)) {
+            h = at::empty_like(f2);
+            check(grkan_hidden_fwd(f1.data_ptr(), W1.data_ptr(), b1 ? b1->data_ptr() : nullptr, A2.data_ptr(), B2.data_ptr(), h.data_ptr(),
+                                   f2.data_ptr(), s1.rows, s1.D, (int32_t)hidden, G2, A2.dim() == 1, stream_of(x)),
+                  "grkan_hidden_fwd");
+        } else {
+            h = at::linear(f1.view({s1.rows, s1.D}), W1, b1);
+            check(grkan_fwd_model(h.data_ptr(), A2.data_ptr(), B2.data_ptr(), f2.data_ptr(), s1.rows, (int32_t)hidden, G2, 5, 4,
+                                  GRKAN_BF16, GRKAN_BF16, A2.dim() == 1, stream_of(x)),
+                  "grkan_fwd");
+        }
         ctx->save_for_backward({x, A1, B1, W1, A2, B2, W2, b1 ? *b1 : Tensor(), b2 ? *b2 : Tensor(), f1, h, f2});
         ctx->saved_data["biases"] = (int64_t)(b1 ? 1 : 0) + (b2 ? 2 : 0);
         ctx->saved_data["wgrad"] = (int64_t)(wgrad1 ? 1 : 0) + (wgrad2 ? 2 : 0);
@@ -341,7 +351,7 @@ struct Block : public torch::autograd::Function<Block> {
         Tensor dh;
         // (as the kernel reads them: a saved-tensor hook may have made float32 of them, which the rational function takes)
         if (!graph && A2.scalar_type() == at::kBFloat16 && A2.size(-1) == 6 && B2.size(1) == 4 &&
-            grkan_hidden_supported((int32_t)D, (int32_t)hidden, G)) {
+            grkan_hidden_pays(rows, (int32_t)D, (int32_t)hidden, G, 1)) {
             dh = at::empty_like(h);
             out[4] = at::empty_like(A2);
             out[5] = at::empty_like(B2);

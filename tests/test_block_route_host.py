@@ -104,3 +104,22 @@ def test_passes_without_a_gradient(entries):
             assert [name for name, _ in entries] == ["block"]
             assert block.eval()._native_block(_x(requires_grad)) is None
     assert block.train()._native_block(_x(False)) is None  # with a graph, and no gradient wanted for x
+
+
+def test_where_the_hidden_kernels_pay():
+    """Small calls always (a launch less); large ones by the compute units that get a workgroup, 8 * (32 / slabs) * slabs."""
+    from paper_2505_13813_amd import binding
+
+    lib = binding.load_library()
+    for rows, K, N, forward, backward in (
+            (25216, 192, 768, 1, 1), (25216, 384, 1536, 1, 1), (50432, 256, 1024, 1, 1), (50432, 512, 2048, 1, 1),
+            (50432, 640, 2560, 1, 1),                           # 240 units
+            (6304, 768, 3072, 1, 1), (25216, 768, 3072, 1, 0),  # 192 units, which is enough for the forward kernel
+            (50432, 768, 1536, 1, 1),                           # 240
+            (12608, 768, 4352, 0, 0), (5000, 768, 4352, 1, 1),  # 136
+            (12608, 512, 4352, 0, 0), (12608, 640, 5120, 0, 0), (12608, 256, 4352, 1, 0),
+            (25216, 384, 7680, 1, 0), (25216, 192, 4608, 1, 1),
+            (25216, 320, 1280, 0, 0)):                          # not built
+        G = 8
+        assert lib.grkan_hidden_supported(K, N, G) == (K != 320)
+        assert (lib.grkan_hidden_pays(rows, K, N, G, 0), lib.grkan_hidden_pays(rows, K, N, G, 1)) == (forward, backward), (rows, K, N)

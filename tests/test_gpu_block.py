@@ -209,3 +209,20 @@ def test_coefficients_of_another_type_from_saved_tensor_hooks():
         y = block(x)
     with pytest.raises(Exception, match="grkan_bwd"):
         _gradients(torch, y, leaves, False)
+
+
+@pytest.mark.parametrize("dim,hidden,rows", [(256, 4352, 5600), (512, 4352, 5530), (768, 3072, 7900)])
+def test_large_blocks_by_two_kernels(dim, hidden, rows):
+    """Sizes at which the hidden kernels leave compute units idle: the backward one, or both, are replaced by a product and the
+    rational function's kernel."""
+    import torch
+
+    from paper_2505_13813_amd import binding, nn as gnn
+
+    lib = binding.load_library()
+    assert lib.grkan_hidden_pays(rows, dim, hidden, 8, 0) == (dim != 512) and not lib.grkan_hidden_pays(rows, dim, hidden, 8, 1)
+    torch.manual_seed(dim)
+    block = gnn.KATMlp(dim, hidden).to("cuda:0", torch.bfloat16)
+    x = torch.randn(2, rows // 2, dim, device="cuda:0").to(torch.bfloat16).requires_grad_()
+    _same_gradients(torch, block, lambda f: f(x), [x] + list(block.parameters()), False)
+    assert _near(block(x), _layers(block)(x))
