@@ -7,7 +7,7 @@ pytestmark = pytest.mark.gpu
 
 BF16 = 2.0 ** -8  # half a unit in the last place, relative
 
-# rows, K, N, G: one token, ragged last tiles, one tile, fewer tiles than parts, several tiles per part; one and several slabs,
+# rows, K, N, G: one token, ragged last tiles, one tile, fewer tiles than parts, two tiles per part; one and several slabs,
 # groups of one and of several wavefronts, more than one group per wavefront's neighbours
 SHAPES = [(1, 192, 768, 8), (33, 192, 384, 4), (4133, 192, 768, 2), (31, 256, 256, 8), (2100, 256, 1024, 8), (4111, 256, 768, 24),
           (32, 384, 384, 1), (47, 384, 1536, 8), (2090, 384, 1536, 48), (4001, 384, 768, 8), (75, 512, 512, 4),
@@ -97,19 +97,47 @@ def test_shared_numerator_and_no_bias():
     assert bool((close <= BF16 * one[3].float().abs() + 2.0 ** -20 * each[3].float().abs().sum(0)).all())
 
 
-def test_tokens_past_the_end_add_nothing():
-    """The last tile's missing tokens repeat the last one's h in the loads: an infinite one must not reach other sums."""
+# Seventeen slabs leave eight parts (one per XCD): four or five tiles for each, the last one ragged.  From the third tile of a part on
+# a token buffer is written again after it has been read, and tiles are loaded two ahead.
+LONG = [(34 * (16 if K == 768 else 32) + 7, K, 17 * slab, G) for K, slab, G in
+        ((192, 384, 17), (256, 256, 34), (384, 384, 51), (512, 256, 17), (640, 256, 8), (768, 256, 34))]
+
+
+@pytest.mark.parametrize("rows,K,N,G", LONG)
+def test_several_tiles_per_part(oracle, rows, K, N, G):
+    from paper_2505_13813_amd import binding
+
+    wavefronts = N // G // 32  # of a part that share a group (32 channels each); one row of ten sums for each
+    parts = binding.load_library().grkan_hidden_workspace_bytes(rows, K, N, G) // (G * wavefronts * 40)
+    tiles = -(-rows // (16 if K == 768 else 32))
+    assert parts == 8 and tiles == 35
+    test_hidden_kernels(oracle, rows, K, N, G)
+
+
+@pytest.mark.parametrize("rows,K", [(37, 384), (1, 192), (17, 768), (33, 768), (63, 256)])
+def test_tokens_past_the_end_add_nothing(rows, K):
+    """The last tile's missing tokens repeat the last one's h and dout in the loads.  With tokens of dout = 0 in their place,
+    which add zeros to the same sums, every gradient has the same bits; the last token is the largest, so that each repeat of it
+    would show."""
     import torch
 
-    rows, K, N, G = 37, 384, 1536, 8
+    N, G = 4 * K, 8
     d = _operands(torch, rows, K, N, G)
-    d["y"][-1] = float("inf")
-    d["dout"][-1] = 0.0
-    whole = _call(torch, d, rows, K, N, G)
-    less = {k: v[:-1].contiguous() if k in ("y", "dout") else v for k, v in d.items()}
-    part = _call(torch, less, rows - 1, K, N, G)
+    d["dout"][-1] *= 100.0
+    whole = -(-rows // 32) * 32
+    more = dict(d, y=torch.cat([d["y"], _operands(torch, whole - rows, K, N, G)["y"]]),
+                dout=torch.cat([d["dout"], torch.zeros(whole - rows, K, device="cuda:0", dtype=torch.bfloat16)]))
+    got, want = _call(torch, d, rows, K, N, G), _call(torch, more, whole, K, N, G)
     for i in range(3):
-        assert torch.equal(whole[i][:-1], part[i])
+        assert torch.equal(got[i], want[i][:rows])
+    assert torch.equal(got[3], want[3]) and torch.equal(got[4], want[4])
+    # and an infinite token stays among its own outputs
+    d["y"][-1], d["dout"][-1] = float("inf"), 0.0
+    if rows > 1:
+        less = {k: v[:-1].contiguous() if k in ("y", "dout") else v for k, v in d.items()}
+        whole, part = _call(torch, d, rows, K, N, G), _call(torch, less, rows - 1, K, N, G)
+        for i in range(3):
+            assert torch.equal(whole[i][:-1], part[i])
 
 
 def _block(torch, dim=192, rows=600, bias=True):
