@@ -10,12 +10,13 @@
 // short contraction at 420 - 560 TFLOP/s and leaves the result to be read again.
 //
 // A wavefront keeps the weights of its CW hidden channels (all of one coefficient group) for the whole kernel: in vector
-// registers, and what does not fit there in LDS that it alone reads.  Tokens pass by in tiles of 32, shared by the
-// workgroup's eight wavefronts through two LDS buffers, one barrier per tile.  The accumulators of 16 tokens are all
+// registers, and what does not fit there (K = 384 two steps of 32, 512 two, 640 four, 768 six) in LDS that it alone reads, again
+// for every 16 tokens.  Tokens pass by in tiles of TR (32; 16 at K = 768), shared by the workgroup's NW wavefronts (eight; twelve
+// at K = 192 and 384) through two LDS buffers, one barrier per tile.  The accumulators of 16 tokens are all
 // that is live of the result; which hidden channel a matrix row stands for is chosen so that a lane ends up with
 // 16 bytes of consecutive channels, and the rational function, the loads of h and the stores work on the
 // accumulators' layout as it is.  Coefficients are wave-uniform (scalar registers) and the coefficient sums stay in
-// registers to the end: one workspace row per wavefront, added by the same second stage as the elementwise backward pass.
+// registers to the end: one workspace row per wavefront and part of the tokens, added by the same second stage as the elementwise backward pass.
 #include <hip/hip_runtime.h>
 
 #include <mutex>

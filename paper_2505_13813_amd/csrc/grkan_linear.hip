@@ -82,8 +82,8 @@ struct LinArgs {
     int32_t a_stride;  // MODEL: m + 1, or 0 where all groups share one numerator row
 };
 
-// The small kernel: eight wavefronts multiply, eight evaluate F; two or three buffers of F of a 64-k block for each
-// group of WN multiplying wavefronts, and a ring of two blocks of 2 KB weight tiles per multiplying wavefront
+// The small kernel: eight wavefronts multiply, eight evaluate F; two buffers of F of a period (one or two 64-k blocks) for
+// each group of WN multiplying wavefronts, and a ring of two blocks of 2 KB weight tiles per multiplying wavefront
 constexpr int kMulWaves = 8;
 constexpr int kSmallWaves = 2 * kMulWaves;
 constexpr int kXAhead = 4; // periods x is loaded ahead

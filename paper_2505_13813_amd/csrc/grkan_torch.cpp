@@ -267,12 +267,13 @@ struct Product : public torch::autograd::Function<Product> {
 
 // The two GR-KAN layers of an MLP block: f1 = F1(x), h = f1 W1^T + b1 and f2 = F2(h), out = f2 W2^T + b2.  Where it is the
 // faster route (grkan_hidden_pays, by direction) h and f2 come from one kernel, and in the backward pass the product with W2 and
-// F2's gradients, so that dF2 is never written; elsewhere from torch's product and the rational function.  Saves what the layers by
-// themselves save.  `wgrad1`, `wgrad2`: whether the layers' weight gradients take grkan_linear_wgrad at this size.
+// F2's gradients, so that dF2 is never written; elsewhere from torch's product and the rational function.  Saves what
+// the layers by themselves save.  `wgrad`: whether the weight gradients take grkan_linear_wgrad (one answer for both: the second
+// layer's sizes are the first one's in the other order).
 struct Block : public torch::autograd::Function<Block> {
     static Tensor forward(AutogradContext *ctx, const Tensor &x, const Tensor &A1, const Tensor &B1, const Tensor &W1,
                           const Tensor &A2, const Tensor &B2, const Tensor &W2, const std::optional<Tensor> &b1,
-                          const std::optional<Tensor> &b2, bool wgrad1, bool wgrad2)
+                          const std::optional<Tensor> &b2, bool wgrad)
     {
         const Sizes s1 = sizes_of(x, A1, B1);
         const int64_t hidden = W1.size(0);
@@ -295,7 +296,7 @@ struct Block : public torch::autograd::Function<Block> {
         }
         ctx->save_for_backward({x, A1, B1, W1, A2, B2, W2, b1 ? *b1 : Tensor(), b2 ? *b2 : Tensor(), f1, h, f2});
         ctx->saved_data["biases"] = (int64_t)(b1 ? 1 : 0) + (b2 ? 2 : 0);
-        ctx->saved_data["wgrad"] = (int64_t)(wgrad1 ? 1 : 0) + (wgrad2 ? 2 : 0);
+        ctx->saved_data["wgrad"] = wgrad;
         return at::_unsafe_view(at::linear(f2, W2, b2), x.sizes());
     }
 
@@ -312,10 +313,11 @@ struct Block : public torch::autograd::Function<Block> {
     static variable_list backward(AutogradContext *ctx, const variable_list &grads)
     {
         const auto saved = ctx->get_saved_variables();
-        variable_list out(11);
+        variable_list out(10);
         if (!grads[0].defined())
             return out;
-        const int64_t biases = ctx->saved_data["biases"].toInt(), wgrad = ctx->saved_data["wgrad"].toInt();
+        const int64_t biases = ctx->saved_data["biases"].toInt();
+        const bool wgrad = ctx->saved_data["wgrad"].toBool();
         const bool has1 = (biases & 1) != 0, has2 = (biases & 2) != 0;
         const Tensor &A1 = saved[1], &B1 = saved[2], &W1 = saved[3], &A2 = saved[4], &B2 = saved[5];
         const bool want_b1 = has1 && ctx->needs_input_grad(7), want_b2 = has2 && ctx->needs_input_grad(has1 ? 8 : 7);
@@ -340,7 +342,7 @@ struct Block : public torch::autograd::Function<Block> {
         } else {
             f2 = as_saved(saved[11], x, {rows, hidden});
         }
-        gradients_of(dout, f2, want_w2, want_b2, (wgrad & 2) != 0, out[6], out[8]);
+        gradients_of(dout, f2, want_w2, want_b2, wgrad, out[6], out[8]);
         if (!want_dh)
             return out;
         if (!graph) {
@@ -370,7 +372,7 @@ struct Block : public torch::autograd::Function<Block> {
         if (want_w1 || want_b1) {
             if (!graph)
                 f1 = as_saved(saved[9], x, x.sizes()).view({rows, D});
-            gradients_of(dh, f1, want_w1, want_b1, (wgrad & 1) != 0, out[3], out[7]);
+            gradients_of(dh, f1, want_w1, want_b1, wgrad, out[3], out[7]);
         }
         if (want_first) {
             const variable_list d = Rational::in_backward(x, dh.mm(W1).view(x.sizes()), A1, B1);
@@ -422,8 +424,7 @@ std::optional<Tensor> product(const Tensor &y, const Tensor &W, const std::optio
 // The MLP block in training, with a gradient wanted for its input and every parameter.  (Hooks and the like on its
 // modules are the caller's to check.  In a pass without a graph nothing tells whether one is wanted for the input.)
 std::optional<Tensor> block(const Tensor &x, const Tensor &A1, const Tensor &B1, const Tensor &W1, const std::optional<Tensor> &b1,
-                            const Tensor &A2, const Tensor &B2, const Tensor &W2, const std::optional<Tensor> &b2, bool wgrad1,
-                            bool wgrad2)
+                            const Tensor &A2, const Tensor &B2, const Tensor &W2, const std::optional<Tensor> &b2, bool wgrad)
 {
     if (!plain_context() || !on_current_gpu(x))
         return std::nullopt;
@@ -446,7 +447,7 @@ std::optional<Tensor> block(const Tensor &x, const Tensor &A1, const Tensor &B1,
         if (reinterpret_cast<uintptr_t>(t->data_ptr()) % 16 != 0)
             return std::nullopt;
     // (contiguous: as for Rational)
-    return Block::apply(x.contiguous(), A1, B1, W1, A2, B2, W2, b1, b2, wgrad1, wgrad2);
+    return Block::apply(x.contiguous(), A1, B1, W1, A2, B2, W2, b1, b2, wgrad);
 }
 
 // What layer_packed reads of a layer's parameters: the packed weights, the bias, and a row of coefficients for every
@@ -600,13 +601,13 @@ PYBIND11_MODULE(_native, mod)
         return args.call([&] { return product(y, W, bias); });
     });
     mod.def("block", [](handle x_, handle A1_, handle B1_, handle W1_, handle b1_, handle A2_, handle B2_, handle W2_, handle b2_,
-                        bool wgrad1, bool wgrad2) {
+                        bool wgrad) {
         Arguments args;
         const Tensor x = args.tensor(x_), A1 = args.tensor(A1_), B1 = args.tensor(B1_), W1 = args.tensor(W1_);
         const std::optional<Tensor> b1 = args.optional(b1_);
         const Tensor A2 = args.tensor(A2_), B2 = args.tensor(B2_), W2 = args.tensor(W2_);
         const std::optional<Tensor> b2 = args.optional(b2_);
-        return args.call([&] { return block(x, A1, B1, W1, b1, A2, B2, W2, b2, wgrad1, wgrad2); });
+        return args.call([&] { return block(x, A1, B1, W1, b1, A2, B2, W2, b2, wgrad); });
     });
     mod.def("layer_model", [](handle x_, handle A_, handle B_, handle W_, handle bias_) {
         Arguments args;

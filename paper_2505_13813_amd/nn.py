@@ -543,5 +543,4 @@ class KATMlp(nn.Module):
         hidden = params[2].shape[0] if params[2].dim() else 0
         if not dim or not hidden:
             return None
-        pays = wgrad_pays(x.numel() // dim, dim, hidden)
-        return binding.load_native().block(x, *params, pays, pays)
+        return binding.load_native().block(x, *params, wgrad_pays(x.numel() // dim, dim, hidden))
