@@ -144,11 +144,14 @@ struct Undifferentiable : public torch::autograd::Function<Undifferentiable> {
 };
 
 // y = F(x); A [G, m+1] or, shared by the groups, [m+1]; all contiguous.  (A copy made in here would have no history: a second
-// derivative with respect to what it was made of would not reach Undifferentiable.)
+// derivative with respect to what it was made of would not reach Undifferentiable.)  `known`: y, where it is there already and
+// only its history is wanted.
 struct Rational : public torch::autograd::Function<Rational> {
-    static Tensor forward(AutogradContext *ctx, const Tensor &x, const Tensor &A, const Tensor &B)
+    static Tensor forward(AutogradContext *ctx, const Tensor &x, const Tensor &A, const Tensor &B, const std::optional<Tensor> &known)
     {
         ctx->save_for_backward({x, A, B});
+        if (known)
+            return known->view_as(*known);
         const Sizes s = sizes_of(x, A, B);
         Tensor y = at::empty_like(x, at::MemoryFormat::Contiguous);
         check(grkan_fwd_model(x.data_ptr(), A.data_ptr(), B.data_ptr(), y.data_ptr(), s.rows, s.D, s.G, s.m, s.n, *io_of(x),
@@ -162,8 +165,10 @@ struct Rational : public torch::autograd::Function<Rational> {
         const auto saved = ctx->get_saved_variables();
         const Tensor &x = saved[0], &A = saved[1], &B = saved[2];
         if (!grads[0].defined())
-            return {Tensor(), Tensor(), Tensor()};
-        return in_backward(x, grads[0].contiguous(), A, B);
+            return variable_list(4);
+        variable_list out = in_backward(x, grads[0].contiguous(), A, B);
+        out.resize(4); // (none for `known`)
+        return out;
     }
 
     // {dx, dA, dB} inside a backward pass; where a graph of it is wanted, behind Undifferentiable.
@@ -224,12 +229,15 @@ Tensor linear_of_rows(const Tensor &y, const Tensor &W, const std::optional<Tens
 }
 
 // out = y W^T + bias with dW and dbias from grkan_linear_wgrad; saves what torch's linear saves: each operand where
-// the gradient of the other is wanted.
+// the gradient of the other is wanted.  `known`: out, as for Rational.
 struct Product : public torch::autograd::Function<Product> {
-    static Tensor forward(AutogradContext *ctx, const Tensor &y, const Tensor &W, const std::optional<Tensor> &bias)
+    static Tensor forward(AutogradContext *ctx, const Tensor &y, const Tensor &W, const std::optional<Tensor> &bias,
+                          const std::optional<Tensor> &known)
     {
         ctx->save_for_backward({W.requires_grad() ? y : Tensor(), y.requires_grad() ? W : Tensor()});
         ctx->saved_data["has_bias"] = bias.has_value();
+        if (known)
+            return known->view_as(*known);
         return linear_of_rows(y, W, bias);
     }
 
@@ -239,7 +247,7 @@ struct Product : public torch::autograd::Function<Product> {
         const Tensor &y = saved[0], &W = saved[1];
         const Tensor &dout = grads[0];
         if (!dout.defined())
-            return {Tensor(), Tensor(), Tensor()};
+            return variable_list(4);
         const bool want_y = ctx->needs_input_grad(0), want_w = ctx->needs_input_grad(1);
         const bool want_b = ctx->saved_data["has_bias"].toBool() && ctx->needs_input_grad(2);
         const int64_t D_out = dout.size(-1);
@@ -261,7 +269,7 @@ struct Product : public torch::autograd::Function<Product> {
             dW = dout2.t().mm(y2);
         if (want_b && !db.defined())
             db = dout2.sum(0);
-        return {dy, dW, db};
+        return {dy, dW, db, Tensor()};
     }
 };
 
@@ -294,7 +302,10 @@ struct Block : public torch::autograd::Function<Block> {
                                   GRKAN_BF16, GRKAN_BF16, A2.dim() == 1, stream_of(x)),
                   "grkan_fwd");
         }
-        ctx->save_for_backward({x, A1, B1, W1, A2, B2, W2, b1 ? *b1 : Tensor(), b2 ? *b2 : Tensor(), f1, h, f2});
+        // (the biases' values are not read again: they may be written to before the backward pass)
+        ctx->save_for_backward({x, A1, B1, W1, A2, B2, W2, f1, h, f2});
+        if (b1)
+            ctx->saved_data["b1"] = *b1;
         ctx->saved_data["biases"] = (int64_t)(b1 ? 1 : 0) + (b2 ? 2 : 0);
         ctx->saved_data["wgrad"] = wgrad;
         return at::_unsafe_view(at::linear(f2, W2, b2), x.sizes());
@@ -329,24 +340,25 @@ struct Block : public torch::autograd::Function<Block> {
         const Tensor W2 = as_saved(saved[6], x, {D, hidden});
         const Tensor dout = as_saved(grads[0].reshape({rows, D}), x, {rows, D});
         Tensor f1, h, f2;
-        // With a graph of this pass wanted, the activations are formed again, with their history, and every gradient by
-        // operations that torch differentiates, each from the one behind it.  (torch::autograd::grad of the block formed again would
-        // not stop at the block's inputs: on its way to a parameter it would walk their history too, and run their hooks.)
+        // With a graph of this pass wanted, the activations get their history back, and every gradient is formed by operations that
+        // torch differentiates, each from the one behind it.  (torch::autograd::grad of the block formed again would not stop at the
+        // block's inputs: on its way to a parameter it would walk their history too, and run their hooks.)
         const bool graph = at::GradMode::is_enabled();
+        f2 = as_saved(saved[9], x, {rows, hidden});
         if (graph) {
             check_saved(x, x, A1, B1);
-            f1 = Rational::apply(x, A1, B1).view({rows, D});
-            h = at::linear(f1, as_saved(W1, x, {hidden, D}), has1 ? std::optional<Tensor>(saved[7]) : std::nullopt);
+            f1 = Rational::apply(x, A1, B1, as_saved(saved[7], x, x.sizes())).view({rows, D});
+            h = as_saved(saved[8], x, {rows, hidden});
             check_saved(h, h, A2, B2);
-            f2 = Rational::apply(h, A2, B2);
-        } else {
-            f2 = as_saved(saved[11], x, {rows, hidden});
+            h = Product::apply(f1, as_saved(W1, x, {hidden, D}),
+                               has1 ? std::optional<Tensor>(ctx->saved_data["b1"].toTensor()) : std::nullopt, h);
+            f2 = Rational::apply(h, A2, B2, f2);
         }
         gradients_of(dout, f2, want_w2, want_b2, wgrad, out[6], out[8]);
         if (!want_dh)
             return out;
         if (!graph) {
-            h = as_saved(saved[10], x, {rows, hidden});
+            h = as_saved(saved[8], x, {rows, hidden});
             check_saved(h, h, A2, B2);
         }
         const int32_t G = (int32_t)B2.size(0);
@@ -371,7 +383,7 @@ struct Block : public torch::autograd::Function<Block> {
         }
         if (want_w1 || want_b1) {
             if (!graph)
-                f1 = as_saved(saved[9], x, x.sizes()).view({rows, D});
+                f1 = as_saved(saved[7], x, x.sizes()).view({rows, D});
             gradients_of(dh, f1, want_w1, want_b1, wgrad, out[3], out[7]);
         }
         if (want_first) {
@@ -406,7 +418,7 @@ std::optional<Tensor> rational(const Tensor &x, const Tensor &A, const Tensor &B
     const bool degrees = (m == 5 && n == 4) || (m == 3 && n == 2) || (m == 7 && n == 6);
     if (!degrees || G <= 0 || D <= 0 || D > INT32_MAX || D % G != 0 || x.numel() == 0)
         return std::nullopt;
-    return Rational::apply(x.contiguous(), A.contiguous(), B.contiguous());
+    return Rational::apply(x.contiguous(), A.contiguous(), B.contiguous(), std::nullopt);
 }
 
 // The product of a bfloat16 layer in training.  (Hooks and the like on the linear module are the caller's to check.)
@@ -418,7 +430,7 @@ std::optional<Tensor> product(const Tensor &y, const Tensor &W, const std::optio
     if (y.scalar_type() != at::kBFloat16 || W.scalar_type() != at::kBFloat16 || (bias && bias->scalar_type() != at::kBFloat16) ||
         W.dim() != 2 || y.dim() < 1 || y.size(-1) != W.size(1) || !W.is_contiguous())
         return std::nullopt;
-    return Product::apply(y, W, bias);
+    return Product::apply(y, W, bias, std::nullopt);
 }
 
 // The MLP block in training, with a gradient wanted for its input and every parameter.  (Hooks and the like on its

@@ -226,3 +226,43 @@ def test_large_blocks_by_two_kernels(dim, hidden, rows):
     x = torch.randn(2, rows // 2, dim, device="cuda:0").to(torch.bfloat16).requires_grad_()
     _same_gradients(torch, block, lambda f: f(x), [x] + list(block.parameters()), False)
     assert _near(block(x), _layers(block)(x))
+
+
+def test_biases_may_be_written_to_before_the_backward_pass():
+    """No gradient depends on a bias's value but through the activations, which are kept."""
+    import torch
+
+    block, x = _block(torch)
+    leaves = [x] + list(block.parameters())
+    W1, W2 = block.fc1.linear.weight, block.fc2.linear.weight
+    biases = [(fc.linear.bias, fc.linear.bias.detach().clone()) for fc in (block.fc1, block.fc2)]
+
+    def passes(f, write):
+        out = []
+        for create_graph in (False, True):
+            y = f(x)
+            with torch.no_grad():
+                for bias, _ in biases if write else ():
+                    bias.add_(1.0)
+            out += _gradients(torch, y, leaves, create_graph)
+            with torch.no_grad():
+                for bias, was in biases if write else ():
+                    bias.copy_(was)
+        dW2 = out[len(leaves) + [leaf is W2 for leaf in leaves].index(True)]  # with a graph
+        return out + list(torch.autograd.grad(dW2.float().pow(2).sum(), [W1, x]))
+
+    got, untouched, layers = passes(block, True), passes(block, False), passes(_layers(block), True)
+    for g, u, w in zip(got, untouched, layers):
+        assert _near(g, u) and _near(g, w)
+
+
+def test_passes_without_a_graph_have_the_same_bits():
+    """In training mode; the input of such a pass takes no gradient, or is an inference tensor."""
+    import torch
+
+    block, x = _block(torch)
+    want = block(x)
+    for mode in (torch.no_grad, torch.inference_mode):
+        with mode():
+            for z in (x, x.detach(), x.clone()):
+                assert torch.equal(block(z), want)
