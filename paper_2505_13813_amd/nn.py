@@ -516,7 +516,7 @@ class KATMlp(nn.Module):
 
     def _native_block(self, x):
         """The block in bfloat16 training as one native autograd function (the hidden activation's product and rational
-        function in one kernel each way), or None where that route is not taken: where calling the two layers would do
+        function in one kernel each way where that is the faster route), or None where that route is not taken: where calling the two layers would do
         anything else than their parts do, or a parameter or x takes no gradient.  A pass without a gradient in training
         mode may be the first half of one with (reentrant checkpointing): both take the same kernels, and in the first x has
         lost its gradient if anything came before the block.  (Only where x takes none in the second pass either, a block
