@@ -1306,14 +1306,15 @@ struct SmallVariant {
 //   16 x 64: 5.5 / 6.8 / 10.1    32 x 128: 8.1 / 10.8 / 16.6    64 x 192: 11.6 / 17.2 / 29
 //   64 x 384: 14.6 / 22 / 38 alone, 24 / 44 where rounds follow each other
 //   112 x 768: 41 / - / 133   112 x 384: - / 43 / -   112 x 192: 24 / - / -
-// (before F had wavefronts of its own: 6.6 / 7.8 / 11.7, 8.5 / 12.2 / 20.5, 13.2 / 21 / 36 and 15.8 / 24.5 / 45).  With
-// these lines the tile taken is at most 6 % slower than the best of the five at all but nine of 234 sizes, and nowhere
-// more than 20 %.
+// (before F had wavefronts of its own: 6.6 / 7.8 / 11.7, 8.5 / 12.2 / 20.5, 13.2 / 21 / 36 and 15.8 / 24.5 / 45).  The last
+// line's slope decides ties with 64 x 192 at D_in = 4096, where three rounds of that are as long as two of this by the estimate and
+// 17 % longer by the clock (3,152 rows of 4096 -> 2304 130 us against 111).  With these lines the tile taken is within 5 % of the
+// best of the five at 1,089 of 1,100 sizes (eleven D_in, ten D_out, ten row counts) and nowhere more than 18 % above it.
 static const SmallVariant kSmall[] = {
     {1, 4, 1, 4.8, 1.9},
     {2, 4, 2, 4.6, 4.2},
     {4, 3, 4, 5.9, 7.9},
-    {4, 3, 8, 6.0, 12.6},
+    {4, 3, 8, 6.0, 12.55},
 };
 // Whether the tiles of one channel block share an XCD (else: those of one token block); the small tiles only.
 static bool is_n_major(int64_t rows, int32_t D_out) { return rows < D_out; }

@@ -129,3 +129,14 @@ def test_weight_gradient_rule():
     assert not wgrad_pays(25216, 1024, 4096)                                     # 132 tiles: 413 us against 340
     assert not wgrad_pays(12608, 2688, 2880)                                     # 210 tiles: 218 us against 213
     assert not wgrad_pays(25216, 3136, 3072) and not wgrad_pays(25216, 384, 1532)
+
+
+def test_tile_where_two_estimates_meet():
+    """Two rounds of 64 x 384 against three of 64 x 192 at D_in = 4096 (measured: 111 us against 130); and the neighbours that the
+    same line decides, three rounds of 64 x 384 against one of 112 x 768 at D_in = 3072 (133 against 126)."""
+    from paper_2505_13813_amd import binding
+
+    for sizes in ((3152, 4096, 2304), (6304, 4096, 1024), (9456, 4096, 768), (12608, 4096, 500)):
+        assert binding.grkan_linear_tile(*sizes) == (64, 384)
+    for sizes in ((9456, 3072, 1536), (6304, 3072, 2304)):
+        assert binding.grkan_linear_tile(*sizes) == (112, 768)
