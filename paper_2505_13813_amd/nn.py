@@ -516,11 +516,12 @@ class KATMlp(nn.Module):
 
     def _native_block(self, x):
         """The block in bfloat16 training as one native autograd function (the hidden activation's product and rational
-        function in one kernel each way where that is the faster route), or None where that route is not taken: where calling the two layers would do
-        anything else than their parts do, or a parameter or x takes no gradient.  A pass without a gradient in training
-        mode may be the first half of one with (reentrant checkpointing): both take the same kernels, and in the first x has
-        lost its gradient if anything came before the block.  (Only where x takes none in the second pass either, a block
-        right behind an input of a checkpointed segment that needs none, do the two passes differ, by the rounding.)"""
+        function in one kernel each way where that is the faster route), or None where that route is not taken: where calling
+        the two layers would do anything else than their parts do, or a parameter or x takes no gradient.  A pass without a
+        gradient in training mode may be the first half of one with (reentrant checkpointing): both take the same kernels, and
+        in the first x has lost its gradient if anything came before the block.  (Only where x takes none in the second pass
+        either, a block right behind an input of a checkpointed segment that needs none, do the two passes differ, by the
+        rounding.)"""
         if x.dtype is not torch.bfloat16 or not (x.requires_grad if torch.is_grad_enabled() else self.training):
             return None
         if torch.is_autocast_enabled() or torch.compiler.is_compiling():
