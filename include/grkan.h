@@ -351,6 +351,30 @@ grkan_status_t grkan_hidden_bwd(const void *dout, const void *W, const void *h, 
                                 void *hip_stream);
 
 /*
+ * The products of a bfloat16 KAT MLP block:
+ *
+ *   transposed == 0:  out[r, o] = sum_k x[r, k] W[o, k] (+ bias[o])     W [N, K]
+ *   transposed != 0:  out[r, o] = sum_k x[r, k] W[k, o] (+ bias[o])     W [K, N]
+ *
+ * float32 sums, rounded to bfloat16 (nearest even).  With A and B (transposed == 0 only) out = F of that rounded result, as
+ * grkan_fwd_model of degrees (5, 4) on it: A [G, 6] (or [6], shared_numerator), B [G, 4].
+ * x [rows, K], W, bias [N] or NULL, out [rows, N], A, B: DEVICE, bfloat16, contiguous; x, W and out 16-byte aligned, bias 8; out
+ * must not overlap the others.  Nothing is allocated.  Results are the same from run to run; the order of the sums depends
+ * on the tile, which depends on the sizes.
+ * grkan_product_supported: K a multiple of 64 and N one of 8 (each at most 2^20), at most 2^30 rows; F: N / G a multiple of 8.
+ * Anything else is GRKAN_ERR_UNSUPPORTED.
+ * grkan_product_estimate_us, grkan_product_tile: host-only; the estimated device time (0 for sizes that are not supported),
+ * and the tile that is used, with the workgroups per compute unit.
+ */
+int32_t grkan_product_supported(int64_t rows, int32_t K, int32_t N);
+double grkan_product_estimate_us(int64_t rows, int32_t K, int32_t N, int32_t rational);
+grkan_status_t grkan_product_tile(int64_t rows, int32_t K, int32_t N, int32_t rational, int32_t *tile_rows,
+                                  int32_t *tile_channels, int32_t *per_unit);
+grkan_status_t grkan_product(const void *x, const void *W, const void *bias, void *out, int64_t rows, int32_t K,
+                             int32_t N, int32_t transposed, const void *A, const void *B, int32_t G,
+                             int32_t shared_numerator, void *hip_stream);
+
+/*
  * grkan_bwd for callers that cannot allocate device memory or pass a workspace:
  * code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Same arguments, results and kernels as grkan_bwd (bit-identical

@@ -95,6 +95,14 @@ def load_library():
     lib.grkan_linear_wgrad.restype = ctypes.c_int
     lib.grkan_linear_wgrad_workspace_bytes.argtypes = [i64, i32, i32]
     lib.grkan_linear_wgrad_workspace_bytes.restype = sz
+    lib.grkan_product_supported.argtypes = [i64, i32, i32]
+    lib.grkan_product_supported.restype = i32
+    lib.grkan_product_estimate_us.argtypes = [i64, i32, i32, i32]
+    lib.grkan_product_estimate_us.restype = ctypes.c_double
+    lib.grkan_product_tile.argtypes = [i64, i32, i32, i32, vp, vp, vp]
+    lib.grkan_product_tile.restype = ctypes.c_int
+    lib.grkan_product.argtypes = [vp, vp, vp, vp, i64, i32, i32, i32, vp, vp, i32, i32, vp]
+    lib.grkan_product.restype = ctypes.c_int
     lib.grkan_hidden_supported.argtypes = [i32, i32, i32]
     lib.grkan_hidden_supported.restype = i32
     lib.grkan_hidden_pays.argtypes = [i64, i32, i32, i32, i32]
@@ -375,6 +383,20 @@ def grkan_linear_fwd(x, A, B, W, bias=None, out=None, out_dtype=None, stream=Non
 def grkan_linear_estimate_us(rows: int, D_in: int, D_out: int) -> float:
     """Estimated device time of grkan_linear_fwd in microseconds (host only)."""
     return float(load_library().grkan_linear_estimate_us(int(rows), int(D_in), int(D_out)))
+
+
+def grkan_product_estimate_us(rows: int, K: int, N: int, rational: bool = False) -> float:
+    """Estimated device time of grkan_product; 0 for sizes it does not take."""
+    return float(load_library().grkan_product_estimate_us(int(rows), int(K), int(N), int(bool(rational))))
+
+
+def grkan_product_tile(rows: int, K: int, N: int, rational: bool = False) -> Tuple[int, int, int]:
+    """Rows and channels of the tile grkan_product runs these sizes in, and workgroups per compute unit."""
+    out = [ctypes.c_int32() for _ in range(3)]
+    st = load_library().grkan_product_tile(int(rows), int(K), int(N), int(bool(rational)), *(ctypes.byref(v) for v in out))
+    if st:
+        raise GrkanError(st, "grkan_product_tile")
+    return tuple(v.value for v in out)
 
 
 def grkan_linear_tile(rows: int, D_in: int, D_out: int) -> Tuple[int, int]:

@@ -10,8 +10,10 @@ PKG = Path(__file__).resolve().parent
 CSRC = PKG / "csrc"
 LIB = PKG / "libgrkan.so"
 SOURCES = [CSRC / "grkan_kernels.hip", CSRC / "grkan_plan.cpp", CSRC / "grkan_alg1_baseline.hip",
-           CSRC / "grkan_linear.hip", CSRC / "grkan_linear_grad.hip", CSRC / "grkan_hidden.hip"]
-HEADERS = [CSRC / "grkan_walk.h", CSRC / "grkan_plan.h", CSRC / "grkan_elem.h", PKG.parent / "include" / "grkan.h",
+           CSRC / "grkan_linear.hip", CSRC / "grkan_linear_grad.hip", CSRC / "grkan_hidden.hip",
+           CSRC / "grkan_product.hip"]
+HEADERS = [CSRC / "grkan_walk.h", CSRC / "grkan_plan.h", CSRC / "grkan_elem.h", CSRC / "grkan_tile.h",
+           PKG.parent / "include" / "grkan.h",
            PKG.parent / "include" / "grkan_alg1.h"]
 
 # the C++ autograd route of the PyTorch front end: host code only, over the C ABI of the library above

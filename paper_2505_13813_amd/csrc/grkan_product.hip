@@ -1,0 +1,443 @@
+// The matrix products of a KAT MLP block on gfx950 (MI355X), bfloat16 in and out, float32 sums:
+//
+//     out = x W^T + bias          (W [N, K], forward)           optionally out = F(x W^T + bias), F the group-wise rational
+//     out = x W                   (W [K, N], backward)          function of the next layer on the rounded result
+//
+// A workgroup owns a tile of rows x channels and walks K in stages of 64: whole 128-byte lines of both operands come to LDS by
+// LDS-direct loads, NBUF stages deep.  16-byte pieces of a row are permuted (xor with the row number), so that operand reads
+// hit all banks; where W has the contraction as its slow dimension it comes as it lies and is transposed on the way out of LDS
+// (ds_read_b64_tr_b16), its rows numbered so that both operands count k alike.
+//
+//   * Wavefronts of their own (LD of them) issue the loads: a wavefront that waits to hand a load to a busy memory pipe cannot
+//     issue matrix instructions meanwhile.  6,304 x 3072 -> 768 in 160 x 128 tiles 33.3 -> 28.9 us, 25,216 x 1536 -> 384 in 224 x 192
+//     33.3 -> 30.1.  (The 320 x 256 tile has no registers for a third wavefront per SIMD, and hides more behind a longer stage.)
+//   * The others multiply, with one barrier per stage: it stands behind the first of TM rows of tiles, when every wavefront has the
+//     stage's operands in registers.  Behind it the next stage's are read, each row of tiles behind the last use of its registers,
+//     W's into a second set.  (With the reads just in front of their use, and the barrier among them, 160 x 128 with two workgroups
+//     per unit took 45.6 us for 3,152 x 3072 -> 768, with this order 36.8.)
+//   * The result leaves through LDS in whole rows; F is evaluated there, where a lane holds eight channels of one group.
+//
+// Measured on one MI355X against the library's product, us (by itself, over the same buffers):
+//   25,216 x 1536 -> 384  29 against 35 - 38    6,304 x 3072 -> 768  28 against 32 - 36    6,304 x 768 -> 3072  31 against 48 (37 with F)
+//   25,216 x 384 -> 1536  37 against 59         25,216 x 3072 -> 768 89 against 146        50,432 x 768 -> 3072 227 - 237 against 227
+// What bounds it: at 6,304 x 3072 -> 768 the loads alone take 24 of the 29 us, the matrix instructions alone 19, the LDS
+// reads alone 16 (launch, first loads and result 5 in each); at 25,216 x 3072 -> 768 59, 66 and 33 of 97, with the clock at
+// 2.2 GHz.
+#include <hip/hip_runtime.h>
+
+#include <mutex>
+
+#include "grkan_plan.h"
+#include "grkan_tile.h"
+
+namespace grkan {
+namespace product {
+
+using namespace tile;
+
+constexpr int kM = 5, kN = 4;
+
+struct Args {
+    const char *x;    // bfloat16 [M, K]
+    const char *W;    // bfloat16 [N, K]; TRANSPOSED: [K, N]
+    const char *bias; // bfloat16 [N] or NULL
+    char *out;        // bfloat16 [M, N]
+    CoefRows coef;    // RATIONAL: of F
+    int64_t M;
+    int32_t N, K;
+    int32_t dg;       // RATIONAL: channels per group
+    int32_t tiles_n, tiles, per_xcd;
+};
+
+// A wavefront's share is TM x TN tiles of 16 x 16, a workgroup WM x WN such wavefronts and LD that load; PER workgroups per
+// compute unit.
+template <int TM_, int TN_, int WM_, int WN_, int NBUF_, int LD_, int PER_ = 1> struct Shape {
+    static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_, NBUF = NBUF_, LD = LD_, PER = PER_;
+    static constexpr int BM = 16 * TM * WM, BN = 16 * TN * WN, kWaves = WM * WN, kThreads = 64 * (kWaves + LD);
+    static constexpr int kFetchers = LD ? LD : kWaves;      // wavefronts that load
+    static constexpr uint32_t kXB = BM * 128u, kWB = BN * 128u, kStage = kXB + kWB;
+    static constexpr int kLoads = (BM + BN) / 8;            // of a stage, 1 KB each
+    static constexpr int kHi = (kLoads + kFetchers - 1) / kFetchers, kLo = kLoads / kFetchers, kRem = kLoads % kFetchers;
+    static constexpr uint32_t kPitch = BN * 2 + 16;         // of the result's rows in LDS
+    static constexpr int kParts = (size_t)BM * kPitch > 160 * 1024 ? 2 : 1, kMP = (TM + kParts - 1) / kParts; // it leaves in parts
+    static constexpr size_t kMain = (size_t)NBUF * kStage, kRows = (size_t)WM * kMP * 16 * kPitch;
+    static constexpr size_t kLds = kMain > kRows ? kMain : kRows;
+    static_assert(PER * kLds <= 160 * 1024 && TM >= 2 && (kWaves + LD) % 4 == 0, "");
+};
+
+template <class SH, bool TRANSPOSED, bool RATIONAL>
+__global__ __launch_bounds__(SH::kThreads, SH::PER *SH::kThreads / 256) void product_kernel(const Args a)
+{
+    constexpr int TM = SH::TM, TN = SH::TN, NBUF = SH::NBUF, BM = SH::BM, BN = SH::BN;
+    constexpr uint32_t NP = BN / 16; // 32-byte column pairs of a row of W, TRANSPOSED
+    extern __shared__ __align__(16) char smem[];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t i16 = (uint32_t)lane & 15u, g4 = (uint32_t)lane >> 4;
+    const bool computes = SH::LD == 0 || wave < SH::kWaves, fetches = SH::LD == 0 || wave >= SH::kWaves;
+
+    // workgroups go round-robin over the 8 XCDs; each gets a run of tiles in row order, whose rows of x its L2 fetches once
+    const int32_t lin = ((int32_t)blockIdx.x & 7) * a.per_xcd + ((int32_t)blockIdx.x >> 3);
+    if (lin >= a.tiles)
+        return;
+    const int32_t tm = __builtin_amdgcn_readfirstlane(lin / a.tiles_n);
+    const int32_t tn = lin - tm * a.tiles_n;
+    const int64_t row0 = (int64_t)tm * BM;
+    const int32_t col0 = tn * BN;
+    const int32_t T = a.K / 64;
+    const uint32_t ldk = (uint32_t)a.K * 2u, ldn = (uint32_t)a.N * 2u;
+
+    // ---- loads: load u of a stage fills KB u of its buffer.  x (and W): rows of 128 bytes, 16-byte piece p of row r at slot
+    // p xor (r / 2 mod 8).  W transposed: 64 rows of BN channels, slot row r holding k = 8 (r / 4 mod 4) + r mod 4 + 4 (r / 16 mod 2)
+    // of its 32, column pairs rotated by the row.  Rows and columns past the end repeat the last (their results are not stored).
+    const int fw = SH::LD ? wave - SH::kWaves : wave;
+    uint32_t off[SH::kHi];
+    {
+        const int64_t left = a.M - row0;
+        const uint32_t last_x = left < BM ? (uint32_t)left - 1u : (uint32_t)BM - 1u;
+        const uint32_t last_w = a.N - col0 < BN ? (uint32_t)(a.N - col0) - 1u : (uint32_t)BN - 1u;
+#pragma unroll
+        for (int q = 0; q < SH::kHi; ++q) {
+            const uint32_t u = (uint32_t)(fw + q * SH::kFetchers);
+            const bool isx = u * 8u < (uint32_t)BM;
+            if (isx || !TRANSPOSED) {
+                const uint32_t row = (isx ? u * 8u : u * 8u - BM) + ((uint32_t)lane >> 3), last = isx ? last_x : last_w;
+                const uint32_t piece = ((uint32_t)lane & 7u) ^ ((row >> 1) & 7u);
+                off[q] = (row < last ? row : last) * ldk + piece * 16u;
+            } else {
+                const uint32_t e = (u - BM / 8u) * 64u + (uint32_t)lane;
+                const uint32_t r = e / (2u * NP), s = e % (2u * NP);
+                const uint32_t rot = BN % 128 == 0 ? (r & 15u) % NP : ((r & 15u) >> 1) % NP;
+                const uint32_t k = (r & 32u) + 8u * ((r >> 2) & 3u) + (r & 3u) + ((r >> 4) & 1u) * 4u;
+                const uint32_t c = 2u * (((s >> 1) + NP - rot) % NP) + (s & 1u), most = (last_w + 1u) / 8u - 1u;
+                off[q] = k * ldn + (c < most ? c : most) * 16u;
+            }
+        }
+    }
+    const uint64_t x_base = reinterpret_cast<uint64_t>(a.x) + (uint64_t)row0 * ldk;
+    const uint64_t w_base = reinterpret_cast<uint64_t>(a.W) + (TRANSPOSED ? (uint64_t)(uint32_t)col0 * 2u : (uint64_t)(uint32_t)col0 * ldk);
+    auto fetch_one = [&](auto qc, int32_t t, uint32_t buf) {
+        constexpr int q = decltype(qc)::value;
+        const int u = fw + q * SH::kFetchers;
+        if ((q + 1) * SH::kFetchers <= SH::kLoads || u < SH::kLoads) {
+            const uint64_t base = u * 8 < BM ? x_base + (uint64_t)t * 128u : w_base + (uint64_t)t * (TRANSPOSED ? (uint64_t)ldn * 64u : 128u);
+            load_to_lds(uniform_u64(base), off[q], lds0 + buf + (uint32_t)u * 1024u);
+        }
+    };
+    auto wait_for = [&](auto ahead, bool more) { // all but the last `ahead` stages' loads, then for everyone
+        constexpr int kAhead = decltype(ahead)::value;
+        if (!more)
+            wait_loads<0>();
+        else if (SH::kRem == 0 || fw < SH::kRem)
+            wait_loads<kAhead * SH::kHi>();
+        else
+            wait_loads<kAhead * SH::kLo>();
+        asm volatile("s_barrier" ::: "memory");
+    };
+
+    // ---- operand reads: 16 rows (x) or 16 channels (W) x 32 k, lane (i, g) row or channel i, k = 8 g ..
+    const int wm = wave / SH::WN, wn = wave % SH::WN;
+    const uint32_t piece0 = g4 ^ ((i16 >> 1) & 7u);
+    const uint32_t x_at = lds0 + ((uint32_t)(wm * TM * 16) + i16) * 128u + piece0 * 16u; // second half of 64 k: xor 64
+    const uint32_t w_at = lds0 + SH::kXB + ((uint32_t)(wn * TN * 16) + i16) * 128u + piece0 * 16u;
+    uint32_t wt_at[TN];
+    if constexpr (TRANSPOSED) {
+        const uint32_t r15 = g4 * 4u + (i16 >> 2), rot = BN % 128 == 0 ? r15 % NP : (r15 >> 1) % NP;
+#pragma unroll
+        for (int n = 0; n < TN; ++n)
+            wt_at[n] = lds0 + SH::kXB + r15 * (BN * 2u) + (((uint32_t)(wn * TN + n) + rot) % NP) * 32u + (i16 & 3u) * 8u;
+    }
+    auto read_x = [&](uint32_t buf, int h, int m) { return lds_read16(((x_at + buf) ^ (uint32_t)(h * 64)) + (uint32_t)m * 2048u); };
+    auto read_w = [&](uint32_t buf, int h, int n) {
+        if constexpr (TRANSPOSED) {
+            const uint32_t at = wt_at[n] + buf + (uint32_t)(h * 32) * (BN * 2u);
+            const u32x2 lo = __builtin_bit_cast(u32x2, lds_read_transposed(at));
+            const u32x2 hi = __builtin_bit_cast(u32x2, lds_read_transposed(at + 16u * (BN * 2u)));
+            return u32x4{lo[0], lo[1], hi[0], hi[1]};
+        } else {
+            return lds_read16(((w_at + buf) ^ (uint32_t)(h * 64)) + (uint32_t)n * 2048u);
+        }
+    };
+
+    f32x4 acc[TM][TN];
+#pragma unroll
+    for (int m = 0; m < TM; ++m)
+#pragma unroll
+        for (int n = 0; n < TN; ++n)
+            acc[m][n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+    // One step of 32 k, half h of stage t: multiplies with x and wc while the next step's operands are read into x, each row of
+    // tiles behind its own last use, and wn_.  In the second half, behind the first row of tiles, the barrier: every
+    // wavefront has its operands of this stage, so that its buffer is free for stage t + NBUF, and stage t + 1 has landed.
+    // (Behind the last stage the next buffer is read too, and not used.)
+    auto step = [&](auto hc, int32_t t, uint32_t buf, uint32_t buf_next, u32x4(&x)[TM], u32x4(&wc)[TN], u32x4(&wn_)[TN]) {
+        constexpr int h = decltype(hc)::value;
+        const uint32_t from = h == 1 ? buf_next : buf;
+        const bool more = t + NBUF < T;
+        static_for<0, TM>([&](auto mc) {
+            constexpr int m = decltype(mc)::value;
+            if constexpr (h == 1 && m == 1 && SH::LD > 0)
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            if constexpr (h == 1 && m == 1 && SH::LD == 0)
+                wait_for(std::integral_constant<int, NBUF - 2>{}, t + NBUF - 1 < T);
+            if constexpr (m == 0)
+                x[TM - 1] = read_x(buf, h, TM - 1);
+            else
+                x[m - 1] = read_x(from, 1 - h, m - 1);
+            if constexpr (m >= 1) {
+                constexpr int n0 = (m - 1) * TN / (TM - 1), n1 = m * TN / (TM - 1);
+                static_for<n0, n1>([&](auto nc) { wn_[decltype(nc)::value] = read_w(from, 1 - h, decltype(nc)::value); });
+            }
+            if constexpr (h == 1 && m >= 1 && SH::LD == 0) {
+                constexpr int q0 = (m - 1) * SH::kHi / (TM - 1), q1 = m * SH::kHi / (TM - 1);
+                if constexpr (q1 > q0)
+                    if (more)
+                        static_for<q0, q1>([&](auto qc) { fetch_one(qc, t + NBUF, buf); });
+            }
+            fence_schedule();
+#pragma unroll
+            for (int n = 0; n < TN; ++n)
+                acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wc[n]), __builtin_bit_cast(bf16x8, x[m]),
+                                                                    acc[m][n], 0, 0, 0);
+            fence_schedule();
+        });
+    };
+    auto advance = [&](uint32_t b) { return b + SH::kStage == NBUF * SH::kStage ? 0u : b + SH::kStage; };
+
+    // every wavefront passes T + 1 barriers here
+    if (fetches) {
+        static_for<0, NBUF>([&](auto sc) {
+            constexpr int s = decltype(sc)::value;
+            if (s < T)
+                static_for<0, SH::kHi>([&](auto qc) { fetch_one(qc, s, (uint32_t)s * SH::kStage); });
+        });
+        wait_for(std::integral_constant<int, NBUF - 1>{}, NBUF <= T);
+    } else {
+        asm volatile("s_barrier" ::: "memory");
+    }
+    if (!computes) {
+        uint32_t buf = 0;
+        for (int32_t t = 0; t < T; ++t) {
+            wait_for(std::integral_constant<int, NBUF - 2>{}, t + NBUF - 1 < T);
+            if (t + NBUF < T)
+                static_for<0, SH::kHi>([&](auto qc) { fetch_one(qc, t + NBUF, buf); });
+            buf = advance(buf);
+        }
+    } else {
+        u32x4 x[TM], wa[TN], wb[TN]; // (as words: carried around the loop as bfloat16 the compiler takes them apart)
+#pragma unroll
+        for (int n = 0; n < TN; ++n)
+            wa[n] = read_w(0, 0, n);
+#pragma unroll
+        for (int m = 0; m < TM - 1; ++m)
+            x[m] = read_x(0, 0, m);
+        uint32_t buf = 0;
+        for (int32_t t = 0; t < T; ++t) {
+            const uint32_t next = advance(buf);
+            step(std::integral_constant<int, 0>{}, t, buf, next, x, wa, wb);
+            step(std::integral_constant<int, 1>{}, t, buf, next, x, wb, wa);
+            buf = next;
+        }
+    }
+
+    // ---- result: bias, bfloat16, to LDS; from there in whole rows, eight channels a lane, through F
+    __syncthreads();
+    u32x2 bias[TN];
+#pragma unroll
+    for (int n = 0; n < TN; ++n) {
+        const int32_t c = col0 + (wn * TN + n) * 16 + (int32_t)g4 * 4;
+        bias[n] = computes && a.bias && c < a.N ? *(const u32x2 *)(a.bias + (size_t)c * 2u) : u32x2{0u, 0u};
+    }
+    constexpr int LR = BN / 8, RP = SH::kThreads / LR, MP = SH::kMP; // lanes per row, rows at a time
+    const int32_t c = col0 + (tid % LR) * 8;
+    const bool in = tid < RP * LR && c < a.N;
+    Coef<kM, kN> co;
+    if constexpr (RATIONAL)
+        if (in)
+            co = load_coef<kM, kN, false, true>(a.coef, c / a.dg);
+    const int64_t left = a.M - row0;
+    const int rows = left < BM ? (int)left : BM;
+    char *const to = a.out + ((size_t)row0 * (size_t)a.N + (size_t)c) * 2u;
+    static_for<0, SH::kParts>([&](auto pc) {
+        constexpr int m0 = decltype(pc)::value * MP, m1 = m0 + MP < TM ? m0 + MP : TM; // rows of tiles in this part
+        if (m0 > 0)
+            __syncthreads();
+        if (computes) {
+#pragma unroll
+            for (int m = m0; m < m1; ++m) {
+                const uint32_t at = lds0 + ((uint32_t)(wm * MP + m - m0) * 16u + i16) * SH::kPitch + (uint32_t)(wn * TN * 32) + g4 * 8u;
+#pragma unroll
+                for (int n = 0; n < TN; ++n) {
+                    const f32x4 v = acc[m][n];
+                    *(__attribute__((address_space(3))) u32x2 *)(uintptr_t)(at + (uint32_t)n * 32u) =
+                        u32x2{pack(v[0] + low(bias[n][0]), v[1] + high(bias[n][0])), pack(v[2] + low(bias[n][1]), v[3] + high(bias[n][1]))};
+                }
+            }
+        }
+        __syncthreads();
+        if (in) {
+#pragma unroll 2
+            for (int l = tid / LR; l < SH::WM * MP * 16; l += RP) {
+                const int m = m0 + l / 16 % MP, r = (l / (MP * 16) * TM + m) * 16 + l % 16;
+                if (m >= m1 || r >= rows)
+                    continue;
+                u32x4 v = lds_read16(lds0 + (uint32_t)l * SH::kPitch + (uint32_t)(tid % LR) * 16u);
+                if constexpr (RATIONAL)
+                    v = rational8(v, co);
+                *(u32x4 *)(to + (size_t)r * ldn) = v;
+            }
+        }
+    });
+}
+
+// --------------------------------------------------------------------------
+// host side
+// --------------------------------------------------------------------------
+using Kernel = void (*)(const Args);
+
+// us of a call: once + rounds (round + T (stage + fill share)), T = K / 64 and share of the compute units that a round gives a tile
+// on average (the more do, the slower the loads and the clock).  Two workgroups on a unit: a round of one each and one of two.
+struct Variant {
+    int32_t BM, BN, threads, per_cu;
+    size_t lds;
+    Kernel kernel[3]; // W [N, K]; with F; W [K, N]
+    double once, round, stage, fill, round2, stage2;
+};
+
+template <class SH> static constexpr Variant variant(double once, double round, double stage, double fill, double round2 = 0, double stage2 = 0)
+{
+    return Variant{SH::BM, SH::BN, SH::kThreads, SH::PER, SH::kLds,
+                   {product_kernel<SH, false, false>, product_kernel<SH, false, true>, product_kernel<SH, true, false>},
+                   once, round, stage, fill, round2, stage2};
+}
+
+// Of fourteen tiles these six are the ones that together lose least to the best of all (2 % in the mean) at 110 measured sizes: ten
+// pairs N, K of 192 .. 3072 and 256 .. 3072, 197 - 50,432 rows.  The figures are least squares over the same
+// sizes (residuals 4 - 9 %); the tile that the estimate takes is 2.8 % slower than the best of all fourteen in the mean, 25 %
+// at most (calls of 9 - 20 us).  Large tiles move less through the L2 and LDS for each product, small ones fill the chip:
+//   320 x 256 / 224 x 192 / 160 x 128 / two of 160 x 128 / 96 x 128 / 64 x 64, us
+//   25,216 x 384 -> 1536  37 / 43 / 48 / 39 / 57 / 65      25,216 x 1536 -> 384  42 / 29 / 32 / 31 / 44 / 45
+//    6,304 x 768 -> 3072  31 / 35 / 44 / 34 / 58 / 59       3,152 x 3072 -> 768  72 / 38 / 24 / 38 / 20 / 29
+//      788 x 1536 -> 384  39 / 22 / 13 / 19 / 10 / 7
+static const Variant kVariants[] = {
+    variant<Shape<10, 4, 2, 4, 2, 0>>(0.75, 7.56, 1.22, 0.545), variant<Shape<7, 3, 2, 4, 3, 4>>(1.49, 5.35, 0.573, 0.354),
+    variant<Shape<5, 2, 2, 4, 4, 4>>(1.68, 3.50, 0.318, 0.199), variant<Shape<5, 4, 2, 2, 2, 0, 2>>(2.95, 1.72, 0.632, 0, 3.58, 0.988),
+    variant<Shape<3, 2, 2, 4, 4, 4>>(2.04, 2.44, 0.233, 0.144), variant<Shape<2, 2, 2, 2, 4, 4>>(2.97, 0.68, 0.140, 0.026)};
+
+static int64_t tiles_of(const Variant &v, int64_t rows, int32_t N) { return (rows + v.BM - 1) / v.BM * ((N + v.BN - 1) / v.BN); }
+
+static double estimate_us(const Variant &v, int64_t rows, int32_t K, int32_t N, bool rational)
+{
+    const double T = K / 64, f = rational ? 6.0 * v.BM * v.BN / 81920 : 0.0; // F of a tile: 6 us at 320 x 256
+    const int64_t tiles = tiles_of(v, rows, N), per_xcd = (tiles + 7) / 8, rounds = (per_xcd + 31) / 32;
+    if (v.per_cu == 2)
+        return v.once + (double)(rounds % 2) * (v.round + v.stage * T + f) + (double)(rounds / 2) * (v.round2 + v.stage2 * T + f);
+    return v.once + (double)rounds * (v.round + T * (v.stage + v.fill * ((double)tiles / ((double)rounds * 256))) + f);
+}
+
+static const Variant *pick(int64_t rows, int32_t K, int32_t N, bool rational)
+{
+    const Variant *best = nullptr;
+    double least = 0;
+    for (const Variant &v : kVariants) {
+        const double us = estimate_us(v, rows, K, N, rational);
+        if (!best || us < least) {
+            best = &v;
+            least = us;
+        }
+    }
+    return best;
+}
+
+// 16-byte pieces of rows, lane offsets of 32 bits, tiles counted in 31.
+static bool supported(int64_t rows, int32_t K, int32_t N)
+{
+    return rows >= 0 && rows <= (int64_t)1 << 30 && K > 0 && K % 64 == 0 && K <= 1 << 20 && N > 0 && N % 8 == 0 && N <= 1 << 20 &&
+           (rows + 63) / 64 * ((N + 63) / 64) < INT32_MAX / 16;
+}
+
+static bool allow_lds(const Variant &v, int which)
+{
+    static std::mutex mu;
+    static bool done[64][sizeof(kVariants) / sizeof(kVariants[0])][3];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64)
+        return false;
+    std::lock_guard<std::mutex> lock(mu);
+    bool &is = done[dev][&v - kVariants][which];
+    if (!is)
+        is = hipFuncSetAttribute(reinterpret_cast<const void *>(v.kernel[which]), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                 (int)v.lds) == hipSuccess;
+    return is;
+}
+
+} // namespace product
+} // namespace grkan
+
+using namespace grkan;
+
+extern "C" int32_t grkan_product_supported(int64_t rows, int32_t K, int32_t N) { return product::supported(rows, K, N); }
+
+extern "C" double grkan_product_estimate_us(int64_t rows, int32_t K, int32_t N, int32_t rational)
+{
+    if (rows <= 0 || !product::supported(rows, K, N))
+        return 0;
+    return product::estimate_us(*product::pick(rows, K, N, rational != 0), rows, K, N, rational != 0);
+}
+
+extern "C" grkan_status_t grkan_product_tile(int64_t rows, int32_t K, int32_t N, int32_t rational, int32_t *tile_rows, int32_t *tile_channels,
+                                             int32_t *per_unit)
+{
+    if (!tile_rows || !tile_channels || !per_unit)
+        return GRKAN_ERR_NULL;
+    if (rows <= 0 || !product::supported(rows, K, N))
+        return GRKAN_ERR_UNSUPPORTED;
+    const product::Variant *const v = product::pick(rows, K, N, rational != 0);
+    *tile_rows = v->BM;
+    *tile_channels = v->BN;
+    *per_unit = v->per_cu;
+    return GRKAN_OK;
+}
+
+extern "C" grkan_status_t grkan_product(const void *x, const void *W, const void *bias, void *out, int64_t rows, int32_t K, int32_t N,
+                                        int32_t transposed, const void *A, const void *B, int32_t G, int32_t shared_numerator,
+                                        void *hip_stream)
+{
+    if (rows < 0 || K <= 0 || N <= 0)
+        return GRKAN_ERR_SHAPE;
+    const bool rational = A != nullptr || B != nullptr;
+    if (rational && (G <= 0 || N % G != 0))
+        return GRKAN_ERR_SHAPE;
+    if (!product::supported(rows, K, N) || (rational && (transposed || N / G % 8 != 0)))
+        return GRKAN_ERR_UNSUPPORTED;
+    if ((rows > 0 && (!x || !W || !out)) || (rational && (!A || !B)))
+        return GRKAN_ERR_NULL;
+    auto address = [](const void *p) { return reinterpret_cast<uintptr_t>(p); };
+    if ((address(x) | address(W) | address(out)) % 16 != 0 || address(bias) % 8 != 0 || (address(A) | address(B)) % 2 != 0)
+        return GRKAN_ERR_ALIGN;
+    if (rows == 0)
+        return GRKAN_OK;
+    const product::Variant &v = *product::pick(rows, K, N, rational);
+    product::Args a;
+    a.x = static_cast<const char *>(x);
+    a.W = static_cast<const char *>(W);
+    a.bias = static_cast<const char *>(bias);
+    a.out = static_cast<char *>(out);
+    a.coef = CoefRows{A, B, shared_numerator ? 0 : product::kM + 1, 1};
+    a.M = rows;
+    a.N = N;
+    a.K = K;
+    a.dg = rational ? N / G : N;
+    a.tiles_n = (N + v.BN - 1) / v.BN;
+    a.tiles = (int32_t)product::tiles_of(v, rows, N);
+    a.per_xcd = (a.tiles + 7) / 8;
+    const int which = transposed ? 2 : rational ? 1 : 0;
+    if (!product::allow_lds(v, which))
+        return GRKAN_ERR_LAUNCH;
+    void *args[] = {&a};
+    return hipLaunchKernel(reinterpret_cast<const void *>(v.kernel[which]), dim3((unsigned)a.per_xcd * 8u), dim3((unsigned)v.threads), args,
+                           v.lds, static_cast<hipStream_t>(hip_stream)) == hipSuccess
+               ? GRKAN_OK
+               : GRKAN_ERR_LAUNCH;
+}

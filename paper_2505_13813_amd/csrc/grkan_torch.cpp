@@ -273,6 +273,22 @@ struct Product : public torch::autograd::Function<Product> {
     }
 };
 
+bool aligned(const Tensor &t, uintptr_t to) { return reinterpret_cast<uintptr_t>(t.data_ptr()) % to == 0; }
+
+// x W^T + bias or, transposed, x W of bfloat16 rows (contiguous, as W) from the kernel where it takes them, from torch elsewhere.
+Tensor product_of_rows(const Tensor &x, const Tensor &W, const std::optional<Tensor> &bias, bool transposed)
+{
+    const int64_t rows = x.size(0), K = x.size(1), N = W.size(transposed ? 1 : 0);
+    if (K > INT32_MAX || N > INT32_MAX || !grkan_product_supported(rows, (int32_t)K, (int32_t)N) || !aligned(x, 16) || !aligned(W, 16) ||
+        (bias && !aligned(*bias, 8)))
+        return transposed ? x.mm(W) : at::linear(x, W, bias);
+    Tensor out = at::empty({rows, N}, x.options());
+    check(grkan_product(x.data_ptr(), W.data_ptr(), bias ? bias->data_ptr() : nullptr, out.data_ptr(), rows, (int32_t)K, (int32_t)N, transposed,
+                        nullptr, nullptr, 1, 0, stream_of(x)),
+          "grkan_product");
+    return out;
+}
+
 // The two GR-KAN layers of an MLP block: f1 = F1(x), h = f1 W1^T + b1 and f2 = F2(h), out = f2 W2^T + b2.  Where it is the
 // faster route (grkan_hidden_pays, by direction) h and f2 come from one kernel, and in the backward pass the product with W2 and
 // F2's gradients, so that dF2 is never written; elsewhere from torch's product and the rational function.  Saves what
@@ -297,7 +313,7 @@ struct Block : public torch::autograd::Function<Block> {
                                    f2.data_ptr(), s1.rows, s1.D, (int32_t)hidden, G2, A2.dim() == 1, stream_of(x)),
                   "grkan_hidden_fwd");
         } else {
-            h = at::linear(f1.view({s1.rows, s1.D}), W1, b1);
+            h = product_of_rows(f1.view({s1.rows, s1.D}), W1, b1, false);
             check(grkan_fwd_model(h.data_ptr(), A2.data_ptr(), B2.data_ptr(), f2.data_ptr(), s1.rows, (int32_t)hidden, G2, 5, 4,
                                   GRKAN_BF16, GRKAN_BF16, A2.dim() == 1, stream_of(x)),
                   "grkan_fwd");
@@ -308,7 +324,7 @@ struct Block : public torch::autograd::Function<Block> {
             ctx->saved_data["b1"] = *b1;
         ctx->saved_data["biases"] = (int64_t)(b1 ? 1 : 0) + (b2 ? 2 : 0);
         ctx->saved_data["wgrad"] = wgrad;
-        return at::_unsafe_view(at::linear(f2, W2, b2), x.sizes());
+        return at::_unsafe_view(product_of_rows(f2, W2, b2, false), x.sizes());
     }
 
     // A saved tensor as its hooks returned it, in the form the kernels read.
@@ -376,7 +392,7 @@ struct Block : public torch::autograd::Function<Block> {
                                    A2.dim() == 1, stream_of(x)),
                   "grkan_hidden_bwd");
         } else {
-            const variable_list d = Rational::in_backward(h, dout.mm(W2), A2, B2);
+            const variable_list d = Rational::in_backward(h, graph ? dout.mm(W2) : product_of_rows(dout, W2, std::nullopt, true), A2, B2);
             dh = d[0];
             out[4] = d[1];
             out[5] = d[2];
@@ -387,7 +403,8 @@ struct Block : public torch::autograd::Function<Block> {
             gradients_of(dh, f1, want_w1, want_b1, wgrad, out[3], out[7]);
         }
         if (want_first) {
-            const variable_list d = Rational::in_backward(x, dh.mm(W1).view(x.sizes()), A1, B1);
+            const Tensor df1 = graph ? dh.mm(W1) : product_of_rows(dh, as_saved(W1, x, {hidden, D}), std::nullopt, true);
+            const variable_list d = Rational::in_backward(x, df1.view(x.sizes()), A1, B1);
             std::copy(d.begin(), d.end(), out.begin());
         }
         return out;
@@ -558,6 +575,48 @@ std::optional<Tensor> layer_model(const Tensor &x_in, const Tensor &A, const Ten
     return out;
 }
 
+// The MLP block in inference, on a bfloat16 module's own parameters: F1(x), the first product with the second layer's rational
+// function on its rounded result, the second product.  Nothing is converted, packed or kept.
+std::optional<Tensor> block_inference(const Tensor &x_in, const Tensor &A1, const Tensor &B1, const Tensor &W1, const std::optional<Tensor> &b1,
+                                      const Tensor &A2, const Tensor &B2, const Tensor &W2, const std::optional<Tensor> &b2)
+{
+    if (at::GradMode::is_enabled() || !plain_context() || !on_current_gpu(x_in))
+        return std::nullopt;
+    for (const Tensor *t : {&x_in, &A1, &B1, &W1, &A2, &B2, &W2, b1 ? &*b1 : &x_in, b2 ? &*b2 : &x_in})
+        if (!plain(*t, x_in.device()) || t->scalar_type() != at::kBFloat16 || (t != &x_in && !t->is_contiguous()))
+            return std::nullopt;
+    if (x_in.dim() < 1 || x_in.numel() == 0 || W1.dim() != 2 || W2.dim() != 2 || x_in.size(-1) != W1.size(1) || W2.size(1) != W1.size(0) ||
+        (b1 && (b1->dim() != 1 || b1->size(0) != W1.size(0))) || (b2 && (b2->dim() != 1 || b2->size(0) != W2.size(0))))
+        return std::nullopt;
+    const int64_t D = W1.size(1), hidden = W1.size(0), D_out = W2.size(0), rows = x_in.numel() / D;
+    auto coefficients = [](const Tensor &A, const Tensor &B, int64_t channels) {
+        return B.dim() == 2 && B.size(1) == 4 && A.dim() >= 1 && A.dim() <= 2 && A.size(-1) == 6 &&
+               (A.dim() == 1 || A.size(0) == B.size(0)) && B.size(0) > 0 && channels % B.size(0) == 0;
+    };
+    if (D > INT32_MAX || hidden > INT32_MAX || D_out > INT32_MAX || !coefficients(A1, B1, D) || !coefficients(A2, B2, hidden) ||
+        hidden / B2.size(0) % 8 != 0 || !grkan_product_supported(rows, (int32_t)D, (int32_t)hidden) ||
+        !grkan_product_supported(rows, (int32_t)hidden, (int32_t)D_out))
+        return std::nullopt;
+    const Tensor x = x_in.contiguous();
+    if (!aligned(W1, 16) || !aligned(W2, 16) || (b1 && !aligned(*b1, 8)) || (b2 && !aligned(*b2, 8)))
+        return std::nullopt;
+    auto shape = x.sizes().vec();
+    shape.back() = D_out;
+    const Tensor f1 = at::empty_like(x), f2 = at::empty({rows, hidden}, x.options());
+    Tensor out = at::empty(shape, x.options());
+    void *const stream = stream_of(x);
+    check(grkan_fwd_model(x.data_ptr(), A1.data_ptr(), B1.data_ptr(), f1.data_ptr(), rows, (int32_t)D, (int32_t)B1.size(0), 5, 4, GRKAN_BF16,
+                          GRKAN_BF16, A1.dim() == 1, stream),
+          "grkan_fwd");
+    check(grkan_product(f1.data_ptr(), W1.data_ptr(), b1 ? b1->data_ptr() : nullptr, f2.data_ptr(), rows, (int32_t)D, (int32_t)hidden, 0,
+                        A2.data_ptr(), B2.data_ptr(), (int32_t)B2.size(0), A2.dim() == 1, stream),
+          "grkan_product");
+    check(grkan_product(f2.data_ptr(), W2.data_ptr(), b2 ? b2->data_ptr() : nullptr, out.data_ptr(), rows, (int32_t)hidden, (int32_t)D_out, 0,
+                        nullptr, nullptr, 1, 0, stream),
+          "grkan_product");
+    return out;
+}
+
 // No function mode, or device contexts alone (torch.set_default_device: they act on factory functions only).
 bool no_function_mode()
 {
@@ -620,6 +679,14 @@ PYBIND11_MODULE(_native, mod)
         const Tensor A2 = args.tensor(A2_), B2 = args.tensor(B2_), W2 = args.tensor(W2_);
         const std::optional<Tensor> b2 = args.optional(b2_);
         return args.call([&] { return block(x, A1, B1, W1, b1, A2, B2, W2, b2, wgrad); });
+    });
+    mod.def("block_inference", [](handle x_, handle A1_, handle B1_, handle W1_, handle b1_, handle A2_, handle B2_, handle W2_, handle b2_) {
+        Arguments args;
+        const Tensor x = args.tensor(x_), A1 = args.tensor(A1_), B1 = args.tensor(B1_), W1 = args.tensor(W1_);
+        const std::optional<Tensor> b1 = args.optional(b1_);
+        const Tensor A2 = args.tensor(A2_), B2 = args.tensor(B2_), W2 = args.tensor(W2_);
+        const std::optional<Tensor> b2 = args.optional(b2_);
+        return args.call([&] { return block_inference(x, A1, B1, W1, b1, A2, B2, W2, b2); });
     });
     mod.def("layer_model", [](handle x_, handle A_, handle B_, handle W_, handle bias_) {
         Arguments args;

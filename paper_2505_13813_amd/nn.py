@@ -128,12 +128,33 @@ def one_kernel_is_faster(rows: int, D_in: int, D_out: int) -> bool:
     at fifteen sizes it passes by a gain of 5 % or more, most of them where the library's own choice of tile is a poor
     one.  3072 -> 768: 197 rows 10.1 us against 27.7, 1,576 30 against 28.1, 6,304 42.5 against 51, 25,216 128 against
     195; 768 -> 3072: 1,576 rows 15.5 against 28, 6,304 44 against 56, 12,608 85 against 71.)"""
+    return binding.grkan_linear_estimate_us(rows, D_in, D_out) <= _two_kernels_us(rows, D_in, D_out)
+
+
+def _two_kernels_us(rows: int, D_in: int, D_out: int) -> float:
     def product_us(tile, us_per_1k):
         rounds = -(-(-(-rows // tile) * -(-D_out // tile)) // 256)
         return rounds * (6.0 + us_per_1k * D_in / 1024)
 
-    two_us = rows * D_in * 4 / 5.5e6 + min(product_us(256, 24.0), product_us(128, 4.0))
-    return binding.grkan_linear_estimate_us(rows, D_in, D_out) <= max(27.0, two_us)
+    return max(27.0, rows * D_in * 4 / 5.5e6 + min(product_us(256, 24.0), product_us(128, 4.0)))
+
+
+@lru_cache(maxsize=1024)
+def block_products_are_faster(rows: int, D: int, hidden: int, D_out: int, one1: bool, one2: bool) -> bool:
+    """Whether an MLP block in inference runs as F1, the first product with F2 on its result, and the second product
+    (grkan_product), instead of its two layers one by one; one1, one2: whether the one-kernel layer covers them.  F1 takes
+    3.3 us and 5.5 TB/s; two layers no less than the 17 us of their host time.  (Measured on MI355X, widths 192 - 768, 49 - 50,432
+    rows, us of the layers / this: 192 at 6,304 rows 45 / 22, 384 44 / 34, 512 69 / 54, 768 85 / 73; 768 at 25,216 270 / 265, 9,456
+    of 384 48.5 / 49.2.  The layers win at few rows of a wide model, where each is one round of small tiles: 768 at 49
+    rows 17.4 / 18.8, at 197 19.4 / 22.3, 512 at 394 17.1 / 18.1.)"""
+    def layer_us(D_in, D_out, one):
+        two = _two_kernels_us(rows, D_in, D_out)
+        return min(two, binding.grkan_linear_estimate_us(rows, D_in, D_out)) if one else two
+
+    first, second = binding.grkan_product_estimate_us(rows, D, hidden, True), binding.grkan_product_estimate_us(rows, hidden, D_out, False)
+    if not first or not second:
+        return False
+    return 3.3 + rows * D * 4 / 5.5e6 + first + second <= max(17.0, layer_us(D, hidden, one1) + layer_us(hidden, D_out, one2))
 
 
 class GRKANLayerFunction(torch.autograd.Function):
@@ -497,8 +518,9 @@ class KATMlp(nn.Module):
 
     `fused`: of the second layer, as GRKANLinear has it (the first one is fused in evaluation mode only).  With the default,
     "inference", bfloat16 training on the GPU runs the whole block as one autograd function where that applies
-    (_native_block), with the hidden activation's product and rational function in one kernel where that is faster; "never"
-    and "always" leave training to the two layers."""
+    (_native_block), with the hidden activation's product and rational function in one kernel where that is faster, and inference
+    as three kernels that write F2(h) instead of h where that is (_native_inference); "never" and "always" leave both to the two
+    layers."""
 
     def __init__(self, dim: int, hidden: int | None = None, groups: int = 8,
                  degrees: Tuple[int, int] = (M_DEGREE, N_DEGREE), fused: str = "inference"):
@@ -512,7 +534,48 @@ class KATMlp(nn.Module):
 
     def forward(self, x):
         out = self._native_block(x)
+        if out is None:
+            out = self._native_inference(x)
         return self.fc2(self.fc1(x)) if out is None else out
+
+    def _plain_parameters(self):
+        """Numerator, denominator, weight and bias of both layers, or None where calling the two layers would do anything else
+        than their parts do."""
+        params = []
+        for fc in (self._modules.get("fc1"), self._modules.get("fc2")):
+            if not _only_a(GRKANLinear, fc) or fc.fused != "inference":
+                return None
+            linear, rational = fc._modules.get("linear"), fc._modules.get("rational")
+            if not _only_a(nn.Linear, linear) or not _only_a(GroupRational, rational) or "coefficient_rows" in rational.__dict__:
+                return None
+            if "bias" not in linear._parameters:  # a buffer or a plain tensor, that only linear's own forward reads
+                return None
+            params += [rational._parameters.get("numerator"), rational._parameters.get("denominator"),
+                       linear._parameters.get("weight"), linear._parameters.get("bias")]
+        return params
+
+    def _native_inference(self, x):
+        """The block in bfloat16 inference as F1, a product with F2 on its result and a product, on the parameters themselves,
+        or None where that route is not taken (as _native_block; in training mode a pass without a gradient takes that one's
+        kernels or the layers, as the pass with one does)."""
+        if x.dtype is not torch.bfloat16 or torch.is_grad_enabled() or self.training or not x.is_cuda:
+            return None
+        if torch.compiler.is_compiling() or _autocast_elsewhere():
+            return None
+        params = self._plain_parameters()
+        if params is None or self.fc1.training or self.fc2.training:
+            return None
+        if any(p is None for i, p in enumerate(params) if i % 4 != 3) or params[2].dim() != 2 or params[6].dim() != 2:
+            return None
+        dim = x.shape[-1] if x.dim() else 0
+        if not dim or not params[2].shape[0] or params[1].dim() != 2 or params[5].dim() != 2 or not params[0].dim() or not params[4].dim():
+            return None
+        (hidden, _), D_out = params[2].shape, params[6].shape[0]
+        covered = [bool(p[1].shape[0]) and _fused_shapes(t, p[1].shape[0], p[0].shape[-1], p[2])
+                   for t, p in ((x, params[:4]), (params[6], params[4:]))]
+        if not block_products_are_faster(x.numel() // dim, dim, hidden, D_out, *covered):
+            return None
+        return binding.load_native().block_inference(x, *params)
 
     def _native_block(self, x):
         """The block in bfloat16 training as one native autograd function (the hidden activation's product and rational
@@ -526,17 +589,9 @@ class KATMlp(nn.Module):
             return None
         if torch.is_autocast_enabled() or torch.compiler.is_compiling():
             return None
-        params = []
-        for fc in (self._modules.get("fc1"), self._modules.get("fc2")):
-            if not _only_a(GRKANLinear, fc) or fc.fused != "inference":
-                return None
-            linear, rational = fc._modules.get("linear"), fc._modules.get("rational")
-            if not _only_a(nn.Linear, linear) or not _only_a(GroupRational, rational) or "coefficient_rows" in rational.__dict__:
-                return None
-            if "bias" not in linear._parameters:  # a buffer or a plain tensor, that only linear's own forward reads
-                return None
-            params += [rational._parameters.get("numerator"), rational._parameters.get("denominator"),
-                       linear._parameters.get("weight"), linear._parameters.get("bias")]
+        params = self._plain_parameters()
+        if params is None:
+            return None
         for i, p in enumerate(params):
             if type(p) is not nn.Parameter and not (p is None and i % 4 == 3):
                 return None

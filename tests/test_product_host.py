@@ -1,0 +1,45 @@
+"""grkan_product without a GPU: what it refuses, and the rule for its tile."""
+import ctypes
+
+import pytest
+
+from paper_2505_13813_amd import binding
+from paper_2505_13813_amd import nn as gnn
+
+
+def test_product_rejects_on_the_host():
+    lib = binding.load_library()
+    names = ("x", "W", "bias", "out", "rows", "K", "N", "transposed", "A", "B", "G", "shared", "stream")
+    good = [16, 16, 8, 16, 4, 192, 64, 0, 2, 2, 8, 1, None]
+
+    def status(**changes):
+        return lib.grkan_product(*[changes.get(n, v) for n, v in zip(names, good)])
+
+    assert status(rows=0) == 0 and status(rows=0, x=None, out=None, bias=None) == 0
+    assert all(status(**{p: None}) == 1 for p in ("x", "W", "out", "A", "B"))
+    assert all(status(**{p: v}) == 4 for p, v in (("x", 8), ("W", 8), ("out", 8), ("bias", 4), ("A", 1), ("B", 1)))
+    assert status(rows=-1) == 2 and status(K=0) == 2 and status(G=0) == 2 and status(G=3) == 2
+    assert status(K=96) == 8 and status(N=68, G=1) == 8 and status(G=16) == 8 and status(transposed=1) == 8
+    assert status(rows=(1 << 30) + 1) == 8 and status(K=(1 << 20) + 64) == 8
+    assert not lib.grkan_product_supported(4, 100, 64) and lib.grkan_product_supported(4, 64, 8)
+    assert binding.grkan_product_estimate_us(4, 100, 64) == 0 and binding.grkan_product_estimate_us(0, 64, 64) == 0
+    with pytest.raises(binding.GrkanError):
+        binding.grkan_product_tile(0, 64, 64)
+    one = ctypes.c_int32()
+    assert lib.grkan_product_tile(4, 64, 64, 0, ctypes.byref(one), None, ctypes.byref(one)) == 1
+
+
+def test_tiles_grow_with_the_call():
+    tile = binding.grkan_product_tile
+    assert tile(197, 1536, 384) == (64, 64, 1)
+    assert tile(3152, 3072, 768) == (96, 128, 1)
+    assert tile(6304, 3072, 768) == (160, 128, 1)
+    assert tile(25216, 1536, 384) == (224, 192, 1)
+    assert tile(6304, 768, 3072) == tile(25216, 3072, 768) == (320, 256, 1)
+
+
+def test_rule_of_the_blocks_inference_route():
+    faster = gnn.block_products_are_faster
+    assert faster(6304, 768, 3072, 768, True, True) and faster(197, 192, 768, 192, False, True)
+    assert not faster(49, 768, 3072, 768, True, True) and not faster(197, 768, 3072, 768, True, True)
+    assert not faster(400, 96, 384, 96, False, False)  # K = 96 is no multiple of 64
