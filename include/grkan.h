@@ -322,6 +322,17 @@ grkan_status_t grkan_linear_wgrad(const void *dout, const void *y, void *dW, voi
                                   grkan_dtype_t io, void *hip_stream);
 
 /*
+ * The gradients of two products over the same rows (an MLP block's) in one launch, each as grkan_linear_wgrad's:
+ * both fill the chip together, so that half as many partial sums are written.  bfloat16.
+ */
+size_t grkan_linear_wgrad_pair_workspace_bytes(int64_t rows, int32_t D_in1, int32_t D_out1, int32_t D_in2,
+                                               int32_t D_out2);
+grkan_status_t grkan_linear_wgrad_pair(const void *dout1, const void *y1, void *dW1, void *dbias1, int32_t D_in1,
+                                       int32_t D_out1, const void *dout2, const void *y2, void *dW2, void *dbias2,
+                                       int32_t D_in2, int32_t D_out2, void *workspace, size_t workspace_bytes,
+                                       int64_t rows, void *hip_stream);
+
+/*
  * The hidden activation of a KAT MLP block in training: the product that makes or receives it and the second layer's
  * rational function on it, in one kernel each way, on a bfloat16 model's own parameters.
  *

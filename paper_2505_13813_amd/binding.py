@@ -95,6 +95,10 @@ def load_library():
     lib.grkan_linear_wgrad.restype = ctypes.c_int
     lib.grkan_linear_wgrad_workspace_bytes.argtypes = [i64, i32, i32]
     lib.grkan_linear_wgrad_workspace_bytes.restype = sz
+    lib.grkan_linear_wgrad_pair_workspace_bytes.argtypes = [i64, i32, i32, i32, i32]
+    lib.grkan_linear_wgrad_pair_workspace_bytes.restype = sz
+    lib.grkan_linear_wgrad_pair.argtypes = [vp, vp, vp, vp, i32, i32, vp, vp, vp, vp, i32, i32, vp, sz, i64, vp]
+    lib.grkan_linear_wgrad_pair.restype = ctypes.c_int
     lib.grkan_product_supported.argtypes = [i64, i32, i32]
     lib.grkan_product_supported.restype = i32
     lib.grkan_product_estimate_us.argtypes = [i64, i32, i32, i32]

@@ -217,6 +217,28 @@ bool weight_gradients(Tensor dout2, Tensor y2, bool want_b, Tensor &dW, Tensor &
     return true;
 }
 
+// The same of two products over the same rows (contiguous, 16-byte aligned) in one launch.
+bool both_weight_gradients(const Tensor &dout1, const Tensor &y1, bool want_b1, Tensor &dW1, Tensor &db1, const Tensor &dout2, const Tensor &y2,
+                           bool want_b2, Tensor &dW2, Tensor &db2)
+{
+    const int64_t rows = y1.size(0), in1 = y1.size(1), out1 = dout1.size(1), in2 = y2.size(1), out2 = dout2.size(1);
+    const size_t need = grkan_linear_wgrad_pair_workspace_bytes(rows, (int32_t)in1, (int32_t)out1, (int32_t)in2, (int32_t)out2);
+    if (need == 0)
+        return false;
+    const Tensor ws = at::empty({(int64_t)need}, y1.options().dtype(at::kByte));
+    dW1 = at::empty({out1, in1}, y1.options());
+    dW2 = at::empty({out2, in2}, y1.options());
+    if (want_b1)
+        db1 = at::empty({out1}, y1.options());
+    if (want_b2)
+        db2 = at::empty({out2}, y1.options());
+    check(grkan_linear_wgrad_pair(dout1.data_ptr(), y1.data_ptr(), dW1.data_ptr(), want_b1 ? db1.data_ptr() : nullptr, (int32_t)in1,
+                                  (int32_t)out1, dout2.data_ptr(), y2.data_ptr(), dW2.data_ptr(), want_b2 ? db2.data_ptr() : nullptr,
+                                  (int32_t)in2, (int32_t)out2, ws.data_ptr(), need, rows, stream_of(y1)),
+          "grkan_linear_wgrad_pair");
+    return true;
+}
+
 // torch's linear.  The result is no view of another tensor: torch refuses to write (y += x) to an output of an autograd
 // function that is one.
 Tensor linear_of_rows(const Tensor &y, const Tensor &W, const std::optional<Tensor> &bias)
@@ -370,7 +392,10 @@ struct Block : public torch::autograd::Function<Block> {
                                has1 ? std::optional<Tensor>(ctx->saved_data["b1"].toTensor()) : std::nullopt, h);
             f2 = Rational::apply(h, A2, B2, f2);
         }
-        gradients_of(dout, f2, want_w2, want_b2, wgrad, out[6], out[8]);
+        // (both layers' weight gradients in one launch where both are wanted)
+        const bool pair = want_w1 && want_w2 && wgrad && !graph;
+        if (!pair)
+            gradients_of(dout, f2, want_w2, want_b2, wgrad, out[6], out[8]);
         if (!want_dh)
             return out;
         if (!graph) {
@@ -400,7 +425,11 @@ struct Block : public torch::autograd::Function<Block> {
         if (want_w1 || want_b1) {
             if (!graph)
                 f1 = as_saved(saved[7], x, x.sizes()).view({rows, D});
-            gradients_of(dh, f1, want_w1, want_b1, wgrad, out[3], out[7]);
+            if (!pair || !both_weight_gradients(dh, f1, want_b1, out[3], out[7], dout, f2, want_b2, out[6], out[8])) {
+                gradients_of(dh, f1, want_w1, want_b1, wgrad, out[3], out[7]);
+                if (pair)
+                    gradients_of(dout, f2, want_w2, want_b2, wgrad, out[6], out[8]);
+            }
         }
         if (want_first) {
             const Tensor df1 = graph ? dh.mm(W1) : product_of_rows(dh, as_saved(W1, x, {hidden, D}), std::nullopt, true);
