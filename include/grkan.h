@@ -386,6 +386,26 @@ grkan_status_t grkan_product(const void *x, const void *W, const void *bias, voi
                              int32_t shared_numerator, void *hip_stream);
 
 /*
+ * The whole backward pass of a bfloat16 KAT MLP block, out = F2(h) W2^T + b2 with h = F1(x) W1^T + b1: the parts above in five
+ * launches (grkan_hidden_bwd or a product and the rational function, grkan_product, the rational function,
+ * grkan_linear_wgrad_pair, one for all second stages).  rows >= 1; D, hidden and G2 as grkan_hidden_supported(D, hidden, G2);
+ * G1 divides D.
+ *   x, f1 = F1(x), dout, dx, df1 [rows, D]; h, f2 = F2(h), dh [rows, hidden]; W1, dW1 [hidden, D]; W2, dW2 [D, hidden]; db1
+ *   [hidden], db2 [D], each or NULL; A1, B1, A2, B2 and their gradients as for grkan_bwd_model (shared1, shared2: one numerator row
+ *   for all groups).  All DEVICE, bfloat16, contiguous; tensors 16-byte aligned.  dh and df1 are scratch.
+ * `alloc` is asked more than once during the call, each time as grkan_bwd_model asks it.
+ */
+typedef struct {
+    int64_t rows;
+    int32_t D, hidden, G1, G2, shared1, shared2;
+    const void *x, *f1, *h, *f2, *dout;
+    const void *A1, *B1, *W1, *A2, *B2, *W2;
+    void *dx, *dA1, *dB1, *dW1, *db1, *dA2, *dB2, *dW2, *db2;
+    void *dh, *df1;
+} grkan_block_bwd_t;
+grkan_status_t grkan_block_bwd(const grkan_block_bwd_t *block, grkan_alloc_t alloc, void *alloc_context, void *hip_stream);
+
+/*
  * grkan_bwd for callers that cannot allocate device memory or pass a workspace:
  * code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Same arguments, results and kernels as grkan_bwd (bit-identical

@@ -11,8 +11,8 @@ CSRC = PKG / "csrc"
 LIB = PKG / "libgrkan.so"
 SOURCES = [CSRC / "grkan_kernels.hip", CSRC / "grkan_plan.cpp", CSRC / "grkan_alg1_baseline.hip",
            CSRC / "grkan_linear.hip", CSRC / "grkan_linear_grad.hip", CSRC / "grkan_hidden.hip",
-           CSRC / "grkan_product.hip"]
-HEADERS = [CSRC / "grkan_walk.h", CSRC / "grkan_plan.h", CSRC / "grkan_elem.h", CSRC / "grkan_tile.h",
+           CSRC / "grkan_product.hip", CSRC / "grkan_block.hip"]
+HEADERS = [CSRC / "grkan_walk.h", CSRC / "grkan_plan.h", CSRC / "grkan_elem.h", CSRC / "grkan_tile.h", CSRC / "grkan_stage2.h",
            PKG.parent / "include" / "grkan.h",
            PKG.parent / "include" / "grkan_alg1.h"]
 

@@ -32,6 +32,14 @@ struct CoefRows {
     int32_t bf16;     // 1: bfloat16 rows, 0: float32
 };
 
+struct CoefSums {
+    const float *partial;
+    int32_t rows_per_group;
+    CoefRows coef;
+    void *dA, *dB;
+    int32_t G;
+};
+
 // UNIFORM: g is the same in all lanes, and the coefficients stay in scalar registers (there is no scalar load
 // of 16 bits; a value loaded by the lanes is moved back).
 template <int M, int N, bool UNIFORM, bool BF16> __device__ __forceinline__ Coef<M, N> load_coef(const CoefRows &rows, int g)

@@ -407,7 +407,7 @@ static void divide(const Variant &v, int64_t rows, int32_t N, Args *a)
 
 static grkan_status_t run(bool backward, const void *x, const void *W, const void *bias, void *h, void *out, const CoefRows &coef,
                           void *dA, void *dB, void *workspace, size_t workspace_bytes, int64_t rows, int32_t K, int32_t N, int32_t G,
-                          hipStream_t stream)
+                          hipStream_t stream, CoefSums *later = nullptr)
 {
     if (rows < 0 || K <= 0 || N <= 0 || G <= 0)
         return GRKAN_ERR_SHAPE;
@@ -447,10 +447,28 @@ static grkan_status_t run(bool backward, const void *x, const void *W, const voi
                             dim3(64 * v->waves), args, v->lds, stream) != hipSuccess)
             return GRKAN_ERR_LAUNCH;
     }
+    if (later) {
+        *later = CoefSums{a.partial, rows_per_group, coef, dA, dB, G};
+        return GRKAN_OK;
+    }
     return backward ? run_stage2(a.partial, rows_per_group, coef, dA, dB, G, kM, kN, stream) : GRKAN_OK;
 }
 
 } // namespace hidden
+
+grkan_status_t hidden_bwd_stage1(const void *dout, const void *W, const void *h, const CoefRows &coef, void *dh, void *dA, void *dB,
+                                 grkan_alloc_t alloc, void *alloc_context, int64_t rows, int32_t K, int32_t N, int32_t G, CoefSums *later,
+                                 hipStream_t stream)
+{
+    const size_t need = grkan_hidden_workspace_bytes(rows, K, N, G);
+    if (need == 0)
+        return GRKAN_ERR_UNSUPPORTED;
+    void *const workspace = alloc(need, alloc_context);
+    if (!workspace)
+        return GRKAN_ERR_WORKSPACE;
+    return hidden::run(true, dout, W, nullptr, const_cast<void *>(h), dh, coef, dA, dB, workspace, need, rows, K, N, G, stream, later);
+}
+
 } // namespace grkan
 
 using namespace grkan;

@@ -33,6 +33,7 @@
 
 #include "grkan_elem.h"
 #include "grkan_plan.h"
+#include "grkan_stage2.h"
 
 namespace grkan {
 
@@ -521,28 +522,7 @@ __global__ __launch_bounds__(kThreadsPerWg) void grkan_bwd_stage1_kernel(const B
     }
 }
 
-// Stage 2.  One workgroup per group, of one wavefront when the group has at
-// most 64 workspace rows and of four otherwise (the flat walk leaves one row
-// per stage-1 workgroup; reading hundreds of rows with 64 lanes is a chain of
-// dependent memory latencies).  Thread t adds rows t, t + T, ... in double; the
-// T thread sums go through LDS, each block of 64 of them is added in thread
-// order, then the blocks in block order.  Every order is fixed by T and the row
-// count; dA / dB are overwritten.
-// With one numerator row shared by the groups (G_shared > 0) the workgroups below
-// G_shared write dB only, and M + 1 more, of four wavefronts, add one numerator
-// sum each over the rows of all groups the same way.
-constexpr int kStage2MaxThreads = 4 * kWave;
-
 static int stage2_threads(int32_t rows_per_group) { return rows_per_group > kWave ? kStage2MaxThreads : kWave; }
-
-// A coefficient's gradient in the coefficients' type.
-__device__ __forceinline__ void store_coef_grad(void *p, int32_t i, double v, int32_t bf16)
-{
-    if (bf16)
-        static_cast<uint16_t *>(p)[i] = narrow_one<bf16_t>((float)v);
-    else
-        static_cast<float *>(p)[i] = (float)v;
-}
 
 template <int M, int N>
 __global__ __launch_bounds__(kStage2MaxThreads) void grkan_bwd_stage2_kernel(const float *__restrict__ partial,
@@ -551,94 +531,7 @@ __global__ __launch_bounds__(kStage2MaxThreads) void grkan_bwd_stage2_kernel(con
                                                                              void *__restrict__ dB,
                                                                              int32_t G_shared, int32_t bf16)
 {
-    constexpr int kNumCoef = M + 1 + N;
-    constexpr int kBlocks = kStage2MaxThreads / kWave;
-    __shared__ double thread_sum[kNumCoef][kStage2MaxThreads];
-    __shared__ double block_sum[kNumCoef][kBlocks];
-    const int g = blockIdx.x;
-    const int tid = threadIdx.x;
-    const int T = blockDim.x; // 64 or 256
-    if (G_shared > 0 && g >= G_shared) {
-        const int k = g - G_shared;
-        if (bf16) {
-            // bfloat16: every group's gradient is rounded, then the rounded ones are added in float32 (what
-            // converting and summing the groups' gradients gives); a wavefront takes every T / 64th group
-            float t = 0.0f;
-            for (int c = tid / kWave; c < G_shared; c += T / kWave) {
-                double s = 0.0;
-#pragma unroll 4
-                for (int r = tid & (kWave - 1); r < rows_per_group; r += kWave)
-                    s += (double)partial[((int64_t)c * rows_per_group + r) * kNumCoef + k];
-                for (int d = kWave / 2; d > 0; d /= 2)
-                    s += __shfl_xor(s, d);
-                t += widen_one<bf16_t>(narrow_one<bf16_t>((float)s));
-            }
-            if ((tid & (kWave - 1)) == 0)
-                block_sum[0][tid / kWave] = (double)t;
-            __syncthreads();
-            if (tid == 0) {
-                float v = 0.0f;
-                for (int b = 0; b < T / kWave; ++b)
-                    v += (float)block_sum[0][b];
-                store_coef_grad(dA, k, (double)v, bf16);
-            }
-            return;
-        }
-        double s = 0.0;
-#pragma unroll 8
-        for (int64_t r = tid; r < (int64_t)G_shared * rows_per_group; r += T)
-            s += (double)partial[r * kNumCoef + k];
-        thread_sum[0][tid] = s;
-        __syncthreads();
-        if (tid < T / kWave) {
-            double t = 0.0;
-            for (int l = 0; l < kWave; ++l)
-                t += thread_sum[0][tid * kWave + l];
-            block_sum[0][tid] = t;
-        }
-        __syncthreads();
-        if (tid == 0) {
-            double t = 0.0;
-            for (int b = 0; b < T / kWave; ++b)
-                t += block_sum[0][b];
-            store_coef_grad(dA, k, t, bf16);
-        }
-        return;
-    }
-    const float *base = partial + (size_t)g * rows_per_group * kNumCoef;
-
-    double s[kNumCoef];
-#pragma unroll
-    for (int k = 0; k < kNumCoef; ++k)
-        s[k] = 0.0;
-#pragma unroll 4
-    for (int r = tid; r < rows_per_group; r += T) {
-#pragma unroll
-        for (int k = 0; k < kNumCoef; ++k)
-            s[k] += (double)base[(size_t)r * kNumCoef + k];
-    }
-#pragma unroll
-    for (int k = 0; k < kNumCoef; ++k)
-        thread_sum[k][tid] = s[k];
-    __syncthreads();
-    const int nblocks = T / kWave;
-    if (tid < kNumCoef * nblocks) {
-        const int k = tid / nblocks, b = tid - k * nblocks;
-        double t = 0.0;
-        for (int l = 0; l < kWave; ++l)
-            t += thread_sum[k][b * kWave + l];
-        block_sum[k][b] = t;
-    }
-    __syncthreads();
-    if (tid < kNumCoef) {
-        double t = 0.0;
-        for (int b = 0; b < nblocks; ++b)
-            t += block_sum[tid][b];
-        if (tid > M)
-            store_coef_grad(dB, g * N + (tid - (M + 1)), t, bf16);
-        else if (G_shared == 0)
-            store_coef_grad(dA, g * (M + 1) + tid, t, bf16);
-    }
+    stage2_block<M, N>(partial, rows_per_group, dA, dB, G_shared, bf16, (int)blockIdx.x);
 }
 
 // --------------------------------------------------------------------------
@@ -1107,7 +1000,7 @@ grkan_status_t run_stage2(const float *partial, int32_t rows_per_group, const Co
 
 static grkan_status_t bwd_impl(const void *x, const void *dy, const CoefRows &coef, void *dx, void *dA, void *dB,
                                const Workspace &ws, int64_t rows, int32_t D, int32_t G, int32_t m, int32_t n,
-                               grkan_dtype_t io, void *hip_stream)
+                               grkan_dtype_t io, void *hip_stream, CoefSums *later = nullptr)
 {
     const DegreeOps *ops = nullptr;
     grkan_status_t st = check_common(rows, D, G, m, n, io, &ops);
@@ -1176,7 +1069,17 @@ static grkan_status_t bwd_impl(const void *x, const void *dy, const CoefRows &co
     // Stage 1 writes every workspace row stage 2 reads (one per workgroup and group, zeros included),
     // so nothing has to be cleared beforehand; with no rows there are no workspace rows and stage 2
     // writes zeros.
+    if (later) {
+        *later = CoefSums{a.partial, pl.partials_per_group, coef, dA, dB, G};
+        return GRKAN_OK;
+    }
     return run_stage2(a.partial, pl.partials_per_group, coef, dA, dB, G, m, n, stream);
+}
+
+grkan_status_t bwd_model_stage1(const void *x, const void *dy, const CoefRows &coef, void *dx, void *dA, void *dB, grkan_alloc_t alloc,
+                                void *alloc_context, int64_t rows, int32_t D, int32_t G, CoefSums *later, hipStream_t stream)
+{
+    return bwd_impl(x, dy, coef, dx, dA, dB, Workspace{nullptr, 0, false, alloc, alloc_context}, rows, D, G, 5, 4, GRKAN_BF16, stream, later);
 }
 
 } // namespace grkan

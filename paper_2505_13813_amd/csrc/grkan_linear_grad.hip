@@ -35,6 +35,7 @@
 #include <mutex>
 
 #include "grkan_plan.h"
+#include "grkan_stage2.h"
 #include "grkan_tile.h"
 
 namespace grkan {
@@ -297,7 +298,8 @@ __global__ __launch_bounds__(kThreads, kThreads / 256) void grkan_linear_wgrad_k
 }
 
 // Adds the partials in range order.  For each product first workgroups of four consecutive elements of dW per lane, then
-// workgroups of 16 columns of dbias, 16 lanes per column that add every 16th row, then in lane order.
+// workgroups of 16 columns of dbias, 16 lanes per column that add every 16th row, then in lane order.  An MLP block's pass ends
+// with it: the second stages of both rational functions' coefficient sums are workgroups of it too (COEF).
 struct Sum {
     const float *part, *bpart;
     char *dW, *dbias;
@@ -308,14 +310,26 @@ struct Sum {
 struct SumArgs {
     Sum s[2];
     int32_t splits;
+    int32_t coef_blocks[2]; // COEF: in front of the others (their chains of sums are the longest)
+    CoefSums coef[2];
 };
 
-__global__ __launch_bounds__(256) void grkan_linear_wgrad_sum_kernel(const SumArgs a)
+template <bool COEF> __global__ __launch_bounds__(256) void grkan_linear_wgrad_sum_kernel(SumArgs a)
 {
     const int tid = threadIdx.x;
-    const bool second = (int32_t)blockIdx.x >= a.s[0].blocks;
+    int32_t id = (int32_t)blockIdx.x;
+    if constexpr (COEF) {
+        if (id < a.coef_blocks[0] + a.coef_blocks[1]) {
+            const bool last = id >= a.coef_blocks[0];
+            const CoefSums c = a.coef[last ? 1 : 0];
+            stage2_block<5, 4>(c.partial, c.rows_per_group, c.dA, c.dB, c.coef.a_stride == 0 ? c.G : 0, 1, id - (last ? a.coef_blocks[0] : 0));
+            return;
+        }
+        id -= a.coef_blocks[0] + a.coef_blocks[1];
+    }
+    const bool second = id >= a.s[0].blocks;
     const Sum s = a.s[second ? 1 : 0];
-    const int32_t block = (int32_t)blockIdx.x - (second ? a.s[0].blocks : 0);
+    const int32_t block = id - (second ? a.s[0].blocks : 0);
     if (block < s.main_blocks) {
         const int64_t e = ((int64_t)block * 256 + tid) * 4;
         if (e >= s.elems)
@@ -419,7 +433,7 @@ struct Operands {
 };
 
 static grkan_status_t run(int64_t rows, const Size *size, const Operands *op, int n, void *workspace, size_t workspace_bytes,
-                          hipStream_t stream)
+                          hipStream_t stream, const CoefSums *coef = nullptr)
 {
     Plan pl;
     const grkan_status_t st = make_plan(rows, size, n, &pl);
@@ -474,12 +488,33 @@ static grkan_status_t run(int64_t rows, const Size *size, const Operands *op, in
     if (hipLaunchKernel(reinterpret_cast<const void *>(grkan_linear_wgrad_kernel), dim3((unsigned)a.per_xcd * 8u), dim3(kThreads),
                         args, kLds, stream) != hipSuccess)
         return GRKAN_ERR_LAUNCH;
-    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(grkan_linear_wgrad_sum_kernel), dim3((unsigned)blocks), dim3(256),
-                                         args2, 0, stream);
+    if (coef)
+        for (int k = 0; k < 2; ++k) {
+            sum.coef[k] = coef[k];
+            sum.coef_blocks[k] = coef[k].G + (coef[k].coef.a_stride == 0 ? 6 : 0);
+            blocks += sum.coef_blocks[k];
+        }
+    const void *const kernel = coef ? reinterpret_cast<const void *>(grkan_linear_wgrad_sum_kernel<true>)
+                                    : reinterpret_cast<const void *>(grkan_linear_wgrad_sum_kernel<false>);
+    const hipError_t e = hipLaunchKernel(kernel, dim3((unsigned)blocks), dim3(256), args2, 0, stream);
     return e == hipSuccess ? GRKAN_OK : GRKAN_ERR_LAUNCH;
 }
 
 } // namespace wgrad
+
+grkan_status_t wgrad_pair_and_sums(const grkan_block_bwd_t &b, grkan_alloc_t alloc, void *alloc_context, const CoefSums (&sums)[2],
+                                   hipStream_t stream)
+{
+    const wgrad::Size size[2] = {{b.D, b.hidden}, {b.hidden, b.D}};
+    const wgrad::Operands op[2] = {{b.dh, b.f1, b.dW1, b.db1}, {b.dout, b.f2, b.dW2, b.db2}};
+    wgrad::Plan pl;
+    const grkan_status_t st = wgrad::make_plan(b.rows, size, 2, &pl);
+    if (st != GRKAN_OK)
+        return st;
+    void *const workspace = alloc(pl.bytes(), alloc_context);
+    return wgrad::run(b.rows, size, op, 2, workspace, pl.bytes(), stream, sums);
+}
+
 } // namespace grkan
 
 using namespace grkan::wgrad;

@@ -24,6 +24,7 @@
 #include <initializer_list>
 #include <optional>
 #include <tuple>
+#include <vector>
 
 #include "../../include/grkan.h"
 
@@ -99,6 +100,25 @@ struct Scratch {
     {
         if (error)
             std::rethrow_exception(error);
+    }
+};
+
+// Several of them.
+struct Scratches {
+    at::TensorOptions options;
+    std::vector<Tensor> memory;
+    std::exception_ptr error;
+
+    static void *alloc(size_t bytes, void *self) noexcept
+    {
+        auto *s = static_cast<Scratches *>(self);
+        try {
+            s->memory.push_back(at::empty({(int64_t)bytes}, s->options));
+            return s->memory.back().data_ptr();
+        } catch (...) {
+            s->error = std::current_exception();
+            return nullptr;
+        }
     }
 };
 
@@ -394,6 +414,34 @@ struct Block : public torch::autograd::Function<Block> {
         }
         // (both layers' weight gradients in one launch where both are wanted)
         const bool pair = want_w1 && want_w2 && wgrad && !graph;
+        if (pair && want_first && coefficients_of(A1, B1, x, D) && coefficients_of(A2, B2, x, hidden)) {
+            const Tensor W = as_saved(W1, x, {hidden, D});
+            f1 = as_saved(saved[7], x, x.sizes());
+            h = as_saved(saved[8], x, {rows, hidden});
+            Scratches scratch{x.options().dtype(at::kByte), {}, nullptr};
+            const Tensor dh = at::empty_like(h), df1 = at::empty({rows, D}, x.options());
+            out[0] = at::empty_like(x);
+            out[1] = at::empty_like(A1);
+            out[2] = at::empty_like(B1);
+            out[3] = at::empty({hidden, D}, x.options());
+            out[4] = at::empty_like(A2);
+            out[5] = at::empty_like(B2);
+            out[6] = at::empty({D, hidden}, x.options());
+            if (want_b1)
+                out[7] = at::empty({hidden}, x.options());
+            if (want_b2)
+                out[8] = at::empty({D}, x.options());
+            const grkan_block_bwd_t b{rows, (int32_t)D, (int32_t)hidden, (int32_t)B1.size(0), (int32_t)B2.size(0), A1.dim() == 1, A2.dim() == 1,
+                                      x.data_ptr(), f1.data_ptr(), h.data_ptr(), f2.data_ptr(), dout.data_ptr(), A1.data_ptr(), B1.data_ptr(),
+                                      W.data_ptr(), A2.data_ptr(), B2.data_ptr(), W2.data_ptr(), out[0].data_ptr(), out[1].data_ptr(),
+                                      out[2].data_ptr(), out[3].data_ptr(), want_b1 ? out[7].data_ptr() : nullptr, out[4].data_ptr(),
+                                      out[5].data_ptr(), out[6].data_ptr(), want_b2 ? out[8].data_ptr() : nullptr, dh.data_ptr(), df1.data_ptr()};
+            const grkan_status_t st = grkan_block_bwd(&b, &Scratches::alloc, &scratch, stream_of(x));
+            if (scratch.error)
+                std::rethrow_exception(scratch.error);
+            check(st, "grkan_block_bwd");
+            return out;
+        }
         if (!pair)
             gradients_of(dout, f2, want_w2, want_b2, wgrad, out[6], out[8]);
         if (!want_dh)
@@ -437,6 +485,14 @@ struct Block : public torch::autograd::Function<Block> {
             std::copy(d.begin(), d.end(), out.begin());
         }
         return out;
+    }
+
+    // Coefficients as grkan_block_bwd reads them (a saved-tensor hook may have made something else of them).
+    static bool coefficients_of(const Tensor &A, const Tensor &B, const Tensor &x, int64_t channels)
+    {
+        return plain(A, x.device()) && plain(B, x.device()) && A.scalar_type() == at::kBFloat16 && B.scalar_type() == at::kBFloat16 &&
+               A.is_contiguous() && B.is_contiguous() && B.dim() == 2 && B.size(1) == 4 && B.size(0) > 0 && channels % B.size(0) == 0 &&
+               A.dim() >= 1 && A.dim() <= 2 && A.size(-1) == 6 && (A.dim() == 1 || A.size(0) == B.size(0));
     }
 
     static void gradients_of(const Tensor &dout, const Tensor &y, bool want_w, bool want_b, bool wgrad, Tensor &dW, Tensor &db)
