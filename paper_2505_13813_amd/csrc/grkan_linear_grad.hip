@@ -11,25 +11,27 @@
 // A block's two products share one launch: the partial tiles that fill the chip are 38 MB in all, whatever the sizes, written and
 // read once instead of twice.
 //
-//   * Both operands have the contraction as their slow dimension.  Stages of 64 rows come to LDS as they lie
-//     in memory (LDS-direct loads of whole 384-byte row pieces, three buffers) and are transposed on the way into the matrix
+//   * Both operands have the contraction as their slow dimension.  Stages of 32 rows come to LDS as they lie
+//     in memory (LDS-direct loads of whole 384-byte row pieces, six buffers) and are transposed on the way into the matrix
 //     cores by ds_read_b64_tr_b16, which hands lane (i, g) of a wavefront the rows 4 g .. 4 g + 3 of column i.  The rows of a
-//     32-row step are numbered alike for both operands, which is all a contraction needs.
+//     stage are numbered alike for both operands, which is all a contraction needs.
 //   * 32-byte column pairs of a row are rotated by half the row number, so that the 16 rows a transposing
 //     read touches fall into different banks (rows are 384 bytes = 1.5 bank sweeps apart).
-//   * Four wavefronts multiply, one per SIMD, a 96 x 96 quadrant each: 12 KB of reads for 36 matrix instructions; transposing
-//     reads run at about 110 B per clock and CU, so that a 96 x 48 share would be bound by them.  One barrier per stage, behind
-//     the first row of tiles of its second half; the next step's operands are read behind the last use of the registers they go to.
-//   * Four wavefronts load, and add up the columns of dOut for dbias while they wait: tiles that see the same columns take
-//     turns by the stage.
+//   * Eight wavefronts multiply, two per SIMD, 96 x 48 each.  (Four of 96 x 96 read a third less, but one per SIMD does
+//     not issue its reads beside its own matrix instructions: 0.76 - 0.82 us per 64 rows against 0.71 without loads.)  One barrier
+//     per stage, behind the first row of tiles; the next stage's operands are read between the matrix instructions, each
+//     behind the last use of the registers it goes to.
+//   * Four wavefronts load.  The column sums for dbias are matrix products with ones that they make meanwhile; tiles that see
+//     the same columns of dOut take turns by the stage.  (Added up lane by lane they cost the whole kernel a tenth of its time.)
 //
 // Measured on one MI355X, both gradients of one product, 25,216 rows, against the library's product + column sum (us):
 //   384 x 1536: 41 against 171     192 x 768: 28 against 189     768 x 3072: 120 against 270
-// and of a block's two products, in two launches (eight wavefronts that loaded, read and multiplied in turn) / in two / in one:
-//   384: 90 / 83 / 65     192: 57 / 55 / 34     512: 154 / 132 / 131     768: 266 / 241 / 224     768 at 3,152 rows: 67 / 62 / 42
-// What bounds it: at 384 (50 stages for each workgroup) the matrix instructions of a stage take 0.48 us, the transposing reads
-// 0.38, the loads 0.49 and all together 0.8 - 1; reads and matrix instructions overlap poorly with one multiplying wavefront
-// per SIMD, which has the registers for no second one.  The second kernel, which reads the partial tiles, takes 7 - 8 us.
+// and of a block's two products, in two launches of eight wavefronts that loaded, read and multiplied in turn / in one of this:
+//   384: 90 / 65     192: 57 / 33     512: 154 / 122     768: 266 / 220     768 at 3,152 rows: 67 / 42
+// What bounds it: at 384 (50 times 64 rows for each workgroup) 64 rows take 0.53 - 0.59 us of matrix instructions (0.48 at 2.4
+// GHz), 0.71 with the transposing reads, 0.82 with loads that hit the L2 and 0.9 - 1.0 with the rows from memory, where the
+// loads alone take 0.55; the loads move 4 TB/s where they miss the last-level cache (row pieces of 384 bytes, which eight workgroups
+// fetch next to each other).  The second kernel, which reads the partial tiles, takes 7 - 8 us, writing them about as much.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -44,17 +46,17 @@ namespace wgrad {
 using namespace tile;
 
 constexpr int kTile = 192;                       // rows and columns of a tile of dW
-constexpr int kRows = 64;                        // rows of dOut and Y per stage
+constexpr int kRows = 32;                        // rows of dOut and Y per stage
 constexpr int kPairs = kTile / 16;               // 32-byte column pairs per row
 constexpr uint32_t kRowB = kTile * 2;            // bytes of a row piece
-constexpr uint32_t kOperand = kRows * kRowB;     // 24576: one operand of one stage
+constexpr uint32_t kOperand = kRows * kRowB;     // 12288: one operand of one stage
 constexpr uint32_t kStage = 2 * kOperand;
-constexpr int kBuffers = 3;
+constexpr int kBuffers = 6;
 constexpr uint32_t kLds = kBuffers * kStage;     // 147456
-constexpr int kMul = 4, kLoaders = 4;            // wavefronts
+constexpr int kMul = 8, kLoaders = 4;            // wavefronts
 constexpr int kThreads = 64 * (kMul + kLoaders);
-constexpr int kLoads = (int)(kStage / 1024 / kLoaders); // LDS-direct loads per loading wavefront and stage: 12
-constexpr int kSub = 6;                          // 16 x 16 tiles of a wavefront each way
+constexpr int kLoads = (int)(kStage / 1024 / kLoaders); // LDS-direct loads per loading wavefront and stage: 6
+constexpr int kO = 6, kI = 3;                    // 16 x 16 tiles of a wavefront: columns of dOut, of Y
 
 struct Problem {
     const char *dout; // bfloat16 [rows, Do]
@@ -106,6 +108,9 @@ __global__ __launch_bounds__(kThreads, kThreads / 256) void grkan_linear_wgrad_k
     const int32_t T = (int32_t)(n_stages * (split + 1) / a.splits - s0);
     auto advance = [&](uint32_t b) { return b + kStage == kBuffers * kStage ? 0u : b + kStage; };
 
+    const uint32_t r15 = (uint32_t)(lane >> 4) * 4u + (uint32_t)(lane & 15) / 4u; // row (mod 16) a lane addresses
+    const uint32_t lane_at = lds0 + r15 * kRowB + (uint32_t)(lane & 3) * 8u;
+
     // every wavefront passes T + 1 barriers in the branches
     if (wave >= kMul) {
         // ---- loads: 16-byte piece e of an operand's stage sits at LDS byte 16 e: row e / 24, slot e % 24, which holds column
@@ -150,14 +155,16 @@ __global__ __launch_bounds__(kThreads, kThreads / 256) void grkan_linear_wgrad_k
         };
         static_assert(kLoads % 2 == 0 && kOperand / 1024 % kLoaders == 0, "");
 
-        // ---- column sums for dbias: lane of the first three loading wavefronts -> 8 columns (piece c of 24) and 8 rows of every
-        // stage that is this tile's turn (the tiles that see the same columns of dOut take turns)
-        const uint32_t l192 = (uint32_t)(fw * 64 + lane), piece = l192 % 24u, r8 = l192 / 24u * 8u;
-        const bool sums = p.bpart && fw < 3;
-        float bsum[8];
+        // ---- column sums for dbias: products with ones, of three sub-tiles of 16 columns for each loading wavefront, in every stage that
+        // is this tile's turn (the tiles that see the same columns of dOut take turns)
+        uint32_t at_sum[3];
+        f32x4 sums[3];
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
-            bsum[k] = 0.0f;
+        for (int k = 0; k < 3; ++k) {
+            at_sum[k] = lane_at + (((uint32_t)(fw * 3 + k) + (r15 >> 1)) % (uint32_t)kPairs) * 32u;
+            sums[k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+        const u32x4 ones = u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
 
         static_for<0, kBuffers>([&](auto sc) {
             constexpr int s = decltype(sc)::value;
@@ -173,19 +180,11 @@ __global__ __launch_bounds__(kThreads, kThreads / 256) void grkan_linear_wgrad_k
         uint32_t buf = 0;
         int32_t turn = (int32_t)(s0 % p.tiles_i);
         for (int32_t t = 0; t < T; ++t) {
-            if (sums && turn == ti) {
+            if (p.bpart && turn == ti)
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const uint32_t row = r8 + (uint32_t)j;
-                    const uint32_t slot = ((piece >> 1) + ((row & 15u) >> 1)) % (uint32_t)kPairs;
-                    const u32x4 v = lds_read16(lds0 + buf + row * kRowB + slot * 32u + (piece & 1u) * 16u);
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        bsum[2 * k] += low(v[k]);
-                        bsum[2 * k + 1] += high(v[k]);
-                    }
-                }
-            }
+                for (int k = 0; k < 3; ++k)
+                    sums[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ones),
+                                                                      __builtin_bit_cast(bf16x8, fragment(at_sum[k] + buf)), sums[k], 0, 0, 0);
             turn = turn + 1 == p.tiles_i ? 0 : turn + 1;
             if (t + kBuffers < T)
                 wait_loads<(kBuffers - 2) * kLoads>();
@@ -196,100 +195,99 @@ __global__ __launch_bounds__(kThreads, kThreads / 256) void grkan_linear_wgrad_k
                 fetch(t + kBuffers, buf); // every wavefront has left it
             buf = advance(buf);
         }
-        __syncthreads(); // the operands have been read for the last time
-        if (sums) {
+        if (p.bpart && lane < 16)
 #pragma unroll
-            for (int k = 0; k < 8; ++k)
-                *(__attribute__((address_space(3))) float *)(uintptr_t)(lds0 + (r8 / 8u * 192u + piece * 8u + (uint32_t)k) * 4u) = bsum[k];
-        }
-        __syncthreads();
-        if (sums) {
-            float v = 0.0f;
-#pragma unroll
-            for (int r = 0; r < 8; ++r)
-                v += *(const __attribute__((address_space(3))) float *)(uintptr_t)(lds0 + ((uint32_t)r * 192u + l192) * 4u);
-            const int32_t o = to * kTile + (int32_t)l192;
-            if (o < p.Do)
-                p.bpart[((int64_t)split * p.tiles_i + ti) * p.Do + o] = v;
-        }
+            for (int k = 0; k < 3; ++k) {
+                const int32_t o = to * kTile + (fw * 3 + k) * 16 + lane;
+                if (o < p.Do)
+                    p.bpart[((int64_t)split * p.tiles_i + ti) * p.Do + o] = sums[k][0];
+            }
         return;
     }
 
-    // ---- multiplying wavefront: quadrant (o half oh, i half ih).  Y is the row operand of the matrix instruction, so that a lane
-    // ends up with four consecutive i of one o.
-    const int oh = wave >> 1, ih = wave & 1;
-    const uint32_t r15 = (uint32_t)(lane >> 4) * 4u + (uint32_t)(lane & 15) / 4u; // row (mod 16) a lane addresses
-    const uint32_t lane_at = lds0 + r15 * kRowB + (uint32_t)(lane & 3) * 8u;
-    uint32_t at_i[kSub], at_o[kSub];
+    // ---- multiplying wavefront: half oh of the tile's columns of dOut, quarter iq of Y's.  Y is the row operand of the matrix
+    // instruction, so that a lane ends up with four consecutive i of one o.
+    const int oh = wave >> 2, iq = wave & 3;
+    uint32_t at_i[kI], at_o[kO];
 #pragma unroll
-    for (int k = 0; k < kSub; ++k) {
-        at_i[k] = lane_at + kOperand + (((uint32_t)(ih * kSub + k) + (r15 >> 1)) % (uint32_t)kPairs) * 32u;
-        at_o[k] = lane_at + (((uint32_t)(oh * kSub + k) + (r15 >> 1)) % (uint32_t)kPairs) * 32u;
-    }
-    f32x4 acc[kSub][kSub]; // [o sub-tile][i sub-tile]
+    for (int k = 0; k < kI; ++k)
+        at_i[k] = lane_at + kOperand + (((uint32_t)(iq * kI + k) + (r15 >> 1)) % (uint32_t)kPairs) * 32u;
 #pragma unroll
-    for (int m = 0; m < kSub; ++m)
+    for (int k = 0; k < kO; ++k)
+        at_o[k] = lane_at + (((uint32_t)(oh * kO + k) + (r15 >> 1)) % (uint32_t)kPairs) * 32u;
+    f32x4 acc[kO][kI];
 #pragma unroll
-        for (int n = 0; n < kSub; ++n)
+    for (int m = 0; m < kO; ++m)
+#pragma unroll
+        for (int n = 0; n < kI; ++n)
             acc[m][n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
-    // One step of 32 rows, half h of a stage: multiplies with x and wc while the next step's operands are read into x, each
-    // behind its own last use, and wn.  In the second half, behind the first row of tiles, the barrier: every wavefront has its
-    // operands of this stage, and the next one has landed.  (Behind the last stage the next buffer is read too, and not used.)
-    auto step = [&](auto hc, uint32_t buf, uint32_t buf_next, u32x4(&x)[kSub], u32x4(&wc)[kSub], u32x4(&wn)[kSub]) {
-        constexpr int h = decltype(hc)::value;
-        const uint32_t here = buf + (uint32_t)h * 32u * kRowB, from = h == 1 ? buf_next : buf + 32u * kRowB;
-        static_for<0, kSub>([&](auto mc) {
+    // One stage: multiplies with x and wc while the next one's operands are read into x, each behind its own last use, and wn.
+    // Behind the first row of tiles the barrier: every wavefront has its operands of this stage, and the next one has landed.
+    // (Behind the last stage the next buffer is read too, and not used.)
+    auto step = [&](auto hc, uint32_t from, u32x4(&x)[kO - 1], u32x4(&last)[2], u32x4(&wc)[kI], u32x4(&wn)[kI]) {
+        constexpr int h = decltype(hc)::value; // which of `last`
+        static_for<0, kO>([&](auto mc) {
             constexpr int m = decltype(mc)::value;
-            if constexpr (h == 1 && m == 1)
+            if constexpr (m == 1)
                 asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            if constexpr (m == 0)
-                x[kSub - 1] = fragment(at_o[kSub - 1] + here);
-            else
-                x[m - 1] = fragment(at_o[m - 1] + from);
-            if constexpr (m >= 1) {
-                constexpr int n0 = (m - 1) * kSub / (kSub - 1), n1 = m * kSub / (kSub - 1);
-                static_for<n0, n1>([&](auto nc) { wn[decltype(nc)::value] = fragment(at_i[decltype(nc)::value] + from); });
-            }
-            fence_schedule();
-#pragma unroll
-            for (int n = 0; n < kSub; ++n)
-                acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wc[n]), __builtin_bit_cast(bf16x8, x[m]),
+            // reads between the matrix instructions: one after the other they would wait for the LDS with the matrix core idle
+            // (wn's first, long before they are used; `last` has two sets of registers, so that it is read with the others)
+            constexpr int n0 = m > 0 ? (2 * m - 2 < kI ? 2 * m - 2 : kI) : 0, n1 = 2 * m < kI ? 2 * m : kI;
+            constexpr int kX = m > 0 ? 1 : 0, kOps = kX + (n1 - n0) + (m == kO - 1 ? 1 : 0);
+            static_for<0, kI>([&](auto nc) {
+                constexpr int n = decltype(nc)::value;
+                static_for<0, kOps>([&](auto oc) {
+                    constexpr int o = decltype(oc)::value;
+                    if constexpr (o * kI / kOps == n) {
+                        if constexpr (o < kX)
+                            x[m - 1] = fragment(at_o[m - 1] + from);
+                        else if constexpr (o < kX + n1 - n0)
+                            wn[n0 + o - kX] = fragment(at_i[n0 + o - kX] + from);
+                        else
+                            last[1 - h] = fragment(at_o[kO - 1] + from);
+                    }
+                });
+                fence_schedule();
+                acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wc[n]), __builtin_bit_cast(bf16x8, m < kO - 1 ? x[m < kO - 1 ? m : 0] : last[h]),
                                                                     acc[m][n], 0, 0, 0);
-            fence_schedule();
+                fence_schedule();
+            });
         });
     };
     asm volatile("s_barrier" ::: "memory");
     {
-        u32x4 x[kSub], wa[kSub], wb[kSub];
+        u32x4 x[kO - 1], last[2], wa[kI], wb[kI];
 #pragma unroll
-        for (int k = 0; k < kSub; ++k)
+        for (int k = 0; k < kI; ++k)
             wa[k] = fragment(at_i[k]);
 #pragma unroll
-        for (int k = 0; k < kSub - 1; ++k)
+        for (int k = 0; k < kO - 1; ++k)
             x[k] = fragment(at_o[k]);
+        last[0] = fragment(at_o[kO - 1]);
         uint32_t buf = 0;
-        for (int32_t t = 0; t < T; ++t) {
-            const uint32_t next = advance(buf);
-            step(std::integral_constant<int, 0>{}, buf, next, x, wa, wb);
-            step(std::integral_constant<int, 1>{}, buf, next, x, wb, wa);
-            buf = next;
+        int32_t t = 0;
+        for (; t + 1 < T; t += 2) {
+            const uint32_t next = advance(buf), after = advance(next);
+            step(std::integral_constant<int, 0>{}, next, x, last, wa, wb);
+            step(std::integral_constant<int, 1>{}, after, x, last, wb, wa);
+            buf = after;
         }
+        if (t < T)
+            step(std::integral_constant<int, 0>{}, advance(buf), x, last, wa, wb);
     }
-    __syncthreads();
-    __syncthreads(); // (of the loading wavefronts' column sums)
 
     // ---- the partial tile goes to memory
     const int32_t o_lane = to * kTile + oh * 96 + (lane & 15);
-    const int32_t i_lane = ti * kTile + ih * 96 + (lane >> 4) * 4;
+    const int32_t i_lane = ti * kTile + iq * 48 + (lane >> 4) * 4;
 #pragma unroll
-    for (int m = 0; m < kSub; ++m) {
+    for (int m = 0; m < kO; ++m) {
         const int32_t o = o_lane + m * 16;
         if (o >= p.Do)
             continue;
         float *const row = p.part + ((int64_t)split * p.Do + o) * p.Di;
 #pragma unroll
-        for (int n = 0; n < kSub; ++n) {
+        for (int n = 0; n < kI; ++n) {
             const int32_t i = i_lane + n * 16;
             if (i < p.Di)
                 *(f32x4 *)(row + i) = acc[m][n];
@@ -393,11 +391,11 @@ static grkan_status_t make_plan(int64_t rows, const Size *size, int n, Plan *pl)
         tiles += mine;
     }
     const int64_t stages = (rows + kRows - 1) / kRows;
-    // as many row ranges as fill the 256 compute units once (one workgroup each: 144 KB of LDS), each of four
+    // as many row ranges as fill the 256 compute units once (one workgroup each: 144 KB of LDS), each of eight
     // stages at least: a shorter one would mostly fill and drain its pipeline and write its partial tile
     int64_t splits = 256 / tiles;
-    if (splits > stages / 4)
-        splits = stages / 4;
+    if (splits > stages / 8)
+        splits = stages / 8;
     if (splits < 1)
         splits = 1;
     if (tiles * splits > INT32_MAX / 16)

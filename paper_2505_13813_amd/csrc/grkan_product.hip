@@ -62,7 +62,10 @@ template <int TM_, int TN_, int WM_, int WN_, int NBUF_, int LD_, int PER_ = 1> 
     static constexpr int kParts = (size_t)BM * kPitch > 160 * 1024 ? 2 : 1, kMP = (TM + kParts - 1) / kParts; // it leaves in parts
     static constexpr size_t kMain = (size_t)NBUF * kStage, kRows = (size_t)WM * kMP * 16 * kPitch;
     static constexpr size_t kLds = kMain > kRows ? kMain : kRows;
-    static_assert(PER * kLds <= 160 * 1024 && TM >= 2 && (kWaves + LD) % 4 == 0, "");
+    // Registers of their own for the last row of tiles' next operand: it can then be read with the others, well in front of the
+    // barrier that waits for all reads.  (The largest tile has none left.)
+    static constexpr bool kTwoLast = TM * TN < 40;
+    static_assert(2 * (TM - 1) >= TN && PER * kLds <= 160 * 1024 && TM >= 2 && (kWaves + LD) % 4 == 0, "");
 };
 
 template <class SH, bool TRANSPOSED, bool RATIONAL>
@@ -171,7 +174,7 @@ __global__ __launch_bounds__(SH::kThreads, SH::PER *SH::kThreads / 256) void pro
     // tiles behind its own last use, and wn_.  In the second half, behind the first row of tiles, the barrier: every
     // wavefront has its operands of this stage, so that its buffer is free for stage t + NBUF, and stage t + 1 has landed.
     // (Behind the last stage the next buffer is read too, and not used.)
-    auto step = [&](auto hc, int32_t t, uint32_t buf, uint32_t buf_next, u32x4(&x)[TM], u32x4(&wc)[TN], u32x4(&wn_)[TN]) {
+    auto step = [&](auto hc, int32_t t, uint32_t buf, uint32_t buf_next, u32x4(&x)[TM - 1], u32x4(&last)[2], u32x4(&wc)[TN], u32x4(&wn_)[TN]) {
         constexpr int h = decltype(hc)::value;
         const uint32_t from = h == 1 ? buf_next : buf;
         const bool more = t + NBUF < T;
@@ -181,26 +184,33 @@ __global__ __launch_bounds__(SH::kThreads, SH::PER *SH::kThreads / 256) void pro
                 asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
             if constexpr (h == 1 && m == 1 && SH::LD == 0)
                 wait_for(std::integral_constant<int, NBUF - 2>{}, t + NBUF - 1 < T);
-            if constexpr (m == 0)
-                x[TM - 1] = read_x(buf, h, TM - 1);
-            else
-                x[m - 1] = read_x(from, 1 - h, m - 1);
-            if constexpr (m >= 1) {
-                constexpr int n0 = (m - 1) * TN / (TM - 1), n1 = m * TN / (TM - 1);
-                static_for<n0, n1>([&](auto nc) { wn_[decltype(nc)::value] = read_w(from, 1 - h, decltype(nc)::value); });
-            }
-            if constexpr (h == 1 && m >= 1 && SH::LD == 0) {
-                constexpr int q0 = (m - 1) * SH::kHi / (TM - 1), q1 = m * SH::kHi / (TM - 1);
-                if constexpr (q1 > q0)
-                    if (more)
-                        static_for<q0, q1>([&](auto qc) { fetch_one(qc, t + NBUF, buf); });
-            }
-            fence_schedule();
-#pragma unroll
-            for (int n = 0; n < TN; ++n)
-                acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wc[n]), __builtin_bit_cast(bf16x8, x[m]),
+            // reads (and loads) between the matrix instructions: one after the other they would wait for the LDS with the matrix
+            // core idle
+            constexpr int n0 = m > 0 ? (2 * m - 2 < TN ? 2 * m - 2 : TN) : 0, n1 = 2 * m < TN ? 2 * m : TN; // W's of this group
+            constexpr int kX = m > 0 ? 1 : 0, kLast = m == (SH::kTwoLast ? TM - 1 : 0) ? 1 : 0;
+            constexpr bool loads = h == 1 && m >= 1 && SH::LD == 0;
+            constexpr int q0 = loads ? (m - 1) * SH::kHi / (TM - 1) : 0, q1 = loads ? m * SH::kHi / (TM - 1) : 0;
+            constexpr int kOps = kX + (n1 - n0) + kLast + (q1 - q0);
+            static_for<0, TN>([&](auto nc) {
+                constexpr int n = decltype(nc)::value;
+                static_for<0, kOps>([&](auto oc) {
+                    constexpr int o = decltype(oc)::value;
+                    if constexpr (o * TN / kOps == n) {
+                        if constexpr (o < kX)
+                            x[m - 1] = read_x(from, 1 - h, m - 1);
+                        else if constexpr (o < kX + n1 - n0)
+                            wn_[n0 + o - kX] = read_w(from, 1 - h, n0 + o - kX);
+                        else if constexpr (o < kX + n1 - n0 + kLast)
+                            last[SH::kTwoLast ? 1 - h : 0] = SH::kTwoLast ? read_x(from, 1 - h, TM - 1) : read_x(buf, h, TM - 1);
+                        else if (more)
+                            fetch_one(std::integral_constant<int, q0 + o - kX - kLast - (n1 - n0)>{}, t + NBUF, buf);
+                    }
+                });
+                fence_schedule();
+                acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wc[n]), __builtin_bit_cast(bf16x8, m < TM - 1 ? x[m < TM - 1 ? m : 0] : last[SH::kTwoLast ? h : 0]),
                                                                     acc[m][n], 0, 0, 0);
-            fence_schedule();
+                fence_schedule();
+            });
         });
     };
     auto advance = [&](uint32_t b) { return b + SH::kStage == NBUF * SH::kStage ? 0u : b + SH::kStage; };
@@ -225,18 +235,20 @@ __global__ __launch_bounds__(SH::kThreads, SH::PER *SH::kThreads / 256) void pro
             buf = advance(buf);
         }
     } else {
-        u32x4 x[TM], wa[TN], wb[TN]; // (as words: carried around the loop as bfloat16 the compiler takes them apart)
+        u32x4 x[TM - 1], last[2], wa[TN], wb[TN]; // (as words: carried around the loop as bfloat16 the compiler takes them apart)
 #pragma unroll
         for (int n = 0; n < TN; ++n)
             wa[n] = read_w(0, 0, n);
 #pragma unroll
         for (int m = 0; m < TM - 1; ++m)
             x[m] = read_x(0, 0, m);
+        if (SH::kTwoLast)
+            last[0] = read_x(0, 0, TM - 1);
         uint32_t buf = 0;
         for (int32_t t = 0; t < T; ++t) {
             const uint32_t next = advance(buf);
-            step(std::integral_constant<int, 0>{}, t, buf, next, x, wa, wb);
-            step(std::integral_constant<int, 1>{}, t, buf, next, x, wb, wa);
+            step(std::integral_constant<int, 0>{}, t, buf, next, x, last, wa, wb);
+            step(std::integral_constant<int, 1>{}, t, buf, next, x, last, wb, wa);
             buf = next;
         }
     }

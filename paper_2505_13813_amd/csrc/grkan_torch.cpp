@@ -687,8 +687,9 @@ std::optional<Tensor> block_inference(const Tensor &x_in, const Tensor &A1, cons
         return std::nullopt;
     auto shape = x.sizes().vec();
     shape.back() = D_out;
-    const Tensor f1 = at::empty_like(x), f2 = at::empty({rows, hidden}, x.options());
     Tensor out = at::empty(shape, x.options());
+    // (F1(x) has been read when the result is written)
+    const Tensor f1 = D_out == D ? out : at::empty_like(x), f2 = at::empty({rows, hidden}, x.options());
     void *const stream = stream_of(x);
     check(grkan_fwd_model(x.data_ptr(), A1.data_ptr(), B1.data_ptr(), f1.data_ptr(), rows, (int32_t)D, (int32_t)B1.size(0), 5, 4, GRKAN_BF16,
                           GRKAN_BF16, A1.dim() == 1, stream),
