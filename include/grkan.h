@@ -375,12 +375,13 @@ grkan_status_t grkan_hidden_bwd(const void *dout, const void *W, const void *h, 
  * grkan_product_supported: K a multiple of 64 and N one of 8 (each at most 2^20), at most 2^30 rows; F: N / G a multiple of 8.
  * Anything else is GRKAN_ERR_UNSUPPORTED.
  * grkan_product_estimate_us, grkan_product_tile: host-only; the estimated device time (0 for sizes that are not supported),
- * and the tile that is used, with the workgroups per compute unit.
+ * and the tile that is used, with the workgroups per compute unit and how many rows run in it (fewer than all where a
+ * second launch takes the rest in another tile).
  */
 int32_t grkan_product_supported(int64_t rows, int32_t K, int32_t N);
 double grkan_product_estimate_us(int64_t rows, int32_t K, int32_t N, int32_t rational);
 grkan_status_t grkan_product_tile(int64_t rows, int32_t K, int32_t N, int32_t rational, int32_t *tile_rows,
-                                  int32_t *tile_channels, int32_t *per_unit);
+                                  int32_t *tile_channels, int32_t *per_unit, int64_t *rows_in_it);
 grkan_status_t grkan_product(const void *x, const void *W, const void *bias, void *out, int64_t rows, int32_t K,
                              int32_t N, int32_t transposed, const void *A, const void *B, int32_t G,
                              int32_t shared_numerator, void *hip_stream);

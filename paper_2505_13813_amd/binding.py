@@ -103,7 +103,7 @@ def load_library():
     lib.grkan_product_supported.restype = i32
     lib.grkan_product_estimate_us.argtypes = [i64, i32, i32, i32]
     lib.grkan_product_estimate_us.restype = ctypes.c_double
-    lib.grkan_product_tile.argtypes = [i64, i32, i32, i32, vp, vp, vp]
+    lib.grkan_product_tile.argtypes = [i64, i32, i32, i32, vp, vp, vp, vp]
     lib.grkan_product_tile.restype = ctypes.c_int
     lib.grkan_product.argtypes = [vp, vp, vp, vp, i64, i32, i32, i32, vp, vp, i32, i32, vp]
     lib.grkan_product.restype = ctypes.c_int
@@ -394,9 +394,10 @@ def grkan_product_estimate_us(rows: int, K: int, N: int, rational: bool = False)
     return float(load_library().grkan_product_estimate_us(int(rows), int(K), int(N), int(bool(rational))))
 
 
-def grkan_product_tile(rows: int, K: int, N: int, rational: bool = False) -> Tuple[int, int, int]:
-    """Rows and channels of the tile grkan_product runs these sizes in, and workgroups per compute unit."""
-    out = [ctypes.c_int32() for _ in range(3)]
+def grkan_product_tile(rows: int, K: int, N: int, rational: bool = False) -> Tuple[int, int, int, int]:
+    """Rows and channels of the tile grkan_product runs these sizes in, workgroups per compute unit, and how many of the rows
+    run in it (a second launch takes the rest)."""
+    out = [ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int64()]
     st = load_library().grkan_product_tile(int(rows), int(K), int(N), int(bool(rational)), *(ctypes.byref(v) for v in out))
     if st:
         raise GrkanError(st, "grkan_product_tile")

@@ -324,18 +324,22 @@ template <class SH> static constexpr Variant variant(double once, double round, 
                    once, round, stage, fill, round2, stage2};
 }
 
-// Of fourteen tiles these six are the ones that together lose least to the best of all (2 % in the mean) at 110 measured sizes: ten
-// pairs N, K of 192 .. 3072 and 256 .. 3072, 197 - 50,432 rows.  The figures are least squares over the same
-// sizes (residuals 4 - 9 %); the tile that the estimate takes is 2.8 % slower than the best of all fourteen in the mean, 25 %
-// at most (calls of 9 - 20 us).  Large tiles move less through the L2 and LDS for each product, small ones fill the chip:
-//   320 x 256 / 224 x 192 / 160 x 128 / two of 160 x 128 / 96 x 128 / 64 x 64, us
-//   25,216 x 384 -> 1536  37 / 43 / 48 / 39 / 57 / 65      25,216 x 1536 -> 384  42 / 29 / 32 / 31 / 44 / 45
-//    6,304 x 768 -> 3072  31 / 35 / 44 / 34 / 58 / 59       3,152 x 3072 -> 768  72 / 38 / 24 / 38 / 20 / 29
-//      788 x 1536 -> 384  39 / 22 / 13 / 19 / 10 / 7
+// Of fourteen tiles these eight together lose 1 % in the mean to the best of all at 154 measured sizes (fourteen pairs N, K of 192 ..
+// 3072 and 256 .. 3072, 197 - 50,432 rows).  The figures are least squares over the same sizes (residuals 4 - 8 %); the tile that the
+// estimate takes is 1.7 % slower than the best of all fourteen in the mean, 18 % at most.  Large tiles move less through the L2 and
+// LDS for each product, small ones fill the chip:
+//   320 x 256 / 256 x 256 / 224 x 192 / 160 x 192 / 160 x 128 / two of 160 x 128 / 96 x 128 / 64 x 64, us
+//   25,216 x  384 -> 1536  42 / 50 / 57 / 50 / 53 / 43 / 60 / 68
+//   25,216 x 1536 ->  384  44 / 37 / 33 / 40 / 37 / 32 / 47 / 49
+//    9,456 x  768 -> 3072  54 / 48 / 59 / 64 / 72 / 54 / 84 / 88
+//    6,304 x 3072 ->  768  71 / 59 / 40 / 32 / 30 / 42 / 41 / 48
+//    3,152 x 3072 ->  768  70 / 58 / 38 / 30 / 24 / 37 / 20 / 30
+//      788 x 1536 ->  384  38 / 31 / 21 / 17 / 12 / 18 / 9 / 7
 static const Variant kVariants[] = {
-    variant<Shape<10, 4, 2, 4, 2, 0>>(0.75, 7.56, 1.22, 0.545), variant<Shape<7, 3, 2, 4, 3, 4>>(1.49, 5.35, 0.573, 0.354),
-    variant<Shape<5, 2, 2, 4, 4, 4>>(1.68, 3.50, 0.318, 0.199), variant<Shape<5, 4, 2, 2, 2, 0, 2>>(2.95, 1.72, 0.632, 0, 3.58, 0.988),
-    variant<Shape<3, 2, 2, 4, 4, 4>>(2.04, 2.44, 0.233, 0.144), variant<Shape<2, 2, 2, 2, 4, 4>>(2.97, 0.68, 0.140, 0.026)};
+    variant<Shape<10, 4, 2, 4, 2, 0>>(0.22, 8.07, 1.183, 0.679), variant<Shape<8, 4, 2, 4, 2, 0>>(-0.39, 7.27, 0.959, 0.567),
+    variant<Shape<7, 3, 2, 4, 3, 4>>(0.45, 6.37, 0.558, 0.438), variant<Shape<5, 3, 2, 4, 3, 4>>(0.75, 5.09, 0.418, 0.333),
+    variant<Shape<5, 2, 2, 4, 4, 4>>(1.01, 3.72, 0.297, 0.281), variant<Shape<5, 4, 2, 2, 2, 0, 2>>(1.89, 2.36, 0.612, 0, 4.15, 1.067),
+    variant<Shape<3, 2, 2, 4, 4, 4>>(1.74, 2.34, 0.211, 0.199), variant<Shape<2, 2, 2, 2, 4, 4>>(2.95, 0.66, 0.129, 0.047)};
 
 static int64_t tiles_of(const Variant &v, int64_t rows, int32_t N) { return (rows + v.BM - 1) / v.BM * ((N + v.BN - 1) / v.BN); }
 
@@ -348,16 +352,43 @@ static double estimate_us(const Variant &v, int64_t rows, int32_t K, int32_t N, 
     return v.once + (double)rounds * (v.round + T * (v.stage + v.fill * ((double)tiles / ((double)rounds * 256))) + f);
 }
 
-static const Variant *pick(int64_t rows, int32_t K, int32_t N, bool rational)
+static const Variant *best_tile(int64_t rows, int32_t K, int32_t N, bool rational, double *us)
 {
     const Variant *best = nullptr;
-    double least = 0;
     for (const Variant &v : kVariants) {
-        const double us = estimate_us(v, rows, K, N, rational);
-        if (!best || us < least) {
+        const double t = estimate_us(v, rows, K, N, rational);
+        if (!best || t < *us) {
             best = &v;
-            least = us;
+            *us = t;
         }
+    }
+    return best;
+}
+
+// The launches of a call: all rows in one tile, or, where a last round would be nearly empty, whole rounds of one and the rows that are
+// left in another (12,593 x 2048 -> 2048: 105 us in one tile, 92 as 10,240 rows in 320 x 256
+// and 2,353 in a small one; 30,000 x 384 -> 1536 48.8 and 40.2; 9,456 x 768 -> 3072 54 and 49).
+struct Plan {
+    const Variant *first, *second;
+    int64_t first_rows; // all where there is no second
+    double us;
+};
+
+static Plan make_plan(int64_t rows, int32_t K, int32_t N, bool rational)
+{
+    Plan best{nullptr, nullptr, rows, 0};
+    best.first = best_tile(rows, K, N, rational, &best.us);
+    for (const Variant &v : kVariants) {
+        const int64_t tiles_n = (N + v.BN - 1) / v.BN, blocks = (rows + v.BM - 1) / v.BM, at_once = 256 * (int64_t)v.per_cu;
+        const int64_t rounds = blocks * tiles_n / at_once; // whole ones
+        const int64_t take = rounds * at_once / tiles_n;   // row blocks in them
+        if (rounds == 0 || take == 0 || take >= blocks)
+            continue;
+        Plan p{&v, nullptr, take * v.BM, 0};
+        p.second = best_tile(rows - p.first_rows, K, N, rational, &p.us);
+        p.us += estimate_us(v, p.first_rows, K, N, rational) + 1.0;
+        if (p.us < best.us)
+            best = p;
     }
     return best;
 }
@@ -395,20 +426,21 @@ extern "C" double grkan_product_estimate_us(int64_t rows, int32_t K, int32_t N, 
 {
     if (rows <= 0 || !product::supported(rows, K, N))
         return 0;
-    return product::estimate_us(*product::pick(rows, K, N, rational != 0), rows, K, N, rational != 0);
+    return product::make_plan(rows, K, N, rational != 0).us;
 }
 
 extern "C" grkan_status_t grkan_product_tile(int64_t rows, int32_t K, int32_t N, int32_t rational, int32_t *tile_rows, int32_t *tile_channels,
-                                             int32_t *per_unit)
+                                             int32_t *per_unit, int64_t *rows_in_it)
 {
-    if (!tile_rows || !tile_channels || !per_unit)
+    if (!tile_rows || !tile_channels || !per_unit || !rows_in_it)
         return GRKAN_ERR_NULL;
     if (rows <= 0 || !product::supported(rows, K, N))
         return GRKAN_ERR_UNSUPPORTED;
-    const product::Variant *const v = product::pick(rows, K, N, rational != 0);
-    *tile_rows = v->BM;
-    *tile_channels = v->BN;
-    *per_unit = v->per_cu;
+    const product::Plan plan = product::make_plan(rows, K, N, rational != 0);
+    *tile_rows = plan.first->BM;
+    *tile_channels = plan.first->BN;
+    *per_unit = plan.first->per_cu;
+    *rows_in_it = plan.first_rows;
     return GRKAN_OK;
 }
 
@@ -430,26 +462,30 @@ extern "C" grkan_status_t grkan_product(const void *x, const void *W, const void
         return GRKAN_ERR_ALIGN;
     if (rows == 0)
         return GRKAN_OK;
-    const product::Variant &v = *product::pick(rows, K, N, rational);
-    product::Args a;
-    a.x = static_cast<const char *>(x);
-    a.W = static_cast<const char *>(W);
-    a.bias = static_cast<const char *>(bias);
-    a.out = static_cast<char *>(out);
-    a.coef = CoefRows{A, B, shared_numerator ? 0 : product::kM + 1, 1};
-    a.M = rows;
-    a.N = N;
-    a.K = K;
-    a.dg = rational ? N / G : N;
-    a.tiles_n = (N + v.BN - 1) / v.BN;
-    a.tiles = (int32_t)product::tiles_of(v, rows, N);
-    a.per_xcd = (a.tiles + 7) / 8;
+    const product::Plan plan = product::make_plan(rows, K, N, rational);
     const int which = transposed ? 2 : rational ? 1 : 0;
-    if (!product::allow_lds(v, which))
-        return GRKAN_ERR_LAUNCH;
-    void *args[] = {&a};
-    return hipLaunchKernel(reinterpret_cast<const void *>(v.kernel[which]), dim3((unsigned)a.per_xcd * 8u), dim3((unsigned)v.threads), args,
-                           v.lds, static_cast<hipStream_t>(hip_stream)) == hipSuccess
-               ? GRKAN_OK
-               : GRKAN_ERR_LAUNCH;
+    for (int part = 0; part < (plan.second ? 2 : 1); ++part) {
+        const product::Variant &v = part ? *plan.second : *plan.first;
+        const int64_t row0 = part ? plan.first_rows : 0;
+        product::Args a;
+        a.x = static_cast<const char *>(x) + (size_t)row0 * (size_t)K * 2u;
+        a.W = static_cast<const char *>(W);
+        a.bias = static_cast<const char *>(bias);
+        a.out = static_cast<char *>(out) + (size_t)row0 * (size_t)N * 2u;
+        a.coef = CoefRows{A, B, shared_numerator ? 0 : product::kM + 1, 1};
+        a.M = part ? rows - row0 : plan.first_rows;
+        a.N = N;
+        a.K = K;
+        a.dg = rational ? N / G : N;
+        a.tiles_n = (N + v.BN - 1) / v.BN;
+        a.tiles = (int32_t)product::tiles_of(v, a.M, N);
+        a.per_xcd = (a.tiles + 7) / 8;
+        if (!product::allow_lds(v, which))
+            return GRKAN_ERR_LAUNCH;
+        void *args[] = {&a};
+        if (hipLaunchKernel(reinterpret_cast<const void *>(v.kernel[which]), dim3((unsigned)a.per_xcd * 8u), dim3((unsigned)v.threads), args,
+                            v.lds, static_cast<hipStream_t>(hip_stream)) != hipSuccess)
+            return GRKAN_ERR_LAUNCH;
+    }
+    return GRKAN_OK;
 }

@@ -660,6 +660,36 @@ std::optional<Tensor> layer_model(const Tensor &x_in, const Tensor &A, const Ten
     return out;
 }
 
+// The layer in inference as F(x) and the product, on a bfloat16 module's own parameters.
+std::optional<Tensor> layer_product(const Tensor &x_in, const Tensor &A, const Tensor &B, const Tensor &W, const std::optional<Tensor> &bias)
+{
+    if (at::GradMode::is_enabled() || !plain_context() || !on_current_gpu(x_in))
+        return std::nullopt;
+    for (const Tensor *t : {&x_in, &A, &B, &W, bias ? &*bias : &x_in})
+        if (!plain(*t, x_in.device()) || t->scalar_type() != at::kBFloat16 || (t != &x_in && !t->is_contiguous()))
+            return std::nullopt;
+    if (x_in.dim() < 1 || x_in.numel() == 0 || W.dim() != 2 || W.size(1) != x_in.size(-1) || B.dim() != 2 || B.size(1) != 4 ||
+        A.dim() < 1 || A.dim() > 2 || A.size(-1) != 6 || (A.dim() == 2 && A.size(0) != B.size(0)) ||
+        (bias && (bias->dim() != 1 || bias->size(0) != W.size(0))))
+        return std::nullopt;
+    const int64_t D = W.size(1), D_out = W.size(0), G = B.size(0), rows = x_in.numel() / D;
+    if (D > INT32_MAX || D_out > INT32_MAX || G <= 0 || D % G != 0 || !grkan_product_supported(rows, (int32_t)D, (int32_t)D_out) ||
+        !aligned(W, 16) || (bias && !aligned(*bias, 8)))
+        return std::nullopt;
+    const Tensor x = x_in.contiguous();
+    auto shape = x.sizes().vec();
+    shape.back() = D_out;
+    const Tensor f = at::empty_like(x);
+    Tensor out = at::empty(shape, x.options());
+    check(grkan_fwd_model(x.data_ptr(), A.data_ptr(), B.data_ptr(), f.data_ptr(), rows, (int32_t)D, (int32_t)G, 5, 4, GRKAN_BF16, GRKAN_BF16,
+                          A.dim() == 1, stream_of(x)),
+          "grkan_fwd");
+    check(grkan_product(f.data_ptr(), W.data_ptr(), bias ? bias->data_ptr() : nullptr, out.data_ptr(), rows, (int32_t)D, (int32_t)D_out, 0, nullptr,
+                        nullptr, 1, 0, stream_of(x)),
+          "grkan_product");
+    return out;
+}
+
 // The MLP block in inference, on a bfloat16 module's own parameters: F1(x), the first product with the second layer's rational
 // function on its rounded result, the second product.  Nothing is converted, packed or kept.
 std::optional<Tensor> block_inference(const Tensor &x_in, const Tensor &A1, const Tensor &B1, const Tensor &W1, const std::optional<Tensor> &b1,
@@ -779,6 +809,12 @@ PYBIND11_MODULE(_native, mod)
         const Tensor x = args.tensor(x_), A = args.tensor(A_), B = args.tensor(B_), W = args.tensor(W_);
         const std::optional<Tensor> bias = args.optional(bias_);
         return args.call([&] { return layer_model(x, A, B, W, bias); });
+    });
+    mod.def("layer_product", [](handle x_, handle A_, handle B_, handle W_, handle bias_) {
+        Arguments args;
+        const Tensor x = args.tensor(x_), A = args.tensor(A_), B = args.tensor(B_), W = args.tensor(W_);
+        const std::optional<Tensor> bias = args.optional(bias_);
+        return args.call([&] { return layer_product(x, A, B, W, bias); });
     });
     mod.def("pack_layer", [](handle W_, handle bias_, handle A_, handle B_) {
         Arguments args;

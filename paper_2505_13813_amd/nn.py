@@ -103,10 +103,13 @@ def fused_layer_supported(x, A, weight) -> bool:
 
 
 def _fused_shapes(x, G: int, numerator_columns: int, weight) -> bool:
-    D_in = x.shape[-1]
-    return (D_in % 64 == 0 and D_in % G == 0 and (D_in // G) % 32 == 0 and weight.shape[0] % 4 == 0
-            and numerator_columns == M_DEGREE + 1 and x.is_cuda and x.dtype == torch.bfloat16
+    return (_fused_sizes(x.shape[-1], weight.shape[0], G, numerator_columns) and x.is_cuda and x.dtype == torch.bfloat16
             and weight.dtype == torch.bfloat16)
+
+
+def _fused_sizes(D_in: int, D_out: int, G: int, numerator_columns: int) -> bool:
+    return (D_in % 64 == 0 and D_in % G == 0 and (D_in // G) % 32 == 0 and D_out % 4 == 0
+            and numerator_columns == M_DEGREE + 1)
 
 
 def fused_layer_pays(rows: int, D_in: int, D_out: int) -> bool:
@@ -140,21 +143,49 @@ def _two_kernels_us(rows: int, D_in: int, D_out: int) -> float:
 
 
 @lru_cache(maxsize=1024)
-def block_products_are_faster(rows: int, D: int, hidden: int, D_out: int, one1: bool, one2: bool) -> bool:
-    """Whether an MLP block in inference runs as F1, the first product with F2 on its result, and the second product
-    (grkan_product), instead of its two layers one by one; one1, one2: whether the one-kernel layer covers them.  F1 takes
-    3.3 us and 5.5 TB/s; two layers no less than the 17 us of their host time.  (Measured on MI355X, widths 192 - 768, 49 - 50,432
-    rows, us of the layers / this: 192 at 6,304 rows 45 / 22, 384 44 / 34, 512 69 / 54, 768 85 / 73; 768 at 25,216 270 / 265, 9,456
-    of 384 48.5 / 49.2.  The layers win at few rows of a wide model, where each is one round of small tiles: 768 at 49
-    rows 17.4 / 18.8, at 197 19.4 / 22.3, 512 at 394 17.1 / 18.1.)"""
-    def layer_us(D_in, D_out, one):
-        two = _two_kernels_us(rows, D_in, D_out)
-        return min(two, binding.grkan_linear_estimate_us(rows, D_in, D_out)) if one else two
+def layer_product_is_faster(rows: int, D_in: int, D_out: int, one: bool, packed: bool) -> bool:
+    """Whether a GRKANLinear in inference runs F and grkan_product: instead of the one-kernel layer where that would be the
+    route (`one`; on packed weights it is 4 % faster than it estimates), with 4 us to be gained, and instead of F and torch's linear,
+    whose call alone takes 20 us of host time, wherever the product is supported.  F takes 3.3 us and 5.5 TB/s.  (Measured on
+    MI355X at 191 sizes.  us of the one kernel / this: 512 -> 2048 at 12,608 rows 62 / 51, at 50,432 217 / 144, 3072 -> 3072 at
+    3,152 90 / 63, 768 -> 3072 at 25,216 166 / 138; not at 3072 -> 768, 25,216 rows: 130 / 153.)"""
+    product = binding.grkan_product_estimate_us(rows, D_in, D_out)
+    if not product:
+        return False
+    this = 3.3 + rows * D_in * 4 / 5.5e6 + product
+    return not one or this + 4.0 < binding.grkan_linear_estimate_us(rows, D_in, D_out) * (0.96 if packed else 1.0)
 
+
+@lru_cache(maxsize=1024)
+def _layer_route(rows: int, D_in: int, D_out: int, G: int, numerator_columns: int, keep_packed: bool) -> str:
+    """How a GRKANLinear on the GPU runs in evaluation mode: "product", "model" (the one kernel on the parameters), "packed" (the one
+    kernel on the kept copy), or "other"."""
+    if G <= 0 or rows <= 0 or D_in <= 0 or D_in % G or numerator_columns != M_DEGREE + 1:
+        return "other"
+    one = _fused_sizes(D_in, D_out, G, numerator_columns) and one_kernel_is_faster(rows, D_in, D_out)
+    packed = keep_packed and one and fused_layer_pays(rows, D_in, D_out)
+    if layer_product_is_faster(rows, D_in, D_out, one, packed):
+        return "product"
+    return "other" if not one else "packed" if packed else "model"
+
+
+@lru_cache(maxsize=1024)
+def block_products_are_faster(rows: int, D: int, hidden: int, D_out: int, G1: int, G2: int) -> bool:
+    """Whether an MLP block in inference runs as F1, the first product with F2 on its result, and the second product
+    (grkan_product), instead of its two layers one by one.  F1 takes 3.3 us and 5.5 TB/s; two layers no less than the 17 us of their
+    host time.  (Measured on MI355X, widths 192 - 768, 49 - 50,432 rows, us of the layers / this: 192 at 6,304 rows 45 / 22, 384
+    44 / 34, 512 69 / 54, 768 85 / 73; 768 at 25,216 270 / 265, 9,456 of 384 48.5 / 49.2.  The layers win at few rows of a wide
+    model, where each is one round of small tiles: 768 at 49 rows 17.4 / 18.8, at 197 19.4 / 22.3, 512 at 394 17.1 / 18.1.)"""
+    def layer_us(D_in, D_out, G):
+        two = _two_kernels_us(rows, D_in, D_out)
+        return min(two, binding.grkan_linear_estimate_us(rows, D_in, D_out)) if _fused_sizes(D_in, D_out, G, M_DEGREE + 1) else two
+
+    if G1 <= 0 or G2 <= 0 or D % G1 or hidden % G2:
+        return False
     first, second = binding.grkan_product_estimate_us(rows, D, hidden, True), binding.grkan_product_estimate_us(rows, hidden, D_out, False)
     if not first or not second:
         return False
-    return 3.3 + rows * D * 4 / 5.5e6 + first + second <= max(17.0, layer_us(D, hidden, one1) + layer_us(hidden, D_out, one2))
+    return 3.3 + rows * D * 4 / 5.5e6 + first + second <= max(17.0, layer_us(D, hidden, G1) + layer_us(hidden, D_out, G2))
 
 
 class GRKANLayerFunction(torch.autograd.Function):
@@ -483,13 +514,25 @@ class GRKANLinear(nn.Module):
         if not x.dim() or not x.shape[-1]:
             return None
         D_in, D_out = x.shape[-1], weight.shape[0]
+        rows = x.numel() // D_in
+        if x.is_cuda and not (grad or always or self.training or torch.compiler.is_compiling()) and weight.shape[1] == D_in:
+            route = _layer_route(rows, D_in, D_out, denominator.shape[0], numerator.shape[-1], self._keep_packed)
+            if route == "packed" and weight.dtype is torch.bfloat16:
+                params = (weight, bias, numerator, denominator)
+                packed = self._inference_weights(params)
+                if packed is not None:
+                    return self._packed_layer(x, packed, params)
+            elif route != "other":
+                native = binding.load_native()
+                out = (native.layer_product if route == "product" else native.layer_model)(x, numerator, denominator, weight, bias)
+                if out is not None or route == "model":
+                    return out
         if not _fused_shapes(x, denominator.shape[0], numerator.shape[-1], weight) or D_in != weight.shape[1]:
             return None
         if grad:
             A, B = rational.coefficient_rows()
             operands = (x, A.to(torch.float32), B.to(torch.float32), weight)
             return GRKANLayerFunction.apply(*(t.contiguous() for t in operands), bias)
-        rows = x.numel() // D_in
         if not always and not one_kernel_is_faster(rows, D_in, D_out):
             return None
         compiling = torch.compiler.is_compiling()
@@ -563,17 +606,14 @@ class KATMlp(nn.Module):
         if torch.compiler.is_compiling() or _autocast_elsewhere():
             return None
         params = self._plain_parameters()
-        if params is None or self.fc1.training or self.fc2.training:
+        if params is None or self._modules["fc1"].training or self._modules["fc2"].training:
             return None
-        if any(p is None for i, p in enumerate(params) if i % 4 != 3) or params[2].dim() != 2 or params[6].dim() != 2:
+        B1, W1, B2, W2 = params[1], params[2], params[5], params[6]
+        if B1 is None or W1 is None or B2 is None or W2 is None or not x.dim():
             return None
-        dim = x.shape[-1] if x.dim() else 0
-        if not dim or not params[2].shape[0] or params[1].dim() != 2 or params[5].dim() != 2 or not params[0].dim() or not params[4].dim():
-            return None
-        (hidden, _), D_out = params[2].shape, params[6].shape[0]
-        covered = [bool(p[1].shape[0]) and _fused_shapes(t, p[1].shape[0], p[0].shape[-1], p[2])
-                   for t, p in ((x, params[:4]), (params[6], params[4:]))]
-        if not block_products_are_faster(x.numel() // dim, dim, hidden, D_out, *covered):
+        # (what these are is the native entry's to check)
+        dim, hidden, D_out = x.shape[-1], W1.shape[0], W2.shape[0]
+        if not dim or not block_products_are_faster(x.numel() // dim, dim, hidden, D_out, B1.shape[0], B2.shape[0]):
             return None
         return binding.load_native().block_inference(x, *params)
 

@@ -7,12 +7,15 @@ pytestmark = pytest.mark.gpu
 BF16 = 2.0 ** -8  # half a unit in the last place, relative
 
 # rows, K, N, G, (tile, workgroups per unit): every tile; one row, ragged rows and channels, one stage of 64 and fewer stages than
-# buffers, whole tiles, more than one round, groups of 8 channels
+# buffers, whole tiles, more than one round, a second launch for the last rows, groups of 8 channels
 SIZES = [(1, 64, 8, 1, (64, 64, 1)), (130, 192, 200, 25, (64, 64, 1)), (3000, 128, 72, 3, (64, 64, 1)),
          (1570, 128, 1544, 193, (96, 128, 1)), (1570, 2048, 768, 8, (96, 128, 1)), (4700, 320, 768, 96, (160, 128, 1)),
          (4480, 1088, 776, 97, (160, 128, 1)), (3100, 128, 1000, 125, (160, 128, 2)), (9500, 192, 1000, 5, (160, 128, 2)),
-         (9000, 256, 1544, 193, (160, 128, 2)), (25209, 960, 384, 8, (224, 192, 1)), (4100, 960, 1544, 193, (224, 192, 1)),
-         (9500, 1088, 712, 1, (224, 192, 1)), (6304, 768, 3072, 8, (320, 256, 1)), (25001, 704, 760, 5, (320, 256, 1))]
+         (30000, 64, 1544, 193, (160, 128, 2)), (4100, 960, 1544, 193, (160, 192, 1)), (9500, 192, 760, 1, (160, 192, 1)),
+         (25209, 960, 384, 8, (224, 192, 1)), (12501, 256, 1544, 193, (224, 192, 1)), (4100, 128, 3072, 8, (256, 256, 1)),
+         (12501, 256, 1000, 125, (256, 256, 1)), (6304, 768, 3072, 8, (320, 256, 1)), (25001, 704, 760, 5, (320, 256, 1)),
+         (7001, 320, 3072, 8, (320, 256, 1, 6720)), (30000, 768, 760, 95, (320, 256, 1, 27200)),
+         (30000, 1088, 384, 8, (224, 192, 1, 28672))]
 
 
 def _operands(torch, rows, K, N, G):
@@ -53,7 +56,7 @@ def test_product(rows, K, N, G, tile):
 
     from paper_2505_13813_amd import binding
 
-    assert binding.grkan_product_tile(rows, K, N) == tile
+    assert binding.grkan_product_tile(rows, K, N) == tile + ((rows,) if len(tile) == 3 else ())
     d = _operands(torch, rows, K, N, G)
     x, W, bias = d["x"], d["W"], d["bias"]
     want = x.double() @ W.double().t() + bias.double()
@@ -68,7 +71,7 @@ def test_product(rows, K, N, G, tile):
     assert ((bare.double() - (want - bias.double())).abs() <= bound).all()
 
     # (the tile may be another one with F, and its sums in another order: compared where it is the same)
-    with_f = binding.grkan_product_tile(rows, K, N, True) == tile
+    with_f = binding.grkan_product_tile(rows, K, N, True) == binding.grkan_product_tile(rows, K, N)
     for A in (d["A"], d["A"][0].contiguous()):
         f = _product(torch, x, W, bias, A=A, B=d["B"])
         assert torch.isfinite(f.float()).all()
@@ -160,3 +163,38 @@ def test_block_inference_is_left_to_the_layers(monkeypatch):
             assert block._native_inference(x) is None
         assert block._native_inference(x[:0]) is None
     assert block._native_inference(x) is None
+
+
+@pytest.mark.parametrize("K,N,G,rows,bias,shared", [(192, 768, 8, 300, True, True), (512, 2048, 8, 9001, False, True), (320, 72, 8, 77, True, False)])
+def test_layer_inference_through_the_product(K, N, G, rows, bias, shared, monkeypatch):
+    """At sizes of this route: bit for bit the rational function and the product, which the layer's two modules agree with."""
+    import torch
+
+    from paper_2505_13813_amd import binding
+    from paper_2505_13813_amd import nn as gnn
+
+    assert gnn._layer_route(rows, K, N, G, 6, True) == "product"
+    torch.manual_seed(K)
+    layer = gnn.GRKANLinear(K, N, G, init="swish", bias=bias, shared_numerator=shared).to("cuda:0").to(torch.bfloat16).eval()
+    x = torch.randn(rows, K, device="cuda:0").to(torch.bfloat16)
+    with torch.no_grad():
+        for p in layer.parameters():
+            p.add_(torch.randn_like(p) * 0.01)
+        out = layer(x)
+        f = layer.rational(x)
+        assert torch.equal(out, _product(torch, f, layer.linear.weight, layer.linear.bias))
+        want = layer.linear(f)
+        assert (out.double() - want.double()).norm() <= 2 * BF16 * want.double().norm()
+        assert torch.equal(layer(x.view(1, rows, K)[0]), out) and layer(x.view(1, rows, K)).shape == (1, rows, N)
+        hook = layer.linear.register_forward_hook(lambda m, i, o: o + 1)
+        assert torch.equal(layer(x), want + 1)
+        hook.remove()
+    graph, z = torch.cuda.CUDAGraph(), x.clone()
+    with torch.no_grad(), torch.cuda.graph(graph):
+        captured = layer(z)
+    for _ in range(3):
+        with torch.no_grad():
+            z.copy_(torch.randn_like(x))
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(captured, layer(z))

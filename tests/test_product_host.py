@@ -26,20 +26,32 @@ def test_product_rejects_on_the_host():
     with pytest.raises(binding.GrkanError):
         binding.grkan_product_tile(0, 64, 64)
     one = ctypes.c_int32()
-    assert lib.grkan_product_tile(4, 64, 64, 0, ctypes.byref(one), None, ctypes.byref(one)) == 1
+    assert lib.grkan_product_tile(4, 64, 64, 0, ctypes.byref(one), None, ctypes.byref(one), ctypes.byref(ctypes.c_int64())) == 1
 
 
 def test_tiles_grow_with_the_call():
     tile = binding.grkan_product_tile
-    assert tile(197, 1536, 384) == (64, 64, 1)
-    assert tile(3152, 3072, 768) == (96, 128, 1)
-    assert tile(6304, 3072, 768) == (160, 128, 1)
-    assert tile(25216, 1536, 384) == (224, 192, 1)
-    assert tile(6304, 768, 3072) == tile(25216, 3072, 768) == (320, 256, 1)
+    assert tile(197, 1536, 384) == (64, 64, 1, 197)
+    assert tile(3152, 3072, 768) == (96, 128, 1, 3152)
+    assert tile(6304, 3072, 768) == (160, 128, 1, 6304)
+    assert tile(25216, 1536, 384) == (224, 192, 1, 25216)
+    assert tile(6304, 768, 3072) == (320, 256, 1, 6304) and tile(25216, 3072, 768) == (320, 256, 1, 25216)
+    assert tile(12593, 2048, 2048) == (320, 256, 1, 10240)  # one whole round of 32 x 8 tiles, and the rest in another
 
 
 def test_rule_of_the_blocks_inference_route():
     faster = gnn.block_products_are_faster
-    assert faster(6304, 768, 3072, 768, True, True) and faster(197, 192, 768, 192, False, True)
-    assert not faster(49, 768, 3072, 768, True, True) and not faster(197, 768, 3072, 768, True, True)
-    assert not faster(400, 96, 384, 96, False, False)  # K = 96 is no multiple of 64
+    assert faster(6304, 768, 3072, 768, 8, 8) and faster(197, 192, 768, 192, 8, 8)
+    assert not faster(49, 768, 3072, 768, 8, 8) and not faster(197, 768, 3072, 768, 8, 8)
+    assert not faster(400, 96, 384, 96, 8, 8)  # K = 96 is no multiple of 64
+    assert not faster(400, 192, 768, 192, 0, 8) and not faster(400, 192, 768, 192, 5, 8) and not faster(0, 192, 768, 192, 8, 8)
+
+
+def test_rule_of_a_layers_inference_route():
+    route = gnn._layer_route
+    assert route(50432, 512, 2048, 8, 6, True) == route(3152, 3072, 3072, 8, 6, True) == "product"
+    assert route(197, 3072, 768, 8, 6, True) == route(6304, 1536, 384, 8, 6, True) == "model"
+    assert route(25216, 3072, 768, 8, 6, True) == "packed" and route(25216, 3072, 768, 8, 6, False) == "model"
+    assert route(300, 192, 768, 8, 6, True) == "product"       # groups of 24: not the one kernel's
+    assert route(300, 768, 192, 8, 4, True) == "other"         # other degrees
+    assert route(300, 100, 192, 4, 6, True) == "other" and route(0, 768, 192, 8, 6, True) == "other"
