@@ -374,7 +374,8 @@ grkan_status_t grkan_hidden_bwd(const void *dout, const void *W, const void *h, 
  * on the tile, which depends on the sizes.
  * grkan_product_supported: K a multiple of 64 and N one of 8 (each at most 2^20), at most 2^30 rows; F: N / G a multiple of 8.
  * Anything else is GRKAN_ERR_UNSUPPORTED.
- * grkan_product_estimate_us, grkan_product_tile: host-only; the estimated device time (0 for sizes that are not supported),
+ * grkan_product_estimate_us, grkan_product_tile (rational: 0, 1 with F, the tile also 2: with F's backward pass, as
+ * grkan_block_bwd runs it): host-only; the estimated device time (0 for sizes that are not supported),
  * and the tile that is used, with the workgroups per compute unit and how many rows run in it (fewer than all where a
  * second launch takes the rest in another tile).
  */
@@ -388,12 +389,12 @@ grkan_status_t grkan_product(const void *x, const void *W, const void *bias, voi
 
 /*
  * The whole backward pass of a bfloat16 KAT MLP block, out = F2(h) W2^T + b2 with h = F1(x) W1^T + b1: the parts above in five
- * launches (grkan_hidden_bwd or a product and the rational function, grkan_product, the rational function,
- * grkan_linear_wgrad_pair, one for all second stages).  rows >= 1; D, hidden and G2 as grkan_hidden_supported(D, hidden, G2);
+ * launches or four (grkan_hidden_bwd or a product and the rational function, a product and the rational function or both in
+ * one, grkan_linear_wgrad_pair, one for all second stages).  rows >= 1; D, hidden and G2 as grkan_hidden_supported(D, hidden, G2);
  * G1 divides D.
- *   x, f1 = F1(x), dout, dx, df1 [rows, D]; h, f2 = F2(h), dh [rows, hidden]; W1, dW1 [hidden, D]; W2, dW2 [D, hidden]; db1
+ *   x, f1 = F1(x), dout, dx [rows, D]; h, f2 = F2(h), dh [rows, hidden]; W1, dW1 [hidden, D]; W2, dW2 [D, hidden]; db1
  *   [hidden], db2 [D], each or NULL; A1, B1, A2, B2 and their gradients as for grkan_bwd_model (shared1, shared2: one numerator row
- *   for all groups).  All DEVICE, bfloat16, contiguous; tensors 16-byte aligned.  dh and df1 are scratch.
+ *   for all groups).  All DEVICE, bfloat16, contiguous; tensors 16-byte aligned.  dh is scratch.
  * `alloc` is asked more than once during the call, each time as grkan_bwd_model asks it.
  */
 typedef struct {
@@ -402,7 +403,7 @@ typedef struct {
     const void *x, *f1, *h, *f2, *dout;
     const void *A1, *B1, *W1, *A2, *B2, *W2;
     void *dx, *dA1, *dB1, *dW1, *db1, *dA2, *dB2, *dW2, *db2;
-    void *dh, *df1;
+    void *dh;
 } grkan_block_bwd_t;
 grkan_status_t grkan_block_bwd(const grkan_block_bwd_t *block, grkan_alloc_t alloc, void *alloc_context, void *hip_stream);
 

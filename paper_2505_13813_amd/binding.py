@@ -394,11 +394,11 @@ def grkan_product_estimate_us(rows: int, K: int, N: int, rational: bool = False)
     return float(load_library().grkan_product_estimate_us(int(rows), int(K), int(N), int(bool(rational))))
 
 
-def grkan_product_tile(rows: int, K: int, N: int, rational: bool = False) -> Tuple[int, int, int, int]:
+def grkan_product_tile(rows: int, K: int, N: int, rational: int = 0) -> Tuple[int, int, int, int]:
     """Rows and channels of the tile grkan_product runs these sizes in, workgroups per compute unit, and how many of the rows
     run in it (a second launch takes the rest)."""
     out = [ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int64()]
-    st = load_library().grkan_product_tile(int(rows), int(K), int(N), int(bool(rational)), *(ctypes.byref(v) for v in out))
+    st = load_library().grkan_product_tile(int(rows), int(K), int(N), int(rational), *(ctypes.byref(v) for v in out))
     if st:
         raise GrkanError(st, "grkan_product_tile")
     return tuple(v.value for v in out)

@@ -37,12 +37,17 @@ grkan_status_t run_stage2(const float *partial, int32_t rows_per_group, const Co
 struct CoefSums;
 
 // Parts of an MLP block's backward pass, all on bfloat16 tensors and parameters (arguments as grkan_bwd_model, grkan_hidden_bwd
-// and grkan_linear_wgrad_pair have them, checked there); the first two leave their second stage to the last.
+// and grkan_linear_wgrad_pair have them, checked there); all but the last leave their second stage to it.  product_backward: the
+// rational function's backward pass at x with dh W (W [K, N]) as the upstream gradient.
 grkan_status_t bwd_model_stage1(const void *x, const void *dy, const CoefRows &coef, void *dx, void *dA, void *dB, grkan_alloc_t alloc,
                                 void *alloc_context, int64_t rows, int32_t D, int32_t G, CoefSums *later, struct ihipStream_t *stream);
 grkan_status_t hidden_bwd_stage1(const void *dout, const void *W, const void *h, const CoefRows &coef, void *dh, void *dA, void *dB,
                                  grkan_alloc_t alloc, void *alloc_context, int64_t rows, int32_t K, int32_t N, int32_t G, CoefSums *later,
                                  struct ihipStream_t *stream);
+bool product_backward_pays(int64_t rows, int32_t K, int32_t N, int32_t G);
+grkan_status_t product_backward(const void *dh, const void *W, const void *x, const CoefRows &coef, void *dx, void *dA, void *dB,
+                                grkan_alloc_t alloc, void *alloc_context, int64_t rows, int32_t K, int32_t N, int32_t G, CoefSums *later,
+                                struct ihipStream_t *stream);
 grkan_status_t wgrad_pair_and_sums(const grkan_block_bwd_t &b, grkan_alloc_t alloc, void *alloc_context, const CoefSums (&sums)[2],
                                    struct ihipStream_t *stream);
 

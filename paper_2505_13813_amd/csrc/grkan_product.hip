@@ -2,6 +2,7 @@
 //
 //     out = x W^T + bias          (W [N, K], forward)           optionally out = F(x W^T + bias), F the group-wise rational
 //     out = x W                   (W [K, N], backward)          function of the next layer on the rounded result
+//                                                               dx, and F's coefficient sums, with x W as F's upstream gradient
 //
 // A workgroup owns a tile of rows x channels and walks K in stages of 64: whole 128-byte lines of both operands come to LDS by
 // LDS-direct loads, NBUF stages deep.  16-byte pieces of a row are permuted (xor with the row number), so that operand reads
@@ -35,19 +36,25 @@ namespace product {
 
 using namespace tile;
 
-constexpr int kM = 5, kN = 4;
+constexpr int kM = 5, kN = 4, kSums = kM + 1 + kN;
 
 struct Args {
     const char *x;    // bfloat16 [M, K]
     const char *W;    // bfloat16 [N, K]; TRANSPOSED: [K, N]
     const char *bias; // bfloat16 [N] or NULL
     char *out;        // bfloat16 [M, N]
-    CoefRows coef;    // RATIONAL: of F
+    CoefRows coef;    // of F
+    const char *fx;   // kBackward: F's input, bfloat16 [M, N]; out is the gradient for it
+    float *partial;   // kBackward: [groups][partial_rows][kSums]
     int64_t M;
     int32_t N, K;
-    int32_t dg;       // RATIONAL: channels per group
+    int32_t dg;       // F's channels per group
     int32_t tiles_n, tiles, per_xcd;
+    int32_t partial_rows, tile0; // kBackward: rows per group, and row tiles of launches before this one
 };
+
+// What becomes of the product: nothing; F on it; F's backward pass with it.
+enum Then { kPlain, kRational, kBackward };
 
 // A wavefront's share is TM x TN tiles of 16 x 16, a workgroup WM x WN such wavefronts and LD that load; PER workgroups per
 // compute unit.
@@ -68,7 +75,7 @@ template <int TM_, int TN_, int WM_, int WN_, int NBUF_, int LD_, int PER_ = 1> 
     static_assert(2 * (TM - 1) >= TN && PER * kLds <= 160 * 1024 && TM >= 2 && (kWaves + LD) % 4 == 0, "");
 };
 
-template <class SH, bool TRANSPOSED, bool RATIONAL>
+template <class SH, bool TRANSPOSED, Then THEN>
 __global__ __launch_bounds__(SH::kThreads, SH::PER *SH::kThreads / 256) void product_kernel(const Args a)
 {
     constexpr int TM = SH::TM, TN = SH::TN, NBUF = SH::NBUF, BM = SH::BM, BN = SH::BN;
@@ -265,12 +272,24 @@ __global__ __launch_bounds__(SH::kThreads, SH::PER *SH::kThreads / 256) void pro
     const int32_t c = col0 + (tid % LR) * 8;
     const bool in = tid < RP * LR && c < a.N;
     Coef<kM, kN> co;
-    if constexpr (RATIONAL)
+    if constexpr (THEN != kPlain)
         if (in)
             co = load_coef<kM, kN, false, true>(a.coef, c / a.dg);
     const int64_t left = a.M - row0;
     const int rows = left < BM ? (int)left : BM;
-    char *const to = a.out + ((size_t)row0 * (size_t)a.N + (size_t)c) * 2u;
+    const size_t at_c = ((size_t)row0 * (size_t)a.N + (size_t)c) * 2u;
+    char *const to = a.out + at_c;
+    // kBackward: F's input, on its way while the product goes through LDS
+    constexpr int kPass = THEN == kBackward ? (BM + RP - 1) / RP : 1;
+    u32x4 fx[kPass];
+    if constexpr (THEN == kBackward) {
+        static_assert(SH::kParts == 1, "rows of the tile are rows of the result in LDS");
+#pragma unroll
+        for (int j = 0; j < kPass; ++j) {
+            const int r = tid / LR + j * RP;
+            fx[j] = in && r < rows ? *(const u32x4 *)(a.fx + at_c + (size_t)r * ldn) : u32x4{0u, 0u, 0u, 0u};
+        }
+    }
     static_for<0, SH::kParts>([&](auto pc) {
         constexpr int m0 = decltype(pc)::value * MP, m1 = m0 + MP < TM ? m0 + MP : TM; // rows of tiles in this part
         if (m0 > 0)
@@ -288,19 +307,58 @@ __global__ __launch_bounds__(SH::kThreads, SH::PER *SH::kThreads / 256) void pro
             }
         }
         __syncthreads();
-        if (in) {
+        if (THEN != kBackward && in) {
 #pragma unroll 2
             for (int l = tid / LR; l < SH::WM * MP * 16; l += RP) {
                 const int m = m0 + l / 16 % MP, r = (l / (MP * 16) * TM + m) * 16 + l % 16;
                 if (m >= m1 || r >= rows)
                     continue;
                 u32x4 v = lds_read16(lds0 + (uint32_t)l * SH::kPitch + (uint32_t)(tid % LR) * 16u);
-                if constexpr (RATIONAL)
+                if constexpr (THEN == kRational)
                     v = rational8(v, co);
                 *(u32x4 *)(to + (size_t)r * ldn) = v;
             }
         }
     });
+    if constexpr (THEN == kBackward) {
+        // dx of the lane's eight channels, row by row, and the sums over them; a workspace row for every eight channels of the tile
+        float sums[kSums];
+#pragma unroll
+        for (int k = 0; k < kSums; ++k)
+            sums[k] = 0.0f;
+#pragma unroll
+        for (int j = 0; j < kPass; ++j) {
+            const int r = tid / LR + j * RP;
+            if (in && r < rows) {
+                const u32x4 v = lds_read16(lds0 + (uint32_t)r * SH::kPitch + (uint32_t)(tid % LR) * 16u);
+                float dx[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const uint32_t word = fx[j][e / 2], d = v[e / 2];
+                    dx[e] = bwd_elem<false, kM, kN>(e % 2 == 0 ? low(word) : high(word), e % 2 == 0 ? low(d) : high(d), co, sums);
+                }
+                *(u32x4 *)(to + (size_t)r * ldn) = u32x4{pack(dx[0], dx[1]), pack(dx[2], dx[3]), pack(dx[4], dx[5]), pack(dx[6], dx[7])};
+            }
+        }
+        negate_b_sums<kM, kN>(sums);
+        static_assert((size_t)kSums * SH::kThreads * 4 <= SH::kLds, "");
+        __syncthreads(); // the product has been read
+#pragma unroll
+        for (int k = 0; k < kSums; ++k)
+            *(__attribute__((address_space(3))) float *)(uintptr_t)(lds0 + (uint32_t)(k * SH::kThreads + tid) * 4u) = sums[k];
+        __syncthreads();
+        for (int t = tid; t < LR * kSums; t += SH::kThreads) {
+            const int k = t / LR, o = t % LR, oc = col0 + o * 8;
+            if (oc < a.N) {
+                float v = 0.0f;
+                for (int i = 0; i < RP; ++i)
+                    v += *(const __attribute__((address_space(3))) float *)(uintptr_t)(lds0 + (uint32_t)(k * SH::kThreads + i * LR + o) * 4u);
+                const int32_t g = oc / a.dg;
+                const int64_t row = (int64_t)g * a.partial_rows + (int64_t)(a.tile0 + tm) * (a.dg / 8) + (oc - g * a.dg) / 8;
+                a.partial[row * kSums + k] = v;
+            }
+        }
+    }
 }
 
 // --------------------------------------------------------------------------
@@ -313,14 +371,23 @@ using Kernel = void (*)(const Args);
 struct Variant {
     int32_t BM, BN, threads, per_cu;
     size_t lds;
-    Kernel kernel[3]; // W [N, K]; with F; W [K, N]
+    Kernel kernel[4]; // W [N, K]; with F; W [K, N]; with F's backward pass or NULL
     double once, round, stage, fill, round2, stage2;
 };
+
+template <class SH> static constexpr Kernel backward_kernel()
+{
+    if constexpr (SH::kParts == 1)
+        return product_kernel<SH, true, kBackward>;
+    else
+        return nullptr; // a tile that leaves in parts
+}
 
 template <class SH> static constexpr Variant variant(double once, double round, double stage, double fill, double round2 = 0, double stage2 = 0)
 {
     return Variant{SH::BM, SH::BN, SH::kThreads, SH::PER, SH::kLds,
-                   {product_kernel<SH, false, false>, product_kernel<SH, false, true>, product_kernel<SH, true, false>},
+                   {product_kernel<SH, false, kPlain>, product_kernel<SH, false, kRational>, product_kernel<SH, true, kPlain>,
+                    backward_kernel<SH>()},
                    once, round, stage, fill, round2, stage2};
 }
 
@@ -343,20 +410,23 @@ static const Variant kVariants[] = {
 
 static int64_t tiles_of(const Variant &v, int64_t rows, int32_t N) { return (rows + v.BM - 1) / v.BM * ((N + v.BN - 1) / v.BN); }
 
-static double estimate_us(const Variant &v, int64_t rows, int32_t K, int32_t N, bool rational)
+static double estimate_us(const Variant &v, int64_t rows, int32_t K, int32_t N, Then then)
 {
-    const double T = K / 64, f = rational ? 6.0 * v.BM * v.BN / 81920 : 0.0; // F of a tile: 6 us at 320 x 256
+    // F of a tile: 6 us at 320 x 256, its backward pass 17.5
+    const double T = K / 64, f = (then == kRational ? 6.0 : then == kBackward ? 17.5 : 0.0) * v.BM * v.BN / 81920;
     const int64_t tiles = tiles_of(v, rows, N), per_xcd = (tiles + 7) / 8, rounds = (per_xcd + 31) / 32;
     if (v.per_cu == 2)
         return v.once + (double)(rounds % 2) * (v.round + v.stage * T + f) + (double)(rounds / 2) * (v.round2 + v.stage2 * T + f);
     return v.once + (double)rounds * (v.round + T * (v.stage + v.fill * ((double)tiles / ((double)rounds * 256))) + f);
 }
 
-static const Variant *best_tile(int64_t rows, int32_t K, int32_t N, bool rational, double *us)
+static const Variant *best_tile(int64_t rows, int32_t K, int32_t N, Then then, double *us)
 {
     const Variant *best = nullptr;
     for (const Variant &v : kVariants) {
-        const double t = estimate_us(v, rows, K, N, rational);
+        if (then == kBackward && !v.kernel[3])
+            continue;
+        const double t = estimate_us(v, rows, K, N, then);
         if (!best || t < *us) {
             best = &v;
             *us = t;
@@ -374,19 +444,21 @@ struct Plan {
     double us;
 };
 
-static Plan make_plan(int64_t rows, int32_t K, int32_t N, bool rational)
+static Plan make_plan(int64_t rows, int32_t K, int32_t N, Then then)
 {
     Plan best{nullptr, nullptr, rows, 0};
-    best.first = best_tile(rows, K, N, rational, &best.us);
+    best.first = best_tile(rows, K, N, then, &best.us);
     for (const Variant &v : kVariants) {
+        if (then == kBackward && !v.kernel[3])
+            continue;
         const int64_t tiles_n = (N + v.BN - 1) / v.BN, blocks = (rows + v.BM - 1) / v.BM, at_once = 256 * (int64_t)v.per_cu;
         const int64_t rounds = blocks * tiles_n / at_once; // whole ones
         const int64_t take = rounds * at_once / tiles_n;   // row blocks in them
         if (rounds == 0 || take == 0 || take >= blocks)
             continue;
         Plan p{&v, nullptr, take * v.BM, 0};
-        p.second = best_tile(rows - p.first_rows, K, N, rational, &p.us);
-        p.us += estimate_us(v, p.first_rows, K, N, rational) + 1.0;
+        p.second = best_tile(rows - p.first_rows, K, N, then, &p.us);
+        p.us += estimate_us(v, p.first_rows, K, N, then) + 1.0;
         if (p.us < best.us)
             best = p;
     }
@@ -403,7 +475,7 @@ static bool supported(int64_t rows, int32_t K, int32_t N)
 static bool allow_lds(const Variant &v, int which)
 {
     static std::mutex mu;
-    static bool done[64][sizeof(kVariants) / sizeof(kVariants[0])][3];
+    static bool done[64][sizeof(kVariants) / sizeof(kVariants[0])][4];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64)
         return false;
@@ -415,7 +487,82 @@ static bool allow_lds(const Variant &v, int which)
     return is;
 }
 
+static int32_t row_tiles(const Plan &plan, int64_t rows)
+{
+    const int64_t one = (plan.first_rows + plan.first->BM - 1) / plan.first->BM;
+    return (int32_t)(plan.second ? one + (rows - plan.first_rows + plan.second->BM - 1) / plan.second->BM : one);
+}
+
+static grkan_status_t launch(const Plan &plan, Args a, int64_t rows, bool transposed, Then then, hipStream_t stream)
+{
+    const int which = then == kBackward ? 3 : transposed ? 2 : then == kRational ? 1 : 0;
+    const Args all = a;
+    for (int part = 0; part < (plan.second ? 2 : 1); ++part) {
+        const Variant &v = part ? *plan.second : *plan.first;
+        const size_t row0 = part ? (size_t)plan.first_rows : 0;
+        a.x = all.x + row0 * (size_t)a.K * 2u;
+        a.out = all.out + row0 * (size_t)a.N * 2u;
+        a.fx = all.fx ? all.fx + row0 * (size_t)a.N * 2u : nullptr;
+        a.tile0 = part ? (int32_t)((plan.first_rows + plan.first->BM - 1) / plan.first->BM) : 0;
+        a.M = part ? rows - plan.first_rows : plan.first_rows;
+        a.tiles_n = (a.N + v.BN - 1) / v.BN;
+        a.tiles = (int32_t)tiles_of(v, a.M, a.N);
+        a.per_xcd = (a.tiles + 7) / 8;
+        if (!allow_lds(v, which))
+            return GRKAN_ERR_LAUNCH;
+        void *args[] = {&a};
+        if (hipLaunchKernel(reinterpret_cast<const void *>(v.kernel[which]), dim3((unsigned)a.per_xcd * 8u), dim3((unsigned)v.threads), args,
+                            v.lds, stream) != hipSuccess)
+            return GRKAN_ERR_LAUNCH;
+    }
+    return GRKAN_OK;
+}
+
 } // namespace product
+
+// Whether the backward pass of F runs in the product that makes its upstream gradient: that is then not written and read again,
+// and a launch less, but the multiplying wavefronts wait for it.  Whole training blocks, us with F in a launch of its own / here, by
+// elements of dx (rows x N):
+//   0.6 - 3 M  192 138 / 136, 384 140 / 134, 512 162.5 / 158, 768 179 / 175     4.8 M  192 147 / 143.5, 384 175.5 / 171.5, 768 269 / 264
+//   8 - 10 M   192 239 / 236, 384 290.5 / 290.5, 640 350 / 345, 768 446 / 439.5  13 - 19 M  384 546 / 551, 512 443 / 462, 640 656 / 647, 768 841 / 859
+bool product_backward_pays(int64_t rows, int32_t K, int32_t N, int32_t G)
+{
+    return product::supported(rows, K, N) && G > 0 && N % G == 0 && N / G % 8 == 0 && rows * N <= 10000000;
+}
+
+grkan_status_t product_backward(const void *dh, const void *W, const void *x, const CoefRows &coef, void *dx, void *dA, void *dB,
+                                grkan_alloc_t alloc, void *alloc_context, int64_t rows, int32_t K, int32_t N, int32_t G, CoefSums *later,
+                                hipStream_t stream)
+{
+    if (!product::supported(rows, K, N) || rows == 0 || G <= 0 || N % G != 0 || N / G % 8 != 0)
+        return GRKAN_ERR_UNSUPPORTED;
+    if (!dh || !W || !x || !dx || !coef.A || !coef.B || !dA || !dB)
+        return GRKAN_ERR_NULL;
+    auto address = [](const void *p) { return reinterpret_cast<uintptr_t>(p); };
+    if ((address(dh) | address(W) | address(x) | address(dx)) % 16 != 0 ||
+        (address(coef.A) | address(coef.B) | address(dA) | address(dB)) % 2 != 0)
+        return GRKAN_ERR_ALIGN;
+    const product::Plan plan = product::make_plan(rows, K, N, product::kBackward);
+    product::Args a = {};
+    a.x = static_cast<const char *>(dh);
+    a.W = static_cast<const char *>(W);
+    a.out = static_cast<char *>(dx);
+    a.coef = coef;
+    a.fx = static_cast<const char *>(x);
+    a.N = N;
+    a.K = K;
+    a.dg = N / G;
+    const int64_t per_group = (int64_t)product::row_tiles(plan, rows) * (a.dg / 8);
+    if (per_group > INT32_MAX)
+        return GRKAN_ERR_UNSUPPORTED;
+    a.partial_rows = (int32_t)per_group;
+    a.partial = static_cast<float *>(alloc((size_t)G * (size_t)per_group * product::kSums * sizeof(float), alloc_context));
+    if (!a.partial)
+        return GRKAN_ERR_WORKSPACE;
+    *later = CoefSums{a.partial, a.partial_rows, coef, dA, dB, G};
+    return product::launch(plan, a, rows, true, product::kBackward, stream);
+}
+
 } // namespace grkan
 
 using namespace grkan;
@@ -426,7 +573,7 @@ extern "C" double grkan_product_estimate_us(int64_t rows, int32_t K, int32_t N, 
 {
     if (rows <= 0 || !product::supported(rows, K, N))
         return 0;
-    return product::make_plan(rows, K, N, rational != 0).us;
+    return product::make_plan(rows, K, N, rational ? product::kRational : product::kPlain).us;
 }
 
 extern "C" grkan_status_t grkan_product_tile(int64_t rows, int32_t K, int32_t N, int32_t rational, int32_t *tile_rows, int32_t *tile_channels,
@@ -436,7 +583,8 @@ extern "C" grkan_status_t grkan_product_tile(int64_t rows, int32_t K, int32_t N,
         return GRKAN_ERR_NULL;
     if (rows <= 0 || !product::supported(rows, K, N))
         return GRKAN_ERR_UNSUPPORTED;
-    const product::Plan plan = product::make_plan(rows, K, N, rational != 0);
+    const product::Plan plan =
+        product::make_plan(rows, K, N, rational == 2 ? product::kBackward : rational ? product::kRational : product::kPlain);
     *tile_rows = plan.first->BM;
     *tile_channels = plan.first->BN;
     *per_unit = plan.first->per_cu;
@@ -462,30 +610,15 @@ extern "C" grkan_status_t grkan_product(const void *x, const void *W, const void
         return GRKAN_ERR_ALIGN;
     if (rows == 0)
         return GRKAN_OK;
-    const product::Plan plan = product::make_plan(rows, K, N, rational);
-    const int which = transposed ? 2 : rational ? 1 : 0;
-    for (int part = 0; part < (plan.second ? 2 : 1); ++part) {
-        const product::Variant &v = part ? *plan.second : *plan.first;
-        const int64_t row0 = part ? plan.first_rows : 0;
-        product::Args a;
-        a.x = static_cast<const char *>(x) + (size_t)row0 * (size_t)K * 2u;
-        a.W = static_cast<const char *>(W);
-        a.bias = static_cast<const char *>(bias);
-        a.out = static_cast<char *>(out) + (size_t)row0 * (size_t)N * 2u;
-        a.coef = CoefRows{A, B, shared_numerator ? 0 : product::kM + 1, 1};
-        a.M = part ? rows - row0 : plan.first_rows;
-        a.N = N;
-        a.K = K;
-        a.dg = rational ? N / G : N;
-        a.tiles_n = (N + v.BN - 1) / v.BN;
-        a.tiles = (int32_t)product::tiles_of(v, a.M, N);
-        a.per_xcd = (a.tiles + 7) / 8;
-        if (!product::allow_lds(v, which))
-            return GRKAN_ERR_LAUNCH;
-        void *args[] = {&a};
-        if (hipLaunchKernel(reinterpret_cast<const void *>(v.kernel[which]), dim3((unsigned)a.per_xcd * 8u), dim3((unsigned)v.threads), args,
-                            v.lds, static_cast<hipStream_t>(hip_stream)) != hipSuccess)
-            return GRKAN_ERR_LAUNCH;
-    }
-    return GRKAN_OK;
+    const product::Then then = rational ? product::kRational : product::kPlain;
+    product::Args a = {};
+    a.x = static_cast<const char *>(x);
+    a.W = static_cast<const char *>(W);
+    a.bias = static_cast<const char *>(bias);
+    a.out = static_cast<char *>(out);
+    a.coef = CoefRows{A, B, shared_numerator ? 0 : product::kM + 1, 1};
+    a.N = N;
+    a.K = K;
+    a.dg = rational ? N / G : N;
+    return product::launch(product::make_plan(rows, K, N, then), a, rows, transposed != 0, then, static_cast<hipStream_t>(hip_stream));
 }

@@ -419,7 +419,7 @@ struct Block : public torch::autograd::Function<Block> {
             f1 = as_saved(saved[7], x, x.sizes());
             h = as_saved(saved[8], x, {rows, hidden});
             Scratches scratch{x.options().dtype(at::kByte), {}, nullptr};
-            const Tensor dh = at::empty_like(h), df1 = at::empty({rows, D}, x.options());
+            const Tensor dh = at::empty_like(h);
             out[0] = at::empty_like(x);
             out[1] = at::empty_like(A1);
             out[2] = at::empty_like(B1);
@@ -435,7 +435,7 @@ struct Block : public torch::autograd::Function<Block> {
                                       x.data_ptr(), f1.data_ptr(), h.data_ptr(), f2.data_ptr(), dout.data_ptr(), A1.data_ptr(), B1.data_ptr(),
                                       W.data_ptr(), A2.data_ptr(), B2.data_ptr(), W2.data_ptr(), out[0].data_ptr(), out[1].data_ptr(),
                                       out[2].data_ptr(), out[3].data_ptr(), want_b1 ? out[7].data_ptr() : nullptr, out[4].data_ptr(),
-                                      out[5].data_ptr(), out[6].data_ptr(), want_b2 ? out[8].data_ptr() : nullptr, dh.data_ptr(), df1.data_ptr()};
+                                      out[5].data_ptr(), out[6].data_ptr(), want_b2 ? out[8].data_ptr() : nullptr, dh.data_ptr()};
             const grkan_status_t st = grkan_block_bwd(&b, &Scratches::alloc, &scratch, stream_of(x));
             if (scratch.error)
                 std::rethrow_exception(scratch.error);
