@@ -3,9 +3,10 @@ kernels, the group-wise rational module with the paper's model-level
 conventions, the GR-KAN linear layer and the KAT MLP block.
 
 The rational function runs in this package's kernels; the matrix products are
-torch's (library GEMMs), except where the one-kernel layer grkan_linear_fwd is
-selected (GRKANLinear(fused=...)) and for the weight and bias gradients of
-bfloat16 training (grkan_linear_wgrad).  Plain calls run as native autograd
+torch's (library GEMMs), except in bfloat16 on the GPU: the one-kernel layer
+grkan_linear_fwd (GRKANLinear(fused=...)), the products of layers in inference
+and of MLP blocks (grkan_product), and the weight and bias gradients of
+training (grkan_linear_wgrad).  Plain calls run as native autograd
 functions; what those do not take runs in the Python ones here.  Conventions taken from the FlashKAT paper:
   * GR-KAN(x) = W F(x): the rational function is applied to the INPUT of each
     linear layer (Eq. "GR_KAN").
@@ -172,10 +173,11 @@ def _layer_route(rows: int, D_in: int, D_out: int, G: int, numerator_columns: in
 @lru_cache(maxsize=1024)
 def block_products_are_faster(rows: int, D: int, hidden: int, D_out: int, G1: int, G2: int) -> bool:
     """Whether an MLP block in inference runs as F1, the first product with F2 on its result, and the second product
-    (grkan_product), instead of its two layers one by one.  F1 takes 3.3 us and 5.5 TB/s; two layers no less than the 17 us of their
-    host time.  (Measured on MI355X, widths 192 - 768, 49 - 50,432 rows, us of the layers / this: 192 at 6,304 rows 45 / 22, 384
-    44 / 34, 512 69 / 54, 768 85 / 73; 768 at 25,216 270 / 265, 9,456 of 384 48.5 / 49.2.  The layers win at few rows of a wide
-    model, where each is one round of small tiles: 768 at 49 rows 17.4 / 18.8, at 197 19.4 / 22.3, 512 at 394 17.1 / 18.1.)"""
+    (grkan_product), instead of its two layers.  F1 takes 3.3 us and 5.5 TB/s; three launches take no less than 15 us of host time,
+    the layers' two 13.  (Measured on MI355X, widths 192 - 768, 49 - 50,432 rows, us of the layers / this: 192 at 6,304 rows 45 / 22,
+    384 44 / 34, 512 69 / 54, 768 85 / 73; 768 at 25,216 270 / 265, 9,456 of 384 48.5 / 49.2.  The layers win at few rows of a wide
+    model, where each is one round of small tiles: 768 at 49 rows 15.8 / 18.8, at 197 18.7 / 22.3, 512 at 49 13.3 / 16.2, at 394
+    16.1 / 18.1; 768 at 394 31 / 26.)"""
     def layer_us(D_in, D_out, G):
         two = _two_kernels_us(rows, D_in, D_out)
         return min(two, binding.grkan_linear_estimate_us(rows, D_in, D_out)) if _fused_sizes(D_in, D_out, G, M_DEGREE + 1) else two
@@ -185,7 +187,21 @@ def block_products_are_faster(rows: int, D: int, hidden: int, D_out: int, G1: in
     first, second = binding.grkan_product_estimate_us(rows, D, hidden, True), binding.grkan_product_estimate_us(rows, hidden, D_out, False)
     if not first or not second:
         return False
-    return 3.3 + rows * D * 4 / 5.5e6 + first + second <= max(17.0, layer_us(D, hidden, G1) + layer_us(hidden, D_out, G2))
+    products = 3.3 + rows * D * 4 / 5.5e6 + first + second
+    return max(15.0, products) <= max(13.0, layer_us(D, hidden, G1) + layer_us(hidden, D_out, G2))
+
+
+@lru_cache(maxsize=1024)
+def _block_route(rows: int, D: int, hidden: int, D_out: int, G1: int, G2: int, columns1: int, columns2: int) -> str:
+    """How a KATMlp on the GPU runs in evaluation mode: "products", "models" (the one kernel on the parameters for both layers: 256 wide at
+    49 - 788 rows 15.4 - 16.5 us through the layers' calls, 11.8 - 12.8 without them; 512 at 49 16.4 / 13.4), or "layers" (each on its
+    own)."""
+    if D <= 0 or rows <= 0:
+        return "layers"
+    if block_products_are_faster(rows, D, hidden, D_out, G1, G2):
+        return "products"
+    both = (_layer_route(rows, D, hidden, G1, columns1, False), _layer_route(rows, hidden, D_out, G2, columns2, True))
+    return "models" if both == ("model", "model") else "layers"
 
 
 class GRKANLayerFunction(torch.autograd.Function):
@@ -407,7 +423,8 @@ class GRKANLinear(nn.Module):
         in float32) that is kept until a parameter is written to or replaced, the module is moved, converted or
         switched between training and evaluation, or a state is loaded.  Writes through `.data` or a detached alias
         leave no trace that this could be told from: after one, call drop_packed_weights() (or train() / eval()).
-        At all other sizes, in evaluation mode, it reads the parameters themselves and keeps nothing."""
+        At all other sizes, in evaluation mode, it reads the parameters themselves and keeps nothing; so does the layer as F and
+        a matrix product of this package, where that is the fastest of the three (layer_product_is_faster)."""
         super().__init__()
         if in_features % groups:
             raise ValueError("in_features must be a multiple of groups")
@@ -562,7 +579,8 @@ class KATMlp(nn.Module):
     `fused`: of the second layer, as GRKANLinear has it (the first one is fused in evaluation mode only).  With the default,
     "inference", bfloat16 training on the GPU runs the whole block as one autograd function where that applies
     (_native_block), with the hidden activation's product and rational function in one kernel where that is faster, and inference
-    as three kernels that write F2(h) instead of h where that is (_native_inference); "never" and "always" leave both to the two
+    as three kernels that write F2(h) instead of h, or its layers' two without the layers' calls, where that is
+    (_native_inference); "never" and "always" leave both to the two
     layers."""
 
     def __init__(self, dim: int, hidden: int | None = None, groups: int = 8,
@@ -598,9 +616,10 @@ class KATMlp(nn.Module):
         return params
 
     def _native_inference(self, x):
-        """The block in bfloat16 inference as F1, a product with F2 on its result and a product, on the parameters themselves,
-        or None where that route is not taken (as _native_block; in training mode a pass without a gradient takes that one's
-        kernels or the layers, as the pass with one does)."""
+        """The block in bfloat16 inference as F1, a product with F2 on its result and a product, or as its layers' two kernels (what
+        the layers themselves would run, without their calls), on the parameters as they are; None where neither route is taken
+        (as _native_block; in training mode a pass without a gradient takes that one's kernels or the layers, as the pass with
+        one does)."""
         if x.dtype is not torch.bfloat16 or torch.is_grad_enabled() or self.training or not x.is_cuda:
             return None
         if torch.compiler.is_compiling() or _autocast_elsewhere():
@@ -608,14 +627,20 @@ class KATMlp(nn.Module):
         params = self._plain_parameters()
         if params is None or self._modules["fc1"].training or self._modules["fc2"].training:
             return None
-        B1, W1, B2, W2 = params[1], params[2], params[5], params[6]
-        if B1 is None or W1 is None or B2 is None or W2 is None or not x.dim():
+        A1, B1, W1, b1, A2, B2, W2, b2 = params
+        if A1 is None or B1 is None or W1 is None or A2 is None or B2 is None or W2 is None or not x.dim():
             return None
-        # (what these are is the native entry's to check)
-        dim, hidden, D_out = x.shape[-1], W1.shape[0], W2.shape[0]
-        if not dim or not block_products_are_faster(x.numel() // dim, dim, hidden, D_out, B1.shape[0], B2.shape[0]):
+        # (what these are is the native entries' to check)
+        dim = x.shape[-1]
+        route = _block_route(x.numel() // dim if dim else 0, dim, W1.shape[0], W2.shape[0], B1.shape[0], B2.shape[0],
+                             A1.shape[-1], A2.shape[-1])
+        if route == "layers":
             return None
-        return binding.load_native().block_inference(x, *params)
+        native = binding.load_native()
+        if route == "products":
+            return native.block_inference(x, *params)
+        h = native.layer_model(x, A1, B1, W1, b1)
+        return None if h is None else native.layer_model(h, A2, B2, W2, b2)
 
     def _native_block(self, x):
         """The block in bfloat16 training as one native autograd function (the hidden activation's product and rational

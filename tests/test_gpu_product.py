@@ -99,7 +99,7 @@ def _block(torch, dim, bias=True, shared=True):
     return block.eval()
 
 
-@pytest.mark.parametrize("dim,rows,bias,shared", [(192, 197, True, True), (256, 1000, False, True), (384, 2500, True, False), (768, 6304, True, True)])
+@pytest.mark.parametrize("dim,rows,bias,shared", [(192, 197, True, True), (256, 1300, False, True), (384, 2500, True, False), (768, 6304, True, True)])
 def test_block_inference(dim, rows, bias, shared, monkeypatch):
     """Taken at these sizes; against the layers one by one (the hidden activation's bfloat16 roundings may fall differently: a few
     units of bfloat16 over the whole), no graph, strided input, and in a captured graph, replayed with the eager call between."""
@@ -163,6 +163,34 @@ def test_block_inference_is_left_to_the_layers(monkeypatch):
             assert block._native_inference(x) is None
         assert block._native_inference(x[:0]) is None
     assert block._native_inference(x) is None
+
+
+@pytest.mark.parametrize("D,rows", [(512, 1), (512, 394), (768, 197)])
+def test_block_inference_as_its_layers_kernels(D, rows):
+    """Few rows: bit for bit what the two layers give, with strided rows and in a captured graph too; what the kernel does not take is
+    left to the layers."""
+    import torch
+
+    from paper_2505_13813_amd import nn as gnn
+
+    assert gnn._block_route(rows, D, 4 * D, D, 8, 8, 6, 6) == "models"
+    block = _block(torch, D)
+    x = torch.randn(2, rows, D, device="cuda:0").to(torch.bfloat16)
+    with torch.no_grad():
+        want = block.fc2(block.fc1(x[0]))
+        assert torch.equal(block._native_inference(x[0]), want) and torch.equal(block(x[0]), want)
+        strided = torch.stack((x[0], x[1]), dim=-1)[..., 0]
+        assert not strided.is_contiguous() and torch.equal(block(strided), want)
+        graph, z = torch.cuda.CUDAGraph(), x[0].clone()
+        with torch.cuda.graph(graph):
+            captured = block(z)
+        for i in range(3):
+            z.copy_(torch.randn_like(z))
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(captured, block(z)), i
+        block.fc2.linear.weight.data = torch.cat([block.fc2.linear.weight.data.flatten(), x.flatten()[:1]])[1:].view(D, 4 * D)
+        assert block._native_inference(x[0]) is None and block(x[0]).shape == (rows, D)  # misaligned weights
 
 
 @pytest.mark.parametrize("K,N,G,rows,bias,shared", [(192, 768, 8, 300, True, True), (512, 2048, 8, 9001, False, True), (320, 72, 8, 77, True, False)])
