@@ -347,7 +347,7 @@ grkan_status_t grkan_linear_wgrad_pair(const void *dout1, const void *y1, void *
  * grkan_hidden_supported: K of 192, 256, 384, 512, 640 or 768, N a multiple of 256 (K = 192 and 384: of 384) and at most 32 times that, N / G a
  * multiple of 32, at most 2^30 rows.  Anything else is GRKAN_ERR_UNSUPPORTED.
  * workspace: grkan_hidden_workspace_bytes() bytes of device scratch, untouched until the enqueued work has finished.
- * grkan_hidden_pays: whether the kernel of a direction is also the faster route at this size than a library product and
+ * grkan_hidden_pays: whether the kernel of a direction is also the faster route at this size than a product and
  * grkan_fwd / grkan_bwd.
  */
 int32_t grkan_hidden_supported(int32_t K, int32_t N, int32_t G);

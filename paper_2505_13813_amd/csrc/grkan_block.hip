@@ -1,4 +1,4 @@
-// The backward pass of an MLP block as one call: five launches where the parts by themselves take eight.
+// The backward pass of an MLP block as one call: four or five launches where the parts by themselves take eight.
 #include <hip/hip_runtime.h>
 
 #include "grkan_elem.h"

@@ -6,8 +6,8 @@
 //   backward   dF = dY W  (bfloat16, never written),  dh = dF F'(h),  dA, dB
 //
 // Both products contract over the block's width K (192 .. 768) into the wide hidden dimension N = 4 K: 25,216 tokens of
-// 384 -> 1536 are 30 GFLOP, 20 us at the matrix cores' rate, around 77 MB of result.  A library product runs this
-// short contraction at 420 - 560 TFLOP/s and leaves the result to be read again.
+// 384 -> 1536 are 30 GFLOP, 20 us at the matrix cores' rate, around 77 MB of result, that a product by itself leaves to be read
+// again.
 //
 // A wavefront keeps the weights of its CW hidden channels (all of one coefficient group) for the whole kernel: in vector
 // registers, and what does not fit there (K = 384 two steps of 32, 512 two, 640 four, 768 six) in LDS that it alone reads, again
@@ -356,8 +356,12 @@ static const Variant *variant_of(int32_t K, int32_t N, int32_t G)
     return nullptr;
 }
 
-// Whether the kernel is the faster route than a library product and the rational function's own kernel.
+// Whether the kernel is the faster route than a product and the rational function's own kernel.
 //
+// (The table was measured with a library product, which is up to 1.6 times slower here than grkan_product: the line is where the
+// kernel has won by most.  With grkan_product both kernels still pay in whole blocks of widths 192 - 640, 4 x as wide: us with both /
+// neither 192 236 / 264 and 640 1,309 / 1,384 at 50,432 rows, 640 152 / 168 at 3,152.  768 -> 3072, with the forward one / neither:
+// 447 / 434 at 12,608 rows, 844 / 836 at 25,216, 1,637 / 1,619 at 50,432: 1 - 3 % are left there, for one line for both products.)
 // Large calls: a number of slabs that does not divide the 32 compute units of an XCD leaves units without a workgroup, and how
 // many of these the kernel can do without falls with K: the more of the weights is in LDS, the nearer it is to what it replaces.
 // Measured on MI355X in whole training blocks (forward and backward pass, 18 numbers of slabs, 6,304 - 50,432 rows; what the block

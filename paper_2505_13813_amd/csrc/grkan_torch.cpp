@@ -333,9 +333,9 @@ Tensor product_of_rows(const Tensor &x, const Tensor &W, const std::optional<Ten
 
 // The two GR-KAN layers of an MLP block: f1 = F1(x), h = f1 W1^T + b1 and f2 = F2(h), out = f2 W2^T + b2.  Where it is the
 // faster route (grkan_hidden_pays, by direction) h and f2 come from one kernel, and in the backward pass the product with W2 and
-// F2's gradients, so that dF2 is never written; elsewhere from torch's product and the rational function.  Saves what
-// the layers by themselves save.  `wgrad`: whether the weight gradients take grkan_linear_wgrad (one answer for both: the second
-// layer's sizes are the first one's in the other order).
+// F2's gradients, so that dF2 is never written; elsewhere from grkan_product and the rational function.  The backward pass is one
+// call (grkan_block_bwd).  Saves what the layers by themselves save.  `wgrad`: whether the weight gradients take this package's
+// kernel (one answer for both: the second layer's sizes are the first one's in the other order).
 struct Block : public torch::autograd::Function<Block> {
     static Tensor forward(AutogradContext *ctx, const Tensor &x, const Tensor &A1, const Tensor &B1, const Tensor &W1,
                           const Tensor &A2, const Tensor &B2, const Tensor &W2, const std::optional<Tensor> &b1,
