@@ -49,12 +49,20 @@ struct Args {
 template <int KS, int KR, int NT, int NW, int TR> struct Shape {
     static constexpr int K = 32 * KS, CW = 16 * NT;
     static constexpr int kPieces = K / 8;                                    // 16-byte pieces of a token's row
-    static constexpr uint32_t kPitch = K * 2 + 16;                           // rows 16 bytes apart from the next bank
+    // A token's row in LDS.  Up to 384 rows are 16 bytes apart from the next bank: one lane in sixteen of an operand read meets
+    // another's bank, which costs the read a second pass, 38 % of the LDS's cycles at 384.  From 512 on, where the weights in LDS take more of
+    // them, pieces of 16 bytes are permuted (xor with the row number, in blocks of sixteen) instead, and none meets: us forward,
+    // backward at 25,216 rows, padded / permuted 512 72.4 / 69.3, 103.7 / 101.6, 640 109.6 / 106.2, 156.1 / 153.6, 768 168.4 / 164.7,
+    // 232.5 / 229.1.  The addresses are more instructions, though, which is what bounds the narrow ones: 192 37.7 / 38.6 backward, 256
+    // 26.1 / 27.5, 46.4 / 47.3, 384 44.3 / 46.0, 71.9 / 72.4.
+    static constexpr bool kPermuted = K >= 512;
+    static constexpr uint32_t kPitch = K * 2 + (kPermuted ? 0 : 16);
+    static __device__ uint32_t swizzle(uint32_t row) { return kPermuted ? (row & 15u) * 16u : 0u; } // bytes
     static constexpr uint32_t kXBuf = TR * kPitch;
     static constexpr int kKept = KS - KR > 2 ? KS - KR : 2;                  // steps a wavefront's own LDS holds (two while loading)
     static constexpr uint32_t kOwn = kKept * NT * 1024u;
     static constexpr size_t kLds = 2 * kXBuf + NW * kOwn;
-    static_assert(KS % 2 == 0 && NT % 2 == 0 && kLds <= 160 * 1024, "");
+    static_assert(KS % 2 == 0 && NT % 2 == 0 && kLds <= 160 * 1024 && (!kPermuted || K % 128 == 0), "");
 };
 
 template <int KS, int KR, int NT, int NW, int TR, bool BWD>
@@ -62,7 +70,7 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void hidden_kernel(const Args a)
 {
     using S = Shape<KS, KR, NT, NW, TR>;
     constexpr int kTileRows = TR;
-    extern __shared__ __align__(16) char smem[];
+    extern __shared__ __align__(256) char smem[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -167,7 +175,8 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void hidden_kernel(const Args a)
             if ((j + 1) * 64 * NW <= kTileRows * S::kPieces || wave * 64 + j * 64 * NW < kTileRows * S::kPieces)
             {
                 keep_in_loop(t_at[j]);
-                lds_write16(lds0 + buf + (t_at[j] >> 16) * S::kPitch + (t_at[j] & 0xffffu), xr[j]);
+                const uint32_t row = t_at[j] >> 16;
+                lds_write16(lds0 + buf + row * S::kPitch + ((t_at[j] & 0xffffu) ^ S::swizzle(row)), xr[j]);
             }
     };
 
@@ -237,10 +246,10 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void hidden_kernel(const Args a)
                 acc[2 * p] = f32x4{low(bias[p][0]), high(bias[p][0]), low(bias[p][1]), high(bias[p][1])};
                 acc[2 * p + 1] = f32x4{low(bias[p][2]), high(bias[p][2]), low(bias[p][3]), high(bias[p][3])};
             }
-            const uint32_t xf_at = lds0 + buf + ((uint32_t)(16 * st) + i16) * S::kPitch + g4 * 16u;
+            const uint32_t xf_at = lds0 + buf + ((uint32_t)(16 * st) + i16) * S::kPitch + (g4 * 16u ^ S::swizzle(i16));
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
-                const bf16x8 xf = __builtin_bit_cast(bf16x8, lds_read16(xf_at + (uint32_t)s * 64u));
+                const bf16x8 xf = __builtin_bit_cast(bf16x8, lds_read16(S::kPermuted ? (xf_at ^ (uint32_t)(s % 4) * 64u) + (uint32_t)(s / 4) * 256u : xf_at + (uint32_t)s * 64u));
 #pragma unroll
                 for (int n = 0; n < NT; ++n) {
                     bf16x8 wf;
@@ -341,8 +350,8 @@ static constexpr Variant variant(int32_t fwd_units, int32_t bwd_units)
 //   K = 192: 12 wavefronts 20.3 / 37.9   8: 21.9 / 37.6                                 8 of 96 channels 24.2 / 44.5
 //   K = 256:  8 wavefronts 26.5 / 46.2  16: 25.7 / 66 (spills)                          8 of 64 channels 27.9 / 46.9
 //   K = 384: 12 wavefronts 44.1 / 69.9 (two steps of the weights in LDS)  8: 47.0 / 75.2   8 of 64 channels 44.0 / 78.4
-//   K = 512:  8 wavefronts 81.6 / 110   K = 640: 112 / 155   K = 768: 164 / 237
-// (Before bwd_elem took the sign by a clamp; backward since: K = 192 0.5 %, 384 2.7 %, 768 1.3 % less.)
+//   K = 512:  8 wavefronts 69 / 101   K = 640: 107 / 157   K = 768: 162 / 228
+// (192 - 384 before bwd_elem took the sign by a clamp; backward since: K = 192 0.5 %, 384 2.7 % less.)
 static const Variant kVariants[] = {variant<6, 6, 2, 12>(0, 176), variant<8, 8, 2, 8>(0, 192), variant<12, 10, 2, 12>(0, 176),
                                     variant<16, 14, 2, 8>(160, 192), variant<20, 16, 2, 8>(176, 192),
                                     variant<24, 18, 2, 8, 16>(192, 208)};
