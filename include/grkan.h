@@ -322,8 +322,9 @@ grkan_status_t grkan_linear_wgrad(const void *dout, const void *y, void *dW, voi
                                   grkan_dtype_t io, void *hip_stream);
 
 /*
- * The gradients of two products over the same rows (an MLP block's) in one launch, each as grkan_linear_wgrad's:
- * both fill the chip together, so that half as many partial sums are written.  bfloat16.
+ * The gradients of two products over the same rows (an MLP block's), each as grkan_linear_wgrad's: in one launch, where
+ * both fill the chip together and half as many partial sums are written, or, where their tiles together would leave much of
+ * it idle (a rule on the sizes), one after the other, with one launch for all sums.  bfloat16.
  */
 size_t grkan_linear_wgrad_pair_workspace_bytes(int64_t rows, int32_t D_in1, int32_t D_out1, int32_t D_in2,
                                                int32_t D_out2);

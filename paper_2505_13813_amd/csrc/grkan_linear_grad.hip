@@ -8,8 +8,8 @@
 // small (384 x 1536 for KAT-S), so the work is split over the rows: a workgroup owns a 192 x 192 tile of dW
 // and one range of rows, and writes a float32 partial tile; a second kernel adds the partials in range
 // order.  Nothing is atomic and every order is fixed by the sizes, so results are the same from run to run.
-// A block's two products share one launch: the partial tiles that fill the chip are 38 MB in all, whatever the sizes, written and
-// read once instead of twice.
+// A block's two products share one launch where both together still fill the chip (make_plan): the partial tiles that do are 38 MB in
+// all, whatever the sizes, written and read once instead of twice.
 //
 //   * Both operands have the contraction as their slow dimension.  Stages of 32 rows come to LDS as they lie
 //     in memory (LDS-direct loads of whole 384-byte row pieces, six buffers) and are transposed on the way into the matrix
@@ -34,6 +34,7 @@
 // fetch next to each other).  The second kernel, which reads the partial tiles, takes 7 - 8 us, writing them about as much.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "grkan_plan.h"
@@ -302,12 +303,11 @@ struct Sum {
     const float *part, *bpart;
     char *dW, *dbias;
     int64_t elems;
-    int32_t Do, brows;
+    int32_t Do, brows, splits;
     int32_t main_blocks, blocks;
 };
 struct SumArgs {
     Sum s[2];
-    int32_t splits;
     int32_t coef_blocks[2]; // COEF: in front of the others (their chains of sums are the longest)
     CoefSums coef[2];
 };
@@ -334,7 +334,7 @@ template <bool COEF> __global__ __launch_bounds__(256) void grkan_linear_wgrad_s
             return;
         f32x4 v = *(const f32x4 *)(s.part + e);
 #pragma unroll 8
-        for (int32_t k = 1; k < a.splits; ++k)
+        for (int32_t k = 1; k < s.splits; ++k)
             v += *(const f32x4 *)(s.part + (int64_t)k * s.elems + e);
         *(u32x2 *)(s.dW + e * 2) = u32x2{pack(v[0], v[1]), pack(v[2], v[3])};
     } else {
@@ -366,7 +366,8 @@ struct Size {
 };
 
 struct Plan {
-    int32_t tiles_i[2], tiles[2], splits;
+    int32_t tiles_i[2], tiles[2], splits[2];
+    bool together; // both products in one launch
     size_t part_bytes[2], bias_bytes[2];
     size_t bytes() const { return part_bytes[0] + bias_bytes[0] + part_bytes[1] + bias_bytes[1]; }
 };
@@ -393,17 +394,24 @@ static grkan_status_t make_plan(int64_t rows, const Size *size, int n, Plan *pl)
     const int64_t stages = (rows + kRows - 1) / kRows;
     // as many row ranges as fill the 256 compute units once (one workgroup each: 144 KB of LDS), each of eight
     // stages at least: a shorter one would mostly fill and drain its pipeline and write its partial tile
-    int64_t splits = 256 / tiles;
-    if (splits > stages / 8)
-        splits = stages / 8;
-    if (splits < 1)
-        splits = 1;
-    if (tiles * splits > INT32_MAX / 16)
+    auto ranges = [&](int64_t of) { return std::max<int64_t>(1, std::min(256 / of, stages / 8)); };
+    if (tiles * ranges(tiles) > INT32_MAX / 16)
         return GRKAN_ERR_UNSUPPORTED;
-    pl->splits = (int32_t)splits;
+    // Two products: in one launch unless its workgroups walk kLaunch stages more than those of two launches one after the other: what
+    // twice as many partial tiles, and filling the pipeline again, cost.  (256 / tiles rounds down: with 65 - 85 tiles for each product one
+    // launch leaves up to 126 units without a workgroup that two launches of three ranges use; with 43 - 51 it has two ranges for both
+    // against five for each.  MI355X, us of both gradients together / apart: 768, 3840 (80 tiles) at 6,304 rows 89 / 94, at 12,608 159 /
+    // 160, at 25,216 350 / 290; 512, 4096 (66) 82 / 84, 150 / 141, 319 / 262; 768, 2048 (44) at 25,216 180 / 176, at 50,432 352 / 328; 512,
+    // 2048 (33) 127 / 133, 254 / 245; 768, 3072 (64, as many stages in a row either way) 414 / 424.  Whole blocks at the line: 256, 6400
+    // at 6,304 rows, 66 stages, 311 / 323, at 12,608, 131 stages, 595 / 565.)
+    constexpr double kLaunch = 96;
+    const double alone = (double)stages / (double)ranges(pl->tiles[0]) + (n == 2 ? (double)stages / (double)ranges(pl->tiles[1]) : 0);
+    pl->together = n == 1 || (double)stages / (double)ranges(tiles) <= alone + kLaunch;
+    for (int k = 0; k < n; ++k)
+        pl->splits[k] = (int32_t)ranges(pl->together ? tiles : pl->tiles[k]);
     for (int k = 0; k < n; ++k) {
-        pl->part_bytes[k] = (size_t)splits * (size_t)size[k].D_out * (size_t)size[k].D_in * 4;
-        pl->bias_bytes[k] = ((size_t)splits * (size_t)pl->tiles_i[k] * (size_t)size[k].D_out * 4 + 15) / 16 * 16;
+        pl->part_bytes[k] = (size_t)pl->splits[k] * (size_t)size[k].D_out * (size_t)size[k].D_in * 4;
+        pl->bias_bytes[k] = ((size_t)pl->splits[k] * (size_t)pl->tiles_i[k] * (size_t)size[k].D_out * 4 + 15) / 16 * 16;
     }
     return GRKAN_OK;
 }
@@ -451,7 +459,7 @@ static grkan_status_t run(int64_t rows, const Size *size, const Operands *op, in
     Args a = {};
     SumArgs sum = {};
     a.rows = rows;
-    a.splits = sum.splits = pl.splits;
+    a.splits = pl.splits[0];
     char *at = static_cast<char *>(workspace);
     int64_t blocks = 0;
     for (int k = 0; k < n; ++k) {
@@ -473,7 +481,8 @@ static grkan_status_t run(int64_t rows, const Size *size, const Operands *op, in
         s.dbias = static_cast<char *>(op[k].dbias);
         s.elems = (int64_t)p.Do * p.Di;
         s.Do = p.Do;
-        s.brows = pl.splits * p.tiles_i;
+        s.splits = pl.splits[k];
+        s.brows = pl.splits[k] * p.tiles_i;
         const int64_t main_blocks = (s.elems / 4 + 255) / 256, mine = main_blocks + (s.dbias ? (p.Do + 15) / 16 : 0);
         blocks += mine;
         if (blocks > INT32_MAX)
@@ -481,11 +490,21 @@ static grkan_status_t run(int64_t rows, const Size *size, const Operands *op, in
         s.main_blocks = (int32_t)main_blocks;
         s.blocks = (int32_t)mine;
     }
-    a.per_xcd = (a.tiles * a.splits + 7) / 8;
-    void *args[] = {&a}, *args2[] = {&sum};
-    if (hipLaunchKernel(reinterpret_cast<const void *>(grkan_linear_wgrad_kernel), dim3((unsigned)a.per_xcd * 8u), dim3(kThreads),
-                        args, kLds, stream) != hipSuccess)
-        return GRKAN_ERR_LAUNCH;
+    for (int k = 0; k < (pl.together ? 1 : n); ++k) {
+        Args of = a;
+        if (!pl.together) {
+            of.p[0] = a.p[k];
+            of.p[1] = Problem{};
+            of.tiles = of.p[0].tiles;
+            of.splits = pl.splits[k];
+        }
+        of.per_xcd = (of.tiles * of.splits + 7) / 8;
+        void *args[] = {&of};
+        if (hipLaunchKernel(reinterpret_cast<const void *>(grkan_linear_wgrad_kernel), dim3((unsigned)of.per_xcd * 8u), dim3(kThreads),
+                            args, kLds, stream) != hipSuccess)
+            return GRKAN_ERR_LAUNCH;
+    }
+    void *args2[] = {&sum};
     if (coef)
         for (int k = 0; k < 2; ++k) {
             sum.coef[k] = coef[k];

@@ -1,4 +1,4 @@
-"""GPU test of grkan_linear_wgrad_pair: the weight and bias gradients of two products over the same rows in one launch."""
+"""GPU test of grkan_linear_wgrad_pair: the weight and bias gradients of two products over the same rows."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -6,7 +6,8 @@ pytestmark = pytest.mark.gpu
 # rows, (D_in, D_out) of both: one row; around one stage; the last stage partial and alone behind whole ones (buffers wrap);
 # more and fewer tiles in the second, partial tiles, one range of rows and many
 CASES = [(1, (8, 8), (200, 16)), (65, (192, 200), (192, 192)), (257, (64, 768), (768, 64)), (320, (192, 192), (8, 400)),
-         (3001, (384, 1536), (1536, 384)), (8199, (200, 8), (192, 192)), (640, (1536, 1536), (1536, 1600))]
+         (3001, (384, 1536), (1536, 384)), (8199, (200, 8), (192, 192)), (640, (1536, 1536), (1536, 1600)),
+         (10001, (1536, 1632), (1632, 1536)), (16001, (1896, 1096), (1632, 1536))]  # each in a launch of its own
 
 
 @pytest.mark.parametrize("bias", [(True, True), (False, True), (True, False)])
@@ -28,6 +29,10 @@ def test_pair(rows, first, second, bias):
         outs += [dW, db]
         pairs.append((dout, y))
     need = lib.grkan_linear_wgrad_pair_workspace_bytes(rows, *first, *second)
+    each = [lib.grkan_linear_wgrad_workspace_bytes(rows, *size) for size in sizes]
+    apart = need == sum(each)
+    if rows > 9000:
+        assert apart
     ws = torch.empty(need, dtype=torch.uint8, device="cuda:0")
 
     def run():
@@ -47,3 +52,10 @@ def test_pair(rows, first, second, bias):
                 assert (g == 7).all()
         assert (got[2 * k][-8:] == 7).all() and (got[2 * k + 1][-8:] == 7).all()
     assert lib.grkan_linear_wgrad_pair(*args, ws.data_ptr(), need - 16, rows, None) == 5
+    if apart:  # the same row ranges as each by itself: the same bits
+        for k, (D_in, D_out) in enumerate(sizes):
+            at = args[6 * k:6 * k + 4]
+            outs[2 * k].fill_(7.0)
+            assert lib.grkan_linear_wgrad(*at, ws.data_ptr(), each[k], rows, D_in, D_out, binding.GRKAN_BF16,
+                                          torch.cuda.current_stream().cuda_stream) == 0
+            assert torch.equal(outs[2 * k], got[2 * k]) and torch.equal(outs[2 * k + 1], got[2 * k + 1])
