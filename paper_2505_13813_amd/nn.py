@@ -143,18 +143,35 @@ def _two_kernels_us(rows: int, D_in: int, D_out: int) -> float:
     return max(27.0, rows * D_in * 4 / 5.5e6 + min(product_us(256, 24.0), product_us(128, 4.0)))
 
 
+# Weights (D_in x D_out) up to which grkan_product's estimate was measured beside the other routes (3072 x 3072, 1000 x 8192).  With larger
+# ones it is up to 1.9 times too low: 500 rows of 8192 -> 8192 take 114 us, through torch's linear 74.
+_MOST_PRODUCT_WEIGHTS = 10_000_000
+
+
 @lru_cache(maxsize=1024)
 def layer_product_is_faster(rows: int, D_in: int, D_out: int, one: bool, packed: bool) -> bool:
-    """Whether a GRKANLinear in inference runs F and grkan_product: instead of the one-kernel layer where that would be the
-    route (`one`; on packed weights it is 4 % faster than it estimates), with 4 us to be gained, and instead of F and torch's linear,
-    whose call alone takes 20 us of host time, wherever the product is supported.  F takes 3.3 us and 5.5 TB/s.  (Measured on
-    MI355X at 191 sizes.  us of the one kernel / this: 512 -> 2048 at 12,608 rows 62 / 51, at 50,432 217 / 144, 3072 -> 3072 at
-    3,152 90 / 63, 768 -> 3072 at 25,216 166 / 138; not at 3072 -> 768, 25,216 rows: 130 / 153.)"""
+    """Whether a GRKANLinear in inference runs F and grkan_product.  F takes 3.3 us and 5.5 TB/s.
+
+    Instead of the one-kernel layer, where that would be the route (`one`; on packed weights it is 4 % faster than it
+    estimates), with 4 us to be gained.  (us of the one kernel / this: 512 -> 2048 at 12,608 rows 57 / 46, at 50,432 217 / 144.)
+
+    Instead of F and torch's linear, whose call alone takes 27 us with F's: up to 512 channels always (no size of these was slower by more than
+    1 %); above, where the estimate, with a margin that grows with D_in (it is 7 us too low for few rows of 3072), is below
+    what one_kernel_is_faster counts for torch's.  The library reaches 1.1 - 1.35 PFLOP/s where its rounds of tiles are full, this 0.9 - 1.1.
+    Where D_out is no multiple of 64 it reaches 0.5 - 0.9.  (Measured on MI355X at 32 pairs D_in, D_out, 16 - 40,000 rows; us of torch's / this:
+    768 -> 3072 at 2,048 rows 29 / 21, at 5,000 31 / 33, at 16,384 81 / 93, at 25,216 139 / 138; 3072 -> 3072 at 5,000 84 / 92, at
+    25,216 494 / 430; 1024 -> 1024 at 16,384 45 / 48, 1024 -> 1000 78 / 47.  Of 390 sizes two lose more than 3 % to the route without
+    grkan_product, the most 1024 -> 4096 at 12,608 rows, 107 / 116; to the faster of both the rule loses 0.8 % in the mean.)"""
     product = binding.grkan_product_estimate_us(rows, D_in, D_out)
-    if not product:
+    if not product or D_in * D_out > _MOST_PRODUCT_WEIGHTS:
         return False
     this = 3.3 + rows * D_in * 4 / 5.5e6 + product
-    return not one or this + 4.0 < binding.grkan_linear_estimate_us(rows, D_in, D_out) * (0.96 if packed else 1.0)
+    if one:
+        return this + 4.0 < binding.grkan_linear_estimate_us(rows, D_in, D_out) * (0.96 if packed else 1.0)
+    if D_in <= 512:
+        return True
+    two = _two_kernels_us(rows, D_in, D_out)
+    return this <= 1.35 * two if D_out % 64 else this * (1.0 + D_in / 12288) <= two
 
 
 @lru_cache(maxsize=1024)

@@ -49,9 +49,19 @@ def test_rule_of_the_blocks_inference_route():
 
 def test_rule_of_a_layers_inference_route():
     route = gnn._layer_route
-    assert route(50432, 512, 2048, 8, 6, True) == route(3152, 3072, 3072, 8, 6, True) == "product"
+    assert route(50432, 512, 2048, 8, 6, True) == route(3152, 768, 3072, 8, 6, True) == "product"
     assert route(197, 3072, 768, 8, 6, True) == route(6304, 1536, 384, 8, 6, True) == "model"
     assert route(25216, 3072, 768, 8, 6, True) == "packed" and route(25216, 3072, 768, 8, 6, False) == "model"
     assert route(300, 192, 768, 8, 6, True) == "product"       # groups of 24: not the one kernel's
     assert route(300, 768, 192, 8, 4, True) == "other"         # other degrees
     assert route(300, 100, 192, 4, 6, True) == "other" and route(0, 768, 192, 8, 6, True) == "other"
+
+
+def test_layers_that_torchs_product_is_faster_for():
+    """Sizes at which F and torch's linear were measured 5 - 57 % faster than F and this product, and neighbours at which they are not."""
+    route = gnn._layer_route
+    for size in ((16384, 768, 3072), (16384, 768, 2048), (5000, 3072, 3072), (2048, 3072, 768), (16384, 1024, 1024), (25216, 2048, 512),
+                 (500, 4096, 4096), (500, 8192, 8192), (8192, 4096, 16384), (1000, 16384, 4096)):
+        assert route(*size, 8, 6, True) == "other", size
+    for size in ((25216, 2048, 1000), (16384, 1024, 1000), (40000, 512, 2048), (25216, 192, 768), (2048, 640, 2560), (256, 320, 1000)):
+        assert route(*size, 8, 6, True) == "product", size
