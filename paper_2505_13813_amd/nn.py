@@ -155,7 +155,7 @@ def layer_product_is_faster(rows: int, D_in: int, D_out: int, one: bool, packed:
     Instead of the one-kernel layer, where that would be the route (`one`; on packed weights it is 4 % faster than it
     estimates), with 4 us to be gained.  (us of the one kernel / this: 512 -> 2048 at 12,608 rows 57 / 46, at 50,432 217 / 144.)
 
-    Instead of F and torch's linear, whose call alone takes 27 us with F's: up to 512 channels always (no size of these was slower by more than
+    Instead of F and torch's linear, which take 31 us of host time through the module: up to 512 channels always (no size of these was slower by more than
     1 %); above, where the estimate, with a margin that grows with D_in (it is 7 us too low for few rows of 3072), is below
     what one_kernel_is_faster counts for torch's.  The library reaches 1.1 - 1.35 PFLOP/s where its rounds of tiles are full, this 0.9 - 1.1.
     Where D_out is no multiple of 64 it reaches 0.5 - 0.9.  (Measured on MI355X at 32 pairs D_in, D_out, 16 - 40,000 rows; us of torch's / this:
@@ -171,7 +171,7 @@ def layer_product_is_faster(rows: int, D_in: int, D_out: int, one: bool, packed:
     if D_in <= 512:
         return True
     two = _two_kernels_us(rows, D_in, D_out)
-    return this <= 1.35 * two if D_out % 64 else this * (1.0 + D_in / 12288) <= two
+    return this <= 1.35 * two if D_out % 64 else this * (1.0 + D_in / 12288) <= max(31.0, two)
 
 
 @lru_cache(maxsize=1024)

@@ -63,5 +63,5 @@ def test_layers_that_torchs_product_is_faster_for():
     for size in ((16384, 768, 3072), (16384, 768, 2048), (5000, 3072, 3072), (2048, 3072, 768), (16384, 1024, 1024), (25216, 2048, 512),
                  (500, 4096, 4096), (500, 8192, 8192), (8192, 4096, 16384), (1000, 16384, 4096)):
         assert route(*size, 8, 6, True) == "other", size
-    for size in ((25216, 2048, 1000), (16384, 1024, 1000), (40000, 512, 2048), (25216, 192, 768), (2048, 640, 2560), (256, 320, 1000)):
+    for size in ((25216, 2048, 1000), (16384, 1024, 1000), (40000, 512, 2048), (25216, 192, 768), (2048, 640, 2560), (256, 320, 1000), (2048, 1024, 4096)):
         assert route(*size, 8, 6, True) == "product", size
