@@ -190,22 +190,25 @@ def _layer_route(rows: int, D_in: int, D_out: int, G: int, numerator_columns: in
 @lru_cache(maxsize=1024)
 def block_products_are_faster(rows: int, D: int, hidden: int, D_out: int, G1: int, G2: int) -> bool:
     """Whether an MLP block in inference runs as F1, the first product with F2 on its result, and the second product
-    (grkan_product), instead of its two layers.  F1 takes 3.3 us and 5.5 TB/s; three launches take no less than 15 us of host time,
-    the layers' two 13.  (Measured on MI355X, widths 192 - 768, 49 - 50,432 rows, us of the layers / this: 192 at 6,304 rows 45 / 22,
-    384 44 / 34, 512 69 / 54, 768 85 / 73; 768 at 25,216 270 / 265, 9,456 of 384 48.5 / 49.2.  The layers win at few rows of a wide
-    model, where each is one round of small tiles: 768 at 49 rows 15.8 / 18.8, at 197 18.7 / 22.3, 512 at 49 13.3 / 16.2, at 394
-    16.1 / 18.1; 768 at 394 31 / 26.)"""
+    (grkan_product), instead of its two layers.  F1 takes 3.3 us and 5.5 TB/s; three launches take no less than 15 us of host time, the
+    layers' two 13 by themselves and 19 through the layers' calls, behind the look at this rule.  (Measured on MI355X, widths 128 - 4096,
+    8 - 40,000 rows, us of the layers / this: 192 at 6,304 rows 45 / 22, 384 44 / 34, 512 69 / 54, 768 85 / 73; 768 at 25,216 270 / 265,
+    1024 at 25,216 442 / 403; 768 -> 768 at 49 rows 18.9 / 15.9.  The layers win at few rows of a wide model, where each is one round of small
+    tiles: 768 at 49 rows 15.8 / 18.8, at 197 18.7 / 22.3, 512 at 49 13.3 / 16.2, at 394 16.1 / 18.1, 1024 at 49 17.7 / 22.4; 768 at
+    394 31 / 26.  With both contractions short the estimate is up to 7 us too low at 25,216 rows: 256 -> 256 34 / 36.  With weights past the measured ones this is too low, as for layers: 2048 at 394 rows 63 / 67, 4096 at 197 121 / 135.)"""
     def layer_us(D_in, D_out, G):
         two = _two_kernels_us(rows, D_in, D_out)
         return min(two, binding.grkan_linear_estimate_us(rows, D_in, D_out)) if _fused_sizes(D_in, D_out, G, M_DEGREE + 1) else two
 
-    if G1 <= 0 or G2 <= 0 or D % G1 or hidden % G2:
+    if G1 <= 0 or G2 <= 0 or D % G1 or hidden % G2 or max(D, D_out) * hidden > _MOST_PRODUCT_WEIGHTS:
         return False
     first, second = binding.grkan_product_estimate_us(rows, D, hidden, True), binding.grkan_product_estimate_us(rows, hidden, D_out, False)
     if not first or not second:
         return False
-    products = 3.3 + rows * D * 4 / 5.5e6 + first + second
-    return max(15.0, products) <= max(13.0, layer_us(D, hidden, G1) + layer_us(hidden, D_out, G2))
+    products = 3.3 + rows * D * 4 / 5.5e6 + first + second + (rows / 3500 if max(D, hidden) <= 512 else 0.0)
+    calls = (_layer_route(rows, D, hidden, G1, M_DEGREE + 1, False), _layer_route(rows, hidden, D_out, G2, M_DEGREE + 1, True))
+    host = 13.0 if calls == ("model", "model") else 19.0
+    return max(15.0, products) <= max(host, layer_us(D, hidden, G1) + layer_us(hidden, D_out, G2))
 
 
 @lru_cache(maxsize=1024)
@@ -616,21 +619,30 @@ class KATMlp(nn.Module):
             out = self._native_inference(x)
         return self.fc2(self.fc1(x)) if out is None else out
 
-    def _plain_parameters(self):
-        """Numerator, denominator, weight and bias of both layers, or None where calling the two layers would do anything else
-        than their parts do."""
+    def _layers_parameters(self):
+        """Numerator, denominator, weight and bias of both layers, or None where a layer or a part of one is of another kind."""
         params = []
         for fc in (self._modules.get("fc1"), self._modules.get("fc2")):
-            if not _only_a(GRKANLinear, fc) or fc.fused != "inference":
+            if type(fc) is not GRKANLinear:
                 return None
             linear, rational = fc._modules.get("linear"), fc._modules.get("rational")
-            if not _only_a(nn.Linear, linear) or not _only_a(GroupRational, rational) or "coefficient_rows" in rational.__dict__:
-                return None
-            if "bias" not in linear._parameters:  # a buffer or a plain tensor, that only linear's own forward reads
+            if type(linear) is not nn.Linear or type(rational) is not GroupRational:
                 return None
             params += [rational._parameters.get("numerator"), rational._parameters.get("denominator"),
                        linear._parameters.get("weight"), linear._parameters.get("bias")]
         return params
+
+    def _plain_calls(self) -> bool:
+        """Whether calling the two layers (of the usual kinds) would do nothing else than their parts do."""
+        for fc in (self._modules["fc1"], self._modules["fc2"]):
+            if not _only_a(GRKANLinear, fc) or fc.fused != "inference":
+                return False
+            linear, rational = fc._modules["linear"], fc._modules["rational"]
+            if not _only_a(nn.Linear, linear) or not _only_a(GroupRational, rational) or "coefficient_rows" in rational.__dict__:
+                return False
+            if "bias" not in linear._parameters:  # a buffer or a plain tensor, that only linear's own forward reads
+                return False
+        return True
 
     def _native_inference(self, x):
         """The block in bfloat16 inference as F1, a product with F2 on its result and a product, or as its layers' two kernels (what
@@ -641,17 +653,18 @@ class KATMlp(nn.Module):
             return None
         if torch.compiler.is_compiling() or _autocast_elsewhere():
             return None
-        params = self._plain_parameters()
-        if params is None or self._modules["fc1"].training or self._modules["fc2"].training:
+        params = self._layers_parameters()
+        if params is None:
             return None
         A1, B1, W1, b1, A2, B2, W2, b2 = params
         if A1 is None or B1 is None or W1 is None or A2 is None or B2 is None or W2 is None or not x.dim():
             return None
+        # (the look at the sizes first: where the layers are called after all, it is all that this adds to them)
         # (what these are is the native entries' to check)
         dim = x.shape[-1]
         route = _block_route(x.numel() // dim if dim else 0, dim, W1.shape[0], W2.shape[0], B1.shape[0], B2.shape[0],
                              A1.shape[-1], A2.shape[-1])
-        if route == "layers":
+        if route == "layers" or self._modules["fc1"].training or self._modules["fc2"].training or not self._plain_calls():
             return None
         native = binding.load_native()
         if route == "products":
@@ -671,8 +684,8 @@ class KATMlp(nn.Module):
             return None
         if torch.is_autocast_enabled() or torch.compiler.is_compiling():
             return None
-        params = self._plain_parameters()
-        if params is None:
+        params = self._layers_parameters()
+        if params is None or not self._plain_calls():
             return None
         for i, p in enumerate(params):
             if type(p) is not nn.Parameter and not (p is None and i % 4 == 3):

@@ -45,6 +45,9 @@ def test_rule_of_the_blocks_inference_route():
     assert not faster(49, 768, 3072, 768, 8, 8) and not faster(197, 768, 3072, 768, 8, 8)
     assert not faster(400, 96, 384, 96, 8, 8)  # K = 96 is no multiple of 64
     assert not faster(400, 192, 768, 192, 0, 8) and not faster(400, 192, 768, 192, 5, 8) and not faster(0, 192, 768, 192, 8, 8)
+    # where the layers are called one by one (the second on its packed copy) their calls' host time counts; weights past the measured ones
+    assert faster(49, 768, 768, 768, 8, 8) and faster(1576, 256, 256, 256, 8, 8) and not faster(25216, 256, 256, 256, 8, 8)
+    assert not faster(394, 2048, 8192, 2048, 8, 8) and not faster(197, 4096, 16384, 4096, 8, 8)
 
 
 def test_rule_of_a_layers_inference_route():
