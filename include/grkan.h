@@ -389,13 +389,15 @@ grkan_status_t grkan_product(const void *x, const void *W, const void *bias, voi
                              int32_t shared_numerator, void *hip_stream);
 
 /*
- * The whole backward pass of a bfloat16 KAT MLP block, out = F2(h) W2^T + b2 with h = F1(x) W1^T + b1: the parts above in five
- * launches or four (grkan_hidden_bwd or a product and the rational function, a product and the rational function or both in
- * one, grkan_linear_wgrad_pair, one for all second stages).  rows >= 1; D, hidden and G2 as grkan_hidden_supported(D, hidden, G2);
+ * The whole backward pass of a bfloat16 KAT MLP block, out = F2(h) W2^T + b2 with h = F1(x) W1^T + b1: the parts above
+ * (grkan_hidden_bwd or a product and the rational function, a product and the rational function or both in one,
+ * grkan_linear_wgrad_pair, one launch for all second stages).  Four launches at best, six with both rational functions apart, one more
+ * for each product whose rows take two and for weight gradients that take one each.  rows >= 1; D, hidden and G2 as grkan_hidden_supported(D, hidden, G2);
  * G1 divides D.
  *   x, f1 = F1(x), dout, dx [rows, D]; h, f2 = F2(h), dh [rows, hidden]; W1, dW1 [hidden, D]; W2, dW2 [D, hidden]; db1
  *   [hidden], db2 [D], each or NULL; A1, B1, A2, B2 and their gradients as for grkan_bwd_model (shared1, shared2: one numerator row
- *   for all groups).  All DEVICE, bfloat16, contiguous; tensors 16-byte aligned.  dh is scratch.
+ *   for all groups).  All DEVICE, bfloat16, contiguous; tensors 16-byte aligned.  dh is scratch: it holds the gradient of h
+ *   afterwards, and may hold that of f2 meanwhile.
  * `alloc` is asked more than once during the call, each time as grkan_bwd_model asks it.
  */
 typedef struct {

@@ -1,4 +1,6 @@
-// The backward pass of an MLP block as one call: four or five launches where the parts by themselves take eight.
+// The backward pass of an MLP block as one call: four launches where each rational function runs inside the product beside it, one more for
+// each that does not, where the rows of a product are split (grkan_product_tile), or where the weight gradients take a launch each;
+// the parts by themselves take three more (their second stages, and the sums of the weight gradients).
 #include <hip/hip_runtime.h>
 
 #include "grkan_elem.h"
@@ -24,12 +26,10 @@ extern "C" grkan_status_t grkan_block_bwd(const grkan_block_bwd_t *b, grkan_allo
         st = hidden_bwd_stage1(b->dout, b->W2, b->h, c2, b->dh, b->dA2, b->dB2, alloc, alloc_context, b->rows, b->D, b->hidden, b->G2, &sums[1],
                                stream);
     } else {
-        void *const df2 = alloc((size_t)b->rows * (size_t)b->hidden * 2, alloc_context);
-        if (!df2)
-            return GRKAN_ERR_WORKSPACE;
-        st = grkan_product(b->dout, b->W2, nullptr, df2, b->rows, b->D, b->hidden, 1, nullptr, nullptr, 1, 0, hip_stream);
+        // (dF2, the largest tensor of the pass, is dh's memory until F2's backward pass writes dh over it, element by element)
+        st = grkan_product(b->dout, b->W2, nullptr, b->dh, b->rows, b->D, b->hidden, 1, nullptr, nullptr, 1, 0, hip_stream);
         if (st == GRKAN_OK)
-            st = bwd_model_stage1(b->h, df2, c2, b->dh, b->dA2, b->dB2, alloc, alloc_context, b->rows, b->hidden, b->G2, &sums[1], stream);
+            st = bwd_model_stage1(b->h, b->dh, c2, b->dh, b->dA2, b->dB2, alloc, alloc_context, b->rows, b->hidden, b->G2, &sums[1], stream);
     }
     if (st == GRKAN_OK && product_backward_pays(b->rows, b->hidden, b->D, b->G1)) {
         st = product_backward(b->dh, b->W1, b->x, c1, b->dx, b->dA1, b->dB1, alloc, alloc_context, b->rows, b->hidden, b->D, b->G1, &sums[0],

@@ -12,7 +12,9 @@ BF16 = 2.0 ** -8  # half a unit in the last place, relative
 # 16-byte pieces, or above ten million elements of dx)
 CASES = [(1, 192, 384, 8, 4, (64, 64)), (1000, 192, 768, 8, 8, (64, 64)), (650, 192, 768, 64, 8, None), (9501, 256, 512, 4, 8, (96, 128)),
          (9501, 384, 1536, 8, 8, (160, 128)), (8207, 640, 2560, 16, 8, (160, 192)), (25001, 256, 1024, 32, 8, (160, 128)),
-         (25000, 256, 2048, 8, 8, (160, 128)), (52000, 192, 384, 8, 4, (224, 192)), (52300, 192, 384, 3, 4, None)]
+         (25000, 256, 2048, 8, 8, (160, 128)), (52000, 192, 384, 8, 4, (224, 192)), (52300, 192, 384, 3, 4, None),
+         # F2 apart too, at the second both; at the first the product that makes its upstream gradient takes two launches
+         (7901, 768, 3072, 8, 8, (160, 192)), (13100, 768, 3072, 8, 8, None)]
 
 
 class Call(ctypes.Structure):
@@ -40,6 +42,8 @@ def _run(torch, lib, d, sizes, shared, bias):
     lib.grkan_block_bwd.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p]
     assert lib.grkan_block_bwd(ctypes.byref(call), ctypes.cast(alloc, ctypes.c_void_p), None, torch.cuda.current_stream().cuda_stream) == 0
     torch.cuda.synchronize()
+    # beside the partial sums at most one tensor of rows x D: none of the hidden width
+    assert sum(t.numel() for t in kept) < 2 * rows * D + 48_000_000
     return out
 
 
@@ -47,7 +51,7 @@ def _run(torch, lib, d, sizes, shared, bias):
 def test_block_backward(oracle, rows, D, hidden, G1, G2, tile):
     """dx and F1's gradients against the oracle at x with dh W1 from 64 bits, weight and bias gradients against 64 bits, with the
     bounds of the hidden kernels' and the weight gradients' own tests; F2's side bit for bit as from grkan_hidden_bwd where that
-    runs; bit for bit again; one numerator row for all groups."""
+    runs, and as from grkan_product and grkan_bwd_model where they do; bit for bit again; one numerator row for all groups."""
     import torch
 
     from paper_2505_13813_amd import binding
@@ -94,6 +98,27 @@ def test_block_backward(oracle, rows, D, hidden, G1, G2, tile):
                                     need, rows, D, hidden, G2, 0, torch.cuda.current_stream().cuda_stream) == 0
         torch.cuda.synchronize()
         assert all(torch.equal(t, out[k]) for t, k in zip(each, ("dh", "dA2", "dB2")))
+
+    else:
+        dF2, each = torch.empty_like(d["h"]), [torch.empty_like(out[k]) for k in ("dh", "dA2", "dB2")]
+        stream, kept = torch.cuda.current_stream().cuda_stream, []
+
+        @ctypes.CFUNCTYPE(ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p)
+        def alloc(size, _):
+            kept.append(torch.empty(size, dtype=torch.uint8, device="cuda:0"))
+            return kept[-1].data_ptr()
+
+        assert lib.grkan_product(d["dout"].data_ptr(), d["W2"].data_ptr(), None, dF2.data_ptr(), rows, D, hidden, 1, None, None, 1, 0, stream) == 0
+        exact = d["dout"].double() @ d["W2"].double()
+        terms = d["dout"].double().abs() @ d["W2"].double().abs()
+        assert ((dF2.double() - exact).abs() <= BF16 * exact.abs() + (D + 1) * 2.0 ** -24 * terms).all()
+        del exact, terms
+        at = [ctypes.c_void_p(t.data_ptr()) for t in (d["h"], dF2, d["A2"], d["B2"], *each)]
+        assert lib.grkan_bwd_model(*at, ctypes.cast(alloc, ctypes.c_void_p), None, ctypes.c_int64(rows), hidden, G2, 5, 4, binding.GRKAN_BF16,
+                                   binding.GRKAN_BF16, 0, ctypes.c_void_p(stream)) == 0
+        torch.cuda.synchronize()
+        for t, k in zip(each, ("dh", "dA2", "dB2")):
+            assert torch.equal(t, out[k]), k
 
     again = _run(torch, lib, d, sizes, 0, False)
     assert all(torch.equal(v, again[k]) for k, v in out.items() if k not in ("db1", "db2"))
