@@ -377,10 +377,12 @@ struct Variant {
 
 template <class SH> static constexpr Kernel backward_kernel()
 {
-    if constexpr (SH::kParts == 1)
+    // not the two largest tiles: one leaves in parts, and the other was never the estimate's choice at a size of a block that
+    // product_backward_pays takes
+    if constexpr (SH::kParts == 1 && SH::TM * SH::TN < 32)
         return product_kernel<SH, true, kBackward>;
     else
-        return nullptr; // a tile that leaves in parts
+        return nullptr;
 }
 
 template <class SH> static constexpr Variant variant(double once, double round, double stage, double fill, double round2 = 0, double stage2 = 0)

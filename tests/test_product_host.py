@@ -39,6 +39,13 @@ def test_tiles_grow_with_the_call():
     assert tile(12593, 2048, 2048) == (320, 256, 1, 10240)  # one whole round of 32 x 8 tiles, and the rest in another
 
 
+def test_tiles_of_the_backward_pass_of_f():
+    """Every tile that grkan_block_bwd may take is one that a block it takes reaches: not the two largest, at any size."""
+    tiles = {binding.grkan_product_tile(rows, K, N, 2)[:3] for rows in (1, 197, 3000, 6304, 12608, 25216, 52000)
+             for K in (384, 1536, 3072) for N in (192, 256, 384, 768, 3072)}
+    assert tiles == {(64, 64, 1), (96, 128, 1), (160, 128, 1), (160, 128, 2), (160, 192, 1), (224, 192, 1)}
+
+
 def test_rule_of_the_blocks_inference_route():
     faster = gnn.block_products_are_faster
     assert faster(6304, 768, 3072, 768, 8, 8) and faster(197, 192, 768, 192, 8, 8)
