@@ -381,7 +381,7 @@ static grkan_status_t make_plan(int64_t rows, const Size *size, int n, Plan *pl)
         const int32_t D_in = size[k].D_in, D_out = size[k].D_out;
         if (rows < 0 || D_in <= 0 || D_out <= 0)
             return GRKAN_ERR_SHAPE;
-        // 16-byte pieces of rows; 32-bit lane offsets of 64 rows; row ranges counted in 31 bits
+        // 16-byte pieces of rows; 32-bit lane offsets of 32 rows
         if (D_in % 8 != 0 || D_out % 8 != 0 || D_in > (1 << 24) || D_out > (1 << 24) || rows > ((int64_t)1 << 36))
             return GRKAN_ERR_UNSUPPORTED;
         const int64_t tiles_i = (D_in + kTile - 1) / kTile, mine = (D_out + kTile - 1) / kTile * tiles_i;
@@ -409,6 +409,9 @@ static grkan_status_t make_plan(int64_t rows, const Size *size, int n, Plan *pl)
     pl->together = n == 1 || (double)stages / (double)ranges(tiles) <= alone + kLaunch;
     for (int k = 0; k < n; ++k)
         pl->splits[k] = (int32_t)ranges(pl->together ? tiles : pl->tiles[k]);
+    for (int k = 0; k < n; ++k)
+        if (stages / pl->splits[k] >= INT32_MAX) // a range's stages are counted in 31 bits
+            return GRKAN_ERR_UNSUPPORTED;
     for (int k = 0; k < n; ++k) {
         pl->part_bytes[k] = (size_t)pl->splits[k] * (size_t)size[k].D_out * (size_t)size[k].D_in * 4;
         pl->bias_bytes[k] = ((size_t)pl->splits[k] * (size_t)pl->tiles_i[k] * (size_t)size[k].D_out * 4 + 15) / 16 * 16;

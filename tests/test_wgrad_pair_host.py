@@ -31,3 +31,12 @@ def test_one_launch_for_the_same_ranges():
     lib = binding.load_library()
     both = lib.grkan_linear_wgrad_pair_workspace_bytes(50432, 768, 3072, 3072, 768)
     assert both == lib.grkan_linear_wgrad_workspace_bytes(50432, 768, 3072)
+
+
+def test_rows_that_a_range_can_count():
+    """2^36 rows are 2^31 stages of 32: one range of them is one too many, 256 ranges are not."""
+    lib = binding.load_library()
+    assert lib.grkan_linear_wgrad_workspace_bytes(1 << 36, 8, 8) and not lib.grkan_linear_wgrad_workspace_bytes(1 << 36, 3072, 3072)
+    assert lib.grkan_linear_wgrad_workspace_bytes(1 << 35, 3072, 3072) and not lib.grkan_linear_wgrad_workspace_bytes((1 << 36) + 1, 8, 8)
+    assert not lib.grkan_linear_wgrad_pair_workspace_bytes(1 << 36, 2048, 2048, 2048, 2048)
+    assert lib.grkan_linear_wgrad(16, 16, 16, None, 16, 1 << 40, 1 << 36, 3072, 3072, binding.GRKAN_BF16, None) == 8
