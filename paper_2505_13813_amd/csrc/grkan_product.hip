@@ -80,7 +80,7 @@ __global__ __launch_bounds__(SH::kThreads, SH::PER *SH::kThreads / 256) void pro
 {
     constexpr int TM = SH::TM, TN = SH::TN, NBUF = SH::NBUF, BM = SH::BM, BN = SH::BN;
     constexpr uint32_t NP = BN / 16; // 32-byte column pairs of a row of W, TRANSPOSED
-    extern __shared__ __align__(16) char smem[];
+    extern __shared__ __align__(128) char smem[]; // the second half of a row's 64 k is read at the first's address xor 64
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
