@@ -51,7 +51,8 @@ def _product(torch, x, W, bias, transposed=False, A=None, B=None, guard=3):
 @pytest.mark.parametrize("rows,K,N,G,tile", SIZES)
 def test_product(rows, K, N, G, tile):
     """Both orders of W against 64 bits (one rounding to bfloat16, and sums in 32 bits: at most (K + 1) 2^-24 of the
-    terms' magnitudes), bit for bit again; F bit for bit against grkan_fwd on the rounded product."""
+    terms' magnitudes), bit for bit again; F element by element against 64 bits, and bit for bit against grkan_fwd on the rounded product
+    where both run in the same tile."""
     import torch
 
     from paper_2505_13813_amd import binding
@@ -70,11 +71,25 @@ def test_product(rows, K, N, G, tile):
     bound = BF16 * (want - bias.double()).abs() + (K + 1) * 2.0 ** -24 * terms
     assert ((bare.double() - (want - bias.double())).abs() <= bound).all()
 
-    # (the tile may be another one with F, and its sums in another order: compared where it is the same)
+    # F(h) for h within `off` of the exact product: off by no more than off times the slope's bound, with Q >= 1
+    # |F'| <= sum i |a_i| m^(i-1) + sum |a_i| m^i sum j |b_j| m^(j-1) for |h| <= m, and one rounding
+    off = BF16 * want.abs() + (K + 1) * 2.0 ** -24 * terms
+    m = want.abs() + off
+
+    def bound_of_f(A):
+        a, b = (t.double().repeat_interleave(N // G, 0).t() for t in ((A if A.dim() == 2 else A.expand(G, 6)), d["B"]))
+        num = sum(a[i] * want ** i for i in range(6))
+        exact = num / (1 + sum(b[j] * want ** (j + 1) for j in range(4)).abs())
+        slope = (sum(i * a[i].abs() * m ** (i - 1) for i in range(1, 6))
+                 + sum(a[i].abs() * m ** i for i in range(6)) * sum((j + 1) * b[j].abs() * m ** j for j in range(4)))
+        return exact, off * slope + 2 * BF16 * exact.abs() + 2.0 ** -20 * sum(a[i].abs() * m ** i for i in range(6))
+
+    # (the tile may be another one with F, and its sums in another order: the same bits where it is the same)
     with_f = binding.grkan_product_tile(rows, K, N, True) == binding.grkan_product_tile(rows, K, N)
     for A in (d["A"], d["A"][0].contiguous()):
         f = _product(torch, x, W, bias, A=A, B=d["B"])
-        assert torch.isfinite(f.float()).all()
+        exact, bound = bound_of_f(A)
+        assert ((f.double() - exact).abs() <= bound).all()
         if with_f:
             rows_of_A = (A if A.dim() == 2 else A.expand(G, 6)).float().contiguous()
             import paper_2505_13813_amd as grkan
@@ -101,8 +116,9 @@ def _block(torch, dim, bias=True, shared=True):
 
 @pytest.mark.parametrize("dim,rows,bias,shared", [(192, 197, True, True), (256, 1300, False, True), (384, 2500, True, False), (768, 6304, True, True)])
 def test_block_inference(dim, rows, bias, shared, monkeypatch):
-    """Taken at these sizes; against the layers one by one (the hidden activation's bfloat16 roundings may fall differently: a few
-    units of bfloat16 over the whole), no graph, strided input, and in a captured graph, replayed with the eager call between."""
+    """Taken at these sizes; bit for bit its parts (each with tests of its own values), and row by row near the layers one by one (the
+    hidden activation's bfloat16 roundings may fall differently: a few units of bfloat16 over each row), no graph, strided input, and in a
+    captured graph, replayed with the eager call between."""
     import torch
 
     from paper_2505_13813_amd import binding
@@ -121,7 +137,11 @@ def test_block_inference(dim, rows, bias, shared, monkeypatch):
         out = block(x)
         assert len(calls) == 1
         want = block.fc2(block.fc1(x))
-        assert (out.double() - want.double()).norm() <= 4 * BF16 * want.double().norm() and out.shape == x.shape
+        assert out.shape == x.shape
+        assert ((out.double() - want.double()).norm(dim=-1) <= 4 * BF16 * want.double().norm(dim=-1)).all()
+        one, two = block.fc1, block.fc2
+        f2 = _product(torch, one.rational(x).view(-1, dim), one.linear.weight, one.linear.bias, A=two.rational.numerator, B=two.rational.denominator)
+        assert torch.equal(out.view(-1, dim), _product(torch, f2, two.linear.weight, two.linear.bias))
         strided = torch.stack((x, x), dim=-1)[..., 0]
         assert not strided.is_contiguous() and torch.equal(block(strided), out)
     with torch.inference_mode():
