@@ -350,7 +350,7 @@ static constexpr Variant variant(int32_t fwd_units, int32_t bwd_units)
 //   K = 192: 12 wavefronts 20.3 / 37.9   8: 21.9 / 37.6                                 8 of 96 channels 24.2 / 44.5
 //   K = 256:  8 wavefronts 26.5 / 46.2  16: 25.7 / 66 (spills)                          8 of 64 channels 27.9 / 46.9
 //   K = 384: 12 wavefronts 44.1 / 69.9 (two steps of the weights in LDS)  8: 47.0 / 75.2   8 of 64 channels 44.0 / 78.4
-//   K = 512:  8 wavefronts 69 / 101   K = 640: 107 / 157   K = 768: 162 / 228
+//   K = 512:  8 wavefronts 69 / 102   K = 640: 106 / 154   K = 768: 165 / 229
 // (192 - 384 before bwd_elem took the sign by a clamp; backward since: K = 192 0.5 %, 384 2.7 % less.)
 static const Variant kVariants[] = {variant<6, 6, 2, 12>(0, 176), variant<8, 8, 2, 8>(0, 192), variant<12, 10, 2, 12>(0, 176),
                                     variant<16, 14, 2, 8>(160, 192), variant<20, 16, 2, 8>(176, 192),
@@ -367,10 +367,10 @@ static const Variant *variant_of(int32_t K, int32_t N, int32_t G)
 
 // Whether the kernel is the faster route than a product and the rational function's own kernel.
 //
-// (The table was measured with a library product, which is up to 1.6 times slower here than grkan_product: the line is where the
-// kernel has won by most.  With grkan_product both kernels still pay in whole blocks of widths 192 - 640, 4 x as wide: us with both /
-// neither 192 236 / 264 and 640 1,309 / 1,384 at 50,432 rows, 640 152 / 168 at 3,152.  768 -> 3072, with the forward one / neither:
-// 447 / 434 at 12,608 rows, 844 / 836 at 25,216, 1,637 / 1,619 at 50,432: 1 - 3 % are left there, for one line for both products.)
+// (The table below was measured with a library product, which is up to 1.6 times slower here than grkan_product, and not again: the
+// lines lie where the kernels win against the former.  Against grkan_product both still pay in whole blocks of widths 192 - 640, 4 x as wide:
+// us with both / neither 192 236 / 264 and 640 1,309 / 1,384 at 50,432 rows, 640 152 / 168 at 3,152.  The forward one at 768 -> 3072
+// does not: with it / with neither 447 / 434 at 12,608 rows, 844 / 836 at 25,216, 1,637 / 1,619 at 50,432.)
 // Large calls: a number of slabs that does not divide the 32 compute units of an XCD leaves units without a workgroup, and how
 // many of these the kernel can do without falls with K: the more of the weights is in LDS, the nearer it is to what it replaces.
 // Measured on MI355X in whole training blocks (forward and backward pass, 18 numbers of slabs, 6,304 - 50,432 rows; what the block

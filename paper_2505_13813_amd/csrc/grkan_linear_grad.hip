@@ -25,7 +25,7 @@
 //     the same columns of dOut take turns by the stage.  (Added up lane by lane they cost the whole kernel a tenth of its time.)
 //
 // Measured on one MI355X, both gradients of one product, 25,216 rows, against the library's product + column sum (us):
-//   384 x 1536: 41 against 171     192 x 768: 28 against 189     768 x 3072: 120 against 270
+//   384 x 1536: 41 against 171     192 x 768: 27 against 189     768 x 3072: 108 against 270
 // and of a block's two products, in two launches of eight wavefronts that loaded, read and multiplied in turn / in one of this:
 //   384: 90 / 65     192: 57 / 33     512: 154 / 122     768: 266 / 220     768 at 3,152 rows: 67 / 42
 // What bounds it: at 384 (50 times 64 rows for each workgroup) 64 rows take 0.53 - 0.59 us of matrix instructions (0.48 at 2.4

@@ -21,9 +21,11 @@
 // Measured on one MI355X against the library's product, us (by itself, over the same buffers):
 //   25,216 x 1536 -> 384  29 against 35 - 38    6,304 x 3072 -> 768  28 against 32 - 36    6,304 x 768 -> 3072  31 against 48 (37 with F)
 //   25,216 x 384 -> 1536  37 against 59         25,216 x 3072 -> 768 89 against 146        50,432 x 768 -> 3072 227 - 237 against 227
+// It loses where the library's rounds of tiles are full, or its contraction is split over the chip: 12,608 x 640 -> 2560 46 against 42,
+// 25,216 x 2048 -> 256 34 against 31, x 6400 -> 256 137 against 95, 50,432 x 768 -> 8192 664 against 559.
 // What bounds it: at 6,304 x 3072 -> 768 the loads alone take 24 of the 29 us, the matrix instructions alone 19, the LDS
-// reads alone 16 (launch, first loads and result 5 in each); at 25,216 x 3072 -> 768 59, 66 and 33 of 97, with the clock at
-// 2.2 GHz.
+// reads alone 16 (launch, first loads and result 5 in each); at 25,216 x 3072 -> 768 59, 66 and 33 of the 97 that it took on
+// that card, with the clock at 2.2 GHz.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -527,6 +529,8 @@ static grkan_status_t launch(const Plan &plan, Args a, int64_t rows, bool transp
 // elements of dx (rows x N):
 //   0.6 - 3 M  192 138 / 136, 384 140 / 134, 512 162.5 / 158, 768 179 / 175     4.8 M  192 147 / 143.5, 384 175.5 / 171.5, 768 269 / 264
 //   8 - 10 M   192 239 / 236, 384 290.5 / 290.5, 640 350 / 345, 768 446 / 439.5  13 - 19 M  384 546 / 551, 512 443 / 462, 640 656 / 647, 768 841 / 859
+// These are four times as wide inside as out.  At 1 - 25 times (78 blocks up to the limit) inside is 0 - 5 % less, but for 256 -> 2048 .. 6400
+// at 25,216 rows, 1 - 3 % more.
 bool product_backward_pays(int64_t rows, int32_t K, int32_t N, int32_t G)
 {
     return product::supported(rows, K, N) && G > 0 && N % G == 0 && N / G % 8 == 0 && rows * N <= 10000000;

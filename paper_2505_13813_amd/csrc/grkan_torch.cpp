@@ -271,7 +271,8 @@ Tensor linear_of_rows(const Tensor &y, const Tensor &W, const std::optional<Tens
 }
 
 // out = y W^T + bias with dW and dbias from grkan_linear_wgrad; saves what torch's linear saves: each operand where
-// the gradient of the other is wanted.  `known`: out, as for Rational.
+// the gradient of the other is wanted.  `known`: out, as for Rational.  (The products are torch's: grkan_product was measured in
+// whole blocks and in inference, not in a layer's training.)
 struct Product : public torch::autograd::Function<Product> {
     static Tensor forward(AutogradContext *ctx, const Tensor &y, const Tensor &W, const std::optional<Tensor> &bias,
                           const std::optional<Tensor> &known)

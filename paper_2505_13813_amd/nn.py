@@ -257,13 +257,14 @@ class GRKANLayerFunction(torch.autograd.Function):
 
 
 def wgrad_pays(rows: int, D_in: int, D_out: int) -> bool:
-    """Whether grkan_linear_wgrad is the faster route for the gradients of a bfloat16 product, measured on MI355X
-    against the library's product and column sum at thirty-one shapes of 1 - 256 tiles (192 x 192, one per compute
-    unit at a time) and 512 - 25,216 rows.  Up to 128 tiles, where each unit gets a range of rows of at least one: faster
-    everywhere (25,216 rows: 384 x 1536 45 us against 171, 768 x 3072 125 against 270, 2048 x 2048 224 against 369;
-    640 rows: 16 against 28, 26 against 28, 26.7 against 27.9; 512 rows: the same, but 27 against 26 from 96 tiles on).
-    From 129 tiles on the rows are not split: with 132 - 210 tiles the units that get none make it lose at some row
-    counts (25,216 rows of 1024 x 4096: 413 against 340), with 225 - 256 it is faster again (443 against 562)."""
+    """Whether a bfloat16 product's gradients are grkan_linear_wgrad's rather than the library's product and column sum.  Tiles are 192 x 192,
+    one per compute unit at a time; up to 128 of them the rows are split over the units, above they are not.
+
+    Measured on MI355X at seventeen shapes of 1 - 256 tiles and 256 - 25,216 rows the kernel is the faster one at all of them: us of it / the
+    library at 25,216 rows 384 x 1536 41 / 171, 768 x 3072 108 / 270, 2048 x 2048 187 / 373, 1024 x 4096 (132 tiles) 277 / 339, 3072 x 3072
+    388 / 539; at 640 rows 16 / 29, 24 / 27, 25 / 30, 27 / 30, 30 / 37; at 512 rows 15 / 28, 23 / 27, 26 / 30, 26 / 30, 28 / 33.  The line is
+    narrower than that: it was drawn for the kernel in an earlier form (eight wavefronts that loaded, read and multiplied in turn), which
+    lost with 129 - 223 tiles at some row counts (1024 x 4096 413 / 340), and at 512 rows from 96 tiles on."""
     tiles = -(-D_in // 192) * -(-D_out // 192)
     return (D_in % 8 == 0 and D_out % 8 == 0 and rows >= (512 if tiles <= 64 else 640)
             and (tiles <= 128 or 224 <= tiles <= 256))
