@@ -143,7 +143,7 @@ def _two_kernels_us(rows: int, D_in: int, D_out: int) -> float:
     return max(27.0, rows * D_in * 4 / 5.5e6 + min(product_us(256, 24.0), product_us(128, 4.0)))
 
 
-# Weights (D_in x D_out) up to which grkan_product's estimate was measured beside the other routes (3072 x 3072, 1000 x 8192).  With larger
+# Weights (D_in x D_out) up to which grkan_product's estimate was measured to hold beside the other routes (3072 x 3072).  With larger
 # ones it is up to 1.9 times too low: 500 rows of 8192 -> 8192 take 114 us, through torch's linear 74.
 _MOST_PRODUCT_WEIGHTS = 10_000_000
 
