@@ -144,7 +144,7 @@ def _two_kernels_us(rows: int, D_in: int, D_out: int) -> float:
 
 
 # Weights (D_in x D_out) up to which grkan_product's estimate was measured to hold beside the other routes (3072 x 3072).  With larger
-# ones it is up to 1.9 times too low: 500 rows of 8192 -> 8192 take 114 us, through torch's linear 74.
+# ones it is up to 1.8 times too low (256 rows of 16384 -> 4096: 55 us estimated, 98 taken; through torch's linear 62).
 _MOST_PRODUCT_WEIGHTS = 10_000_000
 
 
